@@ -672,6 +672,8 @@ struct hpf_partition {
   // normalisation in the consuming convolutions, 2 = additionally image-resident kernels for runs of identity
   // bottleneck blocks
   int fuse = 2;
+  int dev = 0, cus = 0;   // device of the arena and its CUs
+  int res_wgs = 0;     // work-groups per micro-batch of the largest image-resident launch
   int res_group = 0;   // micro-batches one image-resident launch may hold on this device (0: path unavailable)
   float bn_momentum = 1.f;   // running statistics: r <- m*r + (1-m)*batch after every training forward; 1: never
   // per-kernel-class timing
@@ -1275,12 +1277,16 @@ hpf_status run_graphed(hpf_partition* p, GraphSlot& slot, const std::vector<cons
   return HPF_OK;
 }
 
-// Image-resident kernels need every work-group of a launch on the chip at once and take a CU each, so two
-// of them must never share the device: launches of this process are chained through one event.
-// The link of the chain is the completion event the last such call recorded anyway (its owner re-records it
-// only after a later launch of its own, so waiting on it never waits for too little).
+// Image-resident kernels need every work-group of a launch on the chip at once and take up to a CU each, so the
+// launches that may run at the same time must fit the device together.  Every call with such launches holds CUs: as
+// many as its largest launch has work-groups.  Calls on one stream follow each other, so a stream holds what its
+// largest unfinished call does; a new call waits for other streams (largest holder first) until what is left and its
+// own need fit.  Any set of calls that can overlap then fits: the newest of them was admitted with all the others
+// counted.  (One launch at a time, as before, made the partitions of a chain, which use 16 of 256 CUs at 16 images per
+// micro-batch, run one after the other: a chain of four partitions of ResNet-110 took 17.3 ms per batch.)
 std::mutex g_res_mu;
-struct ResidentLink { hipEvent_t ev = nullptr; hipStream_t stream = nullptr; const hpf_partition* owner = nullptr; } g_res;
+struct ResidentHold { int dev; hipStream_t stream; hipEvent_t ev; const hpf_partition* owner; int cus; };
+std::vector<ResidentHold> g_res;   // at most one entry per stream: its latest call (whose event covers the earlier ones)
 
 // Launches of this kind are ordered against each other through events recorded at call time, which a stream under
 // capture by the caller cannot take part in: two captured partitions replayed side by side would each wait for CUs
@@ -1289,20 +1295,54 @@ const char* const kNoCaptureMsg =
     "image-resident launches (fusion level 2) cannot be recorded into a caller's graph capture: call "
     "hpf_partition_set_fusion(p, 1) for partitions whose calls are captured";
 
-hpf_status resident_enter(hpf_partition* p, hipStream_t s) {
+// need: work-groups of the call's largest image-resident launch
+hpf_status resident_enter(hpf_partition* p, hipStream_t s, int need) {
   if (!p->resident()) return HPF_OK;
   std::lock_guard<std::mutex> lk(g_res_mu);
-  return g_res.owner ? wait_for(s, g_res.ev, g_res.stream) : HPF_OK;
+  int held = 0;
+  for (const ResidentHold& h : g_res)
+    if (h.dev == p->dev && h.stream != s) held += h.cus;
+  if (held + need <= p->cus) return HPF_OK;
+  held = 0;
+  for (size_t i = 0; i < g_res.size();) {   // drop what has finished
+    const ResidentHold& h = g_res[i];
+    if (h.dev == p->dev && h.stream != s) {
+      if (hipEventQuery(h.ev) == hipSuccess) { g_res.erase(g_res.begin() + (ptrdiff_t)i); continue; }
+      (void)hipGetLastError();   // "not ready" is no error of a later call
+      held += h.cus;
+    }
+    ++i;
+  }
+  std::vector<char> waited(g_res.size(), 0);
+  while (held + need > p->cus) {
+    int big = -1;
+    for (size_t i = 0; i < g_res.size(); ++i)
+      if (!waited[i] && g_res[i].dev == p->dev && g_res[i].stream != s && (big < 0 || g_res[i].cus > g_res[(size_t)big].cus)) big = (int)i;
+    if (big < 0) break;
+    if (hipStreamWaitEvent(s, g_res[(size_t)big].ev, 0) != hipSuccess) return fail(HPF_EDEVICE, "hipStreamWaitEvent failed");
+    waited[(size_t)big] = 1;
+    held -= g_res[(size_t)big].cus;
+  }
+  return HPF_OK;
 }
-// done: the event recorded on s after the call's last launch
-void resident_leave(hpf_partition* p, hipStream_t s, hipEvent_t done) {
+// done: the event recorded on s after the call's last launch (its owner re-records it only after a later launch of its
+// own, so waiting on it never waits for too little)
+void resident_leave(hpf_partition* p, hipStream_t s, hipEvent_t done, int need) {
   if (!p->resident()) return;
   std::lock_guard<std::mutex> lk(g_res_mu);
-  g_res.ev = done; g_res.stream = s; g_res.owner = p;
+  for (ResidentHold& h : g_res)
+    if (h.dev == p->dev && h.stream == s) {
+      h.ev = done; h.owner = p;
+      if (need > h.cus) h.cus = need;
+      return;
+    }
+  g_res.push_back(ResidentHold{p->dev, s, done, p, need});
 }
 void resident_forget(const hpf_partition* p) {   // the partition's events are about to be destroyed (device idle)
   std::lock_guard<std::mutex> lk(g_res_mu);
-  if (g_res.owner == p) g_res = ResidentLink{};
+  for (size_t i = 0; i < g_res.size();)
+    if (g_res[i].owner == p) g_res.erase(g_res.begin() + (ptrdiff_t)i);
+    else ++i;
 }
 // An exchange between the work-groups of an image-resident launch timed out: the batch is invalid.
 hpf_status check_abort_flag(hpf_partition* p) {
@@ -1397,7 +1437,10 @@ hpf_status hpf_partition_create(const hpf_partition_desc* desc, void* device_are
     }
     int max_bands = 1;
     for (const Plan::ResRun& r : P.runs) max_bands = std::max(max_bands, r.bands);
-    p->res_group = resident_max_group(P.d.microbatch * max_bands);
+    p->res_wgs = P.d.microbatch * max_bands;
+    p->res_group = resident_max_group(p->res_wgs);
+    ok(hipGetDevice(&p->dev));
+    ok(hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->dev));
     if (p->res_group >= 1) ok(resident_prepare());
   }
   p->ev_fwd.resize(m); p->ev_bwd.resize(m);
@@ -1470,8 +1513,9 @@ hpf_status forward_group(hpf_partition* p, int32_t mb_first, int32_t count, cons
     if (st != HPF_OK) return st;
   }
   const int gmax = p->group_limit();
+  const int res_need = p->res_wgs * (count < gmax ? count : gmax);
   {
-    const hpf_status st = resident_enter(p, s);
+    const hpf_status st = resident_enter(p, s, res_need);
     if (st != HPF_OK) return st;
   }
   for (int c0 = 0; c0 < count; c0 += gmax) {
@@ -1512,7 +1556,7 @@ hpf_status forward_group(hpf_partition* p, int32_t mb_first, int32_t count, cons
       p->fwd_done[mb] = 1;
     }
     p->fwd_stream[mb_first + c0] = s;
-    resident_leave(p, s, p->ev_fwd[mb_first + c0]);
+    resident_leave(p, s, p->ev_fwd[mb_first + c0], res_need);
   }
   return HPF_OK;
 }
@@ -1549,8 +1593,9 @@ hpf_status backward_group(hpf_partition* p, int32_t mb_first, int32_t count, con
       if (st != HPF_OK) return st;
     }
   const int gmax = p->group_limit();
+  const int res_need = p->res_wgs * (count < gmax ? count : gmax);
   {
-    const hpf_status st = resident_enter(p, s);
+    const hpf_status st = resident_enter(p, s, res_need);
     if (st != HPF_OK) return st;
   }
   for (int c0 = 0; c0 < count; c0 += gmax) {
@@ -1578,7 +1623,7 @@ hpf_status backward_group(hpf_partition* p, int32_t mb_first, int32_t count, con
       ++p->n_bwd;
     }
     p->bwd_stream[mb_first + c0] = s;
-    resident_leave(p, s, p->ev_bwd[mb_first + c0]);
+    resident_leave(p, s, p->ev_bwd[mb_first + c0], res_need);
   }
   return HPF_OK;
 }
