@@ -183,6 +183,8 @@ int resident_max_group(int nmem);   // nmem: work-groups per micro-batch (images
 // their weight gradients go through the grouped per-layer launch and inference through the per-layer kernels.
 int resident_bands(int kind, int C, int MID, int H, int W);
 size_t resident_xchg_bytes(int C, int nmem, int bands);
+// records an exchange slot has room for: whole groups of 32 (the lanes of the register kernels poll that many at a time)
+__host__ __device__ inline int resident_slot_members(int nmem) { return (nmem + 31) / 32 * 32; }
 hipError_t resident_prepare();   // once per process, outside stream capture: raises the kernels' LDS limits
 hipError_t launch_resident_forward(int kind, int g, int C, int MID, const ResArgs& a, hipStream_t stream);
 hipError_t launch_resident_backward(int kind, int g, int C, int MID, const ResArgs& a, hipStream_t stream);
@@ -192,6 +194,12 @@ hipError_t launch_resident_wgrad(int kind, int g, int C, int MID, const ResArgs&
 // Inference forward of a run (BatchNorm by the running statistics in a.running): only the output of the last block
 // is written; no exchange, so there is no limit on the work-groups of a launch (g <= MAX_GROUP micro-batches).
 hipError_t launch_resident_inference(int kind, int g, int C, int MID, const ResArgs& a, hipStream_t stream);
+// The register form of the same launches (kernels_resident_reg.hip), called by the launchers above for the shapes it covers.
+bool resident_reg_shape(int kind, int C, int MID, int H, int W);
+hipError_t resident_reg_prepare();
+hipError_t launch_reg_forward(int g, int MID, const ResArgs& a, hipStream_t stream);
+hipError_t launch_reg_backward(int g, int MID, const ResArgs& a, hipStream_t stream);
+hipError_t launch_reg_inference(int g, int MID, const ResArgs& a, hipStream_t stream);
 
 hipError_t launch_conv_f32(int mode, int g, const PtrTab& src, const float* w_hwio, const PtrTab& out, const PtrTab& add,
                            const ConvGeom& geom, hipStream_t stream);

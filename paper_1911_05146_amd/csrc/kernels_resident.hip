@@ -20,49 +20,10 @@
 
 #include <type_traits>
 
-#include "hpf_device.h"
+#include "hpf_resident.h"
 
 namespace hpf {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef unsigned long long u64;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int RES_NT = 512;            // threads per work-group (8 waves)
-constexpr int RES_NWV = RES_NT / 64;
-constexpr unsigned RES_SPIN_LIMIT = 1u << 19;
-
-// The wave's index within the work-group as a scalar: conditions on it become scalar branches instead of
-// compare / exec-mask sequences.
-__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
-
-__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-
-// {scale, shift} of a BatchNorm channel: bn(x) = x*scale + shift
-__device__ __forceinline__ float2 bn_scale_shift(float mean, float invstd, float gamma, float beta) {
-  const float sc = gamma * invstd;
-  return make_float2(sc, fmaf(-mean, sc, beta));
-}
-
-// Sums within a row of 16 lanes by DPP row rotations (one VALU instruction per step, no LDS round trip).
-// row_sum<N>(v): every lane gets the sum over the lanes of its row that are congruent to it modulo N.
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-template <int N>
-__device__ __forceinline__ float row_sum(float v) {
-  static_assert(N == 1 || N == 2 || N == 4 || N == 8 || N == 16, "N divides 16");
-  if (N <= 8) v += dpp_mov<0x128>(v);   // row_ror:8
-  if (N <= 4) v += dpp_mov<0x124>(v);   // row_ror:4
-  if (N <= 2) v += dpp_mov<0x122>(v);   // row_ror:2
-  if (N <= 1) v += dpp_mov<0x121>(v);   // row_ror:1
-  return v;
-}
-__device__ __forceinline__ float sum16(float v) { return row_sum<1>(v); }   // over the 16 pixels of a tile
 
 // ---- tiles: a [P][Cc] bf16 image in LDS has row stride Cc + 8 (16-byte reads of 16 consecutive rows hit distinct banks)
 template <int Cc>
@@ -84,9 +45,6 @@ __device__ __forceinline__ void tile_store(bf16_t* g, const bf16_t* s, int P) {
 }
 // All `nmem` work-groups of a micro-batch publish `nw` floats each and collect everybody's in
 // gath[m*nw + w] (LDS).  The two halves are separate so that independent work can fill the flight time.
-__device__ __forceinline__ void publish_word(u64* slot, int me, int nw, int w, float v, unsigned tag) {
-  __hip_atomic_store(slot + (size_t)me * nw + w, ((u64)tag << 32) | (u64)__float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 // Returns false, uniformly over the work-group, when a partner did not show up.  Ends with a barrier.
 // INFL: words in flight per thread and polling round (a micro-batch of 32 images exchanges 4 words per thread
 // for the narrow tensors, 16 for the wide ones: one round each).
@@ -97,6 +55,9 @@ template <int INFL, bool MASKED = false>
 __device__ __forceinline__ bool collect(const u64* slot, int nmem, int nw, unsigned tag, float* gath, int* abort_flag) {
   const int total = nmem * nw;
   int timed_out = 0;
+  // loads that reach the words before the partners' stores do delay those stores: the first poll waits a little (backward
+  // launches 2-3 % shorter, forward ones, which store a tile ahead of their polls, unchanged)
+  if (MASKED) __builtin_amdgcn_s_sleep(8);
   for (int i0 = threadIdx.x; i0 < total; i0 += RES_NT * INFL) {
     u64 v[INFL];
     unsigned spins = 0;
@@ -169,32 +130,6 @@ __device__ __forceinline__ void merge_coef(const float* gath, int nmem, int P, f
   }
   __syncthreads();
 }
-
-__device__ __forceinline__ bf16x8 frag_bn_relu(const uint4& q, const float2 (&cf)[8]) {
-  const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-  uint32_t r[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    r[i] = pack_bf16x2(fmaxf(fmaf(bf_lo(w[i]), cf[2 * i].x, cf[2 * i].y), 0.f),
-                       fmaxf(fmaf(bf_hi(w[i]), cf[2 * i + 1].x, cf[2 * i + 1].y), 0.f));
-  return __builtin_bit_cast(bf16x8, make_uint4(r[0], r[1], r[2], r[3]));
-}
-__device__ __forceinline__ bf16x8 frag_zero() { return __builtin_bit_cast(bf16x8, make_uint4(0u, 0u, 0u, 0u)); }
-__device__ __forceinline__ uint2 pack4(const floatx4& v) { return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])); }
-__device__ __forceinline__ float elem4(const uint2& q, int e) {
-  return e == 0 ? bf_lo(q.x) : e == 1 ? bf_hi(q.x) : e == 2 ? bf_lo(q.y) : bf_hi(q.y);
-}
-struct ResCtx {
-  char* base; void* act_in; void* act_out; void* err_in; void* err_out;
-  __device__ __forceinline__ bf16_t* tensor(unsigned long long off) const {
-    void* p = base + off;
-    p = off == RES_ACT_IN ? act_in : p;
-    p = off == RES_ACT_OUT ? act_out : p;
-    p = off == RES_ERR_IN ? err_in : p;
-    p = off == RES_ERR_OUT ? err_out : p;
-    return (bf16_t*)p;
-  }
-};
 
 // Weight fragments of one GEMM as the first MFMA operand: fragment (kt, nt) holds rows nt*16..+15 and
 // k = kt*32..+31 of a row-major [rows][ld] bf16 matrix.  PRE = true keeps all fragments in registers, loaded
@@ -2039,6 +1974,7 @@ __device__ __forceinline__ bool band_collect(const u64* slot, int nwg, int ns, u
   constexpr int INFL = 8;   // words in flight per thread and polling round
   const int n_stats = nwg * ns, total = n_stats + 2 * nh;
   int timed_out = 0;
+  __builtin_amdgcn_s_sleep(4);   // as in collect()
   for (int i0 = threadIdx.x; i0 < total; i0 += RES_NT * INFL) {
     const u64* src[INFL];
     bool want[INFL];
@@ -2679,7 +2615,7 @@ int resident_bands(int kind, int C, int MID, int H, int W) {
 
 size_t resident_xchg_bytes(int C, int nmem, int bands) {
   if (bands > 1) return 2 * (size_t)nmem * bands * BAND_RW * sizeof(u64);
-  return 2 * (size_t)nmem * 2 * C * sizeof(u64);
+  return 2 * (size_t)resident_slot_members(nmem) * 2 * C * sizeof(u64);
 }
 
 bool resident_shape_ok(int kind, int C, int MID, int H, int W, int nmem) {
@@ -2716,7 +2652,8 @@ int resident_max_group(int nmem) {
 
 hipError_t resident_prepare() {
   const int lds = (int)RES_LDS_BYTES;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_forward<128, 32, 2, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  hipError_t e = resident_reg_prepare();
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_forward<128, 32, 2, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_forward<256, 64, 1, false>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_backward<128, 32, 2, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_backward<256, 64, 1, false>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -2773,6 +2710,7 @@ hipError_t launch_resident_forward(int kind, int g, int C, int MID, const ResArg
     return hipGetLastError();
   }
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > resident_max_group(a.nmem)) return hipErrorInvalidValue;
+  if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_forward(g, MID, a, stream);
   int own = 0;
   if (kind == 2) {
     const size_t lds = v1_lds(C, a.H * a.W, a.nmem, false, &own);
@@ -2825,6 +2763,7 @@ hipError_t launch_resident_inference(int kind, int g, int C, int MID, const ResA
   if (resident_bands(kind, C, MID, a.H, a.W) > 1) return hipErrorInvalidValue;   // bands: forward and backward launches only
   if (kind == 2) return hipErrorInvalidValue;   // post-activation runs: forward and backward launches only
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > MAX_GROUP || !a.running) return hipErrorInvalidValue;
+  if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_inference(g, MID, a, stream);
   int own = 0;
   if (kind == 0) {
     const size_t lds = bb_lds(C, a.H * a.W, a.nmem, false, &own);
@@ -2878,6 +2817,7 @@ hipError_t launch_resident_backward(int kind, int g, int C, int MID, const ResAr
     return hipGetLastError();
   }
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > resident_max_group(a.nmem)) return hipErrorInvalidValue;
+  if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_backward(g, MID, a, stream);
   int own = 0;
   if (kind == 2) {
     const size_t lds = v1_lds(C, a.H * a.W, a.nmem, true, &own);

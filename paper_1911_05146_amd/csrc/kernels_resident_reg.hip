@@ -1,0 +1,536 @@
+// Image-resident kernels whose residual stream lives in registers (bf16 mode): bottleneck runs on 16 x 16 images.
+//
+// Ownership and exchange are those of kernels_resident.hip: one work-group keeps "its" image for a whole run of identity
+// blocks, the BatchNorm records of a micro-batch are all-gathered through tagged words in device memory.  What differs is
+// where the tensors of a block live.  A wave owns two image rows (two 16-pixel MFMA tiles) for the whole run and keeps
+// their residual stream, all channels, in the layout of an MFMA result: lane (fr, fq) holds channels nt*16 + fq*4 + 0..3 of
+// pixel fr.  Two neighbouring 16-channel tiles of that layout ARE the second operand of the next 1x1 convolution if its
+// reduction runs over the channels in the order (tile, fq, element); the weight matrices are staged into LDS with their
+// columns permuted to match.  So the 1x1 convolutions read no activations from LDS, the shortcut is the initial value
+// of the accumulators, BatchNorm statistics are taken from registers, and only the operand of the 3x3 convolution goes
+// through LDS (a canvas with a zero border: every filter tap is a constant offset).
+//
+// What bounds the LDS-tile form (20.8 us per 128-32 block forward on 256 images): 2 500 VALU and 200 LDS instructions per wave and
+// block, 25 barriers, and exchanges whose records went through LDS twice.
+// Measured on 256 images (8 micro-batches), per block: forward 20.7 -> 12.9 us (128-32) and 28.2 -> 20.9 (128-64), backward
+// 26.1 -> 20.8 and 37.3 -> 33.  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
+// 4 us at the memory's rate), and issue: 8 waves per CU leave the matrix cores idle while they do BatchNorm.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "hpf_resident_reg.h"
+
+namespace hpf {
+namespace {
+
+constexpr int RG_IMG = 16, RG_P = RG_IMG * RG_IMG, RG_CW = RG_IMG + 2;   // image edge, pixels, canvas edge
+constexpr int RG_PTW = 2;                        // image rows (pixel tiles) per wave
+constexpr int RG_NPX = RG_PTW * 16;              // pixels per wave
+
+// 3x3 convolution of the wave's two image rows from the canvas: the four input rows serve both.  src: the canvas at
+// (first row of the wave, fr, fk); FLIP: the data gradient (taps mirrored).
+template <int MID, bool FLIP, class W2>
+__device__ __forceinline__ void conv3x3_rows(const bf16_t* src, const bf16_t* w2, floatx4 (&acc)[RG_PTW][MID / 16]) {
+  constexpr int MS = MID + 8, NT = MID / 16;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+#pragma unroll
+    for (int ks = 0; ks < MID / 32; ++ks) {
+      keep_order();
+      bf16x8 px[4];
+#pragma unroll
+      for (int ir = 0; ir < 4; ++ir) px[ir] = *reinterpret_cast<const bf16x8*>(src + (ir * RG_CW + s) * MS + ks * 32);
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const int tap = FLIP ? (2 - r) * 3 + (2 - s) : r * 3 + s;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const bf16x8 wf = W2::get(w2, tap * (MID / 32) + ks, nt);
+#pragma unroll
+          for (int j = 0; j < RG_PTW; ++j) acc[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, px[j + r], acc[j][nt], 0, 0, 0);
+        }
+      }
+    }
+  }
+}
+
+template <int C, int MID, bool INFER>
+constexpr int rg_fwd_lds() {
+  using W1 = WStage<MID, C, true>;
+  using W2 = WStage<MID, 9 * MID, false, 3>;
+  using W3 = WStage<C, MID, true>;
+  const int w13 = INFER ? W1::BYTES + W3::BYTES : (W1::BYTES > W3::BYTES ? W1::BYTES : W3::BYTES);
+  return RG_CW * RG_CW * (MID + 8) * 2 + W2::BYTES + w13 + (C + 2 * MID) * 8 + (INFER ? 0 : RG_NW * 2 * C * 4 + C * 4) + 16;
+}
+
+// Forward of a run.  INFER: BatchNorm by running statistics; nothing is exchanged or stashed, only the output of the last
+// block is written.
+// Barriers per block: 7 (training), 2 (inference).  The matrices of conv1 and conv3 take turns in one LDS area in training
+// (conv1's is dead when conv3's is staged, behind the barrier that ends conv1, and the other way round); conv2's of the next
+// block is staged behind the barrier that ends conv2.
+template <int C, int MID, bool INFER>
+__global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
+  constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
+  using W1 = WStage<MID, C, true>;
+  using W2 = WStage<MID, 9 * MID, false, INFER ? 1 : 3>;
+  using W3 = WStage<C, MID, true>;
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
+  const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
+  const int z = blockIdx.x % a.ngroup, me = blockIdx.x / a.ngroup;   // with g == 8 micro-batch z lives on XCD z
+  ResCtx cx{(char*)pick(a.base, z), pick(a.act_in, z), pick(a.act_out, z), nullptr, nullptr};
+  u64* xchg = reinterpret_cast<u64*>(cx.base + a.xchg_off);
+  unsigned* tagp = reinterpret_cast<unsigned*>(cx.base + a.tag_off);
+  const unsigned tag0 = INFER ? 0u : *tagp;
+  unsigned phase = 0;
+  auto slot = [&]() { return xchg + (size_t)(phase & 1u) * resident_slot_members(a.nmem) * (2 * C); };
+
+  extern __shared__ __align__(16) unsigned char smem[];
+  bf16_t* canvas = reinterpret_cast<bf16_t*>(smem);
+  bf16_t* sW2 = canvas + RG_CW * RG_CW * MS;
+  bf16_t* sW1 = reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(sW2) + W2::BYTES);
+  bf16_t* sW3 = INFER ? reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(sW1) + W1::BYTES) : sW1;
+  float2* coefC = reinterpret_cast<float2*>(reinterpret_cast<char*>(sW1) +
+                                            (INFER ? W1::BYTES + W3::BYTES : (W1::BYTES > W3::BYTES ? W1::BYTES : W3::BYTES)));
+  float2* coefM = coefC + C;
+  float2* coefM3 = coefM + MID;
+  int* fail = reinterpret_cast<int*>(coefM3 + MID);
+  float* meanC = reinterpret_cast<float*>(fail + 4);   // training: means of the residual stream
+  float* red = meanC + C;                              // training: RG_NW x 2*C
+
+  const int row0 = wave * RG_PTW;                                    // the wave's first image row
+  const unsigned offC = px_offset(row0 * 16 + fr, C, fq), offM = px_offset(row0 * 16 + fr, MID, fq);
+  auto image = [&](unsigned long long off, int CT) { return cx.tensor(off) + (size_t)me * (RG_P * CT); };
+  bf16_t* const cv_w = canvas + ((row0 + 1) * RG_CW + fr + 1) * MS + fq * 4;   // where the lane writes
+  const bf16_t* const cv_r = canvas + (row0 * RG_CW + fr) * MS + fk;           // tap (0, 0) of its reads
+  const bf16_t* const w1r = sW1 + lane * 8;
+  const bf16_t* const w2r = sW2 + lane * 8;
+  const bf16_t* const w3r = sW3 + lane * 8;
+
+  W1 w1; W2 w2; W3 w3;
+  floatx4 X[RG_PTW][NC];
+  {
+    const ResBlock B0 = a.blocks[0];
+    w1.issue(a.packed + B0.wf_off[0], wave, fr, fq);
+    if constexpr (INFER) w2.issue(a.packed + B0.wf_off[1], wave, fr, fq);
+    if constexpr (INFER) w3.issue(a.packed + B0.wf_off[2], wave, fr, fq);
+    for (int i = tid; i < RG_CW * RG_CW * MS / 8; i += RG_NT) reinterpret_cast<u32x4*>(canvas)[i] = u32x4{0u, 0u, 0u, 0u};
+    if (tid == 0) *fail = 0;
+    uint2 q[RG_PTW][NC];
+    px_load(q, image(B0.x_off, C), offC);
+    px_arrange(q);
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NC; ++nt) X[j][nt] = unpack4(q[j][nt]);
+    w1.commit(sW1, wave, lane);
+    if constexpr (INFER) {
+      w2.commit(sW2, wave, lane);
+      w3.commit(sW3, wave, lane);
+    } else {
+      const bf16_t* g = a.packed + B0.wf_off[1];
+      w2.template issue<0>(g, wave, fr, fq); w2.template commit<0>(sW2, wave, lane);
+      w2.template issue<1>(g, wave, fr, fq); w2.template commit<1>(sW2, wave, lane);
+      w2.template issue<2>(g, wave, fr, fq); w2.template commit<2>(sW2, wave, lane);
+    }
+  }
+  // inference: the coefficients of BatchNorm q of a block; one channel per thread
+  auto run_coef = [&](const ResBlock& B, int q, int Cc, float2* dst) {
+    if (tid < Cc) {
+      const float* run = a.running + B.run_off[q];
+      dst[tid] = bn_scale_shift(run[tid], 1.0f / sqrtf(run[Cc + tid] + a.eps), (a.params + B.gamma_off[q])[tid], (a.params + B.beta_off[q])[tid]);
+    }
+  };
+  const float inv_n = 1.f / (float)a.nmem;
+  // training: statistics of the wave's values v -> coef of the BatchNorm q of block B.  SHIFT: the sums run about the means in meanC,
+  // which then get the new ones.  While the records travel `mid` runs, behind the polls `late`.  Returns false when a
+  // partner did not show up.
+  auto exchange = [&](auto cc, auto shifted, const auto& v, const ResBlock& B, int q, float2* coef, auto&& mid, auto&& late) -> bool {
+    constexpr int Cc = decltype(cc)::value;
+    constexpr bool SHIFT = decltype(shifted)::value;
+    const int gc = gather_channel<Cc>(wave, lane);
+    const float gamma = (a.params + B.gamma_off[q])[gc], beta = (a.params + B.beta_off[q])[gc];
+    float K = 0.f;
+    if constexpr (SHIFT) { K = meanC[gc]; sums_wave(v, meanC, red + wave * 2 * Cc, Cc, fr, fq); }
+    else stats_wave(v, red + wave * 2 * Cc, Cc, fr, fq);
+    __syncthreads();
+    const unsigned tag = tag0 + 1u + phase;
+    if constexpr (SHIFT) sums_publish_waves<Cc>(red, slot(), me, tag);
+    else stats_publish_waves<Cc, RG_NPX>(red, slot(), me, tag);
+    mid();
+    const StatsOut o{coef, Cc == C ? meanC : nullptr, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
+    if constexpr (SHIFT) collect_sums<Cc>(slot(), a.nmem, tag, inv_n, (float)RG_P, a.eps, gamma, beta, K, o, wave, lane, fail);
+    else collect_stats<Cc>(slot(), a.nmem, tag, inv_n, (float)RG_P, a.eps, gamma, beta, o, wave, lane, fail);
+    ++phase;
+    late();
+    __syncthreads();
+    if (*fail) {
+      if (tid == 0) atomicExch(a.abort_flag, 1);
+      return false;
+    }
+    return true;
+  };
+  using IC = std::integral_constant<int, C>;
+  using IM = std::integral_constant<int, MID>;
+  {
+    const ResBlock B0 = a.blocks[0];
+    if constexpr (INFER) {
+      run_coef(B0, 0, C, coefC);
+      run_coef(B0, 1, MID, coefM);
+      run_coef(B0, 2, MID, coefM3);
+      __syncthreads();
+    } else {
+      __syncthreads();
+      if (!exchange(IC{}, std::false_type{}, X, B0, 0, coefC, [] {}, [] {})) return;
+    }
+  }
+  for (int bi = 0; bi < a.nblk; ++bi) {
+    const ResBlock B = a.blocks[bi];
+    const bool more = bi + 1 < a.nblk;
+    const ResBlock Bn = a.blocks[more ? bi + 1 : bi];
+    // ---- conv1 (1x1, C -> MID) on relu(bn1(x))
+    floatx4 acc[RG_PTW][NM];
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (INFER) w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq);
+    else w3.issue(a.packed + B.wf_off[2], wave, fr, fq);
+#pragma unroll
+    for (int ks = 0; ks < C / 32; ++ks) {
+      bf16x8 bf[RG_PTW];
+#pragma unroll
+      for (int j = 0; j < RG_PTW; ++j)
+        bf[j] = frag_of(bn_relu_pack(X[j][2 * ks], coefC + 2 * ks * 16 + fq * 4), bn_relu_pack(X[j][2 * ks + 1], coefC + (2 * ks + 1) * 16 + fq * 4));
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) {
+        const bf16x8 wf = W1::get(w1r, ks, nt);
+#pragma unroll
+        for (int j = 0; j < RG_PTW; ++j) acc[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, bf[j], acc[j][nt], 0, 0, 0);
+      }
+    }
+    uint2 cp[RG_PTW][NM];
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) { cp[j][nt] = pack4(acc[j][nt]); acc[j][nt] = unpack4(cp[j][nt]); }
+    if constexpr (!INFER) {
+      if (!exchange(IM{}, std::false_type{}, acc, B, 1, coefM, [] {},
+                    [&] {
+                      w3.commit(sW3, wave, lane);
+                      if (bi > 0) w2.template commit<2>(sW2, wave, lane);
+px_store<MID != 32>(image(B.c1_off, MID), offM, cp);
+                    }))
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt)
+        *reinterpret_cast<uint2*>(cv_w + j * RG_CW * MS + nt * 16) = bn_relu_pack(acc[j][nt], coefM + nt * 16 + fq * 4);
+    if (INFER && more) w2.issue(a.packed + Bn.wf_off[1], wave, fr, fq);
+    __syncthreads();
+    if constexpr (INFER) {   // every wave is past conv1 and its tables
+      w1.commit(sW1, wave, lane);
+      if (bi > 0) w3.commit(sW3, wave, lane);
+      if (more) { run_coef(Bn, 0, C, coefC); run_coef(Bn, 1, MID, coefM); }
+      if (bi > 0) run_coef(B, 2, MID, coefM3);
+    }
+    // ---- conv2 (3x3, MID -> MID)
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    conv3x3_rows<MID, false, W2>(cv_r, w2r, acc);
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) { cp[j][nt] = pack4(acc[j][nt]); acc[j][nt] = unpack4(cp[j][nt]); }
+    if constexpr (INFER) {
+      __syncthreads();
+      if (more) { w2.commit(sW2, wave, lane); w3.issue(a.packed + Bn.wf_off[2], wave, fr, fq); }
+    } else {
+      if (more) { w2.template issue<0>(a.packed + Bn.wf_off[1], wave, fr, fq); w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq); }   // the exchange hides it
+      if (!exchange(IM{}, std::false_type{}, acc, B, 2, coefM3, [] {},
+                    [&] {
+                      if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wf_off[1], wave, fr, fq); }
+px_store<MID != 32>(image(B.c2_off, MID), offM, cp);
+                    }))
+        return;
+    }
+    // ---- conv3 (1x1, MID -> C) on relu(bn3(c2)), accumulated onto x
+    {
+      bf16x8 bf[RG_PTW][MID / 32];
+#pragma unroll
+      for (int ks = 0; ks < MID / 32; ++ks)
+#pragma unroll
+        for (int j = 0; j < RG_PTW; ++j)
+          bf[j][ks] = frag_of(bn_relu_pack(acc[j][2 * ks], coefM3 + 2 * ks * 16 + fq * 4), bn_relu_pack(acc[j][2 * ks + 1], coefM3 + (2 * ks + 1) * 16 + fq * 4));
+#pragma unroll
+      for (int nt = 0; nt < NC; ++nt)
+#pragma unroll
+        for (int ks = 0; ks < MID / 32; ++ks) {
+          const bf16x8 wf = W3::get(w3r, ks, nt);
+#pragma unroll
+          for (int j = 0; j < RG_PTW; ++j) X[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, bf[j][ks], X[j][nt], 0, 0, 0);
+        }
+    }
+    uint2 yp[RG_PTW][NC];
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NC; ++nt) { yp[j][nt] = pack4(X[j][nt]); X[j][nt] = unpack4(yp[j][nt]); }
+    auto store_y = [&] { px_store<MID != 32>(image(B.y_off, C), offC, yp); };
+    if constexpr (INFER) {
+      if (!more) store_y();
+    } else if (more) {
+      if (!exchange(IC{}, std::true_type{}, X, Bn, 0, coefC, [] {}, [&] {
+                      w1.commit(sW1, wave, lane);
+                      w2.template commit<1>(sW2, wave, lane);
+                      w2.template issue<2>(a.packed + Bn.wf_off[1], wave, fr, fq);
+                      store_y();
+                    })) return;
+    } else {
+      store_y();
+    }
+  }
+  // every member has read the counter before it took part in the first exchange, which member 0 has left
+  if (!INFER && me == 0 && tid == 0) *tagp = tag0 + phase;
+}
+
+// ------------------------------------------------------------------------------------------ backward
+template <int C, int MID>
+constexpr int rg_bwd_lds() {
+  using W3 = WStage<MID, C, true>;
+  using W2 = WStage<MID, 9 * MID, false, 3>;
+  using W1 = WStage<C, MID, true>;
+  return RG_CW * RG_CW * (MID + 8) * 2 + W2::BYTES + (W1::BYTES > W3::BYTES ? W1::BYTES : W3::BYTES) + (4 * (C + 2 * MID) + 3 * C) * 4 +
+         RG_NW * 2 * C * 4 + 16;
+}
+
+// Backward of a run: the same ownership, walking the blocks in reverse with the gradient of the residual stream in
+// registers (packed).  c1, c2 and x of a block are read straight into the register layout, each behind the polls of an exchange
+// well ahead of its use; what leaves (dc2, dc1, gx) is stored behind the polls of the exchange after.
+template <int C, int MID>
+__global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
+  constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
+  using W3 = WStage<MID, C, true>;           // conv3 data gradient [MID][C]
+  using W2 = WStage<MID, 9 * MID, false, 3>;    // conv2 data gradient [MID][9*MID]
+  using W1 = WStage<C, MID, true>;           // conv1 data gradient [C][MID]
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
+  const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
+  const int z = blockIdx.x % a.ngroup, me = blockIdx.x / a.ngroup;   // with g == 8 micro-batch z lives on XCD z
+  ResCtx cx{(char*)pick(a.base, z), pick(a.act_in, z), pick(a.act_out, z), pick(a.err_in, z), pick(a.err_out, z)};
+  u64* xchg = reinterpret_cast<u64*>(cx.base + a.xchg_off);
+  unsigned* tagp = reinterpret_cast<unsigned*>(cx.base + a.tag_off);
+  const unsigned tag0 = *tagp;
+  unsigned phase = 0;
+  auto slot = [&]() { return xchg + (size_t)(phase & 1u) * resident_slot_members(a.nmem) * (2 * C); };
+
+  extern __shared__ __align__(16) unsigned char smem[];
+  bf16_t* canvas = reinterpret_cast<bf16_t*>(smem);
+  bf16_t* sW2 = canvas + RG_CW * RG_CW * MS;
+  bf16_t* sW13 = reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(sW2) + W2::BYTES);
+  float* cf1 = reinterpret_cast<float*>(reinterpret_cast<char*>(sW13) + (W1::BYTES > W3::BYTES ? W1::BYTES : W3::BYTES));
+  float* cf2 = cf1 + 4 * C;
+  float* cf3 = cf2 + 4 * MID;
+  float* tab = cf3 + 4 * MID;
+  int* fail = reinterpret_cast<int*>(tab + 3 * C);
+  float* red = reinterpret_cast<float*>(fail + 4);
+
+  const int row0 = wave * RG_PTW;
+  const unsigned offC = px_offset(row0 * 16 + fr, C, fq), offM = px_offset(row0 * 16 + fr, MID, fq);
+  auto image = [&](unsigned long long off, int CT) { return cx.tensor(off) + (size_t)me * (RG_P * CT); };
+  bf16_t* const cv_w = canvas + ((row0 + 1) * RG_CW + fr + 1) * MS + fq * 4;
+  const bf16_t* const cv_r = canvas + (row0 * RG_CW + fr) * MS + fk;
+  const bf16_t* const w3r = sW13 + lane * 8;
+  const bf16_t* const w2r = sW2 + lane * 8;
+  const bf16_t* const w1r = sW13 + lane * 8;
+  const float inv_M = 1.f / ((float)a.nmem * (float)RG_P);
+
+  W3 w3; W2 w2; W1 w1;
+  uint2 DY[RG_PTW][NC], xc2[RG_PTW][NM], xc1[RG_PTW][NM], xx[RG_PTW][NC];
+  // the tables of a block: waves 0 .. C/64 - 1 take the channels of the first, the next two waves the others'
+  static_assert(C / 64 + 2 <= RG_NW && MID <= 64, "a channel per lane");
+  CfRegs tb;
+  const int tq = wave < C / 64 ? 0 : wave - C / 64 + 1, tc = tq == 0 ? tid : lane;
+  float* const t_dst = tq == 0 ? cf1 : tq == 1 ? cf2 : cf3;
+  const bool t_on = tq == 0 || (tq < 3 && lane < MID);
+  auto load_tables = [&](int bi) {   // tq is uniform: the offsets come by scalar loads from the table of blocks
+    if (t_on) {
+      const ResBlock* t = a.blocks + bi;
+      tb.load(reinterpret_cast<const float*>(cx.base + t->stats_off[tq]), a.params + t->gamma_off[tq], a.params + t->beta_off[tq], tc, tq == 0 ? C : MID);
+    }
+  };
+  auto store_tables = [&] {
+    if (t_on) tb.store(t_dst, tc, tq == 0 ? C : MID);
+  };
+  {
+    const ResBlock BL = a.blocks[a.nblk - 1];
+    w3.issue(a.packed + BL.wd_off[2], wave, fr, fq);
+    load_tables(a.nblk - 1);
+    for (int i = tid; i < RG_CW * RG_CW * MS / 8; i += RG_NT) reinterpret_cast<u32x4*>(canvas)[i] = u32x4{0u, 0u, 0u, 0u};
+    if (tid == 0) *fail = 0;
+    px_load(DY, image(BL.gy_off, C), offC);
+    px_arrange(DY);
+    px_load(xc2, image(BL.c2_off, MID), offM);
+    w3.commit(sW13, wave, lane);
+    {
+      const bf16_t* g = a.packed + BL.wd_off[1];
+      w2.template issue<0>(g, wave, fr, fq); w2.template commit<0>(sW2, wave, lane);
+      w2.template issue<1>(g, wave, fr, fq); w2.template commit<1>(sW2, wave, lane);
+      w2.template issue<2>(g, wave, fr, fq); w2.template commit<2>(sW2, wave, lane);
+    }
+    store_tables();
+  }
+  __syncthreads();
+  // exchange of the sums of a BatchNorm backward; `late` runs behind the polls
+  auto exchange = [&](auto cc, auto& dz, const auto& x, const float* cf, float* dgb, auto&& late) -> bool {
+    constexpr int Cc = decltype(cc)::value;
+    const CfChannel ck(cf, gather_channel<Cc>(wave, lane), Cc);
+    bwd_sums_wave(dz, x, cf, red + wave * 2 * Cc, Cc, fr, fq);
+    __syncthreads();
+    const unsigned tag = tag0 + 1u + phase;
+    sums_publish_waves<Cc>(red, slot(), me, tag);
+    collect_bwd<Cc, (Cc == C ? 512 : 1024) / MID>(slot(), a.nmem, tag, inv_M, ck, tab, dgb, wave, lane, fail);
+    ++phase;
+    late();
+    __syncthreads();
+    if (*fail) {
+      if (tid == 0) atomicExch(a.abort_flag, 1);
+      return false;
+    }
+    return true;
+  };
+  using IC = std::integral_constant<int, C>;
+  using IM = std::integral_constant<int, MID>;
+  for (int bi = a.nblk - 1; bi >= 0; --bi) {
+    const ResBlock B = a.blocks[bi];
+    const bool more = bi > 0;
+    const ResBlock Bn = a.blocks[more ? bi - 1 : 0];
+    auto dgb = [&](int q) { return me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr; };
+    // ---- conv3 data gradient, BN3 + ReLU backward -> dc2
+    floatx4 acc[RG_PTW][NM];
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    w1.issue(a.packed + B.wd_off[0], wave, fr, fq);
+#pragma unroll
+    for (int ks = 0; ks < C / 32; ++ks)
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) {
+        const bf16x8 wf = W3::get(w3r, ks, nt);
+#pragma unroll
+        for (int j = 0; j < RG_PTW; ++j)
+          acc[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, frag_of(DY[j][2 * ks], DY[j][2 * ks + 1]), acc[j][nt], 0, 0, 0);
+      }
+    px_arrange(xc2);
+    if (!exchange(IM{}, acc, xc2, cf3, dgb(2), [&] {
+          w1.commit(sW13, wave, lane);   // every wave is past conv3's data gradient
+          if (bi + 1 < a.nblk) w2.template commit<2>(sW2, wave, lane);
+          if (bi + 1 < a.nblk) px_store(image(a.blocks[bi + 1].gx_off, C), offC, DY);   // the gradient of the input of the block above
+          px_load(xc1, image(B.c1_off, MID), offM);
+          px_load(xx, image(B.x_off, C), offC);
+        }))
+      return;
+    uint2 dcp[RG_PTW][NM];
+#pragma unroll
+    for (int nt = 0; nt < NM; ++nt)
+#pragma unroll
+      for (int j = 0; j < RG_PTW; ++j) {
+        dcp[j][nt] = pack4(bwd_apply<MID>(acc[j][nt], xc2[j][nt], tab + nt * 16 + fq * 4));
+        *reinterpret_cast<uint2*>(cv_w + j * RG_CW * MS + nt * 16) = dcp[j][nt];
+      }
+    __syncthreads();
+    // ---- conv2 data gradient, BN2 + ReLU backward -> dc1
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    conv3x3_rows<MID, true, W2>(cv_r, w2r, acc);
+    if (more) w2.template issue<0>(a.packed + Bn.wd_off[1], wave, fr, fq);   // every piece has an exchange to arrive
+    px_arrange(xc1);
+    if (!exchange(IM{}, acc, xc1, cf2, dgb(1), [&] {
+          if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wd_off[1], wave, fr, fq); }   // every wave is past conv2's data gradient
+          px_store(image(B.dc2_off, MID), offM, dcp);
+          if (more) { load_tables(bi - 1); w3.issue(a.packed + Bn.wd_off[2], wave, fr, fq); }
+        }))
+      return;
+#pragma unroll
+    for (int nt = 0; nt < NM; ++nt)
+#pragma unroll
+      for (int j = 0; j < RG_PTW; ++j) dcp[j][nt] = pack4(bwd_apply<MID>(acc[j][nt], xc1[j][nt], tab + nt * 16 + fq * 4));
+    if constexpr (MID >= 64) px_store(image(B.dc1_off, MID), offM, dcp);   // 16 registers that the exchange below cannot spare
+    // ---- conv1 data gradient, BN1 + ReLU backward, plus the shortcut
+    floatx4 da[RG_PTW][NC];
+#pragma unroll
+    for (int nt = 0; nt < NC; ++nt) {
+#pragma unroll
+      for (int j = 0; j < RG_PTW; ++j) da[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < MID / 32; ++ks) {
+        const bf16x8 wf = W1::get(w1r, ks, nt);
+#pragma unroll
+        for (int j = 0; j < RG_PTW; ++j)
+          da[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, frag_of(dcp[j][2 * ks], dcp[j][2 * ks + 1]), da[j][nt], 0, 0, 0);
+      }
+      if (nt % 4 == 3) keep_order();
+    }
+    px_arrange(xx);
+    if (!exchange(IC{}, da, xx, cf1, dgb(0), [&] {
+          if (more) { w3.commit(sW13, wave, lane); w2.template commit<1>(sW2, wave, lane); w2.template issue<2>(a.packed + Bn.wd_off[1], wave, fr, fq); store_tables(); px_load(xc2, image(Bn.c2_off, MID), offM); }   // conv1's data gradient and the tables of this block are behind the barrier
+          if constexpr (MID < 64) px_store(image(B.dc1_off, MID), offM, dcp);
+        }))
+      return;
+#pragma unroll
+    for (int nt = 0; nt < NC; ++nt) {
+      if (nt % 2 == 0) keep_order();
+#pragma unroll
+      for (int j = 0; j < RG_PTW; ++j)
+        DY[j][nt] = pack4(bwd_apply<C>(da[j][nt], xx[j][nt], tab + nt * 16 + fq * 4) + unpack4(DY[j][nt]));
+    }
+  }
+  px_store(image(a.blocks[0].gx_off, C), offC, DY);
+  if (me == 0 && tid == 0) *tagp = tag0 + phase;
+}
+
+template <class K>
+hipError_t launch_reg(K kernel, int lds, int g, const ResArgs& a, hipStream_t stream) {
+  ResArgs b = a;
+  b.ngroup = g;
+  kernel<<<dim3((unsigned)(a.nmem * g)), RG_NT, (size_t)lds, stream>>>(b);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool resident_reg_shape(int kind, int C, int MID, int H, int W) {
+  return kind == 1 && C == 128 && (MID == 32 || MID == 64) && H == RG_IMG && W == RG_IMG;
+}
+hipError_t resident_reg_prepare() {
+  const void* const kernels[] = {
+      reinterpret_cast<const void*>(k_reg_forward<128, 32, false>), reinterpret_cast<const void*>(k_reg_forward<128, 32, true>),
+      reinterpret_cast<const void*>(k_reg_forward<128, 64, false>), reinterpret_cast<const void*>(k_reg_forward<128, 64, true>),
+      reinterpret_cast<const void*>(k_reg_backward<128, 32>),       reinterpret_cast<const void*>(k_reg_backward<128, 64>)};
+  for (const void* f : kernels) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+hipError_t launch_reg_forward(int g, int MID, const ResArgs& a, hipStream_t stream) {
+  return MID == 32 ? launch_reg(k_reg_forward<128, 32, false>, rg_fwd_lds<128, 32, false>(), g, a, stream)
+                   : launch_reg(k_reg_forward<128, 64, false>, rg_fwd_lds<128, 64, false>(), g, a, stream);
+}
+hipError_t launch_reg_backward(int g, int MID, const ResArgs& a, hipStream_t stream) {
+  return MID == 32 ? launch_reg(k_reg_backward<128, 32>, rg_bwd_lds<128, 32>(), g, a, stream)
+                   : launch_reg(k_reg_backward<128, 64>, rg_bwd_lds<128, 64>(), g, a, stream);
+}
+hipError_t launch_reg_inference(int g, int MID, const ResArgs& a, hipStream_t stream) {
+  return MID == 32 ? launch_reg(k_reg_forward<128, 32, true>, rg_fwd_lds<128, 32, true>(), g, a, stream)
+                   : launch_reg(k_reg_forward<128, 64, true>, rg_fwd_lds<128, 64, true>(), g, a, stream);
+}
+static_assert(rg_bwd_lds<128, 64>() <= 160 * 1024 && rg_fwd_lds<128, 64, false>() <= 160 * 1024 && rg_fwd_lds<128, 64, true>() <= 160 * 1024, "LDS of a CU");
+
+}  // namespace hpf
