@@ -200,6 +200,11 @@ hipError_t resident_reg_prepare();
 hipError_t launch_reg_forward(int g, int MID, const ResArgs& a, hipStream_t stream);
 hipError_t launch_reg_backward(int g, int MID, const ResArgs& a, hipStream_t stream);
 hipError_t launch_reg_inference(int g, int MID, const ResArgs& a, hipStream_t stream);
+// ... and for runs of basic blocks (kernels_resident_basic.hip); infer: kind 0 only
+bool resident_basic_shape(int kind, int C, int H, int W);
+hipError_t resident_basic_prepare();
+hipError_t launch_basic_forward(int kind, int g, int C, const ResArgs& a, bool infer, hipStream_t stream);
+hipError_t launch_basic_backward(int kind, int g, int C, const ResArgs& a, hipStream_t stream);
 
 hipError_t launch_conv_f32(int mode, int g, const PtrTab& src, const float* w_hwio, const PtrTab& out, const PtrTab& add,
                            const ConvGeom& geom, hipStream_t stream);

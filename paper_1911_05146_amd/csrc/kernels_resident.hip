@@ -2653,6 +2653,7 @@ int resident_max_group(int nmem) {
 hipError_t resident_prepare() {
   const int lds = (int)RES_LDS_BYTES;
   hipError_t e = resident_reg_prepare();
+  if (e == hipSuccess) e = resident_basic_prepare();
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_forward<128, 32, 2, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_forward<256, 64, 1, false>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_backward<128, 32, 2, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -2711,6 +2712,7 @@ hipError_t launch_resident_forward(int kind, int g, int C, int MID, const ResArg
   }
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > resident_max_group(a.nmem)) return hipErrorInvalidValue;
   if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_forward(g, MID, a, stream);
+  if (resident_basic_shape(kind, C, a.H, a.W)) return launch_basic_forward(kind, g, C, a, false, stream);
   int own = 0;
   if (kind == 2) {
     const size_t lds = v1_lds(C, a.H * a.W, a.nmem, false, &own);
@@ -2764,6 +2766,7 @@ hipError_t launch_resident_inference(int kind, int g, int C, int MID, const ResA
   if (kind == 2) return hipErrorInvalidValue;   // post-activation runs: forward and backward launches only
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > MAX_GROUP || !a.running) return hipErrorInvalidValue;
   if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_inference(g, MID, a, stream);
+  if (resident_basic_shape(kind, C, a.H, a.W)) return launch_basic_forward(kind, g, C, a, true, stream);
   int own = 0;
   if (kind == 0) {
     const size_t lds = bb_lds(C, a.H * a.W, a.nmem, false, &own);
@@ -2818,6 +2821,7 @@ hipError_t launch_resident_backward(int kind, int g, int C, int MID, const ResAr
   }
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > resident_max_group(a.nmem)) return hipErrorInvalidValue;
   if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_backward(g, MID, a, stream);
+  if (resident_basic_shape(kind, C, a.H, a.W)) return launch_basic_backward(kind, g, C, a, stream);
   int own = 0;
   if (kind == 2) {
     const size_t lds = v1_lds(C, a.H * a.W, a.nmem, true, &own);
