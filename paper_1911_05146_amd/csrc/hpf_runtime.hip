@@ -1278,12 +1278,13 @@ hpf_status run_graphed(hpf_partition* p, GraphSlot& slot, const std::vector<cons
 }
 
 // Image-resident kernels need every work-group of a launch on the chip at once and take up to a CU each, so the
-// launches that may run at the same time must fit the device together.  Every call with such launches holds CUs: as
-// many as its largest launch has work-groups.  Calls on one stream follow each other, so a stream holds what its
+// launches that may run at the same time must fit the device together.  Every call with such launches holds CUs
+// (resident_cus() of its largest launch).  Calls on one stream follow each other, so a stream holds what its
 // largest unfinished call does; a new call waits for other streams (largest holder first) until what is left and its
 // own need fit.  Any set of calls that can overlap then fits: the newest of them was admitted with all the others
-// counted.  (One launch at a time, as before, made the partitions of a chain, which use 16 of 256 CUs at 16 images per
-// micro-batch, run one after the other: a chain of four partitions of ResNet-110 took 17.3 ms per batch.)
+// counted.  A call keeps the lock from its admission until its events are on record, or two threads could be admitted
+// to the same CUs.  (One launch at a time, as before, made the partitions of a chain, which use 16 of 256 CUs at 16
+// images per micro-batch, run one after the other: a chain of four partitions of ResNet-110 took 17.3 ms per batch.)
 std::mutex g_res_mu;
 struct ResidentHold { int dev; hipStream_t stream; hipEvent_t ev; const hpf_partition* owner; int cus; };
 std::vector<ResidentHold> g_res;   // at most one entry per stream: its latest call (whose event covers the earlier ones)
@@ -1295,10 +1296,13 @@ const char* const kNoCaptureMsg =
     "image-resident launches (fusion level 2) cannot be recorded into a caller's graph capture: call "
     "hpf_partition_set_fusion(p, 1) for partitions whose calls are captured";
 
-// need: work-groups of the call's largest image-resident launch
+// CUs that a launch of so many work-groups takes.  They are dealt to the eight dies in turn and stay on theirs, so each
+// die must have room for its share: launches of 100 and 156 work-groups fill 256 CUs but put 13 + 20 on one die of 32.
+int resident_cus(int wgs) { return (wgs + 7) / 8 * 8; }
+
+// need: CUs of the call's largest image-resident launch; g_res_mu is held
 hpf_status resident_enter(hpf_partition* p, hipStream_t s, int need) {
   if (!p->resident()) return HPF_OK;
-  std::lock_guard<std::mutex> lk(g_res_mu);
   int held = 0;
   for (const ResidentHold& h : g_res)
     if (h.dev == p->dev && h.stream != s) held += h.cus;
@@ -1329,7 +1333,6 @@ hpf_status resident_enter(hpf_partition* p, hipStream_t s, int need) {
 // own, so waiting on it never waits for too little)
 void resident_leave(hpf_partition* p, hipStream_t s, hipEvent_t done, int need) {
   if (!p->resident()) return;
-  std::lock_guard<std::mutex> lk(g_res_mu);
   for (ResidentHold& h : g_res)
     if (h.dev == p->dev && h.stream == s) {
       h.ev = done; h.owner = p;
@@ -1513,7 +1516,9 @@ hpf_status forward_group(hpf_partition* p, int32_t mb_first, int32_t count, cons
     if (st != HPF_OK) return st;
   }
   const int gmax = p->group_limit();
-  const int res_need = p->res_wgs * (count < gmax ? count : gmax);
+  const int res_need = resident_cus(p->res_wgs * (count < gmax ? count : gmax));
+  std::unique_lock<std::mutex> admission(g_res_mu, std::defer_lock);
+  if (p->resident()) admission.lock();
   {
     const hpf_status st = resident_enter(p, s, res_need);
     if (st != HPF_OK) return st;
@@ -1593,7 +1598,9 @@ hpf_status backward_group(hpf_partition* p, int32_t mb_first, int32_t count, con
       if (st != HPF_OK) return st;
     }
   const int gmax = p->group_limit();
-  const int res_need = p->res_wgs * (count < gmax ? count : gmax);
+  const int res_need = resident_cus(p->res_wgs * (count < gmax ? count : gmax));
+  std::unique_lock<std::mutex> admission(g_res_mu, std::defer_lock);
+  if (p->resident()) admission.lock();
   {
     const hpf_status st = resident_enter(p, s, res_need);
     if (st != HPF_OK) return st;

@@ -358,6 +358,41 @@ def test_directions_on_different_streams_wait_for_each_other(gpu, oracle):
     part.close()
 
 
+def test_resident_launches_that_fill_the_device_between_them(gpu, oracle):
+    """Two partitions on two streams whose image-resident launches have 100 and 156 work-groups: as many as the device has
+    CUs, but not evenly over its dies, so the library must not let them run side by side.  Same results as one by one."""
+    import torch
+    from parity import device_inputs, rel_err
+    from paper_1911_05146_amd import hpf
+    blk = W.Block(W.BOTTLENECK, 128, 32, 128, 1)
+    parts, inputs, streams = [], [], [torch.cuda.Stream(), torch.cuda.Stream()]
+    for images in (25, 39):
+        spec = W.PartitionSpec(name=f"fill-b{images}", in_h=16, in_w=16, in_c=128, blocks=(blk,) * 4, microbatch=images,
+                               num_microbatches=4, seed=44)
+        inp = W.make_inputs(spec, randomize_affine=True)
+        inputs.append(device_inputs(spec, inp, "bf16")[1])
+        parts.append(hpf.Partition(spec, inp.params, hpf.HPF_BF16))
+
+    def batch(i, stream):
+        parts[i].grad_accum_zero(stream=stream)
+        outs = parts[i].forward_microbatches(0, inputs[i]["act_in"], None, stream=stream)
+        return outs + parts[i].backward_microbatches(0, 4, inputs[i]["err_in"], stream=stream)
+    want = []
+    for i in range(2):
+        outs = batch(i, streams[0])
+        torch.cuda.synchronize()
+        want.append(([o.clone() for o in outs], parts[i].grad_accum_read()))
+    torch.cuda.synchronize()
+    for _ in range(3):
+        got = [batch(i, streams[i]) for i in range(2)]
+        torch.cuda.synchronize()
+        for i in range(2):
+            assert all(torch.equal(x, y) for x, y in zip(got[i], want[i][0]))
+            assert rel_err(parts[i].grad_accum_read(), want[i][1]) < 1e-5   # fp32 atomics, order may differ
+    for p in parts:
+        p.close()
+
+
 def test_two_batches_accumulate_zero_and_step(gpu, oracle):
     """Gradient buffer life cycle over consecutive batches on one handle."""
     from parity import run_gpu_step, rel_err
