@@ -112,6 +112,18 @@ def test_runs_with_weights_through_lds_layerwise(gpu, oracle):
             layerwise(oracle, spec, "bf16", grouped=grouped, blockwise=blockwise)
 
 
+@pytest.mark.parametrize("images", [1, 31, 33])
+@pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 16, 32), (W.BASIC, 32, 32, 16), (W.BASIC, 64, 64, 8),
+                                           (W.POSTACT, 16, 16, 32), (W.POSTACT, 32, 32, 16), (W.POSTACT, 64, 64, 8),
+                                           (W.BOTTLENECK, 128, 32, 16), (W.BOTTLENECK, 128, 64, 16)])
+def test_register_resident_runs_around_the_polled_chunk_layerwise(gpu, oracle, kind, c, mid, hw, images):
+    """Image-resident runs with the residual stream in registers collect the BatchNorm words of 32 images at a time: one image (no
+    partner), a chunk that is not full and one word beyond a chunk.  Two blocks: the first and the last."""
+    spec = W.PartitionSpec(name=f"reg-{kind}-{c}@{hw}x{hw}-b{images}", in_h=hw, in_w=hw, in_c=c,
+                           blocks=(W.Block(kind, c, mid, c, 1),) * 2, microbatch=images, num_microbatches=1, seed=43)
+    layerwise(oracle, spec, "bf16", blockwise=False)
+
+
 def test_convolutions_with_split_reductions_layerwise(gpu, oracle):
     """Plain 3x3 convolution units with long reductions into few output tiles (VGG-16's last two groups: 512 channels on
     4x4 and 2x2 pixels) run with every reduction split over two to four work-groups whose fp32 partial sums a second
