@@ -16,6 +16,10 @@
 //
 // All work-groups of a micro-batch must be on the chip together; the launchers check the grid against
 // the number of CUs, and a bounded spin turns a missing partner into an error flag instead of a hang.
+//
+// Which runs: those that the kernels with the residual stream in registers do not take (kernels_resident_reg.hip: bottlenecks on 16x16
+// images; kernels_resident_basic.hip: basic blocks at 16x32x32, 32x16x16 and 64x8x8), i.e. 256-64 bottlenecks, 128-wide
+// ones on other image sizes, basic blocks on other image sizes, row bands.  The weight gradients of all runs are here.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -1183,7 +1187,6 @@ __global__ void __launch_bounds__(RES_NT) k_bb_forward(const ResArgs a, const in
   constexpr int XS = C + 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
-  // the 16-channel shape is 32 x 32 pixels only: constants instead of kernel arguments (fewer address temporaries)
   const int H = a.H, W = a.W;
   const int P = H * W, npt = P >> 4;
   const int z = blockIdx.x % a.ngroup, me = blockIdx.x / a.ngroup;
@@ -1455,8 +1458,7 @@ __global__ void __launch_bounds__(rw_threads(C)) k_bb_wgrad(const ResWgArgs a) {
 // block; two exchanges per block and direction (statistics of c1 and c2; sums of the two BatchNorm backward passes).
 // Backward: dz = dy*[y > 0] is the gradient of the shortcut and, through BN2's backward (no ReLU of its own), of c2.
 // ResBlock fields used: x, c1, c2, y, gy, dc1, dc2, gx and entries 0 / 1 of the per-BatchNorm / per-convolution arrays.
-// The weight gradients of the 32- and 64-channel runs have a launch of their own (k_v1_wgrad, further down), those of
-// the 16-channel runs go through the grouped per-layer launch; inference goes through the per-layer kernels.
+// The weight gradients have a launch of their own (k_v1_wgrad, further down); inference goes through the per-layer kernels.
 
 // y = relu(c2*scale + shift + x), tile to tile (written over x)
 template <int Cc>
@@ -1484,7 +1486,6 @@ __global__ void __launch_bounds__(RES_NT) k_v1_forward(const ResArgs a, const in
   constexpr int XS = C + 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
-  // the 16-channel shape is 32 x 32 pixels only: constants instead of kernel arguments (fewer address temporaries)
   const int H = a.H, W = a.W;
   const int P = H * W, npt = P >> 4;
   const int z = blockIdx.x % a.ngroup, me = blockIdx.x / a.ngroup;
@@ -1666,7 +1667,6 @@ __global__ void __launch_bounds__(RES_NT) k_v1_backward(const ResArgs a, const i
   constexpr int XS = C + 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
-  // the 16-channel shape is 32 x 32 pixels only: constants instead of kernel arguments (fewer address temporaries)
   const int H = a.H, W = a.W;
   const int P = H * W, npt = P >> 4;
   const int z = blockIdx.x % a.ngroup, me = blockIdx.x / a.ngroup;
