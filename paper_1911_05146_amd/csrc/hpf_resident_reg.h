@@ -171,7 +171,9 @@ __device__ __forceinline__ float halve_sum(const float (&s1)[4], const float (&s
 }
 // ---- BatchNorm statistics from registers.  v: the wave's rounded values.  Sums run about the wave's first pixel, so a large common
 // offset does not cancel; the wave's {mean, M2} over its pixels go to red: the wave's row of 2*Cc floats, at the wave's
-// first channel.
+// first channel.  Plain sums about a value that all work-groups have at hand (the mean of the block before) would be 0.3 us (128-32) / 1.3 us
+// (128-64) per block faster, but the variance then loses a factor (distance / sigma)^2 of its digits: invstd of a channel that a block
+// moves by 40 sigma was off by 1.6e-4 instead of 1e-7.
 template <int PTW, int NTL>
 __device__ __forceinline__ void stats_wave(const floatx4 (&v)[PTW][NTL], float* red, int Cc, int fr, int fq) {
   const bool b3 = fr & 8, b2 = fr & 4, b1 = fr & 2;
@@ -198,32 +200,7 @@ __device__ __forceinline__ void stats_wave(const floatx4 (&v)[PTW][NTL], float* 
     if (!(fr & 1)) dst[nt * 16] = o;
   }
 }
-// The same with a shift that all work-groups know (shift: the channels' values in LDS): plain sums {S1, S2} about it, which the merges
-// of waves and members only add up.  One pass less over the registers than finding a shift of the wave's own.
-template <int PTW, int NTL>
-__device__ __forceinline__ void sums_wave(const floatx4 (&v)[PTW][NTL], const float* shift, float* red, int Cc, int fr, int fq) {
-  const bool b3 = fr & 8, b2 = fr & 4, b1 = fr & 2;
-  float* dst = red + (b3 ? Cc : 0) + fq * 4 + ((fr >> 1) & 3);
-#pragma unroll
-  for (int nt = 0; nt < NTL; ++nt) {
-    const float4 kq = *reinterpret_cast<const float4*>(shift + nt * 16 + fq * 4);
-    const float K[4] = {kq.x, kq.y, kq.z, kq.w};
-    float s1[4], s2[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-#pragma unroll
-      for (int j = 0; j < PTW; ++j) {
-        const float d = v[j][nt][e] - K[e];
-        s1[e] = j == 0 ? d : s1[e] + d;
-        s2[e] = j == 0 ? d * d : fmaf(d, d, s2[e]);
-      }
-    }
-    const float r = halve_sum(s1, s2, b3, b2, b1);
-    if (!(fr & 1)) dst[nt * 16] = r;
-    if (nt % 2) keep_order();
-  }
-}
-// ... published by Cc threads as words 2c and 2c + 1
+// Sums {S1, S2} of the waves (rows of red) added up, published by Cc threads per sum as words 2c and 2c + 1
 template <int Cc, int NPW = RG_NW>   // NPW: waves along the pixels = rows of red
 __device__ __forceinline__ void sums_publish_waves(const float* red, u64* slot, int me, unsigned tag) {
   if ((int)threadIdx.x < 2 * Cc) {
@@ -288,7 +265,7 @@ __device__ __forceinline__ float inv_sqrt(float x) {
   const float r = __builtin_amdgcn_rsqf(x);
   return fmaf(0.5f * r, fmaf(-x * r, r, 1.f), r);
 }
-struct StatsOut { float2* coef; float* mean; float* stats; };   // stats: member 0 only, else null
+struct StatsOut { float2* coef; float* stats; };   // stats: member 0 only, else null
 template <int Cc>
 __device__ __forceinline__ void stats_out(const StatsOut& o, float mean, float var_eps, float gamma, float beta, int wave, int lane) {
   using G = Gather<Cc>;
@@ -297,7 +274,6 @@ __device__ __forceinline__ void stats_out(const StatsOut& o, float mean, float v
   if (mg == 0 && !(wl & 1)) {
     const int c = (wave * G::WPW + wl) >> 1;
     o.coef[c] = bn_scale_shift(mean, is, gamma, beta);
-    if (o.mean) o.mean[c] = mean;
     if (o.stats) { o.stats[c] = mean; o.stats[Cc + c] = is; }
   }
 }
@@ -329,25 +305,6 @@ __device__ __forceinline__ void collect_stats(const u64* slot, int nmem, unsigne
   const float q = fmaf(-s1 * inv_n, s1, s2);
   const float M2 = fmaf(P, q, dpp_mov<0xb1>(sw));   // even lanes: the neighbour's sum of M2
   stats_out<Cc>(o, fmaf(s1, inv_n, m0), fmaf(M2, inv_n / P, eps), gamma, beta, wave, lane);
-}
-// the same for {S1, S2} records about `shift` (this lane's channel)
-template <int Cc>
-__device__ __forceinline__ void collect_sums(const u64* slot, int nmem, unsigned tag, float inv_n, float P, float eps, float gamma, float beta, float shift,
-                                             const StatsOut& o, int wave, int lane, int* fail) {
-  using G = Gather<Cc>;
-  u64 v[G::INFL];
-  float sw = 0.f;
-  for (int b = 0; b < nmem; b += G::CHUNK) {
-    G::poll(v, slot, b, nmem, tag, wave, lane, fail);
-    const int mine = G::lane_members(b, nmem, lane);
-    float f[G::INFL];
-#pragma unroll
-    for (int i = 0; i < G::INFL; ++i) f[i] = i < mine ? __uint_as_float((unsigned)v[i]) : 0.f;
-    sw += tree_sum(f);
-  }
-  sw = lanes_sum<G::WPW>(sw) * (inv_n / P);   // even lanes: mean - shift; odd lanes: mean square about it
-  const float var = fmaxf(fmaf(-sw, sw, dpp_mov<0xb1>(sw)), 0.f);
-  stats_out<Cc>(o, shift + sw, var + eps, gamma, beta, wave, lane);
 }
 // the channel whose words this lane collects
 template <int Cc>

@@ -104,7 +104,7 @@ struct Lane {
 template <int C, bool INFER>
 constexpr int basic_fwd_lds() {
   using G = Geo<C>;
-  return G::CANVAS + G::W::BYTES + 2 * C * 8 + (INFER ? 0 : C * 4 + G::NPW * 2 * C * 4) + 16;
+  return G::CANVAS + G::W::BYTES + 2 * C * 8 + (INFER ? 0 : G::NPW * 2 * C * 4) + 16;
 }
 
 template <int C, bool POST, bool INFER>
@@ -129,8 +129,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
   float2* coef1 = reinterpret_cast<float2*>(smem + G::CANVAS + G::W::BYTES);   // of the first / second BatchNorm
   float2* coef2 = coef1 + C;
   int* fail = reinterpret_cast<int*>(coef2 + C);
-  float* meanX = reinterpret_cast<float*>(fail + 4);   // pre-activation training: means of the residual stream
-  float* red = meanX + C;                              // NPW x 2*C
+  float* red = reinterpret_cast<float*>(fail + 4);     // training: NPW x 2*C
   float* const red_w = red + L.pw * 2 * C + L.cg * NTW * 16;
   const bf16_t* const wr = sW + L.cg * NTW * 512 + lane * 8;
   const int c_at = L.cg * NTW * 16 + fq * 4;           // the lane's first channel
@@ -163,22 +162,16 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
       dst[tid] = bn_scale_shift(run[tid], 1.0f / sqrtf(run[C + tid] + a.eps), (a.params + B.gamma_off[q])[tid], (a.params + B.beta_off[q])[tid]);
     }
   };
-  // statistics of v -> coef of BatchNorm q of block B; `late` runs behind the polls.  SHIFT: sums about meanX (the residual
-  // stream's means, replaced by the new ones)
-  auto exchange = [&](auto shifted, const floatx4 (&v)[PTW][NTW], const ResBlock& B, int q, float2* coef, float* mean, auto&& late) -> bool {
-    constexpr bool SHIFT = decltype(shifted)::value;
+  // statistics of v -> coef of BatchNorm q of block B; `late` runs behind the polls
+  auto exchange = [&](const floatx4 (&v)[PTW][NTW], const ResBlock& B, int q, float2* coef, auto&& late) -> bool {
     const int gc = gather_channel<C>(wave, lane);
     const float gamma = (a.params + B.gamma_off[q])[gc], beta = (a.params + B.beta_off[q])[gc];
-    float K = 0.f;
-    if constexpr (SHIFT) { K = meanX[gc]; sums_wave(v, meanX + L.cg * NTW * 16, red_w, C, fr, fq); }
-    else stats_wave(v, red_w, C, fr, fq);
+    stats_wave(v, red_w, C, fr, fq);
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
-    if constexpr (SHIFT) sums_publish_waves<C, G::NPW>(red, slot(), me, tag);
-    else stats_publish_waves<C, G::NPX, G::NPW>(red, slot(), me, tag);
-    const StatsOut o{coef, mean, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
-    if constexpr (SHIFT) collect_sums<C>(slot(), a.nmem, tag, inv_n, (float)G::P, a.eps, gamma, beta, K, o, wave, lane, fail);
-    else collect_stats<C>(slot(), a.nmem, tag, inv_n, (float)G::P, a.eps, gamma, beta, o, wave, lane, fail);
+    stats_publish_waves<C, G::NPX, G::NPW>(red, slot(), me, tag);
+    const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
+    collect_stats<C>(slot(), a.nmem, tag, inv_n, (float)G::P, a.eps, gamma, beta, o, wave, lane, fail);
     ++phase;
     late();
     __syncthreads();
@@ -188,8 +181,6 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     }
     return true;
   };
-  using Plain = std::false_type;
-  using Shifted = std::true_type;
   {
     const ResBlock B0 = a.blocks[0];
     w.issue(a.packed + B0.wf_off[0], wave, fr, fq);
@@ -205,7 +196,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     w.commit(sW, wave, lane);
     __syncthreads();
     if constexpr (!POST && !INFER)
-      if (!exchange(Plain{}, X, B0, 0, coef1, meanX, [] {})) return;
+      if (!exchange(X, B0, 0, coef1, [] {})) return;
   }
   for (int bi = 0; bi < a.nblk; ++bi) {
     const ResBlock B = a.blocks[bi];
@@ -237,7 +228,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
       w.commit(sW, wave, lane);
     } else {
       w.issue(a.packed + B.wf_off[1], wave, fr, fq);   // the exchange hides it
-      if (!exchange(Plain{}, acc, B, POST ? 0 : 1, coef2, nullptr, [&] {
+      if (!exchange(acc, B, POST ? 0 : 1, coef2, [&] {
             w.commit(sW, wave, lane);
             if constexpr (POST) { if (bi > 0) px_store(image(a.blocks[bi - 1].y_off), L.off, pk); }   // the block before's output
             px_store(image(B.c1_off), L.off, cp);
@@ -261,7 +252,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
         w.commit(sW, wave, lane);
       } else if (more) {
         w.issue(a.packed + Bn.wf_off[0], wave, fr, fq);
-        if (!exchange(Shifted{}, X, Bn, 0, coef1, meanX, [&] {
+        if (!exchange(X, Bn, 0, coef1, [&] {
               w.commit(sW, wave, lane);
               px_store(image(B.y_off), L.off, cp);
             }))
@@ -277,7 +268,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
       conv3x3<C, false>(canvas + L.cr, wr, fq, acc);
       round_to(acc, cp);
       if (more) w.issue(a.packed + Bn.wf_off[0], wave, fr, fq);
-      if (!exchange(Plain{}, acc, B, 1, coef1, nullptr, [&] {
+      if (!exchange(acc, B, 1, coef1, [&] {
             if (more) w.commit(sW, wave, lane);
             px_store(image(B.c2_off), L.off, cp);
           }))

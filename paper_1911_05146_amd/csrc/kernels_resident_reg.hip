@@ -61,7 +61,7 @@ constexpr int rg_fwd_lds() {
   using W2 = WStage<MID, 9 * MID, false, 3>;
   using W3 = WStage<C, MID, true>;
   const int w13 = INFER ? W1::BYTES + W3::BYTES : (W1::BYTES > W3::BYTES ? W1::BYTES : W3::BYTES);
-  return RG_CW * RG_CW * (MID + 8) * 2 + W2::BYTES + w13 + (C + 2 * MID) * 8 + (INFER ? 0 : RG_NW * 2 * C * 4 + C * 4) + 16;
+  return RG_CW * RG_CW * (MID + 8) * 2 + W2::BYTES + w13 + (C + 2 * MID) * 8 + (INFER ? 0 : RG_NW * 2 * C * 4) + 16;
 }
 
 // Forward of a run.  INFER: BatchNorm by running statistics; nothing is exchanged or stashed, only the output of the last
@@ -95,8 +95,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   float2* coefM = coefC + C;
   float2* coefM3 = coefM + MID;
   int* fail = reinterpret_cast<int*>(coefM3 + MID);
-  float* meanC = reinterpret_cast<float*>(fail + 4);   // training: means of the residual stream
-  float* red = meanC + C;                              // training: RG_NW x 2*C
+  float* red = reinterpret_cast<float*>(fail + 4);   // training: RG_NW x 2*C
 
   const int row0 = wave * RG_PTW;                                    // the wave's first image row
   const unsigned offC = px_offset(row0 * 16 + fr, C, fq), offM = px_offset(row0 * 16 + fr, MID, fq);
@@ -142,25 +141,19 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
     }
   };
   const float inv_n = 1.f / (float)a.nmem;
-  // training: statistics of the wave's values v -> coef of the BatchNorm q of block B.  SHIFT: the sums run about the means in meanC,
-  // which then get the new ones.  While the records travel `mid` runs, behind the polls `late`.  Returns false when a
-  // partner did not show up.
-  auto exchange = [&](auto cc, auto shifted, const auto& v, const ResBlock& B, int q, float2* coef, auto&& mid, auto&& late) -> bool {
+  // training: statistics of the wave's values v -> coef of the BatchNorm q of block B.  While the records travel `mid` runs, behind
+  // the polls `late`.  Returns false when a partner did not show up.
+  auto exchange = [&](auto cc, const auto& v, const ResBlock& B, int q, float2* coef, auto&& mid, auto&& late) -> bool {
     constexpr int Cc = decltype(cc)::value;
-    constexpr bool SHIFT = decltype(shifted)::value;
     const int gc = gather_channel<Cc>(wave, lane);
     const float gamma = (a.params + B.gamma_off[q])[gc], beta = (a.params + B.beta_off[q])[gc];
-    float K = 0.f;
-    if constexpr (SHIFT) { K = meanC[gc]; sums_wave(v, meanC, red + wave * 2 * Cc, Cc, fr, fq); }
-    else stats_wave(v, red + wave * 2 * Cc, Cc, fr, fq);
+    stats_wave(v, red + wave * 2 * Cc, Cc, fr, fq);
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
-    if constexpr (SHIFT) sums_publish_waves<Cc>(red, slot(), me, tag);
-    else stats_publish_waves<Cc, RG_NPX>(red, slot(), me, tag);
+    stats_publish_waves<Cc, RG_NPX>(red, slot(), me, tag);
     mid();
-    const StatsOut o{coef, Cc == C ? meanC : nullptr, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
-    if constexpr (SHIFT) collect_sums<Cc>(slot(), a.nmem, tag, inv_n, (float)RG_P, a.eps, gamma, beta, K, o, wave, lane, fail);
-    else collect_stats<Cc>(slot(), a.nmem, tag, inv_n, (float)RG_P, a.eps, gamma, beta, o, wave, lane, fail);
+    const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
+    collect_stats<Cc>(slot(), a.nmem, tag, inv_n, (float)RG_P, a.eps, gamma, beta, o, wave, lane, fail);
     ++phase;
     late();
     __syncthreads();
@@ -181,7 +174,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
       __syncthreads();
     } else {
       __syncthreads();
-      if (!exchange(IC{}, std::false_type{}, X, B0, 0, coefC, [] {}, [] {})) return;
+      if (!exchange(IC{}, X, B0, 0, coefC, [] {}, [] {})) return;
     }
   }
   for (int bi = 0; bi < a.nblk; ++bi) {
@@ -215,7 +208,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
 #pragma unroll
       for (int nt = 0; nt < NM; ++nt) { cp[j][nt] = pack4(acc[j][nt]); acc[j][nt] = unpack4(cp[j][nt]); }
     if constexpr (!INFER) {
-      if (!exchange(IM{}, std::false_type{}, acc, B, 1, coefM, [] {},
+      if (!exchange(IM{}, acc, B, 1, coefM, [] {},
                     [&] {
                       w3.commit(sW3, wave, lane);
                       if (bi > 0) w2.template commit<2>(sW2, wave, lane);
@@ -251,7 +244,7 @@ px_store<MID != 32>(image(B.c1_off, MID), offM, cp);
       if (more) { w2.commit(sW2, wave, lane); w3.issue(a.packed + Bn.wf_off[2], wave, fr, fq); }
     } else {
       if (more) { w2.template issue<0>(a.packed + Bn.wf_off[1], wave, fr, fq); w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq); }   // the exchange hides it
-      if (!exchange(IM{}, std::false_type{}, acc, B, 2, coefM3, [] {},
+      if (!exchange(IM{}, acc, B, 2, coefM3, [] {},
                     [&] {
                       if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wf_off[1], wave, fr, fq); }
 px_store<MID != 32>(image(B.c2_off, MID), offM, cp);
@@ -284,7 +277,7 @@ px_store<MID != 32>(image(B.c2_off, MID), offM, cp);
     if constexpr (INFER) {
       if (!more) store_y();
     } else if (more) {
-      if (!exchange(IC{}, std::true_type{}, X, Bn, 0, coefC, [] {}, [&] {
+      if (!exchange(IC{}, X, Bn, 0, coefC, [] {}, [&] {
                       w1.commit(sW1, wave, lane);
                       w2.template commit<1>(sW2, wave, lane);
                       w2.template issue<2>(a.packed + Bn.wf_off[1], wave, fr, fq);

@@ -124,6 +124,36 @@ def test_register_resident_runs_around_the_polled_chunk_layerwise(gpu, oracle, k
     layerwise(oracle, spec, "bf16", blockwise=False)
 
 
+@pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 16, 32), (W.BASIC, 32, 32, 16), (W.BASIC, 64, 64, 8),
+                                           (W.BOTTLENECK, 128, 32, 16), (W.BOTTLENECK, 128, 64, 16)])
+def test_statistics_of_channels_whose_mean_jumps_between_blocks(gpu, oracle, kind, c, mid, hw):
+    """The first block of a run moves every fourth channel of the residual stream by 40 standard deviations.  The next block's
+    statistics must not feel it: squares summed about any value d standard deviations from the mean lose a factor d^2 = 1600
+    of the variance's digits (measured then: 1.1e-4 ... 1.6e-4).  Bound for invstd: about 20 roundings of 2^-24 in a sum of squares about one of its own
+    pixels (amplified by 1 + 4^2 at most), half of that in the root: 1e-5."""
+    from parity import run_gpu_step
+    from teacher import layerwise_check
+    spec = W.PartitionSpec(name=f"jump-{kind}-{c}-{mid}@{hw}x{hw}", in_h=hw, in_w=hw, in_c=c, blocks=(W.Block(kind, c, mid, c, 1),) * 2,
+                           microbatch=5, num_microbatches=1, seed=47)
+    print(f"\n[case] {spec.name}", flush=True)
+    inp = W.make_inputs(spec, randomize_affine=True)
+    lay = {e.name: e for e in W.param_layout(spec)}
+    P = lambda n: inp.params[lay[n].offset:lay[n].offset + lay[n].size].reshape(lay[n].shape)
+    last = 2 if kind == W.BASIC else 3
+    P(f"block0.bn{last}.gamma")[:] = 0.02      # the last convolution's operand is 4 +- 0.02 everywhere
+    P(f"block0.bn{last}.beta")[:] = 4.0
+    w = P(f"block0.W{last}")
+    w[..., ::4] = 0.0
+    w[w.shape[0] // 2, w.shape[1] // 2, :, ::4] = 10.0 / w.shape[2]   # the centre tap alone, or the border would differ
+    seen, res = run_gpu_step(spec, inp, "bf16", grouped=True, keep=True)
+    part = res.pop("part")
+    try:
+        rep = layerwise_check(oracle, part, spec, seen, res, "bf16")
+    finally:
+        part.close()
+    assert rep.worst["bn.invstd"][0] <= 1e-5, rep.worst["bn.invstd"]
+
+
 def test_convolutions_with_split_reductions_layerwise(gpu, oracle):
     """Plain 3x3 convolution units with long reductions into few output tiles (VGG-16's last two groups: 512 channels on
     4x4 and 2x2 pixels) run with every reduction split over two to four work-groups whose fp32 partial sums a second
