@@ -260,10 +260,11 @@ struct Gather {
   // how many of v[] are members of the micro-batch
   static __device__ __forceinline__ int lane_members(int m0, int nmem, int lane) { return (nmem - m0 - lane / WPW + MG - 1) / MG; }
 };
-// 1 / sqrt(x): the hardware's estimate (1 ulp) and one Newton step
+// 1 / sqrt(x): the hardware's estimate (1 ulp) and one Newton step, which has no meaning for x = 0 and x = infinity (0 * infinity): there the
+// estimate is the value
 __device__ __forceinline__ float inv_sqrt(float x) {
   const float r = __builtin_amdgcn_rsqf(x);
-  return fmaf(0.5f * r, fmaf(-x * r, r, 1.f), r);
+  return r > 0.f && r < INFINITY ? fmaf(0.5f * r, fmaf(-x * r, r, 1.f), r) : r;
 }
 struct StatsOut { float2* coef; float* stats; };   // stats: member 0 only, else null
 template <int Cc>

@@ -154,6 +154,31 @@ def test_statistics_of_channels_whose_mean_jumps_between_blocks(gpu, oracle, kin
     assert rep.worst["bn.invstd"][0] <= 1e-5, rep.worst["bn.invstd"]
 
 
+@pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 16, 32), (W.BASIC, 32, 32, 16), (W.BASIC, 64, 64, 8),
+                                           (W.BOTTLENECK, 128, 32, 16), (W.BOTTLENECK, 128, 64, 16)])
+def test_a_channel_whose_variance_overflows_is_switched_off(gpu, kind, c, mid, hw):
+    """Values of +-3e18 have a sum of squares beyond float32: the variance is infinite, 1 / sqrt of it is 0 (not NaN), the channel's
+    BatchNorm gives beta and every other channel is as without it."""
+    import torch
+    spec = W.PartitionSpec(name=f"overflow-{kind}-{c}-{mid}@{hw}x{hw}", in_h=hw, in_w=hw, in_c=c, blocks=(W.Block(kind, c, mid, c, 1),),
+                           microbatch=5, num_microbatches=1, seed=53)
+    print(f"\n[case] {spec.name}", flush=True)
+    inp = W.make_inputs(spec, randomize_affine=True)
+    x = inp.act_in[0].copy().reshape(5, hw * hw, c)
+    x[..., 0] = np.where(np.arange(hw * hw) % 2, 3e18, -3e18)
+    part = gpu.Partition(spec, inp.params)
+    try:
+        y = part.forward_microbatch(0, torch.from_numpy(x.reshape(inp.act_in[0].shape)).to("cuda:0", torch.bfloat16))
+        torch.cuda.synchronize()
+        st = part.stash_read(0, 0, gpu.HPF_T_STATS0)
+        v = torch.from_numpy(x).to(torch.bfloat16).double().numpy().reshape(-1, c)[:, 1:]
+        assert st[c] == 0.0
+        assert np.allclose(st[c + 1:], 1.0 / np.sqrt(v.var(axis=0) + spec.bn_eps), rtol=1e-5)
+        assert bool(torch.isfinite(y).all())
+    finally:
+        part.close()
+
+
 def test_convolutions_with_split_reductions_layerwise(gpu, oracle):
     """Plain 3x3 convolution units with long reductions into few output tiles (VGG-16's last two groups: 512 channels on
     4x4 and 2x2 pixels) run with every reduction split over two to four work-groups whose fp32 partial sums a second
