@@ -1,6 +1,7 @@
 // Device-side helpers shared by the image-resident kernels (kernels_resident.hip, kernels_resident_reg.hip).
 #pragma once
 #include "hpf_device.h"
+#include "hpf_wait.h"
 
 namespace hpf {
 namespace {
@@ -12,7 +13,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int RES_NT = 512;            // threads per work-group (8 waves)
 constexpr int RES_NWV = RES_NT / 64;
-constexpr unsigned RES_SPIN_LIMIT = 1u << 19;
 
 // The wave's index within the work-group as a scalar: conditions on it become scalar branches instead of
 // compare / exec-mask sequences.

@@ -241,11 +241,10 @@ struct Gather {
   // tensor among 32 work-groups: 2.6 us from publish to coefficients when polled at once, 1.4-1.6 us with the pause; 128-32 blocks
   // forward 357 -> 286 us per launch of 21 blocks; pauses of 8 to 40 measured 303 ... 286 ... 305).
   // The slot has room for a multiple of CHUNK members, so all addresses are one lane offset from uniform bases.
-  static __device__ __forceinline__ void poll(u64 (&v)[INFL], const u64* slot, int m0, int nmem, unsigned tag, int wave, int lane, int* fail) {
+  static __device__ __forceinline__ void poll(u64 (&v)[INFL], const u64* slot, int m0, int nmem, unsigned tag, int wave, int lane, int* fail, SpinBudget& budget) {
     const unsigned off = (unsigned)((lane / WPW) * W + wave * WPW + (lane & (WPW - 1)));
     const int mine = lane_members(m0, nmem, lane);
     const u64* base = slot + (size_t)m0 * W;
-    unsigned spins = 0;
     __builtin_amdgcn_s_sleep(Cc < 128 ? 16 : 8);
     for (;;) {
       bool ok = true;
@@ -254,7 +253,7 @@ struct Gather {
 #pragma unroll
       for (int i = 0; i < INFL; ++i) ok = ok && ((unsigned)(v[i] >> 32) == tag || i >= mine);
       if (__all(ok)) break;
-      if (++spins > RES_SPIN_LIMIT) { *fail = 1; break; }
+      if (!budget.again()) { *fail = 1; break; }
     }
   }
   // how many of v[] are members of the micro-batch
@@ -284,9 +283,10 @@ __device__ __forceinline__ void collect_stats(const u64* slot, int nmem, unsigne
                                               const StatsOut& o, int wave, int lane, int* fail) {
   using G = Gather<Cc>;
   u64 v[G::INFL];
+  SpinBudget budget;
   float m0 = 0.f, s1 = 0.f, s2 = 0.f, sw = 0.f;   // sw: plain sum of the words (the M2 of the odd lanes)
-  for (int b = 0; b < nmem; b += G::CHUNK) {
-    G::poll(v, slot, b, nmem, tag, wave, lane, fail);
+  for (int b = 0; more_chunks(b, nmem, budget); b += G::CHUNK) {
+    G::poll(v, slot, b, nmem, tag, wave, lane, fail, budget);
     const int mine = G::lane_members(b, nmem, lane);
     float f[G::INFL], d[G::INFL];
 #pragma unroll
@@ -369,9 +369,10 @@ __device__ __forceinline__ void collect_bwd(const u64* slot, int nmem, unsigned 
   using G = Gather<Cc, CH>;
   const int mg = lane / G::WPW, wl = lane & (G::WPW - 1), c = (wave * G::WPW + wl) >> 1;
   u64 v[G::INFL];
+  SpinBudget budget;
   float sw = 0.f;
-  for (int b = 0; b < nmem; b += G::CHUNK) {
-    G::poll(v, slot, b, nmem, tag, wave, lane, fail);
+  for (int b = 0; more_chunks(b, nmem, budget); b += G::CHUNK) {
+    G::poll(v, slot, b, nmem, tag, wave, lane, fail, budget);
     const int mine = G::lane_members(b, nmem, lane);
     float f[G::INFL];
 #pragma unroll
