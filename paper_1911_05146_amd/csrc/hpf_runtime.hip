@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/hpf.h"
+#include "hpf_admission.h"
 #include "hpf_kernels.h"
 
 using namespace hpf;
@@ -1277,17 +1278,20 @@ hpf_status run_graphed(hpf_partition* p, GraphSlot& slot, const std::vector<cons
   return HPF_OK;
 }
 
-// Image-resident kernels need every work-group of a launch on the chip at once and take up to a CU each, so the
-// launches that may run at the same time must fit the device together.  Every call with such launches holds CUs
-// (resident_cus() of its largest launch).  Calls on one stream follow each other, so a stream holds what its
-// largest unfinished call does; a new call waits for other streams (largest holder first) until what is left and its
-// own need fit.  Any set of calls that can overlap then fits: the newest of them was admitted with all the others
-// counted.  A call keeps the lock from its admission until its events are on record, or two threads could be admitted
-// to the same CUs.  (One launch at a time, as before, made the partitions of a chain, which use 16 of 256 CUs at 16
-// images per micro-batch, run one after the other: a chain of four partitions of ResNet-110 took 17.3 ms per batch.)
-std::mutex g_res_mu;
-struct ResidentHold { int dev; hipStream_t stream; hipEvent_t ev; const hpf_partition* owner; int cus; };
-std::vector<ResidentHold> g_res;   // at most one entry per stream: its latest call (whose event covers the earlier ones)
+// Image-resident launches of different streams may overlap as long as they fit the device together (hpf_admission.h).  One launch at a
+// time made the partitions of a chain, which use 16 of 256 CUs at 16 images per micro-batch, run one after the other: a chain of four
+// partitions of ResNet-110 took 17.3 instead of 6.5 ms per batch.
+struct HipGpu {
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  static bool finished(hipEvent_t ev) {
+    if (hipEventQuery(ev) == hipSuccess) return true;
+    (void)hipGetLastError();   // "not ready" is no error of a later call
+    return false;
+  }
+  static bool wait(hipStream_t s, hipEvent_t ev) { return hipStreamWaitEvent(s, ev, 0) == hipSuccess; }
+};
+Admission<HipGpu> g_res;
 
 // Launches of this kind are ordered against each other through events recorded at call time, which a stream under
 // capture by the caller cannot take part in: two captured partitions replayed side by side would each wait for CUs
@@ -1300,53 +1304,26 @@ const char* const kNoCaptureMsg =
 // die must have room for its share: launches of 100 and 156 work-groups fill 256 CUs but put 13 + 20 on one die of 32.
 int resident_cus(int wgs) { return (wgs + 7) / 8 * 8; }
 
-// need: CUs of the call's largest image-resident launch; g_res_mu is held
-hpf_status resident_enter(hpf_partition* p, hipStream_t s, int need) {
-  if (!p->resident()) return HPF_OK;
-  int held = 0;
-  for (const ResidentHold& h : g_res)
-    if (h.dev == p->dev && h.stream != s) held += h.cus;
-  if (held + need <= p->cus) return HPF_OK;
-  held = 0;
-  for (size_t i = 0; i < g_res.size();) {   // drop what has finished
-    const ResidentHold& h = g_res[i];
-    if (h.dev == p->dev && h.stream != s) {
-      if (hipEventQuery(h.ev) == hipSuccess) { g_res.erase(g_res.begin() + (ptrdiff_t)i); continue; }
-      (void)hipGetLastError();   // "not ready" is no error of a later call
-      held += h.cus;
-    }
-    ++i;
+// A call with image-resident launches, from its admission to the event behind its last launch; partitions without them pass through
+class ResidentCall {
+ public:
+  ResidentCall(const hpf_partition* p, hipStream_t s) : p_(p), s_(s) {}
+  ~ResidentCall() { if (in_) g_res.leave(p_->dev, s_); }
+  ResidentCall(const ResidentCall&) = delete;
+  ResidentCall& operator=(const ResidentCall&) = delete;
+  // members: micro-batches of the call's largest launch
+  hpf_status enter(int members) {
+    if (!p_->resident()) return HPF_OK;
+    in_ = g_res.enter(p_->dev, p_->cus, s_, resident_cus(p_->res_wgs * members));
+    return in_ ? HPF_OK : fail(HPF_EDEVICE, "hipStreamWaitEvent failed");
   }
-  std::vector<char> waited(g_res.size(), 0);
-  while (held + need > p->cus) {
-    int big = -1;
-    for (size_t i = 0; i < g_res.size(); ++i)
-      if (!waited[i] && g_res[i].dev == p->dev && g_res[i].stream != s && (big < 0 || g_res[i].cus > g_res[(size_t)big].cus)) big = (int)i;
-    if (big < 0) break;
-    if (hipStreamWaitEvent(s, g_res[(size_t)big].ev, 0) != hipSuccess) return fail(HPF_EDEVICE, "hipStreamWaitEvent failed");
-    waited[(size_t)big] = 1;
-    held -= g_res[(size_t)big].cus;
-  }
-  return HPF_OK;
-}
-// done: the event recorded on s after the call's last launch (its owner re-records it only after a later launch of its
-// own, so waiting on it never waits for too little)
-void resident_leave(hpf_partition* p, hipStream_t s, hipEvent_t done, int need) {
-  if (!p->resident()) return;
-  for (ResidentHold& h : g_res)
-    if (h.dev == p->dev && h.stream == s) {
-      h.ev = done; h.owner = p;
-      if (need > h.cus) h.cus = need;
-      return;
-    }
-  g_res.push_back(ResidentHold{p->dev, s, done, p, need});
-}
-void resident_forget(const hpf_partition* p) {   // the partition's events are about to be destroyed (device idle)
-  std::lock_guard<std::mutex> lk(g_res_mu);
-  for (size_t i = 0; i < g_res.size();)
-    if (g_res[i].owner == p) g_res.erase(g_res.begin() + (ptrdiff_t)i);
-    else ++i;
-}
+  void launched(hipEvent_t done) { if (in_) g_res.record(p_->dev, s_, done, p_); }
+
+ private:
+  const hpf_partition* p_;
+  hipStream_t s_;
+  bool in_ = false;
+};
 // An exchange between the work-groups of an image-resident launch timed out: the batch is invalid.
 hpf_status check_abort_flag(hpf_partition* p) {
   if (p->P.runs.empty()) return HPF_OK;
@@ -1469,7 +1446,7 @@ hpf_status hpf_partition_create(const hpf_partition_desc* desc, void* device_are
 void hpf_partition_destroy(hpf_partition* p) {
   if (!p) return;
   (void)hipDeviceSynchronize();
-  resident_forget(p);
+  g_res.forget(p);
   for (hipEvent_t ev : p->ev_fwd) if (ev) (void)hipEventDestroy(ev);
   for (hipEvent_t ev : p->ev_bwd) if (ev) (void)hipEventDestroy(ev);
   if (p->ev_step) (void)hipEventDestroy(p->ev_step);
@@ -1516,11 +1493,9 @@ hpf_status forward_group(hpf_partition* p, int32_t mb_first, int32_t count, cons
     if (st != HPF_OK) return st;
   }
   const int gmax = p->group_limit();
-  const int res_need = resident_cus(p->res_wgs * (count < gmax ? count : gmax));
-  std::unique_lock<std::mutex> admission(g_res_mu, std::defer_lock);
-  if (p->resident()) admission.lock();
+  ResidentCall res(p, s);
   {
-    const hpf_status st = resident_enter(p, s, res_need);
+    const hpf_status st = res.enter(count < gmax ? count : gmax);
     if (st != HPF_OK) return st;
   }
   for (int c0 = 0; c0 < count; c0 += gmax) {
@@ -1561,7 +1536,7 @@ hpf_status forward_group(hpf_partition* p, int32_t mb_first, int32_t count, cons
       p->fwd_done[mb] = 1;
     }
     p->fwd_stream[mb_first + c0] = s;
-    resident_leave(p, s, p->ev_fwd[mb_first + c0], res_need);
+    res.launched(p->ev_fwd[mb_first + c0]);
   }
   return HPF_OK;
 }
@@ -1598,11 +1573,9 @@ hpf_status backward_group(hpf_partition* p, int32_t mb_first, int32_t count, con
       if (st != HPF_OK) return st;
     }
   const int gmax = p->group_limit();
-  const int res_need = resident_cus(p->res_wgs * (count < gmax ? count : gmax));
-  std::unique_lock<std::mutex> admission(g_res_mu, std::defer_lock);
-  if (p->resident()) admission.lock();
+  ResidentCall res(p, s);
   {
-    const hpf_status st = resident_enter(p, s, res_need);
+    const hpf_status st = res.enter(count < gmax ? count : gmax);
     if (st != HPF_OK) return st;
   }
   for (int c0 = 0; c0 < count; c0 += gmax) {
@@ -1630,7 +1603,7 @@ hpf_status backward_group(hpf_partition* p, int32_t mb_first, int32_t count, con
       ++p->n_bwd;
     }
     p->bwd_stream[mb_first + c0] = s;
-    resident_leave(p, s, p->ev_bwd[mb_first + c0], res_need);
+    res.launched(p->ev_bwd[mb_first + c0]);
   }
   return HPF_OK;
 }

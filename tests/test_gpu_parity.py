@@ -358,9 +358,13 @@ def test_directions_on_different_streams_wait_for_each_other(gpu, oracle):
     part.close()
 
 
-def test_resident_launches_that_fill_the_device_between_them(gpu, oracle):
+@pytest.mark.parametrize("threads", [False, True])
+def test_resident_launches_that_fill_the_device_between_them(gpu, oracle, threads):
     """Two partitions on two streams whose image-resident launches have 100 and 156 work-groups: as many as the device has
-    CUs, but not evenly over its dies, so the library must not let them run side by side.  Same results as one by one."""
+    CUs, but not evenly over its dies, so the library must not let them run side by side.  Same results as one by one; issued by one
+    host thread and by one each."""
+    from concurrent.futures import ThreadPoolExecutor
+
     import torch
     from parity import device_inputs, rel_err
     from paper_1911_05146_amd import hpf
@@ -384,7 +388,11 @@ def test_resident_launches_that_fill_the_device_between_them(gpu, oracle):
         want.append(([o.clone() for o in outs], parts[i].grad_accum_read()))
     torch.cuda.synchronize()
     for _ in range(3):
-        got = [batch(i, streams[i]) for i in range(2)]
+        if threads:
+            with ThreadPoolExecutor(2) as ex:
+                got = list(ex.map(batch, range(2), streams))
+        else:
+            got = [batch(i, streams[i]) for i in range(2)]
         torch.cuda.synchronize()
         for i in range(2):
             assert all(torch.equal(x, y) for x, y in zip(got[i], want[i][0]))

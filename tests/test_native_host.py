@@ -40,3 +40,115 @@ int main() { std::printf("%%u %%u %%u\\n", looks(8 * %d, ~0u), looks(8 * %d, 3),
     never, late, limit = map(int, out)
     assert never == limit + 1
     assert late == 4 * chunks
+
+
+FAKE_GPU = '''
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <random>
+#include <set>
+#include <thread>
+#include <atomic>
+#include <chrono>
+#include "hpf_admission.h"
+static std::set<int> g_finished;
+static std::vector<std::pair<int, int>> g_waits;   // stream, event
+struct Fake {
+  using Stream = int; using Event = int;
+  static bool finished(int ev) { return g_finished.count(ev) != 0; }
+  static bool wait(int s, int ev) { g_waits.push_back({s, ev}); return true; }
+};
+#define CHECK(x) do { if (!(x)) { std::printf("failed: %s (line %d)\\n", #x, __LINE__); return 1; } } while (0)
+'''
+
+
+def test_calls_that_fit_are_admitted_while_another_one_is_issuing(tmp_path):
+    """A call that is still capturing its graph holds no lock: threads with other partitions go ahead, on its device as long as both
+    fit and on other devices always.  One that does not fit waits for it on the host, then for its event on the stream."""
+    run_cpp(tmp_path, FAKE_GPU + '''
+int main() {
+  hpf::Admission<Fake> a;
+  CHECK(a.enter(0, 256, 1, 200));                 // device 0, stream 1: under way from here on
+  std::atomic<int> done{0};
+  std::thread other([&] { a.enter(1, 256, 2, 256); a.record(1, 2, 20, nullptr); a.leave(1, 2); ++done; });
+  std::thread fits([&] { a.enter(0, 256, 3, 56); a.record(0, 3, 30, nullptr); a.leave(0, 3); ++done; });
+  for (int i = 0; i < 2000 && done < 2; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(5));
+  const int at_once = done;
+  std::thread too_large([&] { a.enter(0, 256, 4, 100); a.record(0, 4, 40, nullptr); a.leave(0, 4); ++done; });
+  std::this_thread::sleep_for(std::chrono::milliseconds(100));
+  const int blocked = done;
+  a.record(0, 1, 10, nullptr);
+  a.leave(0, 1);
+  other.join(); fits.join(); too_large.join();
+  CHECK(at_once == 2 && blocked == 2 && done == 3);
+  CHECK(g_waits.size() == 1 && g_waits[0] == std::make_pair(4, 10));   // 200 + 56 + 100 > 256: the largest holder is enough
+  return 0;
+}
+''')
+
+
+def test_two_threads_on_one_stream_keep_the_later_event(tmp_path):
+    run_cpp(tmp_path, FAKE_GPU + '''
+int main() {
+  hpf::Admission<Fake> a;
+  CHECK(a.enter(0, 256, 1, 100));
+  std::atomic<int> second{0};
+  std::thread t([&] { a.enter(0, 256, 1, 50); a.record(0, 1, 11, nullptr); a.leave(0, 1); second = 1; });
+  std::this_thread::sleep_for(std::chrono::milliseconds(100));
+  CHECK(second == 0);
+  a.record(0, 1, 10, nullptr);
+  a.leave(0, 1);
+  t.join();
+  CHECK(a.enter(0, 256, 2, 200));
+  CHECK(g_waits.size() == 1 && g_waits[0] == std::make_pair(2, 11));
+  // a call that fails before its first launch leaves no entry behind, a wait on whose event would be an error
+  a.record(0, 2, 20, nullptr); a.leave(0, 2);
+  g_finished = {11, 20};
+  CHECK(a.enter(0, 256, 3, 8)); a.leave(0, 3);
+  CHECK(a.enter(0, 256, 4, 256));
+  CHECK(g_waits.size() == 1);
+  // destroyed owners: nobody waits for their events any more
+  a.record(0, 4, 40, &second); a.leave(0, 4);
+  a.forget(&second);
+  CHECK(a.enter(0, 256, 5, 256) && g_waits.size() == 1);
+  return 0;
+}
+''')
+
+
+@pytest.mark.parametrize("seed", [1, 2, 3])
+def test_calls_that_can_overlap_always_fit(tmp_path, seed):
+    """Random calls on random streams; a call overlaps everything that it does not follow through its stream or through the events that its
+    stream waited for (transitively)."""
+    run_cpp(tmp_path, FAKE_GPU + '''
+int main() {
+  std::mt19937 rng(%d);
+  hpf::Admission<Fake> a;
+  struct Call { int stream, cus; std::set<int> after; };
+  std::map<int, Call> calls;                 // by event
+  std::map<int, std::set<int>> order;        // per stream: all calls its next one follows
+  for (int ev = 1; ev <= 4000; ++ev) {
+    const int s = (int)(rng() %% 6), need = 8 * (1 + (int)(rng() %% (rng() %% 4 ? 8 : 32)));
+    g_waits.clear();
+    CHECK(a.enter(0, 256, s, need));
+    for (auto& w : g_waits) { CHECK(w.first == s); order[s].insert(w.second); auto& f = calls[w.second].after; order[s].insert(f.begin(), f.end()); }
+    std::map<int, int> most;                 // per other stream: the largest call that this one can overlap
+    for (auto& [e, c] : calls)
+      if (c.stream != s && !g_finished.count(e) && !order[s].count(e)) most[c.stream] = std::max(most[c.stream], c.cus);
+    int total = need;
+    for (auto& m : most) total += m.second;
+    CHECK(total <= 256);
+    a.record(0, s, ev, nullptr);
+    a.leave(0, s);
+    calls[ev] = Call{s, need, order[s]};
+    order[s].insert(ev);
+    if (rng() %% 8 == 0)                      // some stream drains
+      for (int e : order[(int)(rng() %% 6)]) g_finished.insert(e);
+    if (ev %% 64 == 0) {                      // forget what has finished
+      for (int e : g_finished) { calls.erase(e); for (auto& o : order) o.second.erase(e); for (auto& c : calls) c.second.after.erase(e); }
+    }
+  }
+  return 0;
+}
+''' % seed)
