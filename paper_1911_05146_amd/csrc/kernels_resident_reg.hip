@@ -141,9 +141,9 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
     }
   };
   const float inv_n = 1.f / (float)a.nmem;
-  // training: statistics of the wave's values v -> coef of the BatchNorm q of block B.  While the records travel `mid` runs, behind
-  // the polls `late`.  Returns false when a partner did not show up.
-  auto exchange = [&](auto cc, const auto& v, const ResBlock& B, int q, float2* coef, auto&& mid, auto&& late) -> bool {
+  // training: statistics of the wave's values v -> coef of the BatchNorm q of block B; `late` runs behind the polls.  Returns false when a
+  // partner did not show up.
+  auto exchange = [&](auto cc, const auto& v, const ResBlock& B, int q, float2* coef, auto&& late) -> bool {
     constexpr int Cc = decltype(cc)::value;
     const int gc = gather_channel<Cc>(wave, lane);
     const float gamma = (a.params + B.gamma_off[q])[gc], beta = (a.params + B.beta_off[q])[gc];
@@ -151,7 +151,6 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
     stats_publish_waves<Cc, RG_NPX>(red, slot(), me, tag);
-    mid();
     const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
     collect_stats<Cc>(slot(), a.nmem, tag, inv_n, (float)RG_P, a.eps, gamma, beta, o, wave, lane, fail);
     ++phase;
@@ -174,7 +173,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
       __syncthreads();
     } else {
       __syncthreads();
-      if (!exchange(IC{}, X, B0, 0, coefC, [] {}, [] {})) return;
+      if (!exchange(IC{}, X, B0, 0, coefC, [] {})) return;
     }
   }
   for (int bi = 0; bi < a.nblk; ++bi) {
@@ -208,12 +207,11 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
 #pragma unroll
       for (int nt = 0; nt < NM; ++nt) { cp[j][nt] = pack4(acc[j][nt]); acc[j][nt] = unpack4(cp[j][nt]); }
     if constexpr (!INFER) {
-      if (!exchange(IM{}, acc, B, 1, coefM, [] {},
-                    [&] {
-                      w3.commit(sW3, wave, lane);
-                      if (bi > 0) w2.template commit<2>(sW2, wave, lane);
-px_store<MID != 32>(image(B.c1_off, MID), offM, cp);
-                    }))
+      if (!exchange(IM{}, acc, B, 1, coefM, [&] {
+            w3.commit(sW3, wave, lane);
+            if (bi > 0) w2.template commit<2>(sW2, wave, lane);
+            px_store<MID != 32>(image(B.c1_off, MID), offM, cp);
+          }))
         return;
     }
 #pragma unroll
@@ -244,11 +242,10 @@ px_store<MID != 32>(image(B.c1_off, MID), offM, cp);
       if (more) { w2.commit(sW2, wave, lane); w3.issue(a.packed + Bn.wf_off[2], wave, fr, fq); }
     } else {
       if (more) { w2.template issue<0>(a.packed + Bn.wf_off[1], wave, fr, fq); w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq); }   // the exchange hides it
-      if (!exchange(IM{}, acc, B, 2, coefM3, [] {},
-                    [&] {
-                      if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wf_off[1], wave, fr, fq); }
-px_store<MID != 32>(image(B.c2_off, MID), offM, cp);
-                    }))
+      if (!exchange(IM{}, acc, B, 2, coefM3, [&] {
+            if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wf_off[1], wave, fr, fq); }
+            px_store<MID != 32>(image(B.c2_off, MID), offM, cp);
+          }))
         return;
     }
     // ---- conv3 (1x1, MID -> C) on relu(bn3(c2)), accumulated onto x
@@ -277,12 +274,13 @@ px_store<MID != 32>(image(B.c2_off, MID), offM, cp);
     if constexpr (INFER) {
       if (!more) store_y();
     } else if (more) {
-      if (!exchange(IC{}, X, Bn, 0, coefC, [] {}, [&] {
-                      w1.commit(sW1, wave, lane);
-                      w2.template commit<1>(sW2, wave, lane);
-                      w2.template issue<2>(a.packed + Bn.wf_off[1], wave, fr, fq);
-                      store_y();
-                    })) return;
+      if (!exchange(IC{}, X, Bn, 0, coefC, [&] {
+            w1.commit(sW1, wave, lane);
+            w2.template commit<1>(sW2, wave, lane);
+            w2.template issue<2>(a.packed + Bn.wf_off[1], wave, fr, fq);
+            store_y();
+          }))
+        return;
     } else {
       store_y();
     }
