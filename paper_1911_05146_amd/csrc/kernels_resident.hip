@@ -1307,9 +1307,8 @@ __global__ void __launch_bounds__(RES_NT) k_bb_forward(const ResArgs a, const in
   if (!INFER && me == 0 && tid == 0) *tagp = tag0 + phase;
 }
 
-template <int C, int PTW, bool PRE, bool WL = false>
+template <int C, int PTW, bool WL>
 __global__ void __launch_bounds__(RES_NT) k_bb_backward(const ResArgs a, const int gath_own) {
-  static_assert(!(WL && PRE), "the LDS form replaces the fetch-where-used form");
   constexpr int XS = C + 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
@@ -1332,7 +1331,7 @@ __global__ void __launch_bounds__(RES_NT) k_bb_backward(const ResArgs a, const i
   float* own = reinterpret_cast<float*>(tab + C);
   auto slot = [&]() { return xchg + (size_t)(phase & 1u) * a.nmem * (2 * C); };
   constexpr int KT = (9 * C + 31) / 32, LD = KT * 32;
-  std::conditional_t<WL, WFragsL<KT, C / 16>, WFrags<KT, C / 16, PRE>> w2, w1;   // data-gradient operands [C][LD]
+  std::conditional_t<WL, WFragsL<KT, C / 16>, WFrags<KT, C / 16, false>> w2, w1;   // data-gradient operands [C][LD]
   bf16_t* sW = reinterpret_cast<bf16_t*>(own + (gath_own ? (size_t)a.nmem * 2 * C : 0));   // WL: the staged matrix
   u32x4 wst[WL ? (KT * (C / 16) + 7) / 8 : 1];
 
@@ -1480,9 +1479,8 @@ __device__ __forceinline__ void tile_join_relu(bf16_t* sx, const bf16_t* sc2, co
   }
 }
 
-template <int C, int PTW, bool PRE, bool WL = false>
+template <int C, int PTW, bool WL>
 __global__ void __launch_bounds__(RES_NT) k_v1_forward(const ResArgs a, const int gath_own) {
-  static_assert(!(WL && PRE), "the LDS form replaces the fetch-where-used form");
   constexpr int XS = C + 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
@@ -1504,7 +1502,7 @@ __global__ void __launch_bounds__(RES_NT) k_v1_forward(const ResArgs a, const in
   float* own = red + V1_RED(C);
   auto slot = [&]() { return xchg + (size_t)(phase & 1u) * a.nmem * (2 * C); };
   constexpr int KT = (9 * C + 31) / 32, LD = KT * 32;     // reduction steps and row length of the packed weights
-  std::conditional_t<WL, WFragsL<KT, C / 16>, WFrags<KT, C / 16, PRE>> w1, w2;
+  std::conditional_t<WL, WFragsL<KT, C / 16>, WFrags<KT, C / 16, false>> w1, w2;
   bf16_t* sW = reinterpret_cast<bf16_t*>(own + (gath_own ? (size_t)a.nmem * 2 * C : 0));   // WL: the staged matrix
   u32x4 wst[WL ? (KT * (C / 16) + 7) / 8 : 1];                                              // WL: its units on their way
 
@@ -1661,9 +1659,8 @@ __device__ __forceinline__ bool v1_bn_bwd_acc(floatx4 (&dz)[PTW][Cc / 16], const
   return true;
 }
 
-template <int C, int PTW, bool PRE, bool WL = false>
+template <int C, int PTW, bool WL>
 __global__ void __launch_bounds__(RES_NT) k_v1_backward(const ResArgs a, const int gath_own) {
-  static_assert(!(WL && PRE), "the LDS form replaces the fetch-where-used form");
   constexpr int XS = C + 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
@@ -1686,7 +1683,7 @@ __global__ void __launch_bounds__(RES_NT) k_v1_backward(const ResArgs a, const i
   float* own = reinterpret_cast<float*>(tab + C);
   auto slot = [&]() { return xchg + (size_t)(phase & 1u) * a.nmem * (2 * C); };
   constexpr int KT = (9 * C + 31) / 32, LD = KT * 32;
-  std::conditional_t<WL, WFragsL<KT, C / 16>, WFrags<KT, C / 16, PRE>> w2, w1;   // data-gradient operands [C][LD]
+  std::conditional_t<WL, WFragsL<KT, C / 16>, WFrags<KT, C / 16, false>> w2, w1;   // data-gradient operands [C][LD]
   bf16_t* sW = reinterpret_cast<bf16_t*>(own + (gath_own ? (size_t)a.nmem * 2 * C : 0));   // WL: the staged matrix
   u32x4 wst[WL ? (KT * (C / 16) + 7) / 8 : 1];
 
@@ -2413,6 +2410,9 @@ size_t v1_lds(int C, int P, int nmem, bool backward, int* own) {
   *own = (size_t)nmem * 2 * C * 4 > tile ? 1 : 0;
   return (backward ? 2 : 3) * tile + fixed + (*own ? (size_t)nmem * 2 * C * 4 : 0);
 }
+// LDS copy of a 3x3 matrix of C channels (rows padded by 8 elements).  It always fits next to the tiles of 32 channels; with 64 the weights are
+// fetched where they are used once the gathered records of many images take its place.
+size_t wl3_bytes(int C) { return (size_t)C * (9 * C + 8) * 2; }
 size_t bb_wgrad_lds(int C, int P, int W) {
   return (size_t)3 * C * (P + 2 * W + 8) * 2 + (size_t)C * (P + 8) * 2 + (size_t)C * 8;
 }
@@ -2478,6 +2478,12 @@ size_t resident_xchg_bytes(int C, int nmem, int bands) {
   return 2 * (size_t)resident_slot_members(nmem) * 2 * C * sizeof(u64);
 }
 
+// Which runs, at how many images per micro-batch.  The limits on nmem are those of the LDS-tile kernels, whose gathered records (2*C floats per
+// image) lie in LDS.  They also hold for the shapes that the register kernels take, which gather nothing in LDS: 128-32 bottlenecks
+// on 16x16 images end at 40 images, 128-64 ones at 72 and 64-channel basic blocks on 8x8 at 255; above, the run goes layer by layer.  That
+// costs (training step / inference of six blocks, one micro-batch: 128-32 with 40 images 267 / 31 us, with 41 660 / 155; 128-64 with
+// 72 473 / 57, with 73 1005 / 204), but calls with image-resident launches are refused on a stream that the caller captures, and
+// partitions above the limit are accepted there.
 bool resident_shape_ok(int kind, int C, int MID, int H, int W, int nmem) {
   const int P = H * W;
   // whole 32-pixel reduction steps in the weight gradients; image rows that keep 16-byte alignment under a row shift
@@ -2487,15 +2493,14 @@ bool resident_shape_ok(int kind, int C, int MID, int H, int W, int nmem) {
   int own = 0;
   if (const int nb = resident_bands(kind, C, MID, H, W); nb > 1)
     return band_fwd_lds(nmem * nb) <= RES_LDS_BYTES && band_bwd_lds(nmem * nb) <= RES_LDS_BYTES;
-  if (kind == 2) {   // post-activation basic blocks: three / two tiles, no weight-gradient launch
-    if (!((C == 16 && P == 1024 && W == 32) || (C == 32 && P <= 256) || (C == 64 && P <= 128)) || MID != C) return false;
-    return v1_lds(C, P, nmem, false, &own) <= RES_LDS_BYTES && v1_lds(C, P, nmem, true, &own) <= RES_LDS_BYTES &&
-           (C == 16 || bb_wgrad_lds(C, P, W) <= RES_LDS_BYTES);
-  }
-  if (kind == 0) {   // basic blocks: C -> C -> C
-    if (!((C == 16 && P == 1024 && W == 32) || (C == 32 && P <= 256) || (C == 64 && P <= 128)) || MID != C) return false;
-    return bb_lds(C, P, nmem, false, &own) <= RES_LDS_BYTES && bb_lds(C, P, nmem, true, &own) <= RES_LDS_BYTES &&
-           (C == 16 || bb_wgrad_lds(C, P, W) <= RES_LDS_BYTES);
+  if (kind == 0 || kind == 2) {   // basic blocks: C -> C -> C, before / after the activation
+    if (MID != C) return false;
+    if (C == 16) return resident_basic_shape(kind, C, H, W);   // the register kernels alone
+    if (!((C == 32 && P <= 256) || (C == 64 && P <= 128)) || bb_wgrad_lds(C, P, W) > RES_LDS_BYTES) return false;
+    // the LDS copy of the weights is part of the 32-channel kernels (it binds at 303 images, more than there are CUs)
+    auto lds = kind == 2 ? v1_lds : bb_lds;
+    const size_t wl = C == 32 ? wl3_bytes(C) : 0;
+    return lds(C, P, nmem, false, &own) + wl <= RES_LDS_BYTES && lds(C, P, nmem, true, &own) + wl <= RES_LDS_BYTES;
   }
   if (!((C == 128 && (MID == 32 || MID == 64) && P <= 256) || (C == 256 && MID == 64 && P <= 128))) return false;
   return fwd_lds(C, MID, P, nmem, &own) <= RES_LDS_BYTES && bwd_lds(C, MID, P, nmem, &own) <= RES_LDS_BYTES;
@@ -2518,9 +2523,9 @@ hipError_t resident_prepare() {
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_forward<256, 64, 1, false>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_backward<128, 32, 2, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_backward<256, 64, 1, false>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  const void* bb[] = {reinterpret_cast<const void*>(k_bb_forward<32, 2, true>),  reinterpret_cast<const void*>(k_bb_forward<64, 1, false>),
-                      reinterpret_cast<const void*>(k_bb_backward<32, 2, true>), reinterpret_cast<const void*>(k_bb_backward<64, 1, false>),
-                      reinterpret_cast<const void*>(k_bb_forward<32, 2, false, false, true>), reinterpret_cast<const void*>(k_bb_backward<32, 2, false, true>),
+  const void* bb[] = {reinterpret_cast<const void*>(k_bb_forward<32, 2, false, false, true>), reinterpret_cast<const void*>(k_bb_backward<32, 2, true>),
+                      reinterpret_cast<const void*>(k_bb_forward<64, 1, false, false, true>), reinterpret_cast<const void*>(k_bb_backward<64, 1, true>),
+                      reinterpret_cast<const void*>(k_bb_forward<64, 1, false>), reinterpret_cast<const void*>(k_bb_backward<64, 1, false>),
                       reinterpret_cast<const void*>(k_bb_wgrad<32>),             reinterpret_cast<const void*>(k_bb_wgrad<64>)};
   for (const void* f : bb)
     if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -2534,11 +2539,9 @@ hipError_t resident_prepare() {
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_backward<256, 64, 1, false, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_v1_wgrad<32>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_v1_wgrad<64>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  const void* v1[] = {reinterpret_cast<const void*>(k_v1_forward<32, 2, true>),  reinterpret_cast<const void*>(k_v1_forward<64, 1, false>),
-                      reinterpret_cast<const void*>(k_v1_backward<32, 2, true>), reinterpret_cast<const void*>(k_v1_backward<64, 1, false>),
-                      reinterpret_cast<const void*>(k_v1_forward<32, 2, false, true>),  reinterpret_cast<const void*>(k_v1_backward<32, 2, false, true>),
-                      reinterpret_cast<const void*>(k_v1_forward<64, 1, false, true>), reinterpret_cast<const void*>(k_v1_backward<64, 1, false, true>),
-                      reinterpret_cast<const void*>(k_bb_forward<64, 1, false, false, true>), reinterpret_cast<const void*>(k_bb_backward<64, 1, false, true>)};
+  const void* v1[] = {reinterpret_cast<const void*>(k_v1_forward<32, 2, true>),  reinterpret_cast<const void*>(k_v1_backward<32, 2, true>),
+                      reinterpret_cast<const void*>(k_v1_forward<64, 1, true>),  reinterpret_cast<const void*>(k_v1_backward<64, 1, true>),
+                      reinterpret_cast<const void*>(k_v1_forward<64, 1, false>), reinterpret_cast<const void*>(k_v1_backward<64, 1, false>)};
   for (const void* f : v1)
     if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_band_forward<64, 16>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -2565,24 +2568,14 @@ hipError_t launch_resident_forward(int kind, int g, int C, int MID, const ResArg
   if (resident_basic_shape(kind, C, a.H, a.W)) return launch_basic_forward(kind, g, C, a, false, stream);
   int own = 0;
   if (kind == 2) {
-    const size_t lds = v1_lds(C, a.H * a.W, a.nmem, false, &own);
-    if (C == 32) {
-      const size_t wl32 = (size_t)32 * (288 + 8) * 2;
-      return lds + wl32 <= RES_LDS_BYTES ? launch_res(k_v1_forward<32, 2, false, true>, lds + wl32, own, g, a, stream)
-                                         : launch_res(k_v1_forward<32, 2, true>, lds, own, g, a, stream);
-    }
-    const size_t wl = (size_t)C * (9 * C + 8) * 2;   // one pixel tile per wave: the 3x3 matrices through LDS where they fit
-    if (lds + wl <= RES_LDS_BYTES) return launch_res(k_v1_forward<64, 1, false, true>, lds + wl, own, g, a, stream);
+    const size_t lds = v1_lds(C, a.H * a.W, a.nmem, false, &own), wl = wl3_bytes(C);
+    if (C == 32) return launch_res(k_v1_forward<32, 2, true>, lds + wl, own, g, a, stream);
+    if (lds + wl <= RES_LDS_BYTES) return launch_res(k_v1_forward<64, 1, true>, lds + wl, own, g, a, stream);
     return launch_res(k_v1_forward<64, 1, false>, lds, own, g, a, stream);
   }
   if (kind == 0) {
-    const size_t lds = bb_lds(C, a.H * a.W, a.nmem, false, &own);
-    if (C == 32) {
-      const size_t wl32 = (size_t)32 * (288 + 8) * 2;
-      return lds + wl32 <= RES_LDS_BYTES ? launch_res(k_bb_forward<32, 2, false, false, true>, lds + wl32, own, g, a, stream)
-                                         : launch_res(k_bb_forward<32, 2, true>, lds, own, g, a, stream);
-    }
-    const size_t wl = (size_t)C * (9 * C + 8) * 2;
+    const size_t lds = bb_lds(C, a.H * a.W, a.nmem, false, &own), wl = wl3_bytes(C);
+    if (C == 32) return launch_res(k_bb_forward<32, 2, false, false, true>, lds + wl, own, g, a, stream);
     if (lds + wl <= RES_LDS_BYTES) return launch_res(k_bb_forward<64, 1, false, false, true>, lds + wl, own, g, a, stream);
     return launch_res(k_bb_forward<64, 1, false>, lds, own, g, a, stream);
   }
@@ -2658,25 +2651,15 @@ hipError_t launch_resident_backward(int kind, int g, int C, int MID, const ResAr
   if (resident_basic_shape(kind, C, a.H, a.W)) return launch_basic_backward(kind, g, C, a, stream);
   int own = 0;
   if (kind == 2) {
-    const size_t lds = v1_lds(C, a.H * a.W, a.nmem, true, &own);
-    if (C == 32) {
-      const size_t wl32 = (size_t)32 * (288 + 8) * 2;
-      return lds + wl32 <= RES_LDS_BYTES ? launch_res(k_v1_backward<32, 2, false, true>, lds + wl32, own, g, a, stream)
-                                         : launch_res(k_v1_backward<32, 2, true>, lds, own, g, a, stream);
-    }
-    const size_t wl = (size_t)C * (9 * C + 8) * 2;
-    if (lds + wl <= RES_LDS_BYTES) return launch_res(k_v1_backward<64, 1, false, true>, lds + wl, own, g, a, stream);
+    const size_t lds = v1_lds(C, a.H * a.W, a.nmem, true, &own), wl = wl3_bytes(C);
+    if (C == 32) return launch_res(k_v1_backward<32, 2, true>, lds + wl, own, g, a, stream);
+    if (lds + wl <= RES_LDS_BYTES) return launch_res(k_v1_backward<64, 1, true>, lds + wl, own, g, a, stream);
     return launch_res(k_v1_backward<64, 1, false>, lds, own, g, a, stream);
   }
   if (kind == 0) {
-    const size_t lds = bb_lds(C, a.H * a.W, a.nmem, true, &own);
-    if (C == 32) {
-      const size_t wl32 = (size_t)32 * (288 + 8) * 2;
-      return lds + wl32 <= RES_LDS_BYTES ? launch_res(k_bb_backward<32, 2, false, true>, lds + wl32, own, g, a, stream)
-                                         : launch_res(k_bb_backward<32, 2, true>, lds, own, g, a, stream);
-    }
-    const size_t wl = (size_t)C * (9 * C + 8) * 2;
-    if (lds + wl <= RES_LDS_BYTES) return launch_res(k_bb_backward<64, 1, false, true>, lds + wl, own, g, a, stream);
+    const size_t lds = bb_lds(C, a.H * a.W, a.nmem, true, &own), wl = wl3_bytes(C);
+    if (C == 32) return launch_res(k_bb_backward<32, 2, true>, lds + wl, own, g, a, stream);
+    if (lds + wl <= RES_LDS_BYTES) return launch_res(k_bb_backward<64, 1, true>, lds + wl, own, g, a, stream);
     return launch_res(k_bb_backward<64, 1, false>, lds, own, g, a, stream);
   }
   const size_t lds = bwd_lds(C, MID, a.H * a.W, a.nmem, &own);

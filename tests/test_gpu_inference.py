@@ -31,7 +31,17 @@ def small_specs():
                            blocks=(W.Block(W.BOTTLENECK, 128, 64, 128, 1),) * 2 + (W.Block(W.BOTTLENECK, 128, 64, 256, 2),) +
                                   (W.Block(W.BOTTLENECK, 256, 64, 256, 1),) * 2,
                            microbatch=3, num_microbatches=2, seed=11)
-    return {"resnet20": r20, "bottleneck_run": bott, "cut_partition": cut, "wide_runs": wide}
+    # runs of the sizes that the LDS-tile kernels take
+    tile_basic = W.PartitionSpec(name="tile-basic", in_h=8, in_w=16, in_c=32,
+                                 blocks=(W.Block(W.BASIC, 32, 32, 32, 1),) * 2 + (W.Block(W.BASIC, 32, 64, 64, 2),) +
+                                        (W.Block(W.BASIC, 64, 64, 64, 1),) * 2,
+                                 microbatch=3, num_microbatches=2, seed=13)
+    tile_bottleneck = W.PartitionSpec(name="tile-bottleneck", in_h=8, in_w=16, in_c=128,
+                                      blocks=(W.Block(W.BOTTLENECK, 128, 32, 128, 1),) * 2 + (W.Block(W.BOTTLENECK, 128, 64, 128, 1),) * 2 +
+                                             (W.Block(W.BOTTLENECK, 128, 64, 256, 2),) + (W.Block(W.BOTTLENECK, 256, 64, 256, 1),) * 2,
+                                      microbatch=3, num_microbatches=2, seed=14)
+    return {"resnet20": r20, "bottleneck_run": bott, "cut_partition": cut, "wide_runs": wide, "tile_basic_runs": tile_basic,
+            "tile_bottleneck_runs": tile_bottleneck}
 
 
 def train_batch(part, spec, t, grouped):
@@ -50,7 +60,7 @@ def train_batch(part, spec, t, grouped):
 
 @pytest.mark.parametrize("mode", ["f32", "bf16"])
 @pytest.mark.parametrize("grouped", [False, True])
-@pytest.mark.parametrize("name", ["resnet20", "bottleneck_run", "cut_partition", "wide_runs"])
+@pytest.mark.parametrize("name", ["resnet20", "bottleneck_run", "cut_partition", "wide_runs", "tile_basic_runs", "tile_bottleneck_runs"])
 def test_running_statistics_and_inference_against_oracle(gpu, oracle, name, grouped, mode):
     import torch
     hpf = gpu

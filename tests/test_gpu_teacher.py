@@ -78,9 +78,9 @@ def test_row_band_runs_layerwise(gpu, oracle):
 
 
 def test_runs_with_weights_through_lds_layerwise(gpu, oracle):
-    """Resident runs whose weight matrices the work-group stages through LDS: 128-64 bottlenecks at 16x16 (through the
-    tile that is idle at the time, conv2 in three rounds), 128-32 at 16x16, 32-channel basic and post-activation blocks,
-    16-channel basic and post-activation blocks at 32x32.
+    """Register-resident runs, whose weight matrices the work-group stages through LDS: 128-64 and 128-32 bottlenecks at
+    16x16 (conv2's matrix in three pieces, conv1's and conv3's in turn in one area), basic and post-activation blocks of
+    32 channels at 16x16 and of 16 channels at 32x32 (one matrix at a time).
     Three blocks, so that the staging of the first block, of a following block and of the last one all run; an odd
     number of images; one call per micro-batch and one for all."""
     runs = {
@@ -91,15 +91,15 @@ def test_runs_with_weights_through_lds_layerwise(gpu, oracle):
         "3x postact32@16x16": (tuple(W.Block(W.POSTACT, 32, 32, 32, 1) for _ in range(3)), 16, 32, False),
         "3x postact16@32x32": (tuple(W.Block(W.POSTACT, 16, 16, 16, 1) for _ in range(3)), 32, 16, False),
     }
-    # 40 images per micro-batch: the gathered 128-channel records then reach into the tile that also takes a weight matrix
+    # 40 images per micro-batch: two chunks of polled members in the forward, five and ten in the backward's exchanges of a 128-64 block,
+    # none of them whole but the first; the largest size of the 128-32 runs
     spec = W.PartitionSpec(name="wide-3x(128-64-128)@16x16-b40", in_h=16, in_w=16, in_c=128, blocks=runs["wide-3x(128-64-128)@16x16"][0],
                            microbatch=40, num_microbatches=2, seed=37)
     layerwise(oracle, spec, "bf16", blockwise=False)
     spec = W.PartitionSpec(name="3x(128-32-128)@16x16-b40", in_h=16, in_w=16, in_c=128, blocks=runs["3x(128-32-128)@16x16"][0],
-                           microbatch=40, num_microbatches=2, seed=37)   # the records fill both narrow tiles
+                           microbatch=40, num_microbatches=2, seed=37)
     layerwise(oracle, spec, "bf16", blockwise=False)
-    # 100 images per micro-batch: the records no longer fit a tile and are gathered in an area of their own, behind
-    # which the staged matrix then lies
+    # 100 images per micro-batch: four chunks of polled members
     for name, blocks, hw, c in (("3x basic32@16x16-b100", runs["3x basic32@16x16"][0], 16, 32),
                                 ("3x basic64@8x8-b100", tuple(W.Block(W.BASIC, 64, 64, 64, 1) for _ in range(3)), 8, 64),
                                 ("3x postact32@16x16-b100", runs["3x postact32@16x16"][0], 16, 32)):
@@ -110,6 +110,25 @@ def test_runs_with_weights_through_lds_layerwise(gpu, oracle):
             spec = W.PartitionSpec(name=f"{name}-b{b}", in_h=hw, in_w=hw, in_c=c, blocks=blocks, microbatch=b,
                                    num_microbatches=m, seed=37)
             layerwise(oracle, spec, "bf16", grouped=grouped, blockwise=blockwise)
+
+
+@pytest.mark.parametrize("kind,c,mid,h,w,images",
+                         # records in an idle tile | in an area of their own, in front of the staged matrix
+                         [(k, 32, 32, 8, 16, b) for k in (W.BASIC, W.POSTACT) for b in (3, 44)] +
+                         # as above | weights fetched where they are used in the forward | in both directions
+                         [(k, 64, 64, 8, 16, b) for k in (W.BASIC, W.POSTACT) for b in (3, 40, 60, 90)] +
+                         [(W.BOTTLENECK, 128, 32, 8, 16, b) for b in (3, 24)] + [(W.BOTTLENECK, 128, 64, 8, 8, b) for b in (3, 20)] +
+                         # staged weights | fetched where they are used, records in an idle tile / an area of their own
+                         [(W.BOTTLENECK, 256, 64, 8, 8, 3), (W.BOTTLENECK, 256, 64, 8, 16, 3), (W.BOTTLENECK, 256, 64, 8, 8, 12)] +
+                         # staged weights behind an area of records | in the forward only
+                         [(W.BOTTLENECK, 256, 64, 4, 8, b) for b in (6, 18)])
+def test_lds_tile_resident_runs_layerwise(gpu, oracle, kind, c, mid, h, w, images):
+    """Image-resident runs of the shapes that the register kernels do not take, whose images and gathered BatchNorm records lie in LDS
+    tiles: every kernel and every place of the records and of the weights, which depend on the number of images.  Three blocks: the
+    first, a following one and the last."""
+    spec = W.PartitionSpec(name=f"tile-{kind}-{c}-{mid}@{h}x{w}-b{images}", in_h=h, in_w=w, in_c=c, blocks=(W.Block(kind, c, mid, c, 1),) * 3,
+                           microbatch=images, num_microbatches=2 if images < 40 else 1, seed=59)
+    layerwise(oracle, spec, "bf16", blockwise=False)
 
 
 @pytest.mark.parametrize("images", [1, 31, 33])
