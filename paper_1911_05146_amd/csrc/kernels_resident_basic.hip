@@ -35,12 +35,13 @@ struct Geo {
 };
 
 // 3x3 convolution from the canvas.  src: tap (0, 0) of the lane's pixel of the wave's first tile (+ fk; 16 channels: + (fq & 1)*8); FLIP: the
-// data gradient (taps mirrored).  w: the staged matrix at the wave's first channel tile, + lane*8.
+// data gradient (taps mirrored).  w: the staged matrix at the wave's first channel tile, + lane*8.  zero: eight zeros (of the border).
 template <int C, bool FLIP>
-__device__ __forceinline__ void conv3x3(const bf16_t* src, const bf16_t* w, int fq, floatx4 (&acc)[Geo<C>::PTW][Geo<C>::NTW]) {
+__device__ __forceinline__ void conv3x3(const bf16_t* src, const bf16_t* zero, const bf16_t* w, int fq, floatx4 (&acc)[Geo<C>::PTW][Geo<C>::NTW]) {
   using G = Geo<C>;
   constexpr int MS = G::MS, CW = G::CW;
-  if constexpr (C == 16) {   // packed weights [16][160], k = tap*16 + c, zero beyond tap 8: lane groups 0-1 take the even tap of a step, 2-3 the odd one
+  if constexpr (C == 16) {   // packed weights [16][160], k = tap*16 + c, zero beyond tap 8: lane groups 0-1 take the even tap of a step, 2-3 the odd one.
+    // The odd half of the last step has no tap: zeros, not another tap's values times the zero weights (0 * infinity)
 #pragma unroll
     for (int st = 0; st < 5; ++st) {
       constexpr int last = 8;
@@ -49,8 +50,10 @@ __device__ __forceinline__ void conv3x3(const bf16_t* src, const bf16_t* w, int 
       const bf16_t* q = src + (fq < 2 ? oa : ob) * MS;
       const bf16x8 wf = G::W::get(w, st, 0);
 #pragma unroll
-      for (int j = 0; j < G::PTW; ++j)
-        acc[j][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, *reinterpret_cast<const bf16x8*>(q + G::tile_off(j)), acc[j][0], 0, 0, 0);
+      for (int j = 0; j < G::PTW; ++j) {
+        const bf16_t* px = 2 * st == last && fq >= 2 ? zero : q + G::tile_off(j);
+        acc[j][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, *reinterpret_cast<const bf16x8*>(px), acc[j][0], 0, 0, 0);
+      }
     }
   } else if constexpr (C == 32) {   // the four input rows of a filter column serve both output rows
 #pragma unroll
@@ -220,7 +223,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     for (int j = 0; j < PTW; ++j)
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    conv3x3<C, false>(canvas + L.cr, wr, fq, acc);
+    conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, acc);
     uint2 cp[PTW][NTW];
     round_to(acc, cp);
     if constexpr (INFER) {
@@ -244,7 +247,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     if constexpr (INFER)
       if (more) run_coef(Bn, 1, coef2);
     if constexpr (!POST) {
-      conv3x3<C, false>(canvas + L.cr, wr, fq, X);
+      conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, X);
       round_to(X, cp);
       if constexpr (INFER) {
         if (!more) { px_store(image(B.y_off), L.off, cp); break; }
@@ -265,7 +268,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
       for (int j = 0; j < PTW; ++j)
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-      conv3x3<C, false>(canvas + L.cr, wr, fq, acc);
+      conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, acc);
       round_to(acc, cp);
       if (more) w.issue(a.packed + Bn.wf_off[0], wave, fr, fq);
       if (!exchange(acc, B, 1, coef1, [&] {
@@ -402,7 +405,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
       to_canvas(DY);
       __syncthreads();
       zero(acc);
-      conv3x3<C, true>(canvas + L.cr, wr, fq, acc);
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc);
       w.issue(a.packed + B.wd_off[0], wave, fr, fq);
       px_arrange(xa);
       if (!exchange(Relu{}, acc, xa, cf2, B, 1, [&] {
@@ -416,7 +419,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
       __syncthreads();
       // ---- conv1 data gradient, BN1 + ReLU backward, plus the shortcut
       zero(acc);
-      conv3x3<C, true>(canvas + L.cr, wr, fq, acc);
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc);
       if (more) { w.issue(a.packed + Bn.wd_off[1], wave, fr, fq); load_tables(bi - 1); }
       px_arrange(xb);
       if (!exchange(Relu{}, acc, xb, cf1, B, 0, [&] {
@@ -452,7 +455,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
       __syncthreads();
       // ---- conv2 data gradient, BN1 + ReLU backward -> dc1
       zero(acc);
-      conv3x3<C, true>(canvas + L.cr, wr, fq, acc);
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc);
       w.issue(a.packed + B.wd_off[0], wave, fr, fq);
       if (more) load_tables(bi - 1);
       px_arrange(xb);
@@ -468,7 +471,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
       __syncthreads();
       px_store(image(B.dc1_off), L.off, dcp);
       // ---- conv1 data gradient plus the shortcut
-      conv3x3<C, true>(canvas + L.cr, wr, fq, dz);
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, dz);
 #pragma unroll
       for (int j = 0; j < PTW; ++j)
 #pragma unroll

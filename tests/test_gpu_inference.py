@@ -232,3 +232,38 @@ def test_inference_group_larger_than_the_chip(gpu, oracle):
     assert e <= 2e-2
     part.close()
     opart.close()
+
+
+@pytest.mark.parametrize("c,h,w", [(16, 32, 32), (32, 16, 16), (64, 8, 8), (32, 8, 16)])
+def test_an_infinite_activation_reaches_its_neighbours_as_infinity(gpu, c, h, w):
+    """With positive weights an activation that overflows makes exactly the pixels that the two 3x3 convolutions reach infinite.  No padding
+    of a reduction may meet it (0 * infinity is NaN; in the middle of an image and in its corners)."""
+    import torch
+    spec = W.PartitionSpec(name=f"inf-{c}@{h}x{w}", in_h=h, in_w=w, in_c=c, blocks=(W.Block(W.BASIC, c, c, c, 1),), microbatch=3,
+                           num_microbatches=1, seed=61)
+    inp = W.make_inputs(spec, randomize_affine=True)
+    for e in W.param_layout(spec):
+        p = inp.params[e.offset:e.offset + e.size]
+        if e.kind == "conv":
+            p[:] = np.abs(p) + 0.01
+        elif e.kind == "gamma":
+            p[:] = 4.0
+    x = inp.act_in[0].copy()
+    spots = [(0, h // 2, w // 2), (1, 0, 0), (2, h - 1, w - 1)]
+    for b, i, j in spots:
+        x[b, i, j, 5] = 3e38                                   # 4 * 3e38 is infinite
+    want = np.zeros((3, h, w), bool)
+    for b, i, j in spots:
+        want[b, max(i - 2, 0):i + 3, max(j - 2, 0):j + 3] = True
+    part = gpu.Partition(spec, inp.params, gpu.HPF_BF16)
+    run = part.bn_running_read().reshape(2, 2, c)
+    run[:, 0], run[:, 1] = 0.0, 1.0
+    part.bn_running_write(run.ravel())
+    try:
+        for level in (2, 1):
+            part.set_fusion(level)
+            y = part.forward_inference(torch.from_numpy(x).to("cuda:0", torch.bfloat16)).float().cpu().numpy()
+            assert not np.isnan(y).any(), level
+            assert np.array_equal(np.isinf(y), np.broadcast_to(want[..., None], y.shape)), level
+    finally:
+        part.close()
