@@ -10,8 +10,8 @@
 //   C = 64,  8 x  8: 4 tiles (two image rows each); two waves share a tile's channels
 // What bounds them is latency: two exchanges per block and direction (1.5 us each) and the chain canvas - barrier -
 // contraction - statistics.  The form with LDS tiles measured 17.4 / 10.7 / 12 us per block forward.  A run of 9 blocks of 32 channels and one
-// of 3 blocks of 64 on 128 images: 139 -> 106 us forward, 154 -> 123 us backward; the three runs of ResNet-110 v1 (51 blocks):
-// 685 -> 485 and 817 -> 570 us.
+// of 3 blocks of 64 on 128 images: 139 -> 104 us forward, 154 -> 120 us backward; the three runs of ResNet-110 v1 (52 blocks):
+// 683 -> 477 and 820 -> 568 us.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -12,8 +12,8 @@
 //
 // What bounds the LDS-tile form (20.8 us per 128-32 block forward on 256 images): 2 500 VALU and 200 LDS instructions per wave and
 // block, 25 barriers, and exchanges whose records went through LDS twice.
-// Measured on 256 images (8 micro-batches), per block: forward 20.7 -> 12.9 us (128-32) and 28.2 -> 20.9 (128-64), backward
-// 26.1 -> 20.8 and 37.3 -> 33.  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
+// Measured on 256 images (8 micro-batches), per block: forward 20.7 -> 13.1 us (128-32) and 28.2 -> 21.9 (128-64), backward
+// 26.1 -> 21.2 and 37.3 -> 35 (4 and 18 registers of the backward spill: 20 and 68 bytes of scratch per lane).  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
 // 4 us at the memory's rate), and issue: 8 waves per CU leave the matrix cores idle while they do BatchNorm.
 #include <hip/hip_runtime.h>
 
