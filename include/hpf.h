@@ -219,15 +219,19 @@ hpf_status hpf_partition_set_graphs(hpf_partition* p, int32_t enable);
  *      up to 128; basic (two 3x3 convolutions) with 32 channels at up to 256 pixels, 64 at up to
  *      128 or 16 at 32 x 32; post-activation basic (kind 2) of the same three shapes; image width 8, 16 or 32,
  *      pixel count a multiple of 32 -- run
- *      in one launch per direction that keeps each image in the LDS of one CU: one work-group per
+ *      in one launch per direction that keeps each image on one CU: one work-group per
  *      image, all of them on the chip together.  Bottleneck 64->16->16->64 at 32 x 32 pixels, whose image
  *      does not fit, runs the same way with each image cut into four bands of eight rows, one work-group
  *      per band (the image rows next to a band travel with the BatchNorm records).  Needs
- *      microbatch (x 4 for banded runs) <= number of CUs; a group call
+ *      microbatch (x 4 for banded runs) <= number of CUs and room for the BatchNorm records of the
+ *      micro-batch in LDS (on 16 x 16 images 40 images of 128->32 bottlenecks, 72 of 128->64 ones;
+ *      above, the blocks run layer by layer); a group call
  *      then processes floor(CUs / that) micro-batches (at most 8) per launch, and launches
- *      of this kind from all streams and partitions of the process are serialised through events
- *      recorded at call time.  A stream that the CALLER is capturing into a graph cannot take part
- *      in that: forward / backward calls on such a stream return HPF_EUNSUPPORTED at level 2 when the
+ *      of this kind from all streams and partitions of the process overlap only as long as their
+ *      work-groups fit the device together: a call that leaves the others no room waits through
+ *      events recorded at call time (and, if one of them is still issuing in another host thread,
+ *      for that thread).  A stream that the CALLER is capturing into a graph cannot take part in
+ *      that: forward / backward calls on such a stream return HPF_EUNSUPPORTED at level 2 when the
  *      partition has such runs -- set level 1 for partitions whose calls are captured.  If a launch
  *      ever waits in vain for its partner work-groups it gives up after about a second and sets a
  *      flag in the arena that marks the handle's results invalid.  The flag is sticky (it stays set
@@ -262,7 +266,7 @@ hpf_status hpf_partition_set_fusion(hpf_partition* p, int32_t level);
  *   every layer launched once for all of them; arguments are (host) arrays of `count` (dev) pointers, the skip
  *   arrays NULL exactly when the single-call arguments would be.
  *   At fusion level 2 the runs of pre-activation blocks with whole images per work-group go through inference
- *   variants of the same kernels (nothing is exchanged, so these launches are not serialised); banded runs and
+ *   variants of the same kernels (nothing is exchanged, so these launches wait for no other); banded runs and
  *   runs of kind-2 blocks use the per-layer kernels. */
 hpf_status hpf_partition_set_bn_momentum(hpf_partition* p, float momentum);
 hpf_status hpf_bn_running_read(hpf_partition* p, float* host_dst, size_t n_floats);
