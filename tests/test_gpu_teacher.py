@@ -91,8 +91,8 @@ def test_runs_with_weights_through_lds_layerwise(gpu, oracle):
         "3x postact32@16x16": (tuple(W.Block(W.POSTACT, 32, 32, 32, 1) for _ in range(3)), 16, 32, False),
         "3x postact16@32x32": (tuple(W.Block(W.POSTACT, 16, 16, 16, 1) for _ in range(3)), 32, 16, False),
     }
-    # 40 images per micro-batch: two chunks of polled members in the forward, five and ten in the backward's exchanges of a 128-64 block,
-    # none of them whole but the first; the largest size of the 128-32 runs
+    # 40 images per micro-batch: two chunks of polled members in the forward, three and five in the exchanges of a 128-64 block's backward;
+    # the largest size of the 128-32 runs
     spec = W.PartitionSpec(name="wide-3x(128-64-128)@16x16-b40", in_h=16, in_w=16, in_c=128, blocks=runs["wide-3x(128-64-128)@16x16"][0],
                            microbatch=40, num_microbatches=2, seed=37)
     layerwise(oracle, spec, "bf16", blockwise=False)
