@@ -47,16 +47,47 @@ __device__ __forceinline__ float block_reduce_sum(float v, float* sh) {
   return r;
 }
 
-// logits[j] = bias[j] + sum_c gs[c] * W[c][j] for one sample, all 256 threads at work whatever the class count: the
-// threads form CS slices over the channels x JT class lanes (JT = the power of two that covers min(classes, 256)),
-// every thread sums its channel slice for its classes and the slices are added in a fixed order through LDS.
-// part: 256 floats of LDS.  Ends with a barrier; lg[0 .. classes) is then complete.
+// Global average pool of one sample into gs[0 .. C) (LDS), C a multiple of 8.  A thread takes 8 channels (16 bytes in
+// bf16) of every S-th pixel and the S pixel slices are added in a fixed order: at 8x8 pixels x 64 channels two loads per
+// thread where one thread per channel walked 64.  part: HEAD_PART floats of LDS.  Ends with a barrier.
+constexpr int HEAD_PART = 16 * 260;   // >= 256 * 8, and 16 rows of 256 with a pad (fc_logits)
+template <class T>
+__device__ __forceinline__ void head_pool(const T* __restrict__ an, float* gs, float* part, int hw, int C) {
+  const float inv_hw = 1.0f / (float)hw;
+  const int groups = C >> 3;
+  for (int g0 = 0; g0 < groups; g0 += 256) {
+    const int ng = min(256, groups - g0), S = 256 / ng, sl = threadIdx.x / ng, gi = threadIdx.x - sl * ng;
+    if (sl < S) {
+      float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int i = sl; i < hw; i += S) {
+        float v[8];
+        load8(an + (size_t)i * C + (g0 + gi) * 8, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] += v[e];
+      }
+      store8(part + (sl * ng + gi) * 8, s);
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < ng * 8; c += 256) {
+      float t = 0.f;
+#pragma unroll 8
+      for (int k = 0; k < S; ++k) t += part[k * ng * 8 + c];
+      gs[g0 * 8 + c] = t * inv_hw;
+    }
+    __syncthreads();
+  }
+}
+
+// logits[j] = bias[j] + sum_c gs[c] * W[c][j] for one sample, all 256 threads at work whatever the class count.
+// part: HEAD_PART floats of LDS.  Ends with a barrier; lg[0 .. classes) is then complete.
 __device__ __forceinline__ void fc_logits(const float* gs, const float* __restrict__ wfc, const float* __restrict__ bfc, float* lg, float* part,
                                           int C, int classes) {
   if (classes <= 16) {
     // few classes (the benchmark heads have 10): every thread takes channels tid, tid + 256, ... for all classes -- its
     // loads are independent of each other (consecutive threads read consecutive weight rows) and in flight together,
-    // where a thread per (class, channel slice) walked C/16 dependent steps; sums by wave shuffles, then over the 4 waves
+    // where a thread per (class, channel slice) walked C/16 dependent steps.  The 256 partial sums of a class are a row
+    // of LDS: 16 threads per class add 16 of them each, then their own by row rotations (16 wave-wide shuffle trees took 5 us).
     float acc[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc[j] = 0.f;
@@ -68,16 +99,19 @@ __device__ __forceinline__ void fc_logits(const float* gs, const float* __restri
         if (j < classes) acc[j] = fmaf(gv, wr[j], acc[j]);
     }
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      float v = acc[j];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      if ((threadIdx.x & 63) == 0) part[(threadIdx.x >> 6) * 16 + j] = v;
-    }
+    for (int j = 0; j < 16; ++j) part[j * 260 + threadIdx.x] = acc[j];
     __syncthreads();
-    if ((int)threadIdx.x < classes) lg[threadIdx.x] = bfc[threadIdx.x] + ((part[threadIdx.x] + part[16 + threadIdx.x]) + (part[32 + threadIdx.x] + part[48 + threadIdx.x]));
+    const int j = threadIdx.x >> 4, sl = threadIdx.x & 15;
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v += part[j * 260 + k * 16 + sl];
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (sl == 0 && j < classes) lg[j] = bfc[j] + v;
     __syncthreads();
     return;
   }
+  // the threads form CS slices over the channels x JT class lanes (JT = the power of two that covers min(classes, 256));
+  // every thread sums its channel slice for its classes and the slices are added in a fixed order through LDS
   int jt = 1;
   while (jt < classes && jt < 256) jt <<= 1;
   const int cs_n = 256 / jt, jl = threadIdx.x % jt, cs = threadIdx.x / jt;
@@ -97,7 +131,8 @@ __device__ __forceinline__ void fc_logits(const float* gs, const float* __restri
   }
 }
 
-// One block per sample.  Dynamic LDS: C + classes floats.
+// One block per sample.  Dynamic LDS: C + classes floats.  Bound by latency (4 to 32 blocks a micro-batch): 25 us at 8x8x64
+// with a thread per channel in the pool and shuffle trees over the classes, now 6.0.
 template <class T>
 __global__ __launch_bounds__(256) void k_head_fwd(PtrTab as, const float* __restrict__ wfc, const float* __restrict__ bfc,
                                                   PtrTab labelss, PtrTab gs_, PtrTab dls, float* loss_accum, int hw, int C,
@@ -106,22 +141,15 @@ __global__ __launch_bounds__(256) void k_head_fwd(PtrTab as, const float* __rest
   const int32_t* __restrict__ labels = (const int32_t*)pick(labelss, blockIdx.z);
   float* __restrict__ g = (float*)pick(gs_, blockIdx.z);
   float* __restrict__ dlogits = (float*)pick(dls, blockIdx.z);
-  extern __shared__ float dyn[];
+  extern __shared__ __attribute__((aligned(16))) float dyn[];
   __shared__ float red[8];
-  __shared__ float part[256];
+  __shared__ __attribute__((aligned(16))) float part[HEAD_PART];
   float* gs = dyn;
   float* lg = dyn + C;
   const int n = blockIdx.x;
-  const T* an = a + (size_t)n * hw * C;
-  const float inv_hw = 1.0f / (float)hw;
-  for (int c = threadIdx.x; c < C; c += blockDim.x) {
-    float s = 0.f;
-    for (int i = 0; i < hw; ++i) s += to_f32(an[(size_t)i * C + c]);
-    s *= inv_hw;
-    gs[c] = s;
-    g[(size_t)n * C + c] = s;
-  }
-  __syncthreads();
+  const int y = labels[n];
+  head_pool(a + (size_t)n * hw * C, gs, part, hw, C);
+  for (int c = threadIdx.x; c < C; c += 256) g[(size_t)n * C + c] = gs[c];
   fc_logits(gs, wfc, bfc, lg, part, C, classes);
   float mx = -3.0e38f;
   for (int j = threadIdx.x; j < classes; j += blockDim.x) mx = fmaxf(mx, lg[j]);
@@ -129,7 +157,6 @@ __global__ __launch_bounds__(256) void k_head_fwd(PtrTab as, const float* __rest
   float den = 0.f;
   for (int j = threadIdx.x; j < classes; j += blockDim.x) den += expf(lg[j] - mx);
   den = block_reduce_sum(den, red);
-  const int y = labels[n];
   for (int j = threadIdx.x; j < classes; j += blockDim.x)
     dlogits[(size_t)n * classes + j] = (expf(lg[j] - mx) / den - (j == y ? 1.f : 0.f)) * inv_div;
   if (threadIdx.x == 0) atomicAdd(loss_accum, -(lg[y] - mx - logf(den)) * inv_div);
@@ -141,52 +168,46 @@ __global__ __launch_bounds__(256) void k_head_logits(PtrTab as, const float* __r
                                                      PtrTab outs, int hw, int C, int classes) {
   const T* __restrict__ a = (const T*)pick(as, blockIdx.z);
   float* __restrict__ out = (float*)pick(outs, blockIdx.z);
-  extern __shared__ float dyn[];
-  __shared__ float part[256];
+  extern __shared__ __attribute__((aligned(16))) float dyn[];
+  __shared__ __attribute__((aligned(16))) float part[HEAD_PART];
   float* gs = dyn;
   float* lg = dyn + C;
   const int n = blockIdx.x;
-  const T* an = a + (size_t)n * hw * C;
-  const float inv_hw = 1.0f / (float)hw;
-  for (int c = threadIdx.x; c < C; c += blockDim.x) {
-    float s = 0.f;
-    for (int i = 0; i < hw; ++i) s += to_f32(an[(size_t)i * C + c]);
-    gs[c] = s * inv_hw;
-  }
-  __syncthreads();
+  head_pool(a + (size_t)n * hw * C, gs, part, hw, C);
   fc_logits(gs, wfc, bfc, lg, part, C, classes);
   for (int j = threadIdx.x; j < classes; j += blockDim.x) out[(size_t)n * classes + j] = lg[j];
 }
 
-// dWfc[c][j] += sum over the samples of all members of g[n][c] * dlogits[n][j]: a thread per output element walks the
-// samples (one atomic per element and launch; a block per sample adding its outer product cost b*g atomics per element).
-// Dynamic LDS: ng * b * classes floats (the dlogits of the launch).
-__global__ __launch_bounds__(256) void k_head_wgrad(PtrTab gs_, PtrTab dls, float* g_wfc, int ng, int b, int C, int classes) {
-  extern __shared__ float sdl[];
-  for (int z = 0; z < ng; ++z) {
-    const float* __restrict__ dl = (const float*)pick(dls, z);
-    for (int i = threadIdx.x; i < b * classes; i += 256) sdl[z * b * classes + i] = dl[i];
-  }
-  __syncthreads();
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= C * classes) return;
-  const int c = i / classes, j = i - c * classes;
-  float s = 0.f;
-  for (int z = 0; z < ng; ++z) {
-    const float* __restrict__ g = (const float*)pick(gs_, z);
-    for (int n = 0; n < b; ++n) s = fmaf(g[(size_t)n * C + c], sdl[(z * b + n) * classes + j], s);
-  }
-  atomicAdd(&g_wfc[i], s);
-}
-
-// One block per sample: dbfc += dlogits, da[n,i,c] = (dlogits[n] . Wfc[c]) / hw (dWfc: k_head_wgrad).
+// Blocks [0, b) of every member, one per sample: dbfc += dlogits, da[n,i,c] = (dlogits[n] . Wfc[c]) / hw.
+// The blocks behind them (member 0 only): dWfc[c][j] += sum over the samples of all members of g[n][c] * dlogits[n][j], a
+// thread per output element walking the samples (one atomic per element and launch; a block per sample adding its outer
+// product cost b*g atomics per element).  One launch: the two parts do not depend on each other.
+// Dynamic LDS: max(C + classes, ng * b * classes) floats.
 template <class T>
 __global__ __launch_bounds__(256) void k_head_bwd(PtrTab gs_, PtrTab dls, const float* __restrict__ wfc, float* g_wfc,
-                                                  float* g_bfc, PtrTab das, int hw, int C, int classes) {
-  (void)gs_; (void)g_wfc;
+                                                  float* g_bfc, PtrTab das, int ng, int b, int hw, int C, int classes) {
+  extern __shared__ float dyn[];
+  if ((int)blockIdx.x >= b) {
+    if (blockIdx.z != 0) return;
+    for (int z = 0; z < ng; ++z) {
+      const float* __restrict__ dl = (const float*)pick(dls, z);
+      for (int i = threadIdx.x; i < b * classes; i += 256) dyn[z * b * classes + i] = dl[i];
+    }
+    __syncthreads();
+    const int i = (blockIdx.x - b) * 256 + threadIdx.x;
+    if (i >= C * classes) return;
+    const int c = i / classes, j = i - c * classes;
+    float s = 0.f;
+    for (int z = 0; z < ng; ++z) {
+      const float* __restrict__ g = (const float*)pick(gs_, z);
+#pragma unroll 8
+      for (int n = 0; n < b; ++n) s = fmaf(g[(size_t)n * C + c], dyn[(z * b + n) * classes + j], s);
+    }
+    atomicAdd(&g_wfc[i], s);
+    return;
+  }
   const float* __restrict__ dlogits = (const float*)pick(dls, blockIdx.z);
   T* __restrict__ da = (T*)pick(das, blockIdx.z);
-  extern __shared__ float dyn[];
   float* dl = dyn;          // classes
   float* dg = dyn + classes;  // C
   const int n = blockIdx.x;
@@ -332,6 +353,15 @@ __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ 
   }
 }
 
+// LDS of the pooling heads: C + classes floats beside head_pool's and fc_logits' own.  Up to 64 KiB together needs nothing; above it
+// the limit of the kernel is stated first (not a stream operation, so a capture does not see it).
+constexpr size_t HEAD_MAX_DYN = 63 * 1024;
+hipError_t head_lds(const void* kernel, size_t dyn) {
+  if (dyn > HEAD_MAX_DYN) return hipErrorInvalidValue;
+  if (dyn + (HEAD_PART + 8) * sizeof(float) <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)HEAD_MAX_DYN);
+}
+
 unsigned grid_for(size_t n, unsigned cap = 2048) {
   size_t g = (n + 255) / 256;
   if (g < 1) g = 1;
@@ -351,6 +381,8 @@ hipError_t launch_head_fwd(int dt, int ng, const PtrTab& a, const float* wfc, co
                            int classes, float divisor, hipStream_t stream) {
   const size_t lds = (size_t)(C + classes) * sizeof(float);
   const dim3 grid((unsigned)b, 1, (unsigned)ng);
+  const hipError_t e = head_lds(dt == DT_BF16 ? reinterpret_cast<const void*>(k_head_fwd<bf16_t>) : reinterpret_cast<const void*>(k_head_fwd<float>), lds);
+  if (e != hipSuccess) return e;
   if (dt == DT_BF16)
     k_head_fwd<bf16_t><<<grid, 256, lds, stream>>>(a, wfc, bfc, labels, gp, dlogits, loss_accum, hw, C, classes, 1.0f / divisor);
   else
@@ -362,6 +394,8 @@ hipError_t launch_head_logits(int dt, int ng, const PtrTab& a, const float* wfc,
                               int hw, int C, int classes, hipStream_t stream) {
   const size_t lds = (size_t)(C + classes) * sizeof(float);
   const dim3 grid((unsigned)b, 1, (unsigned)ng);
+  const hipError_t e = head_lds(dt == DT_BF16 ? reinterpret_cast<const void*>(k_head_logits<bf16_t>) : reinterpret_cast<const void*>(k_head_logits<float>), lds);
+  if (e != hipSuccess) return e;
   if (dt == DT_BF16) k_head_logits<bf16_t><<<grid, 256, lds, stream>>>(a, wfc, bfc, logits, hw, C, classes);
   else k_head_logits<float><<<grid, 256, lds, stream>>>(a, wfc, bfc, logits, hw, C, classes);
   return hipGetLastError();
@@ -369,17 +403,14 @@ hipError_t launch_head_logits(int dt, int ng, const PtrTab& a, const float* wfc,
 
 hipError_t launch_head_bwd(int dt, int ng, const PtrTab& gp, const PtrTab& dlogits, const float* wfc, float* g_wfc,
                            float* g_bfc, const PtrTab& da, int b, int hw, int C, int classes, hipStream_t stream) {
-  const size_t lds = (size_t)(C + classes) * sizeof(float);
-  const dim3 grid((unsigned)b, 1, (unsigned)ng);
-  if (dt == DT_BF16)
-    k_head_bwd<bf16_t><<<grid, 256, lds, stream>>>(gp, dlogits, wfc, g_wfc, g_bfc, da, hw, C, classes);
-  else
-    k_head_bwd<float><<<grid, 256, lds, stream>>>(gp, dlogits, wfc, g_wfc, g_bfc, da, hw, C, classes);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const size_t wl = (size_t)ng * b * classes * sizeof(float);
+  const size_t wl = (size_t)ng * b * classes * sizeof(float), bl = (size_t)(C + classes) * sizeof(float);
   if (wl > 48 * 1024) return hipErrorInvalidValue;
-  k_head_wgrad<<<dim3((unsigned)(((size_t)C * classes + 255) / 256)), 256, wl, stream>>>(gp, dlogits, g_wfc, ng, b, C, classes);
+  const dim3 grid((unsigned)(b + (C * classes + 255) / 256), 1, (unsigned)ng);
+  const size_t lds = wl > bl ? wl : bl;
+  if (dt == DT_BF16)
+    k_head_bwd<bf16_t><<<grid, 256, lds, stream>>>(gp, dlogits, wfc, g_wfc, g_bfc, da, ng, b, hw, C, classes);
+  else
+    k_head_bwd<float><<<grid, 256, lds, stream>>>(gp, dlogits, wfc, g_wfc, g_bfc, da, ng, b, hw, C, classes);
   return hipGetLastError();
 }
 

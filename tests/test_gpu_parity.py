@@ -219,6 +219,16 @@ def test_head_only_and_stem_only_partitions(gpu, oracle, mode):
 
 
 @pytest.mark.parametrize("mode", ["f32", "bf16"])
+@pytest.mark.parametrize("kind,hw,c,classes", [(2, 1, 4096, 10), (2, 1, 2080, 16), (2, 3, 48, 17), (1, 32, 16, 2), (2, 1, 12000, 10)])
+def test_head_shapes(gpu, oracle, mode, kind, hw, c, classes):
+    """The pool's slices (more and fewer pixels than slices, channel groups that divide nothing, more than one pass over the
+    channels), both forms of the logits, and channel counts that take the kernels' LDS beyond 64 KiB."""
+    spec = W.PartitionSpec(name=f"head-{kind}-{hw}-{c}-{classes}", in_h=hw, in_w=hw, in_c=c, blocks=(), has_head=True,
+                           head_bn=kind == 1, num_classes=classes, microbatch=3, num_microbatches=2, seed=11)
+    check(oracle, spec, mode, strict=True)
+
+
+@pytest.mark.parametrize("mode", ["f32", "bf16"])
 def test_deep_partitions_with_relu_always_active(gpu, oracle, mode):
     """beta shifted by +6 puts every pre-activation above 0: no ReLU decision can differ, so the deep
     backward pass (indexing, accumulation, shortcut gradients) must agree element by element."""
