@@ -201,11 +201,11 @@ hpf_status hpf_grad_accum_zero(hpf_partition* p, void* hip_stream);
  * refreshes the bf16 weight copies; clears G; starts the next batch.  Needs all backward calls. */
 hpf_status hpf_sgd_step(hpf_partition* p, float lr, float momentum, void* hip_stream);
 
-/* Forward and backward kernel sequences of a micro-batch are captured into HIP graphs on first use
- * and replayed while the caller passes the same buffers (a call with other pointers re-captures).
- * enable == 0 switches to plain launches; default is enabled.  The default (NULL) stream, a
- * stream that is itself being captured by the caller, and sequences of fewer than 8 launches
- * (cheaper to launch than a graph) always get plain launches. */
+/* Long forward and backward kernel sequences of a call (96 launches and more) are captured into a HIP graph when the
+ * call comes again with the caller pointers of the time before, and replayed as long as the pointers stay the same (the
+ * default stream and streams that are already capturing always get plain launches).  Enabled by default; 0 switches
+ * back to launching every kernel.  Shorter sequences always get plain launches: they leave the device no idle time and
+ * need nothing prepared for new pointers. */
 hpf_status hpf_partition_set_graphs(hpf_partition* p, int32_t enable);
 
 /* How far bf16 mode fuses the kernel schedule; the arithmetic is the same at every level, summation

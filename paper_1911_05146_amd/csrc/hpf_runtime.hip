@@ -657,14 +657,19 @@ enum ProfCat { PROF_NONE = -1, PROF_RES_FWD = 0, PROF_RES_BWD, PROF_RES_WGRAD, P
 const char* const kProfNames[PROF_N] = {"resident_forward", "resident_backward", "resident_wgrad", "wgrad_grouped", "conv_forward",
                                         "conv_dgrad",       "other_forward",     "other_backward"};
 
-// One captured HIP graph of a micro-batch's forward or backward kernel sequence, valid for the caller
-// pointers it was captured with.
+// The kernel sequence of a micro-batch's forward or backward call: caller pointers and launches of the last call and,
+// for long sequences, the HIP graph captured with those pointers.
 struct GraphSlot {
   hipGraphExec_t exec = nullptr;
   std::vector<const void*> key;
-  bool direct = false;   // the sequence is so short that plain launches are cheaper than a graph launch
+  int launches = 0;
 };
-constexpr int kMinGraphLaunches = 8;
+// A plain launch costs the host 3 to 5 us and a dependent one takes the device at least 4.5 us, so the host keeps ahead;
+// a graph launch costs the device a gap of 13 us, and each new set of pointers a capture (0.1 ms for 20 launches).
+// Measured per batch, every call launched plainly / replayed: ResNet-110 partition 453 / 460 us, ResNet-1001 fine cut, ten
+// calls, 1382 / 1449, VGG-16 1668 / 1683, first batch on new buffers 1421 / 1581 and 1829 / 2038.  What a graph saves is
+// host time: ResNet-152 stage 3, 200 and 230 launches a call, 11.59 ms either way, of which the host is busy for 2.4 / 0.3 ms.
+constexpr int kMinGraphLaunches = 96;
 
 struct hpf_partition {
   Plan P;
@@ -1235,25 +1240,26 @@ hpf_status wait_all_backward(hpf_partition* p, hipStream_t s) {
   return HPF_OK;
 }
 
-// Runs `body` (kernel launches on stream s only) through a HIP graph: replayed if one captured with the
-// same caller pointers exists, captured and instantiated first otherwise.  The sequences contain kernel
-// nodes only.  Falls back to direct launches when graphs are off or the stream is already capturing.
+// Runs `body` (kernel launches on stream s only), through a HIP graph where that is the better way: a long sequence that
+// is called again with the pointers of the call before (kMinGraphLaunches).  The sequences contain kernel nodes only.
+// Launches go out one by one when graphs are off or the stream is already capturing.
 template <class Body>
 hpf_status run_graphed(hpf_partition* p, GraphSlot& slot, const std::vector<const void*>& key, hipStream_t s, Ctx& c, Body body) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   // the default (NULL) stream cannot be captured
-  if (!p->use_graphs || p->profiling || s == nullptr || hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+  const bool graphs = p->use_graphs && !p->profiling && s != nullptr && hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+  const bool again = slot.key == key;
+  if (!graphs || !again || slot.launches < kMinGraphLaunches) {
     body();
-    return c.err == hipSuccess ? HPF_OK : fail(HPF_EDEVICE, "%s: %s", c.where, hipGetErrorString(c.err));
+    if (c.err != hipSuccess) return fail(HPF_EDEVICE, "%s: %s", c.where, hipGetErrorString(c.err));
+    if (graphs && !again) {
+      if (slot.exec) { (void)hipGraphExecDestroy(slot.exec); slot.exec = nullptr; }
+      slot.key = key;
+      slot.launches = c.n_launches;
+    }
+    return HPF_OK;
   }
-  if (slot.direct && slot.key == key) {
-    body();
-    return c.err == hipSuccess ? HPF_OK : fail(HPF_EDEVICE, "%s: %s", c.where, hipGetErrorString(c.err));
-  }
-  const bool hit = slot.exec && slot.key == key;
-  if (!hit) {
-    slot.direct = false;
-    if (slot.exec) { (void)hipGraphExecDestroy(slot.exec); slot.exec = nullptr; }
+  if (!slot.exec) {
     hipGraph_t graph = nullptr;
     if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) return fail(HPF_EDEVICE, "hipStreamBeginCapture failed");
     body();
@@ -1261,14 +1267,6 @@ hpf_status run_graphed(hpf_partition* p, GraphSlot& slot, const std::vector<cons
     if (c.err != hipSuccess || e != hipSuccess || !graph) {
       if (graph) (void)hipGraphDestroy(graph);
       return fail(HPF_EDEVICE, "graph capture failed: %s: %s", c.where, hipGetErrorString(c.err != hipSuccess ? c.err : e));
-    }
-    slot.key = key;
-    if (c.n_launches < kMinGraphLaunches) {   // capture recorded the launches without running them: run them now
-      (void)hipGraphDestroy(graph);
-      slot.direct = true;
-      c.n_launches = 0;
-      body();
-      return c.err == hipSuccess ? HPF_OK : fail(HPF_EDEVICE, "%s: %s", c.where, hipGetErrorString(c.err));
     }
     const hipError_t ei = hipGraphInstantiate(&slot.exec, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
@@ -1714,9 +1712,9 @@ hpf_status hpf_partition_set_fusion(hpf_partition* p, int32_t enable) {
   for (int i = 0; i < p->P.d.num_microbatches; ++i)
     if (p->fwd_done[i] && !p->bwd_done[i]) return fail(HPF_ESTATE, "micro-batch %d is between forward and backward", i);
   if (p->fuse != enable) {   // cached graphs hold the other kernel sequence
-    for (GraphSlot& g : p->g_fwd) { if (g.exec) (void)hipGraphExecDestroy(g.exec); g.exec = nullptr; g.direct = false; g.key.clear(); }
-    for (GraphSlot& g : p->g_bwd) { if (g.exec) (void)hipGraphExecDestroy(g.exec); g.exec = nullptr; g.direct = false; g.key.clear(); }
-    for (GraphSlot& g : p->g_inf) { if (g.exec) (void)hipGraphExecDestroy(g.exec); g.exec = nullptr; g.direct = false; g.key.clear(); }
+    for (GraphSlot& g : p->g_fwd) { if (g.exec) (void)hipGraphExecDestroy(g.exec); g.exec = nullptr; g.key.clear(); }
+    for (GraphSlot& g : p->g_bwd) { if (g.exec) (void)hipGraphExecDestroy(g.exec); g.exec = nullptr; g.key.clear(); }
+    for (GraphSlot& g : p->g_inf) { if (g.exec) (void)hipGraphExecDestroy(g.exec); g.exec = nullptr; g.key.clear(); }
   }
   p->fuse = enable;
   return HPF_OK;
@@ -1728,7 +1726,7 @@ hpf_status hpf_partition_set_bn_momentum(hpf_partition* p, float momentum) {
   for (int i = 0; i < p->P.d.num_microbatches; ++i)
     if (p->fwd_done[i] && !p->bwd_done[i]) return fail(HPF_ESTATE, "micro-batch %d is between forward and backward", i);
   if (p->bn_momentum != momentum) {   // cached graphs hold the other kernel sequence / the old factor
-    for (GraphSlot& g : p->g_fwd) { if (g.exec) (void)hipGraphExecDestroy(g.exec); g.exec = nullptr; g.direct = false; g.key.clear(); }
+    for (GraphSlot& g : p->g_fwd) { if (g.exec) (void)hipGraphExecDestroy(g.exec); g.exec = nullptr; g.key.clear(); }
   }
   p->bn_momentum = momentum;
   return HPF_OK;

@@ -23,6 +23,23 @@ def split_model(name: str, blocks: Sequence[W.Block], n_parts: int, in_hw: int, 
                            microbatch, num_microbatches, seed) for p in range(n_parts)]
 
 
+_HW_QUEUES = 4   # hardware queues that the runtime deals a process's streams to (its default)
+
+
+def _streams_apart(torch, device, n):
+    """n streams, each on a hardware queue of its own as long as there are enough of them.  Work of two streams that share a
+    queue runs one after the other: four partitions of ResNet-110 took 5.1 ms per batch on four queues and 7.5 to 12.5 ms
+    where two or more shared one.  The runtime gives a stream the queue that the fewest streams hold when it is first
+    used: after a few streams all queues are held by equally many, and from then on consecutive ones get different queues."""
+    streams = [torch.cuda.Stream(device) for _ in range(_HW_QUEUES + n)]
+    word = torch.empty(1, device=device)
+    for s in streams:
+        with torch.cuda.stream(s):
+            word.zero_()
+    torch.cuda.synchronize(device)
+    return streams[_HW_QUEUES:]
+
+
 class Pipeline:
     """specs: the partitions in model order (the first holds the stem, the last the head); params: the flat
     parameter vector of the whole model (canonical order = concatenation of the partitions' vectors).
@@ -60,8 +77,20 @@ class Pipeline:
             self.parts.append(hpf.Partition(s, piece, compute_dtype, device))
             if fusion is not None:
                 self.parts[-1].set_fusion(fusion)
-        self.streams = [torch.cuda.Stream(self.device) for _ in self.parts]
+        self.streams = _streams_apart(torch, self.device, len(self.parts))
         self._keep = []
+        # Boundary tensors of one batch, per partition and micro-batch: what it sends forward and the gradients it returns.
+        # Kept from batch to batch, so that a call meets the addresses its HIP graph was captured with.  A batch writes
+        # them again in the order of the streams: the forward of (p, i) follows p's backward of (p, i) in the batch
+        # before, which waited for every partition that had read the output; the backward of (p, i) follows p's forward,
+        # which waited for those that had read its gradients and have gone on to this batch.
+        def empty(shape, dtype):
+            return torch.empty(shape, dtype=dtype, device=self.device) if shape else None
+        self._sent = [[{"act": empty(None if p.spec.has_head else p.out_shape, p.tdtype), "skip": empty(p.skip_out_shape, p.tdtype)}
+                       for _ in range(self.m)] for p in self.parts]
+        self._grads = [[{"act": empty(None if p.spec.has_stem else p.in_shape, p.tdtype), "skip": empty(p.skip_in_shape, p.tdtype)}
+                        for _ in range(self.m)] for p in self.parts]
+        torch.cuda.synchronize(self.device)   # the allocator may hand out memory that work on the current stream still uses
 
     @property
     def loss(self):
@@ -78,8 +107,8 @@ class Pipeline:
             self.parts[-1].loss.zero_()
         fwd_done = [[torch.cuda.Event() for _ in units] for _ in range(P)]
         bwd_done = [[torch.cuda.Event() for _ in units] for _ in range(P)]
-        acts = [[None] * self.m for _ in range(P)]   # acts[p][i]: output of partition p (input of p+1)
-        errs = [[None] * self.m for _ in range(P)]   # errs[p][i]: partial error leaving partition p (into p-1)
+        acts = [[t["act"] for t in row] for row in self._sent]    # acts[p][i]: output of partition p (input of p+1)
+        errs = [[t["act"] for t in row] for row in self._grads]   # errs[p][i]: partial error leaving partition p (into p-1)
         # ---- fill and drain, forward: unit u reaches partition p after it left p-1
         for ui, unit in enumerate(units):
             for p, part in enumerate(self.parts):
@@ -88,12 +117,11 @@ class Pipeline:
                     s.wait_event(fwd_done[p - 1][ui])
                 x = [act_in[i] for i in unit] if p == 0 else [acts[p - 1][i] for i in unit]
                 lab = [labels[i] for i in unit] if part.spec.has_head else None
+                out = None if part.spec.has_head else [acts[p][i] for i in unit]
                 if g == 1:
-                    out = [part.forward_microbatch(unit[0], x[0], lab[0] if lab else None, stream=s)]
+                    part.forward_microbatch(unit[0], x[0], lab[0] if lab else None, out[0] if out else None, stream=s)
                 else:
-                    out = part.forward_microbatches(unit[0], x, lab, stream=s) or [None] * g
-                for i, o in zip(unit, out):
-                    acts[p][i] = o
+                    part.forward_microbatches(unit[0], x, lab, out, stream=s)
                 fwd_done[p][ui].record(s)
         # ---- backward: the partial errors travel from the head to the stem
         for ui, unit in enumerate(units):
@@ -102,16 +130,15 @@ class Pipeline:
                 if p < P - 1:
                     s.wait_event(bwd_done[p + 1][ui])
                 e_in = None if part.spec.has_head else [errs[p + 1][i] for i in unit]
+                out = None if part.spec.has_stem else [errs[p][i] for i in unit]
                 if g == 1:
-                    out = [part.backward_microbatch(unit[0], e_in[0] if e_in else None, stream=s)]
+                    part.backward_microbatch(unit[0], e_in[0] if e_in else None, out[0] if out else None, stream=s)
                 else:
-                    out = part.backward_microbatches(unit[0], g, e_in, stream=s) or [None] * g
-                for i, o in zip(unit, out):
-                    errs[p][i] = o
+                    part.backward_microbatches(unit[0], g, e_in, out, stream=s)
                 bwd_done[p][ui].record(s)
-        # the boundary tensors must outlive the queued work: those of the batch before are let go only now that this
+        # the caller's tensors must outlive the queued work: those of the batch before are let go only now that this
         # batch is queued behind it on the same streams
-        self._keep = [self._keep[-4:] if self._keep else None, acts, errs, act_in, labels]
+        self._keep = [self._keep[-2:] if self._keep else None, act_in, labels]
 
     def _run_batch_cut(self, act_in, labels):
         """The same schedule for partitions cut at layer granularity.  Every rank walks its Forward list (receives
@@ -123,8 +150,7 @@ class Pipeline:
             self.parts[-1].loss.zero_()
         fwd_done = [[torch.cuda.Event() for _ in range(self.m)] for _ in range(P)]
         bwd_done = [[torch.cuda.Event() for _ in range(self.m)] for _ in range(P)]
-        sent = [[{} for _ in range(self.m)] for _ in range(P)]       # sent[p][i][tensor]: forward outputs of rank p
-        grads = [[{} for _ in range(self.m)] for _ in range(P)]      # grads[p][i][tensor]: gradients rank p returns for what it received
+        sent, grads = self._sent, self._grads   # [p][i][tensor]: forward outputs of rank p, gradients it returns for what it received
         for i in range(self.m):
             for p, part in enumerate(self.parts):
                 s, L = self.streams[p], self.lists[p]
@@ -132,9 +158,8 @@ class Pipeline:
                 for msg in L.forward_recv:
                     s.wait_event(fwd_done[msg.src][i])
                     got[msg.tensor] = sent[msg.src][i][msg.tensor]
-                out, skip_out = part.forward_microbatch_cut(i, got["act"], got["skip"],
-                                                            labels[i] if part.spec.has_head else None, stream=s)
-                sent[p][i] = {"act": out, "skip": skip_out}
+                part.forward_microbatch_cut(i, got["act"], got["skip"], labels[i] if part.spec.has_head else None,
+                                            sent[p][i]["act"], sent[p][i]["skip"], stream=s)
                 fwd_done[p][i].record(s)
         for i in range(self.m):
             for p in reversed(range(P)):
@@ -143,10 +168,9 @@ class Pipeline:
                 for msg in L.backward_recv:                         # gradients of what this rank sent
                     s.wait_event(bwd_done[msg.dst][i])
                     got[msg.tensor] = grads[msg.dst][i][msg.tensor]
-                err_out, skip_err_out = part.backward_microbatch_cut(i, got["act"], got["skip"], stream=s)
-                grads[p][i] = {"act": err_out, "skip": skip_err_out}
+                part.backward_microbatch_cut(i, got["act"], got["skip"], grads[p][i]["act"], grads[p][i]["skip"], stream=s)
                 bwd_done[p][i].record(s)
-        self._keep = [self._keep[-4:] if self._keep else None, sent, grads, act_in, labels]
+        self._keep = [self._keep[-2:] if self._keep else None, act_in, labels]
 
     def synchronize(self):
         self.torch.cuda.synchronize(self.device)
