@@ -27,23 +27,6 @@ __device__ __forceinline__ float2 bn_scale_shift(float mean, float invstd, float
   return make_float2(sc, fmaf(-mean, sc, beta));
 }
 
-// Sums within a row of 16 lanes by DPP row rotations (one VALU instruction per step, no LDS round trip).
-// row_sum<N>(v): every lane gets the sum over the lanes of its row that are congruent to it modulo N.
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-template <int N>
-__device__ __forceinline__ float row_sum(float v) {
-  static_assert(N == 1 || N == 2 || N == 4 || N == 8 || N == 16, "N divides 16");
-  if (N <= 8) v += dpp_mov<0x128>(v);   // row_ror:8
-  if (N <= 4) v += dpp_mov<0x124>(v);   // row_ror:4
-  if (N <= 2) v += dpp_mov<0x122>(v);   // row_ror:2
-  if (N <= 1) v += dpp_mov<0x121>(v);   // row_ror:1
-  return v;
-}
-__device__ __forceinline__ float sum16(float v) { return row_sum<1>(v); }   // over the 16 pixels of a tile
-
 __device__ __forceinline__ void publish_word(u64* slot, int me, int nw, int w, float v, unsigned tag) {
   __hip_atomic_store(slot + (size_t)me * nw + w, ((u64)tag << 32) | (u64)__float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

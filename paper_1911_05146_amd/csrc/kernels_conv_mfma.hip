@@ -15,8 +15,8 @@
 // lane groups of a wave cover 16 consecutive channels = 32 contiguous bytes per pixel.
 //
 // Work-group: 256 threads = 4 waves arranged WR x WC over a BM (pixels) x BN (channels) tile;
-// K advances 32 per step (one MFMA), double-buffered in LDS with one barrier per step and the
-// next step's global loads in flight during the MFMAs.
+// K advances 64 per step (32 in the 128-row tile), double-buffered in LDS with one barrier per step and the
+// next steps' global loads in flight during the MFMAs.
 #include <mutex>
 
 #include "hpf_device.h"
@@ -27,9 +27,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-constexpr int KC = 32;          // reduction elements per step
+constexpr int KC = 32;          // reduction elements of one MFMA; packed weights are padded to it
 constexpr size_t BIG_MAX_LDS = 128 * 1024;   // dynamic LDS limit set for the 128 x 128 x 64 kernels (stages + coefficients)
-constexpr int LSTR = KC + 8;    // LDS row stride in bf16 (80 bytes: conflict-free 16-byte reads)
 
 // relu(bn(x)) of the 8 bf16 values in q, channels c..c+7 (c a multiple of 8); coef holds per channel
 // {scale = gamma*invstd, shift = beta - mean*scale}, so the operand is max(x*scale + shift, 0).
@@ -164,13 +163,7 @@ __device__ __forceinline__ void conv_epilogue(floatx4 (&acc)[CT][PT], int wr, in
 #pragma unroll
   for (int i = 0; i < CT; ++i)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) {
-        s1[i][v] += __shfl_xor(s1[i][v], o);
-        s2[i][v] += __shfl_xor(s2[i][v], o);
-      }
-    }
+    for (int v = 0; v < 4; ++v) { s1[i][v] = sum16(s1[i][v]); s2[i][v] = sum16(s2[i][v]); }
   if ((lane & 15) == 0) {
 #pragma unroll
     for (int i = 0; i < CT; ++i) {
@@ -197,6 +190,12 @@ __device__ __forceinline__ void conv_epilogue(floatx4 (&acc)[CT][PT], int wr, in
   }
 }
 
+// What bounds the launches this kernel takes (few work-groups, each with one wave per SIMD and nothing to hide behind) is the chain of
+// a step: addresses, LDS reads, MFMA, LDS stores, barrier.  Steps of 64 reduction elements in the 64-row tiles: half as
+// many chains as with 32, and no integer loops in the addresses.  3x3 convolutions of ResNet-20's transitions, 8 images: 64 -> 64
+// channels at 8x8 13.4 -> 10.0 us (two forms of it 13.2 -> 11.5 and 11.1 -> 7.9), 64 -> 32 gradient at 16x16 12.0 -> 10.7; 1x1
+// 256 -> 1024 on 12 544 rows 34.5 -> 30.9.  Four chunks in flight instead of two: no faster (ResNet-20 439 against 433 us per
+// batch), and a work-group less per CU (35.8).
 template <int BM, int BN, int WR, int WC, int MODE, int EPI, int PRO>
 __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __restrict__ wpk, PtrTab outs, PtrTab adds,
                                                    ConvGeom g, ConvEpi epi, ConvPro pro) {
@@ -207,9 +206,11 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
   static_assert(WR * WC == 4, "4 waves");
   constexpr int WPX = BM / WR, WCH = BN / WC, PT = WPX / 16, CT = WCH / 16;
   static_assert(PT >= 1 && CT >= 1, "tile too small");
-  constexpr int A_UNITS = (BM * 4) / 256;
+  constexpr int KS = BM == 64 ? 64 : 32, UPR = KS / 8, RPP = 256 / UPR;   // reduction elements per step, 16-byte units per row, rows per pass of the threads
+  constexpr int LSTR = KS + 8;       // LDS row stride in bf16 (144 or 80 bytes: conflict-free 16-byte reads)
+  constexpr int A_UNITS = BM / RPP;
   static_assert(A_UNITS >= 1, "BM >= 64");
-  constexpr int W_UNITS = (BN * 4 + 255) / 256;
+  constexpr int W_UNITS = (BN + RPP - 1) / RPP;
 
   __shared__ __attribute__((aligned(16))) bf16_t sA[2][BM * LSTR];
   __shared__ __attribute__((aligned(16))) bf16_t sW[2][BN * LSTR];
@@ -217,30 +218,30 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave / WC, wc = wave % WC;
   const int row0 = blockIdx.x * BM, ch0 = blockIdx.y * BN;
-  const int grp = tid & 3;
+  const int grp = tid % UPR, trow = tid / UPR;
   const int HoWo = g.Ho * g.Wo;
   const int sshift = g.stride - 1;  // stride is 1 or 2
 
   int a_img[A_UNITS], a_h[A_UNITS], a_w[A_UNITS];
-  bool a_ok[A_UNITS];
 #pragma unroll
   for (int u = 0; u < A_UNITS; ++u) {
-    const int m = row0 + (tid >> 2) + u * 64;
-    a_ok[u] = m < g.M;
-    const int mm = a_ok[u] ? m : 0;
+    const int m = row0 + trow + u * RPP;
+    const int mm = m < g.M ? m : 0;
     const int img = mm / HoWo;
     const int rem = mm - img * HoWo;
     const int p = rem / g.Wo, q = rem - p * g.Wo;
     a_img[u] = img * g.Hs * g.Ws;
     if (MODE == CONV_FWD) { a_h[u] = p * g.stride - g.pad; a_w[u] = q * g.stride - g.pad; }
     else { a_h[u] = p + g.pad; a_w[u] = q + g.pad; }
+    if (m >= g.M) a_h[u] = -(1 << 20);   // a row outside every image
   }
 
-  // NPRE chunks are kept in flight in registers: at these sizes a work-group lives for a handful of
-  // K steps only, so what matters is how many global loads are outstanding, not the MFMA rate.
-  constexpr int NPRE = 4;
-  struct Slot { uint4 a[A_UNITS]; uint4 w[W_UNITS]; int c; bool av[A_UNITS]; };
-  Slot sl0, sl1, sl2, sl3;   // named, not an array: they must stay in registers
+  // NPRE chunks are kept in flight in registers.  Every load is issued unconditionally (outside the image, the tensor or the reduction
+  // it reads a clamped address and is zeroed when it is stored to LDS; past the last chunk the last one is loaded again), so
+  // the number of outstanding loads is known at every wait.
+  constexpr int NPRE = 2;
+  struct Slot { uint4 a[A_UNITS]; uint4 w[W_UNITS]; int c; bool av[A_UNITS], wv; };
+  Slot sl0, sl1;   // named, not an array: they must stay in registers
   if (PRO) {
     const float* stt = (const float*)pick(pro.stats, blockIdx.z);
     for (int c = tid; c < g.Cs; c += 256) {
@@ -250,27 +251,23 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
     __syncthreads();
   }
 
-  // (filter tap row, tap column, channel) of this thread's 16-byte unit in the chunk that is loaded
-  // next; chunks are loaded in order, so the position advances by KC channels per load (no divisions)
-  int lk = grp * 8, lr, ls, lc;
-  {
-    const int tap = lk / g.Cs;
-    lc = lk - tap * g.Cs;
-    lr = tap / g.R;
-    ls = tap - lr * g.R;
-  }
-  auto load_chunk = [&](int kc, Slot& q) {
-    uint4 (&qa)[A_UNITS] = q.a;
-    uint4 (&qw)[W_UNITS] = q.w;
-    const int c = lc, r = lr, s = ls;
-    const bool kvalid = lk < g.Ktot;
-    lk += KC; lc += KC;
-    while (lc >= g.Cs) { lc -= g.Cs; if (++ls == g.R) { ls = 0; ++lr; } }
+  // filter tap and channel of this thread's unit: k / Cs by a multiplication (exact for the k here: k*Cs < 2^32), tap / 3 likewise (taps 0..8)
+  const uint32_t cs_inv = 0xffffffffu / (uint32_t)g.Cs + 1u;
+  const int nk = (g.Kpad + KS - 1) / KS;
+  int kc_ld = 0;
+  const bf16_t* wrow = wpk + (size_t)(ch0 + trow % BN) * g.Kpad;   // tiles of fewer rows than a pass: the other threads load copies
+  auto load_chunk = [&](Slot& q) {
+    const int k = kc_ld * KS + grp * 8;
+    kc_ld += kc_ld + 1 < nk;
+    const bool kvalid = k < g.Ktot;
+    const int tap = kvalid && g.R != 1 ? (int)__umulhi((uint32_t)k, cs_inv) : 0;
+    const int c = kvalid ? k - tap * g.Cs : 0;
+    const int r = g.R == 1 ? 0 : (tap * 11) >> 5, s = g.R == 1 ? 0 : tap - 3 * r;
     q.c = c;
 #pragma unroll
     for (int u = 0; u < A_UNITS; ++u) {
       int hs, ws;
-      bool v = a_ok[u] && kvalid;
+      bool v = kvalid;
       if (MODE == CONV_FWD) {
         hs = a_h[u] + r; ws = a_w[u] + s;
       } else {
@@ -280,29 +277,25 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
       }
       v = v && (unsigned)hs < (unsigned)g.Hs && (unsigned)ws < (unsigned)g.Ws;
       q.av[u] = v;
-      qa[u] = v ? *reinterpret_cast<const uint4*>(src + (size_t)(a_img[u] + hs * g.Ws + ws) * g.Cs + c)
-                : make_uint4(0u, 0u, 0u, 0u);
+      q.a[u] = *reinterpret_cast<const uint4*>(src + (v ? (size_t)(a_img[u] + hs * g.Ws + ws) * g.Cs + c : (size_t)c));
     }
+    q.wv = KS == KC || k < g.Kpad;     // a last chunk of 32
 #pragma unroll
-    for (int u = 0; u < W_UNITS; ++u) {
-      const int unit = tid + u * 256;
-      if (unit < BN * 4)
-        qw[u] = *reinterpret_cast<const uint4*>(wpk + (size_t)(ch0 + (unit >> 2)) * g.Kpad + kc * KC + (unit & 3) * 8);
-    }
+    for (int u = 0; u < W_UNITS; ++u) q.w[u] = *reinterpret_cast<const uint4*>(wrow + (size_t)u * RPP * g.Kpad + (q.wv ? k : 0));
   };
   auto store_chunk = [&](int buf, const Slot& q) {
-    const uint4 (&qa)[A_UNITS] = q.a;
-    const uint4 (&qw)[W_UNITS] = q.w;
 #pragma unroll
     for (int u = 0; u < A_UNITS; ++u) {
-      uint4 val = qa[u];
-      if (PRO) { if (q.av[u]) val = bn_relu_unit(val, coef, q.c); }
-      *reinterpret_cast<uint4*>(&sA[buf][((tid >> 2) + u * 64) * LSTR + grp * 8]) = val;
+      uint4 val = q.a[u];
+      if (PRO) val = bn_relu_unit(val, coef, q.c);
+      if (!q.av[u]) val = make_uint4(0u, 0u, 0u, 0u);
+      *reinterpret_cast<uint4*>(&sA[buf][(trow + u * RPP) * LSTR + grp * 8]) = val;
     }
 #pragma unroll
     for (int u = 0; u < W_UNITS; ++u) {
-      const int unit = tid + u * 256;
-      if (unit < BN * 4) *reinterpret_cast<uint4*>(&sW[buf][(unit >> 2) * LSTR + (unit & 3) * 8]) = qw[u];
+      uint4 val = q.w[u];
+      if (!q.wv) val = make_uint4(0u, 0u, 0u, 0u);
+      if (BN % RPP == 0 || trow < BN) *reinterpret_cast<uint4*>(&sW[buf][(trow + u * RPP) * LSTR + grp * 8]) = val;
     }
   };
 
@@ -312,40 +305,40 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
 #pragma unroll
     for (int j = 0; j < PT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  const int nk = g.Kpad / KC;
-  load_chunk(0, sl0);
-  if (1 < nk) load_chunk(1, sl1);
-  if (2 < nk) load_chunk(2, sl2);
-  if (3 < nk) load_chunk(3, sl3);
+  load_chunk(sl0);
+  load_chunk(sl1);
   store_chunk(0, sl0);
   __syncthreads();
   const int frag_row = lane & 15, frag_k = (lane >> 4) * 8;
-  // one K step: chunk kc is in LDS buffer kc&1 and its register slot `cur` is free again
-  auto step = [&](int kc, Slot& cur, const Slot& nxt) {
-    if (kc >= nk) return;
-    const int buf = kc & 1;
-    if (kc + NPRE < nk) load_chunk(kc + NPRE, cur);
-    bf16x8 fa[PT], fw[CT];
+  // one step: its chunk is in LDS buffer `buf` and its register slot `cur` is free again; `nxt` holds the chunk behind it
+  auto step = [&](int buf, Slot& cur, const Slot& nxt) {
+    load_chunk(cur);
+    bf16x8 fa[KS / KC][PT], fw[KS / KC][CT];
 #pragma unroll
-    for (int j = 0; j < PT; ++j)
-      fa[j] = *reinterpret_cast<const bf16x8*>(&sA[buf][(wr * WPX + j * 16 + frag_row) * LSTR + frag_k]);
-#pragma unroll
-    for (int i = 0; i < CT; ++i)
-      fw[i] = *reinterpret_cast<const bf16x8*>(&sW[buf][(wc * WCH + i * 16 + frag_row) * LSTR + frag_k]);
-#pragma unroll
-    for (int i = 0; i < CT; ++i)
+    for (int h = 0; h < KS / KC; ++h) {
 #pragma unroll
       for (int j = 0; j < PT; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i], fa[j], acc[i][j], 0, 0, 0);
-    if (kc + 1 < nk) store_chunk(buf ^ 1, nxt);
+        fa[h][j] = *reinterpret_cast<const bf16x8*>(&sA[buf][(wr * WPX + j * 16 + frag_row) * LSTR + h * KC + frag_k]);
+#pragma unroll
+      for (int i = 0; i < CT; ++i)
+        fw[h][i] = *reinterpret_cast<const bf16x8*>(&sW[buf][(wc * WCH + i * 16 + frag_row) * LSTR + h * KC + frag_k]);
+    }
+    store_chunk(buf ^ 1, nxt);
+#pragma unroll
+    for (int h = 0; h < KS / KC; ++h)
+#pragma unroll
+      for (int i = 0; i < CT; ++i)
+#pragma unroll
+        for (int j = 0; j < PT; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[h][i], fa[h][j], acc[i][j], 0, 0, 0);
     __syncthreads();
   };
-  for (int kc0 = 0; kc0 < nk; kc0 += NPRE) {
-    step(kc0, sl0, sl1);
-    step(kc0 + 1, sl1, sl2);
-    step(kc0 + 2, sl2, sl3);
-    step(kc0 + 3, sl3, sl0);
+  int kc0 = 0;
+  for (; kc0 + NPRE <= nk; kc0 += NPRE) {
+    step(0, sl0, sl1);
+    step(1, sl1, sl0);
   }
+  if (kc0 < nk) step(0, sl0, sl1);
 
   static_assert((BN + WR * BN * 2) * 4 <= (int)sizeof(sA), "epilogue scratch fits the staging buffer");
   conv_epilogue<BM, BN, WR, WC, PT, CT, EPI>(acc, wr, wc, blockIdx.x, row0, ch0, reinterpret_cast<float*>(&sA[0][0]), g, epi, add, out);
