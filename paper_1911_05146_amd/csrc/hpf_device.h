@@ -70,4 +70,60 @@ __device__ __forceinline__ float row_sum(float v) {
 }
 __device__ __forceinline__ float sum16(float v) { return row_sum<1>(v); }   // over the 16 pixels of a tile
 
+// Where the consumer of a BatchNorm takes its {mean, invstd} from (bf16 mode).
+enum : int { BN_FROM_STATS = 0, BN_FROM_RECORDS = 1, BN_FROM_RUNNING = 2 };
+// {mean, invstd} of channels [c_base, c_base + nch), nch <= 64, from the statistics records {K, S1, S2, n} of nrows row blocks
+// ([row][C], S1 / S2 sums about K), by a work-group of 256 threads; out(c, mean, invstd) is called by one thread per channel.
+// Two passes in a fixed order: the mean from the block sums, then the squared deviations about it, M2 = sum [S2 - S1^2/n + n (mean_b -
+// mean)^2]; FIN_RECS records of a thread stay in registers, so up to 8 * (256 / nch) rows cost one round trip.  sh: 256 floats of LDS.
+constexpr int FIN_RECS = 8;
+template <class OUT>
+__device__ __forceinline__ void bn_finalize_records(const float4* __restrict__ rec, unsigned nrows, int C, int c_base, int nch, int M, float eps,
+                                                    float* sh, OUT out) {
+  const int rg = 256 / nch, j = (int)threadIdx.x / nch, cl = (int)threadIdx.x - j * nch, c = c_base + cl;
+  const bool on = j < rg && c < C;
+  const float4* p = rec + (on ? c : 0);
+  float4 q[FIN_RECS];
+  auto load = [&](unsigned b0) {   // all loads in flight together
+#pragma unroll
+    for (int i = 0; i < FIN_RECS; ++i) {
+      const unsigned b = b0 + (unsigned)(j + i * rg);
+      q[i] = on && b < nrows ? p[(size_t)b * C] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  const unsigned step = (unsigned)(FIN_RECS * rg), b_last = (nrows - 1) / step * step;
+  float tot = 0.f;
+  for (unsigned b0 = 0; b0 <= b_last; b0 += step) {
+    load(b0);
+#pragma unroll
+    for (int i = 0; i < FIN_RECS; ++i) tot += q[i].w * q[i].x + q[i].y;   // n*K + S1 = sum of the block's values
+  }
+  auto total = [&](float v) {
+    __syncthreads();
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    float t = 0.f;
+    for (int r = 0; r < rg; ++r) t += sh[r * nch + cl];
+    return t;
+  };
+  const float mean = total(tot) / (float)M;
+  float m2 = 0.f;
+  for (unsigned b0 = b_last;; b0 -= step) {   // the last ones are still in registers
+#pragma unroll
+    for (int i = 0; i < FIN_RECS; ++i)
+      if (q[i].w > 0.f) {                     // squared deviations of the block about the overall mean
+        const float s1n = q[i].y / q[i].w, d = q[i].x + s1n - mean;
+        m2 += q[i].z - q[i].y * s1n + q[i].w * d * d;
+      }
+    if (b0 == 0) break;
+    load(b0 - step);
+  }
+  m2 = total(m2);
+  if (on && j == 0) {
+    float var = m2 / (float)M;
+    var = var > 0.f ? var : 0.f;
+    out(c, mean, 1.0f / sqrtf(var + eps));
+  }
+}
+
 }  // namespace hpf

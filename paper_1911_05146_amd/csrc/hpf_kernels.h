@@ -80,12 +80,21 @@ int conv_splitk(int g, const ConvGeom& geom);
 // Optional BatchNorm + ReLU applied to the source tensor while it is staged (forward convolutions):
 // the source is the BatchNorm input x and the operand becomes bf16(max(gamma*((x-mean)*invstd)+beta, 0)),
 // so the normalised activation is never written to memory.  Padding stays zero.
+// The statistics come as they are; as records of `rows` row blocks that a producer left (rows > 0; the launch then also writes them to
+// `stats`); or as running statistics (running != nullptr).
 struct ConvPro {
   int on = 0;
   PtrTab stats{};            // {mean(Cs), invstd(Cs)} float, per member
   const float* gamma = nullptr;
   const float* beta = nullptr;
+  PtrTab records{};
+  unsigned rows = 0;
+  int M = 0;                 // pixel rows that the records cover
+  float eps = 0.f;
+  const float* running = nullptr;   // {mean(Cs), variance(Cs)}
 };
+// The launch takes the statistics of its source as `rows` records (else they are finalised by a launch of their own).
+bool conv_takes_records(int g, const ConvGeom& geom, unsigned rows);
 int conv_mfma_tile_rows(int g, const ConvGeom& geom);   // pixel rows per tile the launcher will use
 hipError_t conv_prepare();                               // once per device before the first convolution launch
 // How often the bf16 convolution kernels stage each element of the source tensor (filter taps x channel tiles);
@@ -215,22 +224,36 @@ hipError_t launch_wgrad_f32(int g, const PtrTab& a, const PtrTab& dy, float* dw,
 // DT_F32 (the check mode reduces and takes the ReLU decision in double).  partials holds
 // bn_partials_floats(C) floats per member.
 size_t bn_partials_floats(int C);
+// The reduction alone (bf16 mode): records {K, S1, S2, n} of *rows row blocks in `partials`.
+hipError_t launch_bn_stats_records(int g, const PtrTab& x, int M, int C, const PtrTab& partials, unsigned* rows, hipStream_t stream);
 hipError_t launch_bn_stats(int dt, int g, const PtrTab& x, int M, int C, float eps, const PtrTab& stats,
                            const PtrTab& partials, hipStream_t stream);
-// Finalize steps alone, for partial records written by a convolution epilogue (nrows record rows).
+// Finalize step alone, for records written by a convolution epilogue or by launch_bn_stats_records (nrows record rows).
 hipError_t launch_bn_stats_finalize(int g, int M, int C, int nrows, float eps, const PtrTab& partials, const PtrTab& stats,
                                     hipStream_t stream);
-hipError_t launch_bn_bwd_finalize(int g, int C, int nrows, const PtrTab& partials, const PtrTab& sums, float* g_gamma,
-                                  float* g_beta, hipStream_t stream);
+// Statistics of a BatchNorm for the kernels that apply it: {mean, invstd} in `stats`; or records (rows > 0, bf16 mode): the kernel
+// finalises them itself and writes `stats`; or running statistics.
+struct BnSource {
+  PtrTab stats{}, records{};
+  unsigned rows = 0;
+  float eps = 0.f;
+  const float* running = nullptr;
+};
 hipError_t launch_bn_apply_relu(int dt, int g, const PtrTab& x, const PtrTab& a, const float* gamma, const float* beta,
-                                const PtrTab& stats, int M, int C, hipStream_t stream);
-// sums of each micro-batch; also atomically added into g_gamma / g_beta (fp32 gradient buffer).
+                                const BnSource& src, int M, int C, hipStream_t stream);
+// Sums of a BatchNorm backward {sum dz, sum dz*xhat} for its apply pass: in `sums`, or (rows > 0, bf16 mode) as records of row blocks,
+// which the apply pass adds up itself; it then also adds the sums of each micro-batch into g_gamma / g_beta.
+struct BnBwdSums {
+  PtrTab sums{}, records{};
+  unsigned rows = 0;
+  float *g_gamma = nullptr, *g_beta = nullptr;
+};
+// The reduction.  fp32 mode: into src->sums, and atomically into g_gamma / g_beta; bf16 mode: records.
 hipError_t launch_bn_bwd_reduce(int dt, int g, const PtrTab& x, const PtrTab& da, const float* gamma, const float* beta,
-                                const PtrTab& stats, int M, int C, const PtrTab& sums, float* g_gamma, float* g_beta,
-                                const PtrTab& partials, hipStream_t stream);
+                                const PtrTab& stats, int M, int C, BnBwdSums* sums, hipStream_t stream);
 // dx = gamma*invstd*(dz - dbeta/M - xhat*dgamma/M) [+ skip]; frozen: dx = gamma*invstd*dz [+ skip].
 hipError_t launch_bn_bwd_apply(int dt, int g, const PtrTab& x, const PtrTab& da, const float* gamma, const float* beta,
-                               const PtrTab& stats, const PtrTab& sums, const PtrTab& skip, const PtrTab& dx, int M,
+                               const PtrTab& stats, const BnBwdSums& sums, const PtrTab& skip, const PtrTab& dx, int M,
                                int C, int frozen, hipStream_t stream);
 hipError_t launch_bn_frozen_stats(int dt, int g, const PtrTab& stats, int C, float eps, hipStream_t stream);
 
@@ -248,7 +271,7 @@ hipError_t launch_maxpool2_bwd(int dt, int g, const PtrTab& x, const PtrTab& dy,
 // Residual join of a post-activation block, y = max(bn(x) + add, 0) (statistics given), and its backward pass:
 // dz = dy * [y > 0]; dadd = dz; dx through the BatchNorm; dgamma / dbeta added into g_gamma / g_beta.
 hipError_t launch_bn_add_relu_apply(int dt, int g, const PtrTab& x, const PtrTab& add, const PtrTab& y, const float* gamma,
-                                    const float* beta, const PtrTab& stats, int M, int C, hipStream_t stream);
+                                    const float* beta, const BnSource& src, int M, int C, hipStream_t stream);
 hipError_t launch_join_bwd(int dt, int g, const PtrTab& x, const PtrTab& y, const PtrTab& dy, const float* gamma, const PtrTab& stats,
                            int M, int C, const PtrTab& sums, float* g_gamma, float* g_beta, const PtrTab& partials, const PtrTab& dx,
                            const PtrTab& dadd, int frozen, hipStream_t stream);

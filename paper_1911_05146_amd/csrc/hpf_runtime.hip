@@ -99,7 +99,8 @@ struct Plan {
   int out_h = 0, out_w = 0, out_c = 0;
   // per-micro-batch region
   size_t mb_bytes = 0, stash_bytes_per_mb = 0;
-  size_t sums_off = 0, partials_off = 0, tickets_off = 0;
+  size_t sums_off = 0, tickets_off = 0;
+  size_t partials_off[2] = {0, 0};   // bf16 mode: a convolution reads the records of its input from one while it writes those of its output to the other
   size_t scratch_off[4] = {0, 0, 0, 0};
   size_t max_elems = 0; int max_c = 0;
   // global regions (bytes from arena base)
@@ -443,7 +444,8 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
   if (max_c > 0) {
     P.sums_off = alloc(2 * (size_t)max_c * sizeof(double)).off;
     const size_t pf = bn_partials_floats(max_c) > max_tile_part ? bn_partials_floats(max_c) : max_tile_part;
-    P.partials_off = alloc(pf * sizeof(float)).off;
+    P.partials_off[0] = P.partials_off[1] = alloc(pf * sizeof(float)).off;
+    if (P.dt == DT_BF16) P.partials_off[1] = alloc(pf * sizeof(float)).off;
   }
   P.tickets_off = alloc(64 * sizeof(unsigned)).off;
   for (int i = 0; i < 4; ++i) P.scratch_off[i] = alloc(max_elems * P.esz).off;
@@ -785,36 +787,48 @@ struct Ctx {
     for (int i = 0; i < g; ++i) chk(launch_copy_bytes(dst.p[i], src.p[i], bytes, s), "copy");
   }
 
-  // part_rows > 0: the producing convolution already wrote that many statistics partial rows.
-  // apply == false: only the statistics (the consuming convolutions normalise while staging)
-  void bn_fwd(const BnPlan& bn, const PtrTab& x, const PtrTab& a, size_t M, int part_rows = 0, bool apply = true) {
+  int part_sel = 0;   // the buffer with the last records written
+  PtrTab partials() const { return mbp(h->P.partials_off[part_sel]); }
+  PtrTab next_partials() { part_sel ^= 1; return partials(); }
+  // The statistics of a BatchNorm with input x for the kernel that applies it.  part_rows > 0: the producing convolution already wrote
+  // that many record rows (fusion levels 1 and 2).
+  BnSource bn_source(const BnPlan& bn, const PtrTab& x, size_t M, int part_rows) {
     const Plan& P = h->P;
-    const PtrTab st = mbp(bn.stats_off);
-    if (inference)
-      chk(launch_bn_running_stats(P.dt, g, st, h->running() + bn.run_off, bn.C, P.d.bn_eps, s), "bn_running_stats");
-    else if (P.d.bn_mode != 0)
-      chk(launch_bn_frozen_stats(P.dt, g, st, bn.C, P.d.bn_eps, s), "bn_frozen_stats");
-    else if (part_rows > 0)
-      chk(launch_bn_stats_finalize(g, (int)M, bn.C, part_rows, P.d.bn_eps, mbp(P.partials_off), st, s), "bn_stats_finalize");
-    else
-      chk(launch_bn_stats(P.dt, g, x, (int)M, bn.C, P.d.bn_eps, st, mbp(P.partials_off), s), "bn_stats");
-    if (apply)
-      chk(launch_bn_apply_relu(P.dt, g, x, a, h->params() + bn.g_off, h->params() + bn.b_off, st, (int)M, bn.C, s), "bn_apply_relu");
+    BnSource src;
+    src.stats = mbp(bn.stats_off); src.eps = P.d.bn_eps;
+    if (inference && P.dt == DT_BF16) {
+      src.running = h->running() + bn.run_off;
+    } else if (inference) {
+      chk(launch_bn_running_stats(P.dt, g, src.stats, h->running() + bn.run_off, bn.C, P.d.bn_eps, s), "bn_running_stats");
+    } else if (P.d.bn_mode != 0) {
+      chk(launch_bn_frozen_stats(P.dt, g, src.stats, bn.C, P.d.bn_eps, s), "bn_frozen_stats");
+    } else if (P.dt == DT_BF16) {
+      src.rows = (unsigned)part_rows;
+      if (part_rows == 0) chk(launch_bn_stats_records(g, x, (int)M, bn.C, next_partials(), &src.rows, s), "bn_stats");
+      src.records = partials();
+    } else {
+      chk(launch_bn_stats(P.dt, g, x, (int)M, bn.C, P.d.bn_eps, src.stats, partials(), s), "bn_stats");
+    }
+    return src;
   }
-  // part_rows > 0: `da` already holds dz and the producing data-gradient wrote that many partial rows.
+  // a = relu(bn(x)), or (apply == false) only the statistics, for the convolutions that normalise while staging
+  BnSource bn_fwd(const BnPlan& bn, const PtrTab& x, const PtrTab& a, size_t M, int part_rows = 0, bool apply = true) {
+    const BnSource src = bn_source(bn, x, M, part_rows);
+    if (apply)
+      chk(launch_bn_apply_relu(h->P.dt, g, x, a, h->params() + bn.g_off, h->params() + bn.b_off, src, (int)M, bn.C, s), "bn_apply_relu");
+    return src;
+  }
+  // part_rows > 0: `da` already holds dz and the producing data-gradient wrote that many record rows.
   void bn_bwd(const BnPlan& bn, const PtrTab& x, const PtrTab& da, const PtrTab& skip, const PtrTab& dx, size_t M,
               int part_rows = 0) {
     const Plan& P = h->P;
     const PtrTab st = mbp(bn.stats_off);
-    if (part_rows > 0)
-      chk(launch_bn_bwd_finalize(g, bn.C, part_rows, mbp(P.partials_off), mbp(P.sums_off), h->grads() + bn.g_off,
-                                 h->grads() + bn.b_off, s),
-          "bn_bwd_finalize");
-    else
-      chk(launch_bn_bwd_reduce(P.dt, g, x, da, h->params() + bn.g_off, h->params() + bn.b_off, st, (int)M, bn.C, mbp(P.sums_off),
-                               h->grads() + bn.g_off, h->grads() + bn.b_off, mbp(P.partials_off), s),
-          "bn_bwd_reduce");
-    chk(launch_bn_bwd_apply(P.dt, g, x, da, h->params() + bn.g_off, h->params() + bn.b_off, st, mbp(P.sums_off), skip, dx, (int)M,
+    BnBwdSums sums;
+    sums.sums = mbp(P.sums_off); sums.records = partials(); sums.rows = (unsigned)part_rows;
+    sums.g_gamma = h->grads() + bn.g_off; sums.g_beta = h->grads() + bn.b_off;
+    if (part_rows == 0)
+      chk(launch_bn_bwd_reduce(P.dt, g, x, da, h->params() + bn.g_off, h->params() + bn.b_off, st, (int)M, bn.C, &sums, s), "bn_bwd_reduce");
+    chk(launch_bn_bwd_apply(P.dt, g, x, da, h->params() + bn.g_off, h->params() + bn.b_off, st, sums, skip, dx, (int)M,
                             bn.C, P.d.bn_mode, s),
         "bn_bwd_apply");
   }
@@ -831,20 +845,27 @@ struct Ctx {
   ConvGeom geom_fwd(const ConvPlan& cv) const { return conv_geom_fwd(cv, h->P.d.microbatch); }
   ConvGeom geom_dgrad(const ConvPlan& cv) const { return conv_geom_dgrad(cv, h->P.d.microbatch); }
   // want_stats: the output feeds a BatchNorm; returns the number of partial rows written (0 = none).
-  // pro_bn (bf16 mode): x is the input of that BatchNorm and the convolution normalises it while staging.
+  // pro_bn (bf16 mode): x is the input of that BatchNorm and the convolution normalises it while staging; src: its statistics.  Records are
+  // finalised here, by the convolution or by a launch in front of it; src then names the finished statistics.
   int conv_fwd(const ConvPlan& cv, const PtrTab& x, const PtrTab& y, const PtrTab& add, bool want_stats = false,
-               const BnPlan* pro_bn = nullptr) {
+               const BnPlan* pro_bn = nullptr, BnSource* src = nullptr) {
     const ConvGeom q = geom_fwd(cv);
     if (h->P.dt == DT_BF16) {
       ConvEpi epi;
       ConvPro pro;
       if (pro_bn) {
-        pro.on = 1; pro.stats = mbp(pro_bn->stats_off);
+        pro.on = 1; pro.stats = src->stats; pro.running = src->running; pro.eps = src->eps;
         pro.gamma = h->params() + pro_bn->g_off; pro.beta = h->params() + pro_bn->b_off;
+        if (src->rows) {
+          pro.M = h->P.d.microbatch * cv.h_in * cv.w_in;
+          if (conv_takes_records(g, q, src->rows)) { pro.records = src->records; pro.rows = src->rows; }
+          else chk(launch_bn_stats_finalize(g, pro.M, pro_bn->C, (int)src->rows, src->eps, src->records, src->stats, s), "bn_stats_finalize");
+          src->rows = 0;
+        }
       }
       int rows = 0;
       if (want_stats && fused() && !inference) {
-        epi.kind = EPI_STATS; epi.partials = mbp(h->P.partials_off);
+        epi.kind = EPI_STATS; epi.partials = next_partials();
         const int bm = conv_mfma_tile_rows(g, q);
         rows = (q.M + bm - 1) / bm;
       }
@@ -865,7 +886,7 @@ struct Ctx {
       ConvEpi epi;
       int rows = 0;
       if (bn && fused()) {
-        epi.kind = EPI_BNBWD; epi.partials = mbp(h->P.partials_off); epi.x = *bn_x; epi.stats = mbp(bn->stats_off);
+        epi.kind = EPI_BNBWD; epi.partials = next_partials(); epi.x = *bn_x; epi.stats = mbp(bn->stats_off);
         epi.gamma = h->params() + bn->g_off; epi.beta = h->params() + bn->b_off;
         const int bm = conv_mfma_tile_rows(g, q);
         rows = (q.M + bm - 1) / bm;
@@ -997,9 +1018,9 @@ void run_forward(Ctx& c, const PtrTab& labels, float* loss_accum) {
         c.bn_fwd(p.bn[0], c1, a1, M_out, rows1);
         if (p.proj) c.conv_fwd(p.pj, x, c.tab(p.sc), Ctx::none());
         const int rows2 = c.conv_fwd(p.cv[1], a1, c2, Ctx::none(), true);
-        c.bn_fwd(p.bn[1], c2, Ctx::none(), M_out, rows2, false);   // statistics only
+        const BnSource src2 = c.bn_source(p.bn[1], c2, M_out, rows2);
         c.chk(launch_bn_add_relu_apply(P.dt, c.g, c2, c.tab(p.sc), y, c.h->params() + p.bn[1].g_off, c.h->params() + p.bn[1].b_off,
-                                       c.mbp(p.bn[1].stats_off), (int)M_out, p.bn[1].C, c.s),
+                                       src2, (int)M_out, p.bn[1].C, c.s),
               "bn_add_relu");
       } else if (p.d.kind == K_CONV_RELU || p.d.kind == K_DENSE) {
         const PtrTab y0 = c.tab(p.y0);
@@ -1022,23 +1043,24 @@ void run_forward(Ctx& c, const PtrTab& labels, float* loss_accum) {
     }
     // bf16: BN + ReLU applied inside the consuming convolutions unless the plan writes the activation out
     PtrTab shortcut{}, src{};
+    BnSource stat;   // of the BatchNorm in front of the next convolution
     bool pro = false;
     Loc lskip_in; lskip_in.kind = CALLER_SKIP_IN;
     Loc lskip_out; lskip_out.kind = CALLER_SKIP_OUT;
     if (p.j0 == 0) {
       const PtrTab x = c.tab(p.x_in);
       pro = bf && !p.mat[0];
-      c.bn_fwd(p.bn[0], x, c.tab(p.a[0]), M_in, part_rows, !pro);
+      stat = c.bn_fwd(p.bn[0], x, c.tab(p.a[0]), M_in, part_rows, !pro);
       // the shortcut value: x, or the projection of relu(bn1(x)); it leaves the partition if the block ends elsewhere
       const PtrTab sc_dst = p.j1 == p.nconv ? c.tab(p.y) : c.tab(lskip_out);
-      if (p.proj) c.conv_fwd(p.pj, pro ? x : c.tab(p.a[0]), sc_dst, Ctx::none(), false, pro ? &p.bn[0] : nullptr);
+      if (p.proj) c.conv_fwd(p.pj, pro ? x : c.tab(p.a[0]), sc_dst, Ctx::none(), false, pro ? &p.bn[0] : nullptr, &stat);
       else if (p.j1 < p.nconv) c.copy(sc_dst, x, M_out * p.d.c_out * P.esz);
       shortcut = p.proj ? sc_dst : x;
       src = pro ? x : c.tab(p.a[0]);
     } else {
       const PtrTab in = c.tab(p.c[p.j0 - 1]);
       pro = bf && !p.mat[p.j0];
-      c.bn_fwd(p.bn[p.j0], in, c.tab(p.a[p.j0]), M_out, 0, !pro);
+      stat = c.bn_fwd(p.bn[p.j0], in, c.tab(p.a[p.j0]), M_out, 0, !pro);
       shortcut = c.tab(lskip_in);
       src = pro ? in : c.tab(p.a[p.j0]);
     }
@@ -1048,10 +1070,10 @@ void run_forward(Ctx& c, const PtrTab& labels, float* loss_accum) {
       const bool next_resident = resident && bi + 1 < P.bp.size() && P.run_at[bi + 1] >= 0;
       const bool feeds_bn = (!last && j + 1 < p.j1) ||
                             (last && ((bi + 1 < P.bp.size() && !next_resident && takes_stats(P.bp[bi + 1])) || (bi + 1 == P.bp.size() && P.d.has_head == 1)));
-      part_rows = c.conv_fwd(p.cv[j], src, out, last ? shortcut : Ctx::none(), feeds_bn, pro ? &p.bn[j] : nullptr);
+      part_rows = c.conv_fwd(p.cv[j], src, out, last ? shortcut : Ctx::none(), feeds_bn, pro ? &p.bn[j] : nullptr, &stat);
       if (j + 1 < p.j1) {
         pro = bf && !p.mat[j + 1];
-        c.bn_fwd(p.bn[j + 1], out, c.tab(p.a[j + 1]), M_out, part_rows, !pro);
+        stat = c.bn_fwd(p.bn[j + 1], out, c.tab(p.a[j + 1]), M_out, part_rows, !pro);
         src = pro ? out : c.tab(p.a[j + 1]);
       }
     }
@@ -1120,7 +1142,7 @@ void run_backward(Ctx& c) {
       const PtrTab t1 = deferred && (p.d.kind == K_CONV_RELU || p.d.kind == K_DENSE) ? c.tab(p.dc[0])
                         : deferred && p.d.kind == K_POSTACT && p.proj ? c.tab(p.dc[2]) : c.scratch(1);
       const PtrTab t3 = deferred && p.d.kind == K_POSTACT ? c.tab(p.dc[0]) : c.scratch(3);
-      const PtrTab sums = c.mbp(P.sums_off), parts = c.mbp(P.partials_off);
+      const PtrTab sums = c.mbp(P.sums_off), parts = c.partials();
       float* g_bias = c.h->grads() + p.bias_off;
       if (p.d.kind == K_POSTACT) {
         const PtrTab c1 = c.tab(p.c[0]), a1 = c.tab(p.a[0]), c2 = c.tab(p.c[1]);
@@ -2037,7 +2059,9 @@ hpf_status hpf_op_bn_relu_forward(hpf_dtype dtype, const void* x, const float* g
   char* ws = (char*)workspace;
   void* partials = ws + op_ws_tickets() + op_ws_sums_bytes(C);
   if (launch_bn_stats(dt, 1, one_ptr(x), M, C, eps, one_ptr(stats), one_ptr(partials), s) != hipSuccess) return fail(HPF_EDEVICE, "launch failed");
-  if (launch_bn_apply_relu(dt, 1, one_ptr(x), one_ptr(a), gamma, beta, one_ptr(stats), M, C, s) != hipSuccess) return fail(HPF_EDEVICE, "launch failed");
+  BnSource src;
+  src.stats = one_ptr(stats);
+  if (launch_bn_apply_relu(dt, 1, one_ptr(x), one_ptr(a), gamma, beta, src, M, C, s) != hipSuccess) return fail(HPF_EDEVICE, "launch failed");
   return HPF_OK;
 }
 
@@ -2052,9 +2076,11 @@ hpf_status hpf_op_bn_relu_backward(hpf_dtype dtype, const void* x, const void* d
   char* ws = (char*)workspace;
   void* sums = ws + op_ws_tickets();
   void* partials = ws + op_ws_tickets() + op_ws_sums_bytes(C);
-  if (launch_bn_bwd_reduce(dt, 1, one_ptr(x), one_ptr(da), gamma, beta, one_ptr(stats), M, C, one_ptr(sums), dgamma, dbeta, one_ptr(partials), s) != hipSuccess)
+  BnBwdSums src;
+  src.sums = one_ptr(sums); src.records = one_ptr(partials); src.g_gamma = dgamma; src.g_beta = dbeta;
+  if (launch_bn_bwd_reduce(dt, 1, one_ptr(x), one_ptr(da), gamma, beta, one_ptr(stats), M, C, &src, s) != hipSuccess)
     return fail(HPF_EDEVICE, "launch failed");
-  if (launch_bn_bwd_apply(dt, 1, one_ptr(x), one_ptr(da), gamma, beta, one_ptr(stats), one_ptr(sums), one_ptr(skip), one_ptr(dx), M, C, 0, s) != hipSuccess)
+  if (launch_bn_bwd_apply(dt, 1, one_ptr(x), one_ptr(da), gamma, beta, one_ptr(stats), src, one_ptr(skip), one_ptr(dx), M, C, 0, s) != hipSuccess)
     return fail(HPF_EDEVICE, "launch failed");
   return HPF_OK;
 }
@@ -2100,7 +2126,9 @@ hpf_status hpf_op_bn_relu_forward_noalloc(hpf_dtype dtype, const void* x, const 
   // every partial record the finalize step reads is written by the statistics kernel of the same call: nothing in
   // the array has to start at zero
   if (launch_bn_stats(dt, 1, one_ptr(x), M, C, eps, one_ptr(stats), one_ptr(partials), s) != hipSuccess) return fail(HPF_EDEVICE, "launch failed");
-  if (launch_bn_apply_relu(dt, 1, one_ptr(x), one_ptr(a), gamma, beta, one_ptr(stats), M, C, s) != hipSuccess) return fail(HPF_EDEVICE, "launch failed");
+  BnSource src;
+  src.stats = one_ptr(stats);
+  if (launch_bn_apply_relu(dt, 1, one_ptr(x), one_ptr(a), gamma, beta, src, M, C, s) != hipSuccess) return fail(HPF_EDEVICE, "launch failed");
   return HPF_OK;
 }
 

@@ -11,10 +11,11 @@
 //           dx = gamma*invstd*(dz - dbeta/M - xhat*dgamma/M) (+ the skip gradient of an identity
 //           shortcut).
 // Reductions: per-thread partial sums -> cross-lane shuffles and LDS across the row groups of a
-// block -> one partial per block in global memory; a second, one-block-per-256-channels kernel adds
-// the partials in a fixed order, so the result does not depend on scheduling (a grid-wide
-// "last block finishes" scheme was measured slower here: its device-scope fence and atomic round
-// trips cost more than a kernel boundary).  The variance uses sums shifted by the first row's
+// block -> one record per block in global memory.  The records are added up in a fixed order, so the result does not depend on
+// scheduling: in bf16 mode by every work-group of the kernel that consumes them, for its own 64 channels (one round trip
+// instead of a launch of 4.7 us between two others; wide tensors with many records and the fp32 mode: by a launch of
+// its own).  A grid-wide "last block finishes" scheme was measured slower: its device-scope fence and atomic round
+// trips cost more than a kernel boundary.  The variance uses sums shifted by the first row's
 // value, which removes the cancellation of the sum-of-squares form.
 //
 // Arithmetic type A: float in bf16 mode; double in the fp32 check mode, where tensors are fp32 but
@@ -56,9 +57,10 @@ struct BnMap {
   bool active;
 };
 
-__device__ __forceinline__ BnMap bn_map(int C) {
+// cg_max: channel groups of 8 per block
+__device__ __forceinline__ BnMap bn_map(int C, int cg_max = 32) {
   const int CG = C >> 3;
-  const int CGB = CG < 32 ? CG : 32;
+  const int CGB = CG < cg_max ? CG : cg_max;
   BnMap m;
   m.rpp = BN_THREADS / CGB;
   m.rl = threadIdx.x / CGB;
@@ -293,17 +295,94 @@ __global__ __launch_bounds__(BN_THREADS) void k_bn_bwd_finalize_wide(int C, unsi
   }
 }
 
-template <class T, class A>
+// The kernels that apply a BatchNorm on statistics of their own making: 64 channels per block (FIN_CG groups of 8), FIN_ROWS rows at a time
+constexpr int FIN_CG = 8;
+
+// {mean, invstd} of a thread's 8 channels.  BN_FROM_RECORDS: finalised by the block (all of its threads call this); the first block of its
+// channels writes them to `stats`.
+template <class A, int SRC>
+struct BnStatsOf {
+  A mu[8], is[8];
+  __device__ __forceinline__ void load(const BnSource& src, int M, int C, const BnMap& m) {
+    A* stats = (A*)pick(src.stats, blockIdx.z);
+    if constexpr (SRC == BN_FROM_RECORDS) {
+      __shared__ float sh[BN_THREADS], fm[2][FIN_CG * 8];
+      const int nch = C < FIN_CG * 8 ? C : FIN_CG * 8, c_base = blockIdx.y * FIN_CG * 8;
+      bn_finalize_records((const float4*)pick(src.records, blockIdx.z), src.rows, C, c_base, nch, M, src.eps, sh, [&](int c, float mean, float is_) {
+        fm[0][c - c_base] = mean;
+        fm[1][c - c_base] = is_;
+        if (blockIdx.x == 0) { stats[c] = mean; stats[C + c] = is_; }
+      });
+      __syncthreads();
+      if (m.active) { load8a(fm[0] + m.c0 - c_base, mu); load8a(fm[1] + m.c0 - c_base, is); }
+    } else if constexpr (SRC == BN_FROM_RUNNING) {
+      if (m.active) {
+        load8t(src.running + m.c0, mu); load8t(src.running + C + m.c0, is);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) is[j] = rsqrt_exact(is[j] + (A)src.eps);
+      }
+    } else {
+      if (m.active) { load8a(stats + m.c0, mu); load8a(stats + C + m.c0, is); }
+    }
+  }
+};
+
+// {sum dz, sum dz*xhat} of a thread's 8 channels, over M (frozen: 0).  FIN: added up by the block from the records; the first block of
+// its channels adds them into the gradients of beta and gamma.
+template <class A, bool FIN>
+struct BnSumsOf {
+  A sb[8], sg[8];
+  __device__ __forceinline__ void load(const BnBwdSums& src, int M, int C, int frozen, const BnMap& m) {
+    if constexpr (FIN) {
+      __shared__ float sh[2][BN_THREADS], fs[2][FIN_CG * 8];
+      const int nch = C < FIN_CG * 8 ? C : FIN_CG * 8, c_base = blockIdx.y * FIN_CG * 8;
+      const int rg = BN_THREADS / nch, j = (int)threadIdx.x / nch, cl = (int)threadIdx.x - j * nch, c = c_base + cl;
+      const float2* __restrict__ p = (const float2*)pick(src.records, blockIdx.z);
+      float a1 = 0.f, a2 = 0.f;
+      const bool on = j < rg && c < C;
+      for (unsigned b0 = 0; b0 < src.rows; b0 += (unsigned)(FIN_RECS * rg)) {   // FIN_RECS records in flight together
+        float2 q[FIN_RECS];
+#pragma unroll
+        for (int i = 0; i < FIN_RECS; ++i) {
+          const unsigned b = b0 + (unsigned)(j + i * rg);
+          q[i] = on && b < src.rows ? p[(size_t)b * C + c] : make_float2(0.f, 0.f);
+        }
+#pragma unroll
+        for (int i = 0; i < FIN_RECS; ++i) { a1 += q[i].x; a2 += q[i].y; }
+      }
+      sh[0][threadIdx.x] = a1; sh[1][threadIdx.x] = a2;
+      __syncthreads();
+      if ((int)threadIdx.x < nch && c < C) {
+        a1 = 0.f; a2 = 0.f;
+        for (int r = 0; r < rg; ++r) { a1 += sh[0][r * nch + cl]; a2 += sh[1][r * nch + cl]; }
+        fs[0][cl] = a1; fs[1][cl] = a2;
+        if (blockIdx.x == 0) { atomicAdd(&src.g_beta[c], a1); atomicAdd(&src.g_gamma[c], a2); }
+      }
+      __syncthreads();
+      if (m.active) { load8a(fs[0] + m.c0 - c_base, sb); load8a(fs[1] + m.c0 - c_base, sg); }
+    } else {
+      const A* sums = (const A*)pick(src.sums, blockIdx.z);
+      if (m.active) { load8a(sums + m.c0, sb); load8a(sums + C + m.c0, sg); }
+    }
+    const A inv_m = frozen ? (A)0 : (A)1 / (A)M;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) { sb[j] *= inv_m; sg[j] *= inv_m; }
+  }
+};
+
+template <class T, class A, int SRC>
 __global__ __launch_bounds__(BN_THREADS) void k_bn_apply_relu(PtrTab xs, PtrTab as, const float* __restrict__ gamma,
-                                                              const float* __restrict__ beta, PtrTab statss, int M,
+                                                              const float* __restrict__ beta, BnSource src, int M,
                                                               int C) {
   const T* __restrict__ x = (const T*)pick(xs, blockIdx.z);
   T* __restrict__ a = (T*)pick(as, blockIdx.z);
-  const A* __restrict__ stats = (const A*)pick(statss, blockIdx.z);
-  const BnMap m = bn_map(C);
+  const BnMap m = bn_map(C, SRC == BN_FROM_RECORDS ? FIN_CG : 32);
+  BnStatsOf<A, SRC> st;
+  st.load(src, M, C, m);
   if (!m.active) return;
-  A mu[8], is[8], g[8], bt[8], v[8];
-  load8a(stats + m.c0, mu); load8a(stats + C + m.c0, is); load8t(gamma + m.c0, g); load8t(beta + m.c0, bt);
+  const A (&mu)[8] = st.mu, (&is)[8] = st.is;
+  A g[8], bt[8], v[8];
+  load8t(gamma + m.c0, g); load8t(beta + m.c0, bt);
   for (int r = blockIdx.x * m.rpp + m.rl; r < M; r += gridDim.x * m.rpp) {
     load8t(x + (size_t)r * C + m.c0, v);
 #pragma unroll
@@ -384,24 +463,22 @@ __global__ __launch_bounds__(BN_THREADS) void k_bn_bwd_finalize(int C, unsigned 
   }
 }
 
-template <class T, class A>
+template <class T, class A, bool FIN>
 __global__ __launch_bounds__(BN_THREADS) void k_bn_bwd_apply(PtrTab xs, PtrTab das, const float* __restrict__ gamma,
-                                                             const float* __restrict__ beta, PtrTab statss, PtrTab sumss,
+                                                             const float* __restrict__ beta, PtrTab statss, BnBwdSums sumss,
                                                              PtrTab skips, PtrTab dxs, int M, int C, int frozen) {
   const T* __restrict__ x = (const T*)pick(xs, blockIdx.z);
   const T* __restrict__ da = (const T*)pick(das, blockIdx.z);
   const A* __restrict__ stats = (const A*)pick(statss, blockIdx.z);
-  const A* __restrict__ sums = (const A*)pick(sumss, blockIdx.z);
   const T* skip = (const T*)pick(skips, blockIdx.z);
   T* dx = (T*)pick(dxs, blockIdx.z);
-  const BnMap m = bn_map(C);
+  const BnMap m = bn_map(C, FIN ? FIN_CG : 32);
+  BnSumsOf<A, FIN> su;
+  su.load(sumss, M, C, frozen, m);
   if (!m.active) return;
-  A mu[8], is[8], g[8], bt[8], sb[8], sg[8], v[8], d[8], k[8];
+  const A (&sb)[8] = su.sb, (&sg)[8] = su.sg;
+  A mu[8], is[8], g[8], bt[8], v[8], d[8], k[8];
   load8a(stats + m.c0, mu); load8a(stats + C + m.c0, is); load8t(gamma + m.c0, g); load8t(beta + m.c0, bt);
-  load8a(sums + m.c0, sb); load8a(sums + C + m.c0, sg);
-  const A inv_m = frozen ? (A)0 : (A)1 / (A)M;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) { sb[j] *= inv_m; sg[j] *= inv_m; }
   for (int r = blockIdx.x * m.rpp + m.rl; r < M; r += gridDim.x * m.rpp) {
     const size_t o = (size_t)r * C + m.c0;
     load8t(x + o, v);
@@ -574,17 +651,19 @@ __global__ __launch_bounds__(256) void k_maxpool2_bwd(PtrTab xs, PtrTab dys, Ptr
 }
 
 // Residual join of a post-activation block: y = max(gamma*xhat + beta + add, 0).
-template <class T, class A>
+template <class T, class A, int SRC>
 __global__ __launch_bounds__(BN_THREADS) void k_bn_add_relu_apply(PtrTab xs, PtrTab adds, PtrTab ys, const float* __restrict__ gamma,
-                                                                  const float* __restrict__ beta, PtrTab statss, int M, int C) {
+                                                                  const float* __restrict__ beta, BnSource src, int M, int C) {
   const T* __restrict__ x = (const T*)pick(xs, blockIdx.z);
   const T* __restrict__ add = (const T*)pick(adds, blockIdx.z);
   T* __restrict__ y = (T*)pick(ys, blockIdx.z);
-  const A* __restrict__ stats = (const A*)pick(statss, blockIdx.z);
-  const BnMap m = bn_map(C);
+  const BnMap m = bn_map(C, SRC == BN_FROM_RECORDS ? FIN_CG : 32);
+  BnStatsOf<A, SRC> st;
+  st.load(src, M, C, m);
   if (!m.active) return;
-  A mu[8], is[8], g[8], bt[8], v[8], k[8];
-  load8a(stats + m.c0, mu); load8a(stats + C + m.c0, is); load8t(gamma + m.c0, g); load8t(beta + m.c0, bt);
+  const A (&mu)[8] = st.mu, (&is)[8] = st.is;
+  A g[8], bt[8], v[8], k[8];
+  load8t(gamma + m.c0, g); load8t(beta + m.c0, bt);
   for (int r = blockIdx.x * m.rpp + m.rl; r < M; r += gridDim.x * m.rpp) {
     const size_t o = (size_t)r * C + m.c0;
     load8t(x + o, v);
@@ -637,25 +716,23 @@ __global__ __launch_bounds__(BN_THREADS) void k_join_bwd_reduce(PtrTab xs, PtrTa
   }
 }
 // dx = gamma*invstd*(dz - dbeta/M - xhat*dgamma/M) (frozen: gamma*invstd*dz) and dadd = dz for the shortcut.
-template <class T, class A>
+template <class T, class A, bool FIN>
 __global__ __launch_bounds__(BN_THREADS) void k_join_bwd_apply(PtrTab xs, PtrTab ys, PtrTab dys, const float* __restrict__ gamma,
-                                                               PtrTab statss, PtrTab sumss, PtrTab dxs, PtrTab dadds, int M, int C,
+                                                               PtrTab statss, BnBwdSums sumss, PtrTab dxs, PtrTab dadds, int M, int C,
                                                                int frozen) {
   const T* __restrict__ x = (const T*)pick(xs, blockIdx.z);
   const T* __restrict__ y = (const T*)pick(ys, blockIdx.z);
   const T* __restrict__ dy = (const T*)pick(dys, blockIdx.z);
   const A* __restrict__ stats = (const A*)pick(statss, blockIdx.z);
-  const A* __restrict__ sums = (const A*)pick(sumss, blockIdx.z);
   T* __restrict__ dx = (T*)pick(dxs, blockIdx.z);
   T* __restrict__ dadd = (T*)pick(dadds, blockIdx.z);
-  const BnMap m = bn_map(C);
+  const BnMap m = bn_map(C, FIN ? FIN_CG : 32);
+  BnSumsOf<A, FIN> su;
+  su.load(sumss, M, C, frozen, m);
   if (!m.active) return;
-  A mu[8], is[8], g[8], sb[8], sg[8], v[8], d[8], yy[8];
+  const A (&sb)[8] = su.sb, (&sg)[8] = su.sg;
+  A mu[8], is[8], g[8], v[8], d[8], yy[8];
   load8a(stats + m.c0, mu); load8a(stats + C + m.c0, is); load8t(gamma + m.c0, g);
-  load8a(sums + m.c0, sb); load8a(sums + C + m.c0, sg);
-  const A inv_m = frozen ? (A)0 : (A)1 / (A)M;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) { sb[j] *= inv_m; sg[j] *= inv_m; }
   for (int r = blockIdx.x * m.rpp + m.rl; r < M; r += gridDim.x * m.rpp) {
     const size_t o = (size_t)r * C + m.c0;
     load8t(x + o, v);
@@ -692,6 +769,22 @@ dim3 apply_grid(int M, int C) {
   return dim3((unsigned)gx, (unsigned)((CG + CGB - 1) / CGB));
 }
 
+// Whether the kernel that applies a BatchNorm adds up the records itself, which costs each of its blocks a round trip and up to 64 channels'
+// records, or a launch in front of it does (4.7 us, nearly all of it latency).  12 544 x 256, 25 rows of records: 8.1 against
+// 4.9 + 4.8 us (backward), 7.5 against 5.6 + 4.8 (forward); x 1024, 49 rows: 21.9 against 19.5 + 4.8; 13 images 32x32x64, 208 rows:
+// slower by 3 us.
+bool finalize_in_apply(unsigned rows, int C) { return (size_t)rows * (C < FIN_CG * 8 ? C : FIN_CG * 8) <= 4096; }
+
+// ... of the kernels that finalise the records themselves: 64 channels per block, and rows enough per block that a launch reads its
+// records about 2000 times
+dim3 finalize_grid(int M, int C, int ng) {
+  const int CG = C / 8, CGB = CG < FIN_CG ? CG : FIN_CG, rpp = BN_THREADS / CGB, gy = (CG + CGB - 1) / CGB;
+  int gx = (M + rpp - 1) / rpp;
+  const int cap = 2048 / (gy * ng);
+  if (gx > cap) gx = cap < 1 ? 1 : cap;
+  return dim3((unsigned)gx, (unsigned)gy, (unsigned)ng);
+}
+
 }  // namespace
 
 size_t bn_partials_floats(int C) { return (size_t)BN_MAX_ROW_BLOCKS * C * 4 * 2; }  // 4 values, sized for double
@@ -720,47 +813,53 @@ hipError_t launch_bn_stats_finalize(int ng, int M, int C, int nrows, float eps, 
   return hipGetLastError();
 }
 
-hipError_t launch_bn_bwd_finalize(int ng, int C, int nrows, const PtrTab& partials, const PtrTab& sums, float* g_gamma,
-                                  float* g_beta, hipStream_t stream) {
-  k_bn_bwd_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(C, (unsigned)nrows, partials, sums, g_gamma, g_beta);
+hipError_t launch_bn_stats_records(int ng, const PtrTab& x, int M, int C, const PtrTab& partials, unsigned* rows, hipStream_t stream) {
+  const BnGrid g = reduce_grid(M, C);
+  k_bn_stats<bf16_t, float><<<dim3(g.grid.x, g.grid.y, (unsigned)ng), BN_THREADS, 0, stream>>>(x, M, C, g.rows_per_block, partials);
+  *rows = g.grid.x;
   return hipGetLastError();
 }
 
 hipError_t launch_bn_apply_relu(int dt, int ng, const PtrTab& x, const PtrTab& a, const float* gamma, const float* beta,
-                                const PtrTab& stats, int M, int C, hipStream_t stream) {
+                                const BnSource& src, int M, int C, hipStream_t stream) {
   dim3 grid = apply_grid(M, C);
   grid.z = (unsigned)ng;
-  if (dt == DT_BF16)
-    k_bn_apply_relu<bf16_t, float><<<grid, BN_THREADS, 0, stream>>>(x, a, gamma, beta, stats, M, C);
-  else
-    k_bn_apply_relu<float, double><<<grid, BN_THREADS, 0, stream>>>(x, a, gamma, beta, stats, M, C);
+  if (dt != DT_BF16) k_bn_apply_relu<float, double, BN_FROM_STATS><<<grid, BN_THREADS, 0, stream>>>(x, a, gamma, beta, src, M, C);
+  else if (src.running) k_bn_apply_relu<bf16_t, float, BN_FROM_RUNNING><<<grid, BN_THREADS, 0, stream>>>(x, a, gamma, beta, src, M, C);
+  else if (src.rows && finalize_in_apply(src.rows, C)) k_bn_apply_relu<bf16_t, float, BN_FROM_RECORDS><<<finalize_grid(M, C, ng), BN_THREADS, 0, stream>>>(x, a, gamma, beta, src, M, C);
+  else {
+    if (src.rows) k_bn_stats_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(M, C, src.rows, src.eps, src.records, src.stats);
+    k_bn_apply_relu<bf16_t, float, BN_FROM_STATS><<<grid, BN_THREADS, 0, stream>>>(x, a, gamma, beta, src, M, C);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_bn_bwd_reduce(int dt, int ng, const PtrTab& x, const PtrTab& da, const float* gamma, const float* beta,
-                                const PtrTab& stats, int M, int C, const PtrTab& sums, float* g_gamma, float* g_beta,
-                                const PtrTab& partials, hipStream_t stream) {
+                                const PtrTab& stats, int M, int C, BnBwdSums* sums, hipStream_t stream) {
   const BnGrid g = reduce_grid(M, C);
   const dim3 grid(g.grid.x, g.grid.y, (unsigned)ng), fin((unsigned)((C + FIN_CH - 1) / FIN_CH), 1, (unsigned)ng);
   if (dt == DT_BF16) {
-    k_bn_bwd_reduce<bf16_t, float><<<grid, BN_THREADS, 0, stream>>>(x, da, gamma, beta, stats, M, C, g.rows_per_block, partials);
-    k_bn_bwd_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(C, g.grid.x, partials, sums, g_gamma, g_beta);
+    k_bn_bwd_reduce<bf16_t, float><<<grid, BN_THREADS, 0, stream>>>(x, da, gamma, beta, stats, M, C, g.rows_per_block, sums->records);
+    sums->rows = g.grid.x;
   } else {
-    k_bn_bwd_reduce<float, double><<<grid, BN_THREADS, 0, stream>>>(x, da, gamma, beta, stats, M, C, g.rows_per_block, partials);
-    k_bn_bwd_finalize<double><<<fin, BN_THREADS, 0, stream>>>(C, g.grid.x, partials, sums, g_gamma, g_beta);
+    k_bn_bwd_reduce<float, double><<<grid, BN_THREADS, 0, stream>>>(x, da, gamma, beta, stats, M, C, g.rows_per_block, sums->records);
+    k_bn_bwd_finalize<double><<<fin, BN_THREADS, 0, stream>>>(C, g.grid.x, sums->records, sums->sums, sums->g_gamma, sums->g_beta);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_bn_bwd_apply(int dt, int ng, const PtrTab& x, const PtrTab& da, const float* gamma, const float* beta,
-                               const PtrTab& stats, const PtrTab& sums, const PtrTab& skip, const PtrTab& dx, int M,
+                               const PtrTab& stats, const BnBwdSums& sums, const PtrTab& skip, const PtrTab& dx, int M,
                                int C, int frozen, hipStream_t stream) {
   dim3 grid = apply_grid(M, C);
   grid.z = (unsigned)ng;
-  if (dt == DT_BF16)
-    k_bn_bwd_apply<bf16_t, float><<<grid, BN_THREADS, 0, stream>>>(x, da, gamma, beta, stats, sums, skip, dx, M, C, frozen);
-  else
-    k_bn_bwd_apply<float, double><<<grid, BN_THREADS, 0, stream>>>(x, da, gamma, beta, stats, sums, skip, dx, M, C, frozen);
+  if (dt == DT_BF16 && finalize_in_apply(sums.rows, C)) {
+    k_bn_bwd_apply<bf16_t, float, true><<<finalize_grid(M, C, ng), BN_THREADS, 0, stream>>>(x, da, gamma, beta, stats, sums, skip, dx, M, C, frozen);
+  } else if (dt == DT_BF16) {
+    k_bn_bwd_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(C, sums.rows, sums.records, sums.sums, sums.g_gamma, sums.g_beta);
+    k_bn_bwd_apply<bf16_t, float, false><<<grid, BN_THREADS, 0, stream>>>(x, da, gamma, beta, stats, sums, skip, dx, M, C, frozen);
+  } else
+    k_bn_bwd_apply<float, double, false><<<grid, BN_THREADS, 0, stream>>>(x, da, gamma, beta, stats, sums, skip, dx, M, C, frozen);
   return hipGetLastError();
 }
 
@@ -828,11 +927,16 @@ hipError_t launch_maxpool2_bwd(int dt, int ng, const PtrTab& x, const PtrTab& dy
 }
 
 hipError_t launch_bn_add_relu_apply(int dt, int ng, const PtrTab& x, const PtrTab& add, const PtrTab& y, const float* gamma,
-                                    const float* beta, const PtrTab& stats, int M, int C, hipStream_t stream) {
+                                    const float* beta, const BnSource& src, int M, int C, hipStream_t stream) {
   dim3 grid = apply_grid(M, C);
   grid.z = (unsigned)ng;
-  if (dt == DT_BF16) k_bn_add_relu_apply<bf16_t, float><<<grid, BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, stats, M, C);
-  else k_bn_add_relu_apply<float, double><<<grid, BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, stats, M, C);
+  if (dt != DT_BF16) k_bn_add_relu_apply<float, double, BN_FROM_STATS><<<grid, BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, src, M, C);
+  else if (src.running) k_bn_add_relu_apply<bf16_t, float, BN_FROM_RUNNING><<<grid, BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, src, M, C);
+  else if (src.rows && finalize_in_apply(src.rows, C)) k_bn_add_relu_apply<bf16_t, float, BN_FROM_RECORDS><<<finalize_grid(M, C, ng), BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, src, M, C);
+  else {
+    if (src.rows) k_bn_stats_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(M, C, src.rows, src.eps, src.records, src.stats);
+    k_bn_add_relu_apply<bf16_t, float, BN_FROM_STATS><<<grid, BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, src, M, C);
+  }
   return hipGetLastError();
 }
 
@@ -843,14 +947,20 @@ hipError_t launch_join_bwd(int dt, int ng, const PtrTab& x, const PtrTab& y, con
   const dim3 grid(g.grid.x, g.grid.y, (unsigned)ng), fin((unsigned)((C + FIN_CH - 1) / FIN_CH), 1, (unsigned)ng);
   dim3 ag = apply_grid(M, C);
   ag.z = (unsigned)ng;
+  BnBwdSums src;
+  src.sums = sums; src.records = partials; src.rows = g.grid.x; src.g_gamma = g_gamma; src.g_beta = g_beta;
   if (dt == DT_BF16) {
     k_join_bwd_reduce<bf16_t, float><<<grid, BN_THREADS, 0, stream>>>(x, y, dy, stats, M, C, g.rows_per_block, partials);
-    k_bn_bwd_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(C, g.grid.x, partials, sums, g_gamma, g_beta);
-    k_join_bwd_apply<bf16_t, float><<<ag, BN_THREADS, 0, stream>>>(x, y, dy, gamma, stats, sums, dx, dadd, M, C, frozen);
+    if (finalize_in_apply(src.rows, C)) {
+      k_join_bwd_apply<bf16_t, float, true><<<finalize_grid(M, C, ng), BN_THREADS, 0, stream>>>(x, y, dy, gamma, stats, src, dx, dadd, M, C, frozen);
+    } else {
+      k_bn_bwd_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(C, g.grid.x, partials, sums, g_gamma, g_beta);
+      k_join_bwd_apply<bf16_t, float, false><<<ag, BN_THREADS, 0, stream>>>(x, y, dy, gamma, stats, src, dx, dadd, M, C, frozen);
+    }
   } else {
     k_join_bwd_reduce<float, double><<<grid, BN_THREADS, 0, stream>>>(x, y, dy, stats, M, C, g.rows_per_block, partials);
     k_bn_bwd_finalize<double><<<fin, BN_THREADS, 0, stream>>>(C, g.grid.x, partials, sums, g_gamma, g_beta);
-    k_join_bwd_apply<float, double><<<ag, BN_THREADS, 0, stream>>>(x, y, dy, gamma, stats, sums, dx, dadd, M, C, frozen);
+    k_join_bwd_apply<float, double, false><<<ag, BN_THREADS, 0, stream>>>(x, y, dy, gamma, stats, src, dx, dadd, M, C, frozen);
   }
   return hipGetLastError();
 }

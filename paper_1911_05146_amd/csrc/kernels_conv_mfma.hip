@@ -45,6 +45,17 @@ __device__ __forceinline__ uint4 bn_relu_unit(const uint4& q, const float2* coef
   return make_uint4(r[0], r[1], r[2], r[3]);
 }
 
+// {scale, shift} of all source channels from finished or running statistics
+template <int NT>
+__device__ __forceinline__ void bn_coefficients(const ConvPro& pro, int Cs, float2* coef) {
+  const float* stt = pro.running ? pro.running : (const float*)pick(pro.stats, blockIdx.z);
+  for (int c = threadIdx.x; c < Cs; c += NT) {
+    const float is = pro.running ? 1.0f / sqrtf(stt[Cs + c] + pro.eps) : stt[Cs + c];
+    const float sc = pro.gamma[c] * is;
+    coef[c] = make_float2(sc, pro.beta[c] - stt[c] * sc);
+  }
+}
+
 // Epilogue of a BM x BN tile whose accumulators are spread over WR x WC waves (wave (wr, wc) holds pixel rows
 // wr*PT*16.. and channels wc*CT*16..): residual add, bf16 store, and the optional per-channel sums (statistics of
 // the stored values, or BatchNorm-backward sums) written as one partial record per tile row and channel.
@@ -243,10 +254,19 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
   struct Slot { uint4 a[A_UNITS]; uint4 w[W_UNITS]; int c; bool av[A_UNITS], wv; };
   Slot sl0, sl1;   // named, not an array: they must stay in registers
   if (PRO) {
-    const float* stt = (const float*)pick(pro.stats, blockIdx.z);
-    for (int c = tid; c < g.Cs; c += 256) {
-      const float sc = pro.gamma[c] * stt[g.Cs + c];
-      coef[c] = make_float2(sc, pro.beta[c] - stt[c] * sc);
+    if (pro.rows) {
+      float* stt = (float*)pick(pro.stats, blockIdx.z);
+      const bool first = blockIdx.x == 0 && blockIdx.y == 0;
+      const int nch = g.Cs < 64 ? g.Cs : 64;
+      for (int c0 = 0; c0 < g.Cs; c0 += nch)
+        bn_finalize_records((const float4*)pick(pro.records, blockIdx.z), pro.rows, g.Cs, c0, nch, pro.M, pro.eps, reinterpret_cast<float*>(&sA[0][0]),
+                            [&](int c, float mean, float is) {
+                              const float sc = pro.gamma[c] * is;
+                              coef[c] = make_float2(sc, pro.beta[c] - mean * sc);
+                              if (first) { stt[c] = mean; stt[g.Cs + c] = is; }
+                            });
+    } else {
+      bn_coefficients<256>(pro, g.Cs, coef);
     }
     __syncthreads();
   }
@@ -400,11 +420,7 @@ __global__ __launch_bounds__(512) void k_conv_big(PtrTab srcs, const bf16_t* __r
     else { a_h[u] = p + g.pad; a_w[u] = q + g.pad; }
   }
   if (PRO) {
-    const float* stt = (const float*)pick(pro.stats, blockIdx.z);
-    for (int c = tid; c < g.Cs; c += 512) {
-      const float sc = pro.gamma[c] * stt[g.Cs + c];
-      coef[c] = make_float2(sc, pro.beta[c] - stt[c] * sc);
-    }
+    bn_coefficients<512>(pro, g.Cs, coef);
     __syncthreads();
   }
 
@@ -774,6 +790,10 @@ int conv_mfma_tile_rows(int ng, const ConvGeom& g) {
   const int t = pick_tile(ng, g);
   return t == 0 || t == 4 ? 128 : 64;
 }
+
+// A launch of its own for the finalize step costs 4.5 us, all of it latency; every work-group doing it costs one round trip and
+// reads rows * Cs records, so up to 64 KiB per work-group (the transitions of the CIFAR ResNets: 4 to 52 KiB) it is the faster way.
+bool conv_takes_records(int ng, const ConvGeom& g, unsigned rows) { return pick_tile(ng, g) != 4 && rows * (size_t)g.Cs <= 4096; }
 
 int conv_splitk(int ng, const ConvGeom& g) {
   if (g.N % 16 != 0 || g.Cs % 8 != 0 || g.Kpad % KC != 0) return 1;

@@ -63,6 +63,18 @@ def test_single_blocks_layerwise(gpu, oracle, mode):
         layerwise(oracle, spec, mode)
 
 
+@pytest.mark.parametrize("images,grouped", [(1, True), (4, False), (5, True)])
+@pytest.mark.parametrize("fusion", [0, 1])
+@pytest.mark.parametrize("blk,hw", [(W.Block(W.BOTTLENECK, 64, 32, 128, 2), 32),   # 64 channels x 64 / 80 rows of records: either side of the limit
+                                    (W.Block(W.BASIC, 48, 80, 80, 2), 16),         # channel counts that divide no work-group, a second slab of 16
+                                    (W.Block(W.POSTACT, 16, 48, 48, 2), 8)])       # fewer rows than row groups
+def test_statistics_from_records_layerwise(gpu, oracle, blk, hw, fusion, images, grouped):
+    """BatchNorm statistics and backward sums that the consuming kernel adds up from the producer's records, or a launch in between."""
+    spec = W.PartitionSpec(name=f"records-{blk.kind}-{blk.c_in}-{blk.c_out}", in_h=hw, in_w=hw, in_c=blk.c_in, blocks=(blk,),
+                           microbatch=images, num_microbatches=2, seed=23)
+    layerwise(oracle, spec, "bf16", grouped=grouped, fusion=fusion, blockwise=False)
+
+
 def test_row_band_runs_layerwise(gpu, oracle):
     """Runs of 64-16-16-64 bottlenecks at 32x32 (the first stage of ResNet-1001): each image is cut into four bands of
     eight rows, one work-group each, and the rows next to a band travel with the BatchNorm records.  Three blocks, so
