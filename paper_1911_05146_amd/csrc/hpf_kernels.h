@@ -52,6 +52,10 @@ struct PackDesc {
   unsigned long long wf_off;  // bf16 [Cout][Kf]  k = tap*Cin + c     (forward operand)
   unsigned long long wd_off;  // bf16 [Cin][Kd]   k = tap*Cout + n    (data-gradient operand); ~0 = none
   int T, Cin, Cout, Kf, Kd;
+  // parameters that are no convolution weights: those between this convolution's and the next's, and (first convolution of the
+  // table) first_len ones from the start of the vector
+  int first_len, rest_len;
+  unsigned long long rest_off;
 };
 
 // Optional reduction fused into the convolution epilogue (the output tile is still in registers):
@@ -304,6 +308,9 @@ hipError_t launch_zero_f32(float* p, size_t n, hipStream_t stream);
 // max_elems: elements of the largest convolution's forward copy (sizes the grid)
 hipError_t launch_pack_weights(const float* params, bf16_t* packed, const PackDesc* table_dev, int n_convs, size_t max_elems,
                                hipStream_t stream);
+// The SGD step of all parameters that the table covers and the refresh of the packed copies in one pass (n_convs >= 1).
+hipError_t launch_sgd_pack(float* params, float* mom, float* grads, bf16_t* packed, const PackDesc* table_dev, int n_convs, size_t max_elems,
+                           float lr, float mu, const int* invalid, hipStream_t stream);
 hipError_t launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t stream);
 // iters rounds of 131 072 flop of bf16 MFMA per wave (8 x 16x16x32, or 4 x 32x32x16 when wide), 4 waves per
 // work-group; sink: workgroups*256 floats

@@ -301,6 +301,12 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
   }
   P.n_params = off;
   P.packed_elems = pk;
+  for (size_t i = 0; i < P.table.size(); ++i) {   // in the order of the parameter vector
+    PackDesc& e = P.table[i];
+    e.first_len = i == 0 ? (int)e.w_off : 0;
+    e.rest_off = e.w_off + (size_t)e.T * e.Cin * e.Cout;
+    e.rest_len = (int)((i + 1 < P.table.size() ? P.table[i + 1].w_off : P.n_params) - e.rest_off);
+  }
   P.n_convs = (int)P.table.size();
 
   // ---- per-micro-batch region
@@ -1714,10 +1720,11 @@ hpf_status hpf_sgd_step(hpf_partition* p, float lr, float momentum, void* hip_st
   if (st != HPF_OK) return st;
   const Plan& P = p->P;
   // a batch whose image-resident launches timed out has no valid gradients: the kernel then leaves everything alone
-  if (launch_sgd(p->params(), p->mom(), p->grads(), P.n_params, lr, momentum, P.runs.empty() ? nullptr : p->abort_flag(), s) != hipSuccess)
-    return fail(HPF_EDEVICE, "sgd failed");
-  if (launch_pack_weights(p->params(), p->packed(), (const PackDesc*)(p->arena + P.table_off), P.n_convs, P.pack_max_elems(), s) != hipSuccess)
-    return fail(HPF_EDEVICE, "pack failed");
+  const int* invalid = P.runs.empty() ? nullptr : p->abort_flag();
+  const hipError_t e = P.n_convs > 0 ? launch_sgd_pack(p->params(), p->mom(), p->grads(), p->packed(), (const PackDesc*)(p->arena + P.table_off), P.n_convs,
+                                                       P.pack_max_elems(), lr, momentum, invalid, s)
+                                     : launch_sgd(p->params(), p->mom(), p->grads(), P.n_params, lr, momentum, invalid, s);   // nothing to pack
+  if (e != hipSuccess) return fail(HPF_EDEVICE, "sgd failed");
   begin_next_batch(p, s);
   return HPF_OK;
 }

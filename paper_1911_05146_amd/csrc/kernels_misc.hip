@@ -1,6 +1,6 @@
 // Small kernels around the convolutions: stem im2col, classification head (global average pool,
 // FC, softmax cross-entropy -- the loss of the last partition, paper Eq. 1-2), SGD with momentum
-// (apply_gradients), weight packing for the MFMA operands, fills and copies.
+// (apply_gradients) with the weight packing for the MFMA operands, fills and copies.
 #include "hpf_device.h"
 
 namespace hpf {
@@ -267,88 +267,95 @@ __global__ __launch_bounds__(256) void k_copy16(u32x4* __restrict__ dst, const u
   if (blockIdx.x == 0 && (int)threadIdx.x < ntail) dtail[threadIdx.x] = stail[threadIdx.x];
 }
 
-// grid (n_convs, Y): the Y blocks of conv i share its work round-robin.  The forward copy is a transpose of the
-// fp32 master ([k][n] -> [n][k]), done in 64 x 64 tiles through LDS so that both the reads and the writes are
-// contiguous; the data-gradient copy keeps n contiguous and is a flat loop.
-__global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ params, bf16_t* __restrict__ packed,
-                                                      const PackDesc* __restrict__ table) {
+// bf16 operand copies of the convolution weights; STEP: behind the SGD step, which then needs no pass of its own (28 bytes per weight
+// instead of 24 + 12, and one launch).  grid (n_convs, Y): the Y blocks of a convolution share its 64 x 64 tiles of the fp32 master
+// [k = tap*Cin + c][n] round-robin.  A tile is updated as it is loaded, and both copies are written from LDS with 16-byte stores: the
+// forward one is its transpose, the data-gradient one takes its rows.  Channel counts and offsets are multiples of 16 (the stem's Cin
+// excepted).  Parameters that are no convolution weights follow the convolution in front of them (rest_*; the first also the ones before it).
+// ResNet-20 (0.27 M parameters): 4.5 + 25 us as two launches with a serial data-gradient copy, now 5.8; VGG-16 (33.6 M): 129 + 77, now 155.
+template <bool STEP>
+__global__ __launch_bounds__(256) void k_sgd_pack(float* __restrict__ params, float* __restrict__ mom, float* __restrict__ grads,
+                                                  bf16_t* __restrict__ packed, const PackDesc* __restrict__ table, float lr, float mu,
+                                                  const int* __restrict__ invalid) {
+  if (STEP && invalid && *invalid) return;
   __shared__ float tile[64][65];
   const PackDesc d = table[blockIdx.x];
-  const float* w = params + d.w_off;
-  {
-    bf16_t* wf = packed + d.wf_off;  // [Cout][Kf], k = tap*Cin + c
-    const int ktot = d.T * d.Cin;
-    const int tk = (d.Kf + 63) / 64, tn = (d.Cout + 63) / 64;
-    const int lx = threadIdx.x & 63, ly = threadIdx.x >> 6;
-    const bool wide = d.Cout % 4 == 0 && d.Kf % 8 == 0 && d.w_off % 4 == 0 && d.wf_off % 8 == 0;   // 16-byte loads along n and 16-byte stores along k
-    for (int t = blockIdx.y; t < tk * tn; t += gridDim.y) {
-      const int k0 = (t / tn) * 64, n0 = (t % tn) * 64;
-      __syncthreads();
-      if (wide) {
-        // load: a thread takes 4 consecutive n of one k row (16 lanes per row, 16 rows per pass)
-        const int c4 = (threadIdx.x & 15) * 4, r0 = threadIdx.x >> 4;
-#pragma unroll
-        for (int r = r0; r < 64; r += 16) {
-          const int k = k0 + r, n = n0 + c4;
-          float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (k < ktot && n < d.Cout) v = *reinterpret_cast<const float4*>(w + (size_t)k * d.Cout + n);
-          tile[r][c4] = v.x; tile[r][c4 + 1] = v.y; tile[r][c4 + 2] = v.z; tile[r][c4 + 3] = v.w;
-        }
-        __syncthreads();
-        // store: a thread takes 8 consecutive k of one n row (8 lanes per row, 32 rows per pass)
-        const int k8 = (threadIdx.x & 7) * 8, nr0 = threadIdx.x >> 3;
-#pragma unroll
-        for (int r = nr0; r < 64; r += 32) {
-          const int n = n0 + r, k = k0 + k8;
-          if (n < d.Cout && k < d.Kf) {
-            uint4 st;
-            st.x = pack_bf16x2(tile[k8][r], tile[k8 + 1][r]); st.y = pack_bf16x2(tile[k8 + 2][r], tile[k8 + 3][r]);
-            st.z = pack_bf16x2(tile[k8 + 4][r], tile[k8 + 5][r]); st.w = pack_bf16x2(tile[k8 + 6][r], tile[k8 + 7][r]);
-            *reinterpret_cast<uint4*>(wf + (size_t)n * d.Kf + k) = st;
-          }
-        }
-        continue;
-      }
-#pragma unroll 4
-      for (int r = ly; r < 64; r += 4) {
-        const int k = k0 + r, n = n0 + lx;
-        tile[r][lx] = (k < ktot && n < d.Cout) ? w[(size_t)k * d.Cout + n] : 0.f;
-      }
-      __syncthreads();
-#pragma unroll 4
-      for (int r = ly; r < 64; r += 4) {
-        const int n = n0 + r, k = k0 + lx;
-        if (n < d.Cout && k < d.Kf) wf[(size_t)n * d.Kf + k] = f32_to_bf16(tile[lx][r]);
+  const int tid = threadIdx.x;
+  if (STEP) {
+    for (int part = 0; part < 2; ++part) {
+      const size_t off = part ? d.rest_off : 0;
+      const int len = part ? d.rest_len : d.first_len;
+      for (int i = blockIdx.y * 256 + tid; i < len; i += gridDim.y * 256) {
+        const float vel = fmaf(mu, mom[off + i], grads[off + i]);
+        mom[off + i] = vel;
+        params[off + i] = fmaf(-lr, vel, params[off + i]);
+        grads[off + i] = 0.f;
       }
     }
   }
-  if (d.wd_off != ~0ull) {
-    bf16_t* wd = packed + d.wd_off;  // [Cin][Kd], k = tap*Cout + n
-    const int ktot = d.T * d.Cout;
-    if (d.Cout % 2 == 0 && d.Kd % 2 == 0 && d.w_off % 2 == 0 && d.wd_off % 2 == 0) {   // pairs of n: 8-byte loads, 4-byte stores, no divisions
-      uint32_t* wd2 = reinterpret_cast<uint32_t*>(wd);
-      const int half = d.Cout >> 1, kd2 = d.Kd >> 1;
-      for (int c = blockIdx.y; c < d.Cin; c += gridDim.y) {
-        for (int tap = 0; tap < d.T; ++tap) {
-          const float* src = w + ((size_t)tap * d.Cin + c) * d.Cout;
-          for (int n2 = threadIdx.x; n2 < half; n2 += 256) {
-            const float2 v = *reinterpret_cast<const float2*>(src + 2 * n2);
-            wd2[(size_t)c * kd2 + tap * half + n2] = pack_bf16x2(v.x, v.y);
+  const int ktot = d.T * d.Cin, tk = (d.Kf + 63) / 64, tn = (d.Cout + 63) / 64;
+  bf16_t* wf = packed + d.wf_off;  // [Cout][Kf], k = tap*Cin + c
+  for (int t = blockIdx.y; t < tk * tn; t += gridDim.y) {
+    const int k0 = (t / tn) * 64, n0 = (t % tn) * 64;
+    __syncthreads();
+    {
+      // load: a thread takes 4 consecutive n of one k row (16 lanes per row, 16 rows per pass)
+      const int c4 = (tid & 15) * 4, r0 = tid >> 4;
+      float4 w[4], v[4], g[4];
+      bool on[4];
+      size_t at[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = k0 + r0 + 16 * i, n = n0 + c4;
+        on[i] = k < ktot && n < d.Cout;
+        at[i] = d.w_off + (on[i] ? (size_t)k * d.Cout + n : (size_t)0);
+        w[i] = *reinterpret_cast<const float4*>(params + at[i]);
+        if (STEP) { v[i] = *reinterpret_cast<const float4*>(mom + at[i]); g[i] = *reinterpret_cast<const float4*>(grads + at[i]); }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (STEP) {
+          v[i].x = fmaf(mu, v[i].x, g[i].x); v[i].y = fmaf(mu, v[i].y, g[i].y); v[i].z = fmaf(mu, v[i].z, g[i].z); v[i].w = fmaf(mu, v[i].w, g[i].w);
+          w[i].x = fmaf(-lr, v[i].x, w[i].x); w[i].y = fmaf(-lr, v[i].y, w[i].y); w[i].z = fmaf(-lr, v[i].z, w[i].z); w[i].w = fmaf(-lr, v[i].w, w[i].w);
+          if (on[i]) {
+            *reinterpret_cast<float4*>(params + at[i]) = w[i];
+            *reinterpret_cast<float4*>(mom + at[i]) = v[i];
+            *reinterpret_cast<float4*>(grads + at[i]) = make_float4(0.f, 0.f, 0.f, 0.f);
           }
         }
-        for (int k2 = (ktot >> 1) + threadIdx.x; k2 < kd2; k2 += 256) wd2[(size_t)c * kd2 + k2] = 0u;   // padding
+        if (!on[i]) w[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        float* q = &tile[r0 + 16 * i][c4];
+        q[0] = w[i].x; q[1] = w[i].y; q[2] = w[i].z; q[3] = w[i].w;
       }
-    } else {
-      const int total = d.Cin * d.Kd;
-      for (int i = blockIdx.y * 256 + threadIdx.x; i < total; i += gridDim.y * 256) {
-        const int c = i / d.Kd, k = i - c * d.Kd;
-        float v = 0.f;
-        if (k < ktot) {
-          const int tap = k / d.Cout, n = k - tap * d.Cout;
-          v = w[((size_t)tap * d.Cin + c) * d.Cout + n];
-        }
-        wd[i] = f32_to_bf16(v);
+    }
+    __syncthreads();
+    // store: a thread takes 8 consecutive elements of a row of either copy (8 lanes per row, 32 rows per pass)
+    const int e8 = (tid & 7) * 8;
+#pragma unroll
+    for (int r = tid >> 3; r < 64; r += 32) {
+      const int n = n0 + r, k = k0 + e8;
+      if (n < d.Cout && k < d.Kf) {
+        uint4 st;
+        st.x = pack_bf16x2(tile[e8][r], tile[e8 + 1][r]); st.y = pack_bf16x2(tile[e8 + 2][r], tile[e8 + 3][r]);
+        st.z = pack_bf16x2(tile[e8 + 4][r], tile[e8 + 5][r]); st.w = pack_bf16x2(tile[e8 + 6][r], tile[e8 + 7][r]);
+        *reinterpret_cast<uint4*>(wf + (size_t)n * d.Kf + k) = st;
       }
+    }
+    if (d.wd_off == ~0ull) continue;
+#pragma unroll
+    for (int r = tid >> 3; r < 64; r += 32) {
+      const int k = k0 + r, n = n0 + e8;
+      if (k >= ktot) continue;
+      const int tap = k / d.Cin, c = k - tap * d.Cin;
+      bf16_t* row = packed + d.wd_off + (size_t)c * d.Kd;   // [Cin][Kd], k = tap*Cout + n
+      if (n < d.Cout) {
+        const float* q = &tile[r][e8];
+        uint4 st;
+        st.x = pack_bf16x2(q[0], q[1]); st.y = pack_bf16x2(q[2], q[3]); st.z = pack_bf16x2(q[4], q[5]); st.w = pack_bf16x2(q[6], q[7]);
+        *reinterpret_cast<uint4*>(row + tap * d.Cout + n) = st;
+      }
+      if (tap == d.T - 1 && n0 + 64 >= d.Cout)              // padding
+        for (int p = d.T * d.Cout + e8; p < d.Kd; p += 64) *reinterpret_cast<uint4*>(row + p) = make_uint4(0u, 0u, 0u, 0u);
     }
   }
 }
@@ -424,13 +431,24 @@ hipError_t launch_zero_f32(float* p, size_t n, hipStream_t stream) {
   return hipGetLastError();
 }
 
+namespace {
+// blocks per convolution: one per tile of the largest one (blocks with nothing to do leave at once)
+dim3 pack_grid(int n_convs, size_t max_elems) {
+  const size_t y = (max_elems + 4095) / 4096;
+  return dim3((unsigned)n_convs, (unsigned)(y < 8 ? 8 : (y > 1024 ? 1024 : y)));
+}
+}  // namespace
+
 hipError_t launch_pack_weights(const float* params, bf16_t* packed, const PackDesc* table_dev, int n_convs, size_t max_elems,
                                hipStream_t stream) {
   if (n_convs <= 0) return hipSuccess;
-  // blocks per convolution: one per 8192 elements of the largest one (blocks with nothing to do leave at once)
-  size_t y = (max_elems + 8191) / 8192;
-  y = y < 8 ? 8 : (y > 1024 ? 1024 : y);
-  k_pack_weights<<<dim3((unsigned)n_convs, (unsigned)y), 256, 0, stream>>>(params, packed, table_dev);
+  k_sgd_pack<false><<<pack_grid(n_convs, max_elems), 256, 0, stream>>>(const_cast<float*>(params), nullptr, nullptr, packed, table_dev, 0.f, 0.f, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_sgd_pack(float* params, float* mom, float* grads, bf16_t* packed, const PackDesc* table_dev, int n_convs, size_t max_elems,
+                           float lr, float mu, const int* invalid, hipStream_t stream) {
+  k_sgd_pack<true><<<pack_grid(n_convs, max_elems), 256, 0, stream>>>(params, mom, grads, packed, table_dev, lr, mu, invalid);
   return hipGetLastError();
 }
 
