@@ -111,9 +111,9 @@ hipError_t launch_conv_mfma(int mode, int g, const PtrTab& src, const bf16_t* wp
                             const ConvPro& pro = ConvPro());
 hipError_t launch_wgrad_mfma(int g, const PtrTab& a, const PtrTab& dy, float* dw, const WgradGeom& geom, hipStream_t stream);
 
-// All weight gradients of a backward pass in one launch per tile class.  An item is one (convolution,
+// All weight gradients of a backward pass, grouped by tile class.  An item is one (convolution,
 // filter tap, BC x BN output tile, slice of pixel rows); the work-group that takes it loops over the
-// group's micro-batches, so one atomic add per output element and item reaches the gradient buffer.
+// group's micro-batches (or a share of them), so one atomic add per output element and item reaches the gradient buffer.
 // a / dy live at byte offsets in each member's arena region (dy_off == WGRAD_DY_CALLER: the caller's
 // err_in buffer of that member).
 constexpr unsigned long long WGRAD_DY_CALLER = ~0ull;
@@ -136,9 +136,14 @@ int wgrad_item_class(const WgradGeom& g);      // WGRAD_CLASS_T9 where it applie
 int wgrad_t9_lds_bytes(int H, int W);          // dynamic LDS of a class-10 launch for that image shape
 void wgrad_tile_dims(int tile_class, int* bc, int* bn);
 hipError_t wgrad_prepare();   // once per device before the first grouped launch
-hipError_t launch_wgrad_grouped(int tile_class, int g, const WgradItem* items_dev, int n_items, const PtrTab& region_base,
-                                const PtrTab& caller_dy, const PtrTab& caller_a, const float* params, float* grads,
-                                hipStream_t stream, int lds_bytes = 0);
+// The items of all classes of a backward call.
+struct WgradLaunch {
+  const WgradItem* items[WGRAD_CLASSES] = {};
+  int n[WGRAD_CLASSES] = {};
+  int t9_lds = 0;            // wgrad_t9_lds_bytes of the class's image shape
+};
+hipError_t launch_wgrad_grouped(const WgradLaunch& l, int g, const PtrTab& region_base, const PtrTab& caller_dy, const PtrTab& caller_a,
+                                const float* params, float* grads, hipStream_t stream, int* n_launches);
 
 // ---- image-resident runs of identity blocks (bf16 mode, BatchNorm on micro-batch statistics)
 // A run is a sequence of consecutive blocks of one kind and shape (bottleneck or basic) with stride 1 and identity

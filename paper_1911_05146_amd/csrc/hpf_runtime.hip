@@ -1232,15 +1232,20 @@ void run_backward(Ctx& c) {
     if (res)
       for (const Plan::ResRun& r : P.runs)
         if (resident_has_wgrad_launch(r.kind, r.C, r.bands)) c.res_wgrad(r);
+    WgradLaunch l;
+    double bytes = 0, flops = 0;
     for (int k = 0; k < WGRAD_CLASSES; ++k) {
-      const std::vector<WgradItem>& items = res ? P.items_nr[k] : P.items[k];
-      if (items.empty()) continue;
-      c.seg(PROF_WGRAD, c.g * (res ? P.wg_nr_bytes : P.wg_bytes)[k], c.g * (res ? P.wg_nr_flops : P.wg_flops)[k]);
-      c.chk(launch_wgrad_grouped(k, c.g, (const WgradItem*)(c.h->arena + (res ? P.items_nr_off : P.items_off)[k]), (int)items.size(),
-                                 bases, caller_dy, caller_a, c.h->params(), c.h->grads(), c.s,
-                                 k == WGRAD_CLASS_T9 ? wgrad_t9_lds_bytes(P.t9_h, P.t9_w) : 0),
-            "wgrad_grouped");
+      l.n[k] = (int)(res ? P.items_nr : P.items)[k].size();
+      if (l.n[k] == 0) continue;
+      l.items[k] = (const WgradItem*)(c.h->arena + (res ? P.items_nr_off : P.items_off)[k]);
+      bytes += (res ? P.wg_nr_bytes : P.wg_bytes)[k];
+      flops += (res ? P.wg_nr_flops : P.wg_flops)[k];
     }
+    if (l.n[WGRAD_CLASS_T9]) l.t9_lds = wgrad_t9_lds_bytes(P.t9_h, P.t9_w);
+    c.seg(PROF_WGRAD, c.g * bytes, c.g * flops);
+    int launches = 0;
+    const hipError_t e = launch_wgrad_grouped(l, c.g, bases, caller_dy, caller_a, c.h->params(), c.h->grads(), c.s, &launches);
+    for (int i = 0; i < launches || (i == 0 && e != hipSuccess); ++i) c.chk(e, "wgrad_grouped");
   }
   c.seg_end();
 }
@@ -1433,7 +1438,7 @@ hpf_status hpf_partition_create(const hpf_partition_desc* desc, void* device_are
     ok(hipMemcpy(p->running(), r0.data(), P.n_running * sizeof(float), hipMemcpyHostToDevice));
     ok(hipMemcpy(p->arena + P.bn_table_off, P.bn_table.data(), P.bn_table.size() * sizeof(BnRunDesc), hipMemcpyHostToDevice));
   }
-  if (!P.items[9].empty() || !P.items[WGRAD_CLASS_T9].empty()) ok(wgrad_prepare());
+  if (P.dt == DT_BF16) ok(wgrad_prepare());
   if (!P.runs.empty()) {
     ok(hipMemcpy(p->arena + P.res_off, P.res_blocks.data(), P.res_blocks.size() * sizeof(ResBlock), hipMemcpyHostToDevice));
     ok(hipMemset(p->abort_flag(), 0, sizeof(int)));

@@ -13,6 +13,8 @@
 // Both MFMA operands need 8 consecutive reduction indices (pixel rows) per lane while memory has
 // the channel contiguous, so the staging threads transpose: each loads 16 bytes (8 channels) of two
 // adjacent rows and writes 8 dwords {row 2j, row 2j+1} into the channel-major LDS tile.
+#include <algorithm>
+
 #include "hpf_device.h"
 
 namespace hpf {
@@ -316,61 +318,71 @@ __global__ __launch_bounds__(256) void k_wgrad_mfma(PtrTab as, PtrTab dys, float
   wgrad_flush<BC, BN>(acc, reinterpret_cast<floatx4*>(smem), dw, g, tap, ct * BC, nt * BN);
 }
 
-// One work-group per item; the micro-batches of the group are accumulated in registers.
+// What the work-group of an item needs besides the item
+struct WgradArgs {
+  int ng;
+  PtrTab bases, caller_dy, caller_a;
+  const float* params;
+  float* grads;
+};
+
+// f(a, dy, base) for the work-group's share of the micro-batches, z0, z0 + dz, ...: accumulated in registers
+template <class F>
+__device__ __forceinline__ void wgrad_members(const WgradItem& it, const WgradArgs& w, int z0, int dz, F&& f) {
+  for (int z = z0; z < w.ng; z += dz) {
+    const char* base = (const char*)pick(w.bases, z);
+    const bf16_t* a = it.a_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(w.caller_a, z) : (const bf16_t*)(base + it.a_off);
+    const bf16_t* dy = it.dy_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(w.caller_dy, z) : (const bf16_t*)(base + it.dy_off);
+    f(a, dy, base);
+  }
+}
+
 template <int BC, int BN>
-__global__ __launch_bounds__(256) void k_wgrad_grouped(const WgradItem* __restrict__ items, int ng, PtrTab bases, PtrTab caller_dy,
-                                                       PtrTab caller_a, const float* __restrict__ params, float* grads) {
+__device__ __forceinline__ void wgrad_item(const WgradItem& it, const WgradArgs& w, int z0, int dz, unsigned char* smem) {
   typedef WgradTile<BC, BN> TT;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[TT::SMEM_BYTES];
   bf16_t* sA = reinterpret_cast<bf16_t*>(smem);
   bf16_t* sD = sA + TT::LDS_A;
-  const WgradItem it = items[blockIdx.x];
   floatx4 acc[TT::CTL][TT::NTL];
 #pragma unroll
   for (int i = 0; i < TT::CTL; ++i)
 #pragma unroll
     for (int j = 0; j < TT::NTL; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int z = 0; z < ng; ++z) {
-    const char* base = (const char*)pick(bases, z);
-    const bf16_t* a = it.a_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(caller_a, z) : (const bf16_t*)(base + it.a_off);
-    const bf16_t* dy = it.dy_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(caller_dy, z) : (const bf16_t*)(base + it.dy_off);
-    if (it.stats_off != WGRAD_NO_BN)
-      wgrad_accumulate<BC, BN>(a, dy, it.g, it.tap, it.c0, it.n0, it.m_begin, it.m_end, sA, sD, acc,
-                               (const float*)(base + it.stats_off), params + it.gamma_off, params + it.beta_off);
-    else
-      wgrad_accumulate<BC, BN>(a, dy, it.g, it.tap, it.c0, it.n0, it.m_begin, it.m_end, sA, sD, acc);
-  }
-  wgrad_flush<BC, BN>(acc, reinterpret_cast<floatx4*>(smem), grads + it.dw_off, it.g, it.tap, it.c0, it.n0);
+  wgrad_members(it, w, z0, dz, [&](const bf16_t* a, const bf16_t* dy, const char* base) {
+    const bool bn = it.stats_off != WGRAD_NO_BN;
+    // one loop with and without a BatchNorm: two of them took the accumulators twice and 64 x 64 items to one wave per SIMD
+    // (VGG-16, 864 items: 110 against 84 us)
+    wgrad_accumulate<BC, BN>(a, dy, it.g, it.tap, it.c0, it.n0, it.m_begin, it.m_end, sA, sD, acc, bn ? (const float*)(base + it.stats_off) : nullptr,
+                             w.params + it.gamma_off, w.params + it.beta_off);
+  });
+  wgrad_flush<BC, BN>(acc, reinterpret_cast<floatx4*>(smem), w.grads + it.dw_off, it.g, it.tap, it.c0, it.n0);
 }
 
 // The 128 x 128 class: every wave owns a 64 x 64 quadrant over the whole reduction, so the sums go straight
 // from the accumulators to the gradient buffer (one atomic per output element and work-group).
-__global__ __launch_bounds__(256, 2) void k_wgrad_grouped_quad(const WgradItem* __restrict__ items, int ng, PtrTab bases, PtrTab caller_dy,
-                                                            PtrTab caller_a, const float* __restrict__ params, float* grads) {
+// TWO: a loop of its own for operands without a BatchNorm (no test per staged unit: ResNet-152 stage 3 2.12 against 2.34 ms; the launch of
+// several classes keeps one loop per class).
+template <bool TWO>
+__device__ __forceinline__ void wgrad_item_quad(const WgradItem& it, const WgradArgs& w, int z0, int dz, unsigned char* smem) {
   constexpr int BC = 128, BN = 128;
   typedef WgradTile<BC, BN, 64> TT;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_q[];
-  bf16_t* sA = reinterpret_cast<bf16_t*>(smem_q);
+  bf16_t* sA = reinterpret_cast<bf16_t*>(smem);
   bf16_t* sD = sA + TT::LDS_A;
-  const WgradItem it = items[blockIdx.x];
   floatx4 acc[BC / 32][BN / 32];
 #pragma unroll
   for (int i = 0; i < BC / 32; ++i)
 #pragma unroll
     for (int j = 0; j < BN / 32; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int z = 0; z < ng; ++z) {
-    const char* base = (const char*)pick(bases, z);
-    const bf16_t* a = it.a_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(caller_a, z) : (const bf16_t*)(base + it.a_off);
-    const bf16_t* dy = it.dy_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(caller_dy, z) : (const bf16_t*)(base + it.dy_off);
-    if (it.stats_off != WGRAD_NO_BN)
-      wgrad_accumulate<BC, BN, true>(a, dy, it.g, it.tap, it.c0, it.n0, it.m_begin, it.m_end, sA, sD, acc,
-                                     (const float*)(base + it.stats_off), params + it.gamma_off, params + it.beta_off);
-    else
+  wgrad_members(it, w, z0, dz, [&](const bf16_t* a, const bf16_t* dy, const char* base) {
+    const bool bn = it.stats_off != WGRAD_NO_BN;
+    if (TWO && !bn)
       wgrad_accumulate<BC, BN, true>(a, dy, it.g, it.tap, it.c0, it.n0, it.m_begin, it.m_end, sA, sD, acc);
-  }
+    else
+      wgrad_accumulate<BC, BN, true>(a, dy, it.g, it.tap, it.c0, it.n0, it.m_begin, it.m_end, sA, sD, acc,
+                                     TWO || bn ? (const float*)(base + it.stats_off) : nullptr, w.params + it.gamma_off, w.params + it.beta_off);
+  });
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int qc = it.c0 + (wave >> 1) * (BC / 2), qn = it.n0 + (wave & 1) * (BN / 2);
-  float* dw = grads + it.dw_off;
+  float* dw = w.grads + it.dw_off;
 #pragma unroll
   for (int i = 0; i < BC / 32; ++i)
 #pragma unroll
@@ -380,6 +392,19 @@ __global__ __launch_bounds__(256, 2) void k_wgrad_grouped_quad(const WgradItem* 
         const int c = qc + i * 16 + (lane >> 4) * 4 + v, n = qn + j * 16 + (lane & 15);
         if (c < it.g.c_valid) atomicAdd(&dw[((size_t)it.tap * it.g.c_valid + c) * it.g.N + n], acc[i][j][v]);
       }
+}
+
+template <int BC, int BN>
+__global__ __launch_bounds__(256) void k_wgrad_grouped(const WgradItem* __restrict__ items, WgradArgs w) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[WgradTile<BC, BN>::SMEM_BYTES];
+  const WgradItem it = items[blockIdx.x];   // a copy: fields of a reference would be read again behind every barrier
+  wgrad_item<BC, BN>(it, w, 0, 1, smem);
+}
+
+__global__ __launch_bounds__(256, 2) void k_wgrad_grouped_quad(const WgradItem* __restrict__ items, WgradArgs w) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_q[];
+  const WgradItem it = items[blockIdx.x];   // a copy: fields of a reference would be read again behind every barrier
+  wgrad_item_quad<true>(it, w, 0, 1, smem_q);
 }
 
 // ---- whole 3x3 convolutions between 16 and 16 channels --------------------------------------------------------
@@ -396,10 +421,7 @@ __host__ __device__ constexpr int t9_sd(int H, int W) { return H * W + 8; }     
 __host__ __device__ constexpr int t9_lds_bytes(int H, int W) { return 16 * (t9_sa(H, W) + t9_sd(H, W)) * 2 + MAX_GROUP * 16 * 8; }   // tiles + {scale, shift} per member and channel
 constexpr int T9_MAX_LDS = t9_lds_bytes(32, 32);   // the widest rows pad the most
 
-__global__ __launch_bounds__(256) void k_wgrad_grouped_t9(const WgradItem* __restrict__ items, int ng, PtrTab bases, PtrTab caller_dy,
-                                                          PtrTab caller_a, const float* __restrict__ params, float* grads) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_t9[];
-  const WgradItem it = items[blockIdx.x];
+__device__ __forceinline__ void wgrad_item_t9(const WgradItem& it, const WgradArgs& w, int z0, int dz, unsigned char* smem_t9) {
   const int H = it.g.H, W = it.g.W;
   const int SA = t9_sa(H, W), SD = t9_sd(H, W);
   bf16_t* sA = reinterpret_cast<bf16_t*>(smem_t9);
@@ -416,7 +438,7 @@ __global__ __launch_bounds__(256) void k_wgrad_grouped_t9(const WgradItem* __res
   }
 
   const int nimg = (it.m_end - it.m_begin) / T9_P, img0 = it.m_begin / T9_P;
-  const int total = ng * nimg;
+  const int total = (w.ng - z0 + dz - 1) / dz * nimg;
   // Loads: 16-byte unit u of an image (pixel u/2, channel half u%2) goes to thread u % 256, so a wave reads 1 KB of
   // contiguous memory per instruction.  Lanes t and t^2 then hold the two pixels of a pair (same channel half): they
   // swap half of their channels (DPP within the quad), so that each ends up with 4 channels of both pixels and writes
@@ -426,10 +448,10 @@ __global__ __launch_bounds__(256) void k_wgrad_grouped_t9(const WgradItem* __res
   Regs set0, set1;                               // two images on their way: a set is refilled as soon as it has been staged
   const int odd = (tid >> 1) & 1;                // this thread's pixels are the odd ones of their pairs
   auto load_image = [&](int i, Regs& rg) {
-    const int z = i / nimg, img = img0 + (i - z * nimg);
-    const char* base = (const char*)pick(bases, z);
-    const bf16_t* a = it.a_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(caller_a, z) : (const bf16_t*)(base + it.a_off);
-    const bf16_t* dy = it.dy_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(caller_dy, z) : (const bf16_t*)(base + it.dy_off);
+    const int q = i / nimg, z = z0 + q * dz, img = img0 + (i - q * nimg);
+    const char* base = (const char*)pick(w.bases, z);
+    const bf16_t* a = it.a_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(w.caller_a, z) : (const bf16_t*)(base + it.a_off);
+    const bf16_t* dy = it.dy_off == WGRAD_DY_CALLER ? (const bf16_t*)pick(w.caller_dy, z) : (const bf16_t*)(base + it.dy_off);
     a += (size_t)img * T9_P * 16 + tid * 8;
     dy += (size_t)img * T9_P * 16 + tid * 8;
 #pragma unroll
@@ -442,11 +464,11 @@ __global__ __launch_bounds__(256) void k_wgrad_grouped_t9(const WgradItem* __res
   // images do not wait for a round trip to memory each
   float2* sCf = reinterpret_cast<float2*>(sD + 16 * SD);
   const bool bn = it.stats_off != WGRAD_NO_BN;
-  if (bn && tid < ng * 16) {
+  if (bn && tid < w.ng * 16) {
     const int z = tid >> 4, c = tid & 15;
-    const float* stt = (const float*)((const char*)pick(bases, z) + it.stats_off);
-    const float sc = params[it.gamma_off + c] * stt[16 + c];
-    sCf[tid] = make_float2(sc, params[it.beta_off + c] - stt[c] * sc);
+    const float* stt = (const float*)((const char*)pick(w.bases, z) + it.stats_off);
+    const float sc = w.params[it.gamma_off + c] * stt[16 + c];
+    sCf[tid] = make_float2(sc, w.params[it.beta_off + c] - stt[c] * sc);
   }
   __syncthreads();
   float2 cf[8];
@@ -483,7 +505,7 @@ __global__ __launch_bounds__(256) void k_wgrad_grouped_t9(const WgradItem* __res
   auto image = [&](int i, Regs& rg) {
     if (bn && i % nimg == 0) {                  // a new member: its coefficients
 #pragma unroll
-      for (int e = 0; e < 8; ++e) cf[e] = sCf[(i / nimg) * 16 + hf * 8 + e];
+      for (int e = 0; e < 8; ++e) cf[e] = sCf[(z0 + i / nimg * dz) * 16 + hf * 8 + e];
     }
 #pragma unroll
     for (int k = 0; k < T9_LD; ++k) {
@@ -531,11 +553,57 @@ __global__ __launch_bounds__(256) void k_wgrad_grouped_t9(const WgradItem* __res
 #pragma unroll
   for (int t = 0; t < 9; ++t) red[(wave * 9 + t) * 64 + lane] = acc[t];
   __syncthreads();
-  float* dw = grads + it.dw_off;
+  float* dw = w.grads + it.dw_off;
   const int c = tid >> 4, n = tid & 15;
   const float* q = reinterpret_cast<const float*>(red) + ((c >> 2) * 16 + n) * 4 + (c & 3);
 #pragma unroll
   for (int t = 0; t < 9; ++t, q += 256) atomicAdd(&dw[t * 256 + tid], (q[0] + q[9 * 256]) + (q[18 * 256] + q[27 * 256]));
+}
+
+__global__ __launch_bounds__(256) void k_wgrad_grouped_t9(const WgradItem* __restrict__ items, WgradArgs w) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_t[];
+  const WgradItem it = items[blockIdx.x];   // a copy: fields of a reference would be read again behind every barrier
+  wgrad_item_t9(it, w, 0, 1, smem_t);
+}
+
+// Several classes in one launch (grid x: their items one class after the other, grid y: the micro-batches dealt to work-groups).  The
+// classes of a small partition have a few tens of items each: launched one by one each costs the latency of its steps and a launch
+// (ResNet-20, six classes of 18 to 80 items: 4.9 ... 10.0 us each, 41 together; in one launch 9.6; a quarter of ResNet-110, 152 items
+// over 8 micro-batches: 36 -> 13 us).
+struct WgradClassList {
+  const WgradItem* items[WGRAD_CLASSES];
+  int first[WGRAD_CLASSES + 1], cls[WGRAD_CLASSES], n;
+};
+__global__ __launch_bounds__(256, 2) void k_wgrad_merged(WgradClassList list, WgradArgs w) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_m[];
+  const int b = blockIdx.x;
+  int cls = list.cls[0], first = 0;
+  const WgradItem* items = list.items[0];
+#pragma unroll
+  for (int i = 1; i < WGRAD_CLASSES; ++i)
+    if (i < list.n && b >= list.first[i]) { cls = list.cls[i]; first = list.first[i]; items = list.items[i]; }
+  const WgradItem it = items[b - first];
+  const int z0 = blockIdx.y, dz = gridDim.y;
+  switch (cls) {
+    case 0: wgrad_item<16, 16>(it, w, z0, dz, smem_m); break;
+    case 1: wgrad_item<16, 32>(it, w, z0, dz, smem_m); break;
+    case 2: wgrad_item<16, 64>(it, w, z0, dz, smem_m); break;
+    case 3: wgrad_item<32, 16>(it, w, z0, dz, smem_m); break;
+    case 4: wgrad_item<32, 32>(it, w, z0, dz, smem_m); break;
+    case 5: wgrad_item<32, 64>(it, w, z0, dz, smem_m); break;
+    case 6: wgrad_item<64, 16>(it, w, z0, dz, smem_m); break;
+    case 7: wgrad_item<64, 32>(it, w, z0, dz, smem_m); break;
+    case 8: wgrad_item<64, 64>(it, w, z0, dz, smem_m); break;
+    case 9: wgrad_item_quad<false>(it, w, z0, dz, smem_m); break;
+    default: wgrad_item_t9(it, w, z0, dz, smem_m); break;
+  }
+}
+
+int wgrad_class_lds(int cls, int t9_lds) {
+  static const int generic[9] = {WgradTile<16, 16>::SMEM_BYTES, WgradTile<16, 32>::SMEM_BYTES, WgradTile<16, 64>::SMEM_BYTES,
+                                 WgradTile<32, 16>::SMEM_BYTES, WgradTile<32, 32>::SMEM_BYTES, WgradTile<32, 64>::SMEM_BYTES,
+                                 WgradTile<64, 16>::SMEM_BYTES, WgradTile<64, 32>::SMEM_BYTES, WgradTile<64, 64>::SMEM_BYTES};
+  return cls < 9 ? generic[cls] : cls == 9 ? WgradTile<128, 128, 64>::QUAD_BYTES : t9_lds;
 }
 
 template <int BC, int BN>
@@ -599,42 +667,47 @@ void wgrad_tile_dims(int tile_class, int* bc, int* bn) {
 hipError_t wgrad_prepare() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_wgrad_grouped_quad), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      WgradTile<128, 128, 64>::QUAD_BYTES);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(k_wgrad_grouped_t9), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             T9_MAX_LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_wgrad_grouped_t9), hipFuncAttributeMaxDynamicSharedMemorySize, T9_MAX_LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_wgrad_merged), hipFuncAttributeMaxDynamicSharedMemorySize, T9_MAX_LDS);
+  return e;
 }
 
-hipError_t launch_wgrad_grouped(int tile_class, int ng, const WgradItem* items_dev, int n_items, const PtrTab& region_base,
-                                const PtrTab& caller_dy, const PtrTab& caller_a, const float* params, float* grads,
-                                hipStream_t stream, int lds_bytes) {
-  if (n_items <= 0) return hipSuccess;
+hipError_t launch_wgrad_grouped(const WgradLaunch& l, int ng, const PtrTab& region_base, const PtrTab& caller_dy, const PtrTab& caller_a,
+                                const float* params, float* grads, hipStream_t stream, int* n_launches) {
+  *n_launches = 0;
   if (ng < 1 || ng > MAX_GROUP) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)n_items);
-#define HPF_WG(BC, BN) \
-  k_wgrad_grouped<BC, BN><<<grid, 256, 0, stream>>>(items_dev, ng, region_base, caller_dy, caller_a, params, grads)
-  switch (tile_class) {
-    case 0: HPF_WG(16, 16); break;
-    case 1: HPF_WG(16, 32); break;
-    case 2: HPF_WG(16, 64); break;
-    case 3: HPF_WG(32, 16); break;
-    case 4: HPF_WG(32, 32); break;
-    case 5: HPF_WG(32, 64); break;
-    case 6: HPF_WG(64, 16); break;
-    case 7: HPF_WG(64, 32); break;
-    case 8: HPF_WG(64, 64); break;
-    case 9:
-      k_wgrad_grouped_quad<<<grid, 256, WgradTile<128, 128, 64>::QUAD_BYTES, stream>>>(items_dev, ng, region_base, caller_dy, caller_a, params,
-                                                                                 grads);
-      break;
-    case WGRAD_CLASS_T9: {
-      // all items of the class have one image shape (checked by the planner): the LDS size comes with the call
-      if (lds_bytes < 4 * 9 * 256 * 4 || lds_bytes > T9_MAX_LDS) return hipErrorInvalidValue;
-      k_wgrad_grouped_t9<<<grid, 256, (size_t)lds_bytes, stream>>>(items_dev, ng, region_base, caller_dy, caller_a, params, grads);
-      break;
+  if (l.n[WGRAD_CLASS_T9] > 0 && (l.t9_lds < 4 * 9 * 256 * 4 || l.t9_lds > T9_MAX_LDS)) return hipErrorInvalidValue;
+  const WgradArgs w{ng, region_base, caller_dy, caller_a, params, grads};
+  // Classes of up to MERGE_ITEMS items go together, the ones with the longest items in front.  A class with more fills the chip by itself, and
+  // its occupancy is its own (ResNet-1001's 1x1 convolutions at 32x32: 1536 items of 18 to 26 KiB of LDS).
+  constexpr int MERGE_ITEMS = 512, MERGE_WGS = 512;
+  static const int order[WGRAD_CLASSES] = {WGRAD_CLASS_T9, 9, 8, 7, 5, 6, 2, 4, 3, 1, 0};
+  WgradClassList list{};
+  int total = 0, lds = 0;
+  for (int k : order)
+    if (l.n[k] > 0 && l.n[k] <= MERGE_ITEMS) {
+      list.items[list.n] = l.items[k]; list.first[list.n] = total; list.cls[list.n] = k;
+      ++list.n;
+      total += l.n[k];
+      lds = std::max(lds, wgrad_class_lds(k, l.t9_lds));
     }
-    default: return hipErrorInvalidValue;
+  if (list.n > 0) {
+    // micro-batches to work-groups of their own as long as the launch does not fill the chip (two work-groups per CU)
+    const int gy = std::min(ng, std::max(1, MERGE_WGS / total));
+    k_wgrad_merged<<<dim3((unsigned)total, (unsigned)gy), 256, (size_t)lds, stream>>>(list, w);
+    ++*n_launches;
   }
+#define HPF_WG(CLS, BC, BN) \
+  if (l.n[CLS] > MERGE_ITEMS) { k_wgrad_grouped<BC, BN><<<l.n[CLS], 256, 0, stream>>>(l.items[CLS], w); ++*n_launches; }
+  HPF_WG(0, 16, 16) HPF_WG(1, 16, 32) HPF_WG(2, 16, 64)
+  HPF_WG(3, 32, 16) HPF_WG(4, 32, 32) HPF_WG(5, 32, 64)
+  HPF_WG(6, 64, 16) HPF_WG(7, 64, 32) HPF_WG(8, 64, 64)
 #undef HPF_WG
+  if (l.n[9] > MERGE_ITEMS) { k_wgrad_grouped_quad<<<l.n[9], 256, WgradTile<128, 128, 64>::QUAD_BYTES, stream>>>(l.items[9], w); ++*n_launches; }
+  if (l.n[WGRAD_CLASS_T9] > MERGE_ITEMS) {   // all items of the class have one image shape (checked by the planner): the LDS size comes with the call
+    k_wgrad_grouped_t9<<<l.n[WGRAD_CLASS_T9], 256, (size_t)l.t9_lds, stream>>>(l.items[WGRAD_CLASS_T9], w);
+    ++*n_launches;
+  }
   return hipGetLastError();
 }
 

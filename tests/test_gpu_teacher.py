@@ -75,6 +75,15 @@ def test_statistics_from_records_layerwise(gpu, oracle, blk, hw, fusion, images,
     layerwise(oracle, spec, "bf16", grouped=grouped, fusion=fusion, blockwise=False)
 
 
+@pytest.mark.parametrize("images,micro", [(1, 1), (3, 3), (1, 8), (4, 7)])
+def test_weight_gradients_of_several_classes_in_one_launch_layerwise(gpu, oracle, images, micro):
+    """Five tile classes and the whole-image one, few items each: one launch whose micro-batches go to work-groups in even and odd shares."""
+    blocks = (W.Block(W.BASIC, 16, 16, 16, 1), W.Block(W.BASIC, 16, 32, 32, 2), W.Block(W.BOTTLENECK, 32, 64, 128, 2),
+              W.Block(W.BOTTLENECK, 128, 16, 64, 1))
+    spec = W.PartitionSpec(name="classes", in_h=32, in_w=32, in_c=16, blocks=blocks, microbatch=images, num_microbatches=micro, seed=29)
+    layerwise(oracle, spec, "bf16", grouped=True, fusion=1, blockwise=False)
+
+
 def test_row_band_runs_layerwise(gpu, oracle):
     """Runs of 64-16-16-64 bottlenecks at 32x32 (the first stage of ResNet-1001): each image is cut into four bands of
     eight rows, one work-group each, and the rows next to a band travel with the BatchNorm records.  Three blocks, so
