@@ -22,6 +22,8 @@
 // ones on other image sizes, basic blocks on other image sizes, row bands.  The weight gradients of all runs are here.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "hpf_resident.h"
@@ -833,14 +835,17 @@ __global__ void __launch_bounds__(RES_NT) k_res_backward(const ResArgs a, const 
 
 // ------------------------------------------------------------------------------------------ weight gradients
 // Weight gradients of the blocks of a run, one launch for all of them.  A work-group takes one (block,
-// convolution [, 64-channel chunk]) and a group of images of one micro-batch; per image it stages the two
-// operands ONCE, transposed (channel-major, so that every MFMA lane finds its 8 consecutive pixels with one
+// convolution [, 64-channel chunk]) and a range of images; it stages the two operands of up to 256 pixels at a time (one image, or
+// several small ones of a micro-batch) ONCE, transposed (channel-major, so that every MFMA lane finds its 8 consecutive pixels with one
 // 16-byte LDS read), runs every filter tap and output tile from LDS, and keeps the sums in registers over its
 // images; one fp32 atomic add per output element and work-group then goes to the gradient buffer.
 //   dw[tap][c][n] += sum_p a[p + shift(tap)][c] * dy[p][n],   a = relu(bn(x)) recomputed while staging.
-// The 3x3 convolution keeps three copies of `a`, shifted by -1 / 0 / +1 pixel along the image row with the
-// wrapped column zeroed, on a canvas with one zero image row above and below: every tap is then an aligned
-// read at offset r*W.
+// 3x3 convolutions: the filter rows are reads of `a` at offset r*W on a canvas with a zero row above and below every image, the filter
+// columns three variants of the one gradient fragment, shifted by a pixel in registers (the pixel that crosses into the next chunk of 8
+// comes from the lane that holds it; at the image border it is zero).  Three shifted copies of `a` in LDS, which this
+// replaces, took twice the staging and 9 instead of 3 reads of `a` per 9 MFMAs.  us per launch,
+// before / now: 17 post-activation blocks of 64 channels, 128 images 128 / 56, of 32 channels 78 / 47; 9 basic blocks of 32 channels 48 / 32;
+// 21 blocks 128-32, 256 images 252 / 228 (4.6 TB/s), 128-64 477 / 367; 110 blocks 256-64, 64 images 430 / 236.
 // Threads per work-group: 4 waves for the 32-wide tensors; 8 for the 64-wide ones, whose 3x3 item fills the LDS
 // of a CU on its own (one work-group per CU) and whose sums would otherwise take 200 registers per lane.
 constexpr int rw_threads(int mid) { return mid >= 64 ? 512 : 256; }
@@ -895,46 +900,82 @@ __device__ __forceinline__ uint4 bn_relu8(const uint4& q, const float2* coef) {
   }
   return make_uint4(r[0], r[1], r[2], r[3]);
 }
-// value of the lane four below / above (same channel group, previous / next pixel pair)
-__device__ __forceinline__ uint4 lanes_up4(const uint4& v) {
-  return make_uint4(__shfl_up(v.x, 4), __shfl_up(v.y, 4), __shfl_up(v.z, 4), __shfl_up(v.w, 4));
-}
-__device__ __forceinline__ uint4 lanes_down4(const uint4& v) {
-  return make_uint4(__shfl_down(v.x, 4), __shfl_down(v.y, 4), __shfl_down(v.z, 4), __shfl_down(v.w, 4));
-}
-
 struct ResWgArgs {
   const ResBlock* blocks;
-  int nmem, ipw, H, W;       // images per micro-batch, images per work-group (divides nmem), image shape
+  int nmem, H, W;            // images per micro-batch, image shape
+  int sub, per_mb;           // images staged at a time (a batch), batches per micro-batch (the last one may hold fewer images)
   int ngroup;                // micro-batches in the launch
+  int zspan;                 // micro-batches that a work-group's range can touch
   PtrTab base, act_in, err_in;
   const float* params;
   float* grads;
 };
 
-struct WgImage {   // where the work-group's image i lives
-  const ResWgArgs& a; int img0;
-  __device__ __forceinline__ ResCtx ctx(int i, int& me) const {
-    const int img = img0 + i, z = img / a.nmem;
-    me = img - z * a.nmem;
+// The work-group's batches [q0, q1): blockIdx.x of gridDim.x shares of all batches of the launch
+struct WgRange {
+  const ResWgArgs& a; int q0, q1;
+  __device__ __forceinline__ WgRange(const ResWgArgs& a_) : a(a_) {
+    const int total = a.ngroup * a.per_mb;
+    q0 = (int)((long)blockIdx.x * total / gridDim.x); q1 = (int)((long)(blockIdx.x + 1) * total / gridDim.x);
+  }
+  __device__ __forceinline__ int z0() const { return q0 / a.per_mb; }
+  // batch q: its micro-batch z, first image and pixels
+  __device__ __forceinline__ ResCtx batch(int q, int& me, int& pixels) const {
+    const int z = q / a.per_mb, b = q - z * a.per_mb;
+    me = b * a.sub;
+    pixels = min(a.sub, a.nmem - me) * a.H * a.W;
     return ResCtx{(char*)pick(a.base, z), pick(a.act_in, z), nullptr, pick(a.err_in, z), nullptr};
   }
 };
 
-// BN table of the `a` operand's channels [c0, c0+CA) -> LDS coef (the group's images share one micro-batch)
+// BN tables of the `a` operand's channels [c0, c0+CA) of the micro-batches of the range -> LDS, coef[z - z0][CA]
 template <int CA, int NTH>
-__device__ __forceinline__ void wg_coef(float2* coef, const float* stats, const float* gamma, const float* beta, int c0, int CT) {
-  for (int c = threadIdx.x; c < CA; c += NTH)
-    coef[c] = bn_scale_shift(stats[c0 + c], stats[CT + c0 + c], gamma[c0 + c], beta[c0 + c]);
+__device__ __forceinline__ void wg_coef(float2* coef, const WgRange& wr, unsigned long long st_off, const float* gamma, const float* beta, int c0, int CT) {
+  const int z0 = wr.z0(), n = (wr.q1 - 1) / wr.a.per_mb - z0 + 1;
+  for (int i = threadIdx.x; i < n * CA; i += NTH) {
+    const int z = i / CA, c = i - z * CA;
+    const float* stats = reinterpret_cast<const float*>((const char*)pick(wr.a.base, z0 + z) + st_off);
+    coef[i] = bn_scale_shift(stats[c0 + c], stats[CT + c0 + c], gamma[c0 + c], beta[c0 + c]);
+  }
 }
+
+// The batches of the range through NS register sets in rotation: a set is refilled as soon as it has been staged, so its loads have the
+// contraction of this batch and the whole turns of the other sets to arrive.  load(q, set), stage(q, set, pixels, buffer), mma(pixels, buffer).
+// NB = 2 tile buffers: one barrier per batch, and a wave stages the next batch while others still multiply this one.
+template <int NS, int NB, class SET, class LOAD, class STAGE, class MMA>
+__device__ __forceinline__ void wg_batches(const WgRange& wr, LOAD&& load, STAGE&& stage, MMA&& mma) {
+  static_assert(NB == 1 || NB == NS, "buffer of a set");
+  SET set[NS];
+#pragma unroll
+  for (int k = 0; k < NS; ++k)
+    if (wr.q0 + k < wr.q1) load(wr.q0 + k, set[k]);
+  for (int q = wr.q0; q < wr.q1; q += NS) {
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+      if (q + k < wr.q1) {
+        int me, pixels;
+        (void)wr.batch(q + k, me, pixels);
+        // the fragments of the batch before are read (and the tables are written, first time)
+        if (NB == 1 || q + k == wr.q0) __syncthreads();
+        stage(q + k, set[k], pixels, NB == 1 ? 0 : k);
+        if (q + k + NS < wr.q1) load(q + k + NS, set[k]);
+        __syncthreads();
+        mma(pixels, NB == 1 ? 0 : k);
+      }
+    }
+  }
+}
+
+template <int CA, int ND, int NTH>
+struct WgSet { PairRegs<CA, NTH> a; PairRegs<ND, NTH> d; };
 
 // 1x1 convolution: a channels [ca0, ca0+CA) of CTA, dy channels [nd0, nd0+ND) of CTD; dw is [CTA][CTD].
 template <int CA, int ND, int NTH>
-__device__ __forceinline__ void res_wgrad_1x1(const ResWgArgs& a, int img0, unsigned long long a_off, int CTA, int ca0,
+__device__ __forceinline__ void res_wgrad_1x1(const ResWgArgs& a, unsigned long long a_off, int CTA, int ca0,
                                               unsigned long long st_off, const float* gamma, const float* beta,
                                               unsigned long long dy_off, int CTD, int nd0, float* dw, unsigned char* smem) {
-  const int P = a.H * a.W, PS = P + 8;
-  const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), fr = lane & 15, fq = lane >> 4, fk = fq * 8;
+  const int P1 = a.H * a.W, PS = a.sub * P1 + 8;
+  const int lane = threadIdx.x & 63, wave = wave_index(), fr = lane & 15, fq = lane >> 4, fk = fq * 8;
   bf16_t* Ta = reinterpret_cast<bf16_t*>(smem);
   bf16_t* Td = Ta + (size_t)CA * PS;
   float2* coef = reinterpret_cast<float2*>(Td + (size_t)ND * PS);
@@ -943,64 +984,43 @@ __device__ __forceinline__ void res_wgrad_1x1(const ResWgArgs& a, int img0, unsi
   floatx4 acc[TPW];
 #pragma unroll
   for (int t = 0; t < TPW; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const WgImage wi{a, img0};
-  auto load_img = [&](int i, PairRegs<CA, NTH>& A, PairRegs<ND, NTH>& D) {
-    int me;
-    const ResCtx cx = wi.ctx(i, me);
-    A.load(cx.tensor(a_off) + (size_t)me * P * CTA, CTA, ca0, P);
-    D.load(cx.tensor(dy_off) + (size_t)me * P * CTD, CTD, nd0, P);
-  };
-  auto stage = [&](const PairRegs<CA, NTH>& A, const PairRegs<ND, NTH>& D) {
+  const WgRange wr(a);
+  using Set = WgSet<CA, ND, NTH>;
+  wg_coef<CA, NTH>(coef, wr, st_off, gamma, beta, ca0, CTA);
+  wg_batches<rw_sets(NTH), 1, Set>(
+      wr,
+      [&](int q, Set& r) {
+        int me, pixels;
+        const ResCtx cx = wr.batch(q, me, pixels);
+        r.a.load(cx.tensor(a_off) + (size_t)me * P1 * CTA, CTA, ca0, pixels);
+        r.d.load(cx.tensor(dy_off) + (size_t)me * P1 * CTD, CTD, nd0, pixels);
+      },
+      [&](int q, const Set& r, int pixels, int) {
+        const float2* cf = coef + (q / a.per_mb - wr.z0()) * CA;
 #pragma unroll
-    for (int u = 0; u < PairRegs<CA, NTH>::NU; ++u) {
-      int pr, cg;
-      PairRegs<CA, NTH>::unit(u, pr, cg);
-      if (2 * pr < P) store_pair(Ta, PS, cg * 8, 2 * pr, bn_relu8(A.v[u][0], coef + cg * 8), bn_relu8(A.v[u][1], coef + cg * 8));
-    }
+        for (int u = 0; u < PairRegs<CA, NTH>::NU; ++u) {
+          int pr, cg;
+          PairRegs<CA, NTH>::unit(u, pr, cg);
+          if (2 * pr < pixels) store_pair(Ta, PS, cg * 8, 2 * pr, bn_relu8(r.a.v[u][0], cf + cg * 8), bn_relu8(r.a.v[u][1], cf + cg * 8));
+        }
 #pragma unroll
-    for (int u = 0; u < PairRegs<ND, NTH>::NU; ++u) {
-      int pr, cg;
-      PairRegs<ND, NTH>::unit(u, pr, cg);
-      if (2 * pr < P) store_pair(Td, PS, cg * 8, 2 * pr, D.v[u][0], D.v[u][1]);
-    }
-  };
-  auto mma = [&]() {
-    for (int ks = 0; ks < P / 32; ++ks) {
+        for (int u = 0; u < PairRegs<ND, NTH>::NU; ++u) {
+          int pr, cg;
+          PairRegs<ND, NTH>::unit(u, pr, cg);
+          if (2 * pr < pixels) store_pair(Td, PS, cg * 8, 2 * pr, r.d.v[u][0], r.d.v[u][1]);
+        }
+      },
+      [&](int pixels, int) {
+        for (int ks = 0; ks < pixels / 32; ++ks) {
 #pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-        const int tile = wave * TPW + t, ct = tile / NTD, nt = tile % NTD;
-        const bf16x8 fa = *reinterpret_cast<const bf16x8*>(Ta + (size_t)(ct * 16 + fr) * PS + ks * 32 + fk);
-        const bf16x8 fd = *reinterpret_cast<const bf16x8*>(Td + (size_t)(nt * 16 + fr) * PS + ks * 32 + fk);
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fd, acc[t], 0, 0, 0);
-      }
-    }
-  };
-  // NS register sets in rotation: an image's loads are issued NS - 1 images before they are staged
-  constexpr int NS = rw_sets(NTH);
-  PairRegs<CA, NTH> as[NS];
-  PairRegs<ND, NTH> ds[NS];
-  {
-    int me;
-    const ResCtx cx = wi.ctx(0, me);
-    wg_coef<CA, NTH>(coef, reinterpret_cast<const float*>(cx.base + st_off), gamma, beta, ca0, CTA);
-  }
-  // a register set is refilled as soon as it has been staged: its loads then have the contraction of this image
-  // and the whole turns of the other sets to arrive
-#pragma unroll
-  for (int k = 0; k < NS; ++k)
-    if (k < a.ipw) load_img(k, as[k], ds[k]);
-  for (int i = 0; i < a.ipw; i += NS) {
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      if (i + k < a.ipw) {
-        __syncthreads();   // the previous image's fragments are read (and coef is written, first time)
-        stage(as[k], ds[k]);
-        if (i + k + NS < a.ipw) load_img(i + k + NS, as[k], ds[k]);
-        __syncthreads();
-        mma();
-      }
-    }
-  }
+          for (int t = 0; t < TPW; ++t) {
+            const int tile = wave * TPW + t, ct = tile / NTD, nt = tile % NTD;
+            const bf16x8 fa = *reinterpret_cast<const bf16x8*>(Ta + (size_t)(ct * 16 + fr) * PS + ks * 32 + fk);
+            const bf16x8 fd = *reinterpret_cast<const bf16x8*>(Td + (size_t)(nt * 16 + fr) * PS + ks * 32 + fk);
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fd, acc[t], 0, 0, 0);
+          }
+        }
+      });
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
     const int tile = wave * TPW + t, ct = tile / NTD, nt = tile % NTD;
@@ -1010,96 +1030,102 @@ __device__ __forceinline__ void res_wgrad_1x1(const ResWgArgs& a, int img0, unsi
   }
 }
 
-// 3x3 convolution, MID -> MID channels, stride 1, zero padding; dw is [9][MID][MID].
+// 3x3 convolution, MID -> MID channels, stride 1, zero padding; dw is [9][MID][MID].  64 channels: one work-group per CU (72 sums per lane), so
+// its own waves have to overlap staging and contraction; 32: three or four work-groups do.
+__host__ __device__ constexpr int wg3_buffers(int mid) { return mid == 64 ? 2 : 1; }
 template <int MID, int NTH>
-__device__ __forceinline__ void res_wgrad_3x3(const ResWgArgs& a, int img0, unsigned long long a_off, unsigned long long st_off,
+__device__ __forceinline__ void res_wgrad_3x3(const ResWgArgs& a, unsigned long long a_off, unsigned long long st_off,
                                               const float* gamma, const float* beta, unsigned long long dy_off, float* dw,
                                               unsigned char* smem) {
-  const int P = a.H * a.W, W = a.W, PS = P + 8, PSH = P + 2 * W + 8;
+  const int P1 = a.H * a.W, W = a.W, PS = a.sub * P1 + 8, PSA = a.sub * (P1 + 2 * W) + 8;
   const bool plain = gamma == nullptr;   // the operand is the stored tensor as it is (no BatchNorm + ReLU in front of the convolution)
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index(), fr = lane & 15, fq = lane >> 4, fk = fq * 8;
-  bf16_t* Tsh = reinterpret_cast<bf16_t*>(smem);          // [3][MID][PSH]: a shifted by s-1 pixels along the row
-  bf16_t* Td = Tsh + (size_t)3 * MID * PSH;               // [MID][PS]
-  float2* coef = reinterpret_cast<float2*>(Td + (size_t)MID * PS);
-  constexpr int NT = MID / 16, PPW = NT * NT / (NTH / 64);
-  static_assert(NT * NT % (NTH / 64) == 0, "tile pairs per wave");         // (input tile, output tile) pairs per wave
+  constexpr int NB = wg3_buffers(MID);
+  const int buf_elems = MID * (PSA + PS);
+  bf16_t* Ta = reinterpret_cast<bf16_t*>(smem);           // [MID][PSA]: image i of the batch at i*(P1 + 2*W), between its zero rows
+  bf16_t* Td = Ta + (size_t)MID * PSA;                    // [MID][PS]; the second buffer follows
+  float2* coef = reinterpret_cast<float2*>(Ta + (size_t)NB * buf_elems);
+  constexpr int NT = MID / 16, PPW = NT * NT / (NTH / 64);   // (input tile, output tile) pairs per wave; they share the input tile
+  static_assert(NT * NT % (NTH / 64) == 0 && NT % PPW == 0, "tile pairs per wave");
   floatx4 acc[PPW][9];
 #pragma unroll
   for (int t = 0; t < PPW; ++t)
 #pragma unroll
     for (int k = 0; k < 9; ++k) acc[t][k] = floatx4{0.f, 0.f, 0.f, 0.f};
-  // the zero image rows above and below
-  for (int i = tid; i < 3 * MID * 2 * W; i += NTH) {
-    const int ch = i / (2 * W), j = i - ch * 2 * W;
-    Tsh[(size_t)ch * PSH + (j < W ? j : P + j)] = 0;
+  for (int i = tid; i < MID * a.sub * W; i += NTH) {      // the zero rows above and below each image, two elements at a time
+    const int ch = i / (a.sub * W), j = i - ch * a.sub * W, im = j / W, e = 2 * (j - im * W);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) *reinterpret_cast<uint32_t*>(Ta + b * buf_elems + (size_t)ch * PSA + im * (P1 + 2 * W) + (e < W ? e : P1 + e)) = 0u;
   }
-  const WgImage wi{a, img0};
-  const int half_w = W >> 1;
-  auto load_img = [&](int i, PairRegs<MID, NTH>& A, PairRegs<MID, NTH>& D) {
-    int me;
-    const ResCtx cx = wi.ctx(i, me);
-    A.load(cx.tensor(a_off) + (size_t)me * P * MID, MID, 0, P);
-    D.load(cx.tensor(dy_off) + (size_t)me * P * MID, MID, 0, P);
-  };
-  auto stage = [&](const PairRegs<MID, NTH>& A, const PairRegs<MID, NTH>& D) {
+  const WgRange wr(a);
+  using Regs = PairRegs<MID, NTH>;
+  using Set = WgSet<MID, MID, NTH>;
+  int shift[Regs::NU];                                    // canvas offset of a unit's pixels
 #pragma unroll
-    for (int u = 0; u < PairRegs<MID, NTH>::NU; ++u) {
-      int pr, cg;
-      PairRegs<MID, NTH>::unit(u, pr, cg);
-      const bool ok = 2 * pr < P;
-      const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-      const uint4 e0 = plain ? A.v[u][0] : bn_relu8(A.v[u][0], coef + cg * 8), e1 = plain ? A.v[u][1] : bn_relu8(A.v[u][1], coef + cg * 8);
-      // the neighbouring pairs of the image row sit four lanes away (the 16 pairs of a wave hold whole rows)
-      uint4 left = lanes_up4(e1), right = lanes_down4(e0);
-      const int pc = pr % half_w;
-      if (pc == 0) left = zero;
-      if (pc == half_w - 1) right = zero;
-      if (ok) {
-        const int pos = 2 * pr + W;
-        store_pair(Tsh, PSH, cg * 8, pos, left, e0);                       // a[col-1]
-        store_pair(Tsh + (size_t)MID * PSH, PSH, cg * 8, pos, e0, e1);     // a[col]
-        store_pair(Tsh + (size_t)2 * MID * PSH, PSH, cg * 8, pos, e1, right);   // a[col+1]
-        store_pair(Td, PS, cg * 8, 2 * pr, D.v[u][0], D.v[u][1]);
-      }
-    }
-  };
-  auto mma = [&]() {
-    for (int ks = 0; ks < P / 32; ++ks) {
+  for (int u = 0; u < Regs::NU; ++u) {
+    int pr, cg;
+    Regs::unit(u, pr, cg);
+    shift[u] = W + 2 * W * (2 * pr / P1);
+  }
+  if (!plain) wg_coef<MID, NTH>(coef, wr, st_off, gamma, beta, 0, MID);
+  wg_batches<rw_sets(NTH), NB, Set>(
+      wr,
+      [&](int q, Set& r) {
+        int me, pixels;
+        const ResCtx cx = wr.batch(q, me, pixels);
+        r.a.load(cx.tensor(a_off) + (size_t)me * P1 * MID, MID, 0, pixels);
+        r.d.load(cx.tensor(dy_off) + (size_t)me * P1 * MID, MID, 0, pixels);
+      },
+      [&](int q, const Set& r, int pixels, int buf) {
+        const float2* cf = coef + (q / a.per_mb - wr.z0()) * MID;
 #pragma unroll
-      for (int t = 0; t < PPW; ++t) {
-        const int pair = wave * PPW + t, ct = pair / NT, nt = pair % NT;
-        const bf16x8 fd = *reinterpret_cast<const bf16x8*>(Td + (size_t)(nt * 16 + fr) * PS + ks * 32 + fk);
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-          const int r = tap / 3, s = tap % 3;
-          const bf16x8 fa = *reinterpret_cast<const bf16x8*>(Tsh + ((size_t)s * MID + ct * 16 + fr) * PSH + ks * 32 + fk + r * W);
-          acc[t][tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fd, acc[t][tap], 0, 0, 0);
+        for (int u = 0; u < Regs::NU; ++u) {
+          int pr, cg;
+          Regs::unit(u, pr, cg);
+          if (2 * pr < pixels) {
+            uint4 e0 = r.a.v[u][0], e1 = r.a.v[u][1];
+            if (!plain) { e0 = bn_relu8(e0, cf + cg * 8); e1 = bn_relu8(e1, cf + cg * 8); }
+            store_pair(Ta + buf * buf_elems, PSA, cg * 8, 2 * pr + shift[u], e0, e1);
+            store_pair(Td + buf * buf_elems, PS, cg * 8, 2 * pr, r.d.v[u][0], r.d.v[u][1]);
+          }
         }
-      }
-    }
-  };
-  constexpr int NS = rw_sets(NTH);
-  PairRegs<MID, NTH> as[NS], ds[NS];
-  {
-    int me;
-    const ResCtx cx = wi.ctx(0, me);
-    if (!plain) wg_coef<MID, NTH>(coef, reinterpret_cast<const float*>(cx.base + st_off), gamma, beta, 0, MID);
-  }
+      },
+      [&](int pixels, int buf) {
+        const int ct = wave * PPW / NT, nt0 = wave * PPW % NT;
+        const bf16_t* pa = Ta + buf * buf_elems + (size_t)(ct * 16 + fr) * PSA + fk;
+        const bf16_t* pd = Td + buf * buf_elems + (size_t)(nt0 * 16 + fr) * PS + fk;
+        int left_in_image = P1;
+        for (int ks = 0; ks < pixels / 32; ++ks, pa += 32, pd += 32) {
+          if (left_in_image == 0) { pa += 2 * W; left_in_image = P1; }
+          left_in_image -= 32;
+          const int col = fk & (W - 1);                   // a step of 32 pixels starts at a row's start
+          bf16x8 f[PPW][3];
 #pragma unroll
-  for (int k = 0; k < NS; ++k)
-    if (k < a.ipw) load_img(k, as[k], ds[k]);
-  for (int i = 0; i < a.ipw; i += NS) {
+          for (int t = 0; t < PPW; ++t) {
+            const u32x4 d = *reinterpret_cast<const u32x4*>(pd + (size_t)t * 16 * PS);
+            uint32_t left = (uint32_t)__builtin_amdgcn_ds_bpermute((lane - 16) * 4, (int)d.w);
+            uint32_t right = (uint32_t)__builtin_amdgcn_ds_bpermute((lane + 16) * 4, (int)d.x);
+            if (col == 0) left = 0u;
+            if (col + 8 >= W) right = 0u;
+            // filter column 0 multiplies input pixel w-1 with gradient pixel w: per input pixel w' the gradient of w'+1; column 2: of w'-1
+            u32x4 dm, dp;
+            dm.x = __builtin_amdgcn_alignbit(d.y, d.x, 16); dm.y = __builtin_amdgcn_alignbit(d.z, d.y, 16);
+            dm.z = __builtin_amdgcn_alignbit(d.w, d.z, 16); dm.w = __builtin_amdgcn_alignbit(right, d.w, 16);
+            dp.x = __builtin_amdgcn_alignbit(d.x, left, 16); dp.y = __builtin_amdgcn_alignbit(d.y, d.x, 16);
+            dp.z = __builtin_amdgcn_alignbit(d.z, d.y, 16); dp.w = __builtin_amdgcn_alignbit(d.w, d.z, 16);
+            f[t][0] = __builtin_bit_cast(bf16x8, dm); f[t][1] = __builtin_bit_cast(bf16x8, d); f[t][2] = __builtin_bit_cast(bf16x8, dp);
+          }
 #pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      if (i + k < a.ipw) {
-        __syncthreads();
-        stage(as[k], ds[k]);
-        if (i + k + NS < a.ipw) load_img(i + k + NS, as[k], ds[k]);   // refilled as soon as staged (see the 1x1 case)
-        __syncthreads();
-        mma();
-      }
-    }
-  }
+          for (int r = 0; r < 3; ++r) {
+            const bf16x8 fa = *reinterpret_cast<const bf16x8*>(pa + r * W);
+#pragma unroll
+            for (int t = 0; t < PPW; ++t)
+#pragma unroll
+              for (int s = 0; s < 3; ++s)
+                acc[t][r * 3 + s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, f[t][s], acc[t][r * 3 + s], 0, 0, 0);
+          }
+        }
+      });
 #pragma unroll
   for (int t = 0; t < PPW; ++t) {
     const int pair = wave * PPW + t, ct = pair / NT, nt = pair % NT;
@@ -1128,30 +1154,32 @@ __device__ __forceinline__ void add_bn_param_grads(const ResWgArgs& a, unsigned 
   }
 }
 
-// grid: (image groups, 2*C/64 + 1 items, blocks of the run).  Items: conv1 in chunks of 64 input channels,
-// conv2, conv3 in chunks of 64 output channels.
-template <int C, int MID>
-__global__ void __launch_bounds__(rw_threads(MID)) k_res_wgrad(const ResWgArgs a) {
+// grid: (image groups, items, blocks of the run).  Items: conv1 in chunks of 64 input channels, conv3 in chunks of 64 output channels (1x1);
+// conv2 (3x3).  One launch for both where MID is 32; with 64 the 3x3 item holds 72 sums per lane, and in a launch of their own the 1x1 items
+// run two work-groups per CU instead of one (21 blocks 128-64, 256 images: 455 us together, 233 + 134 apart).
+enum : int { WG_ALL = 0, WG_1X1 = 1, WG_3X3 = 2 };
+template <int C, int MID, int PART>
+__global__ void __launch_bounds__(rw_threads(MID), PART == WG_1X1 ? 4 : 2) k_res_wgrad(const ResWgArgs a) {
   constexpr int NTH = rw_threads(MID);
   extern __shared__ __align__(16) unsigned char smem[];
   const ResBlock B = a.blocks[blockIdx.z];
-  const int img0 = blockIdx.x * a.ipw;
   constexpr int NCH = C / 64;
-  const int item = blockIdx.y;
-  if (item < NCH)
-    res_wgrad_1x1<64, MID, NTH>(a, img0, B.x_off, C, item * 64, B.stats_off[0], a.params + B.gamma_off[0], a.params + B.beta_off[0],
+  const int item = PART == WG_3X3 ? 2 * NCH : (int)blockIdx.y;
+  if (PART != WG_3X3 && item < NCH)
+    res_wgrad_1x1<64, MID, NTH>(a, B.x_off, C, item * 64, B.stats_off[0], a.params + B.gamma_off[0], a.params + B.beta_off[0],
                            B.dc1_off, MID, 0, a.grads + B.w_off[0], smem);
-  else if (item == NCH) {
-    res_wgrad_3x3<MID, NTH>(a, img0, B.c1_off, B.stats_off[1], a.params + B.gamma_off[1], a.params + B.beta_off[1], B.dc2_off,
+  else if (PART != WG_3X3 && item < 2 * NCH)
+    res_wgrad_1x1<MID, 64, NTH>(a, B.c2_off, MID, 0, B.stats_off[2], a.params + B.gamma_off[2], a.params + B.beta_off[2],
+                           B.gy_off, C, (item - NCH) * 64, a.grads + B.w_off[2], smem);
+  else if (PART != WG_1X1) {
+    res_wgrad_3x3<MID, NTH>(a, B.c1_off, B.stats_off[1], a.params + B.gamma_off[1], a.params + B.beta_off[1], B.dc2_off,
                        a.grads + B.w_off[1], smem);
     if (blockIdx.x == 0) {
       add_bn_param_grads<NTH>(a, B.dgb_off[0], a.grads + B.beta_off[0], a.grads + B.gamma_off[0], C);
       add_bn_param_grads<NTH>(a, B.dgb_off[1], a.grads + B.beta_off[1], a.grads + B.gamma_off[1], MID);
       add_bn_param_grads<NTH>(a, B.dgb_off[2], a.grads + B.beta_off[2], a.grads + B.gamma_off[2], MID);
     }
-  } else
-    res_wgrad_1x1<MID, 64, NTH>(a, img0, B.c2_off, MID, 0, B.stats_off[2], a.params + B.gamma_off[2], a.params + B.beta_off[2],
-                           B.gy_off, C, (item - NCH - 1) * 64, a.grads + B.w_off[2], smem);
+  }
 }
 
 // ------------------------------------------------------------------------------------------ basic blocks
@@ -1436,16 +1464,15 @@ __global__ void __launch_bounds__(rw_threads(C)) k_bb_wgrad(const ResWgArgs a) {
   constexpr int NTH = rw_threads(C);
   extern __shared__ __align__(16) unsigned char smem[];
   const ResBlock B = a.blocks[blockIdx.z];
-  const int img0 = blockIdx.x * a.ipw;
   if (blockIdx.y == 0) {
-    res_wgrad_3x3<C, NTH>(a, img0, B.x_off, B.stats_off[0], a.params + B.gamma_off[0], a.params + B.beta_off[0], B.dc1_off,
+    res_wgrad_3x3<C, NTH>(a, B.x_off, B.stats_off[0], a.params + B.gamma_off[0], a.params + B.beta_off[0], B.dc1_off,
                      a.grads + B.w_off[0], smem);
     if (blockIdx.x == 0) {
       add_bn_param_grads<NTH>(a, B.dgb_off[0], a.grads + B.beta_off[0], a.grads + B.gamma_off[0], C);
       add_bn_param_grads<NTH>(a, B.dgb_off[1], a.grads + B.beta_off[1], a.grads + B.gamma_off[1], C);
     }
   } else
-    res_wgrad_3x3<C, NTH>(a, img0, B.c1_off, B.stats_off[1], a.params + B.gamma_off[1], a.params + B.beta_off[1], B.gy_off,
+    res_wgrad_3x3<C, NTH>(a, B.c1_off, B.stats_off[1], a.params + B.gamma_off[1], a.params + B.beta_off[1], B.gy_off,
                      a.grads + B.w_off[1], smem);
 }
 
@@ -1795,11 +1822,10 @@ __global__ void __launch_bounds__(rw_threads(C)) k_v1_wgrad(const ResWgArgs a) {
   constexpr int NTH = rw_threads(C);
   extern __shared__ __align__(16) unsigned char smem[];
   const ResBlock B = a.blocks[blockIdx.z];
-  const int img0 = blockIdx.x * a.ipw;
   if (blockIdx.y == 0)
-    res_wgrad_3x3<C, NTH>(a, img0, B.x_off, 0, nullptr, nullptr, B.dc1_off, a.grads + B.w_off[0], smem);
+    res_wgrad_3x3<C, NTH>(a, B.x_off, 0, nullptr, nullptr, B.dc1_off, a.grads + B.w_off[0], smem);
   else
-    res_wgrad_3x3<C, NTH>(a, img0, B.c1_off, B.stats_off[0], a.params + B.gamma_off[0], a.params + B.beta_off[0], B.dc2_off,
+    res_wgrad_3x3<C, NTH>(a, B.c1_off, B.stats_off[0], a.params + B.gamma_off[0], a.params + B.beta_off[0], B.dc2_off,
                      a.grads + B.w_off[1], smem);
 }
 
@@ -2413,16 +2439,11 @@ size_t v1_lds(int C, int P, int nmem, bool backward, int* own) {
 // LDS copy of a 3x3 matrix of C channels (rows padded by 8 elements).  It always fits next to the tiles of 32 channels; with 64 the weights are
 // fetched where they are used once the gathered records of many images take its place.
 size_t wl3_bytes(int C) { return (size_t)C * (9 * C + 8) * 2; }
-size_t bb_wgrad_lds(int C, int P, int W) {
-  return (size_t)3 * C * (P + 2 * W + 8) * 2 + (size_t)C * (P + 8) * 2 + (size_t)C * 8;
+// LDS of the weight-gradient items: `sub` images of P pixels at a time, BatchNorm tables of zspan micro-batches
+size_t bb_wgrad_lds(int C, int P, int W, int sub = 1, int zspan = 1) {
+  return (size_t)wg3_buffers(C) * C * (sub * (P + 2 * W) + 8 + sub * P + 8) * 2 + (size_t)zspan * C * 8;
 }
-
-size_t wgrad_lds(int C, int MID, int P, int W) {
-  const size_t one = (size_t)(64 + MID) * (P + 8) * 2 + 64 * 8;
-  const size_t three = (size_t)3 * MID * (P + 2 * W + 8) * 2 + (size_t)MID * (P + 8) * 2 + (size_t)MID * 8;
-  (void)C;
-  return one > three ? one : three;
-}
+size_t wgrad_1x1_lds(int MID, int P, int sub, int zspan) { return (size_t)(64 + MID) * (sub * P + 8) * 2 + (size_t)zspan * 64 * 8; }
 
 // LDS bytes of the two kernels; *own = 1 when the gather area cannot overlay the small tiles
 size_t fwd_lds(int C, int MID, int P, int nmem, int* own) {
@@ -2529,10 +2550,11 @@ hipError_t resident_prepare() {
                       reinterpret_cast<const void*>(k_bb_wgrad<32>),             reinterpret_cast<const void*>(k_bb_wgrad<64>)};
   for (const void* f : bb)
     if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_wgrad<128, 32>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_wgrad<256, 64>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  const void* wide[] = {reinterpret_cast<const void*>(k_res_forward<128, 64, 2, false>), reinterpret_cast<const void*>(k_res_backward<128, 64, 2, false>),
-                        reinterpret_cast<const void*>(k_res_wgrad<128, 64>)};
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_wgrad<128, 32, WG_ALL>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  for (const void* f : {reinterpret_cast<const void*>(k_res_wgrad<256, 64, WG_1X1>), reinterpret_cast<const void*>(k_res_wgrad<256, 64, WG_3X3>),
+                        reinterpret_cast<const void*>(k_res_wgrad<128, 64, WG_1X1>), reinterpret_cast<const void*>(k_res_wgrad<128, 64, WG_3X3>)})
+    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  const void* wide[] = {reinterpret_cast<const void*>(k_res_forward<128, 64, 2, false>), reinterpret_cast<const void*>(k_res_backward<128, 64, 2, false>)};
   for (const void* f : wide)
     if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_forward<256, 64, 1, false, false, true>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -2607,21 +2629,37 @@ hipError_t launch_resident_inference(int kind, int g, int C, int MID, const ResA
   return launch_res(k_res_forward<256, 64, 1, false, true>, lds, 0, g, a, stream);
 }
 
+// Work-groups per item of a weight-gradient launch.  A work-group takes about 3 us per batch of 256 pixels and adds one value per output
+// element with an atomic, 363 of them per ns over the chip: batches/n * 3 us + items*n*sums / 363 per ns is least at the n below (the 64-channel
+// run of ResNet-110-v1 with 15 work-groups per item spent 52 of its 93 us on atomics).  No more of them than `most` in all: a launch that
+// fills the chip gains nothing from shorter items.
+static int wgrad_groups(int batches, int items, int sums, int most) {
+  const int n = (int)std::sqrt(1.1e6 * batches / ((double)items * sums));
+  return std::max(1, std::min({batches, most / items, n}));
+}
+
 hipError_t launch_resident_wgrad(int kind, int g, int C, int MID, const ResArgs& a, hipStream_t stream) {
   if (resident_bands(kind, C, MID, a.H, a.W) > 1) return hipErrorInvalidValue;   // bands: forward and backward launches only
   if (!resident_has_wgrad_launch(kind, C, 1)) return hipErrorInvalidValue;
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > MAX_GROUP) return hipErrorInvalidValue;
   ResWgArgs w{};
   w.blocks = a.blocks; w.nmem = a.nmem; w.H = a.H; w.W = a.W;
-  w.ipw = 1;
-  for (int k = 8; k >= 1; k >>= 1)
-    if (a.nmem % k == 0) { w.ipw = k; break; }
   w.base = a.base; w.act_in = a.act_in; w.err_in = a.err_in; w.params = a.params; w.grads = a.grads;
   w.ngroup = g;
-  const unsigned groups = (unsigned)(g * a.nmem / w.ipw);
+  const int P = a.H * a.W;
+  w.sub = std::min(std::max(1, 256 / P), a.nmem);
+  while (w.sub > 1 && bb_wgrad_lds(MID, P, a.W, w.sub, g) > RES_LDS_BYTES) --w.sub;   // images of few rows, between two zero rows each
+  w.per_mb = (a.nmem + w.sub - 1) / w.sub;
+  const int batches = g * w.per_mb;
+  // shares of the images for a launch of `items` items with `sums` output elements each
+  auto share = [&](int items, int sums, int most) {
+    const int groups = wgrad_groups(batches, items, sums, most);
+    w.zspan = std::min(g, (batches / groups + 1 + w.per_mb - 2) / w.per_mb + 1);
+    return (unsigned)groups;
+  };
   if (kind == 0 || kind == 2) {
-    const size_t lds = bb_wgrad_lds(C, a.H * a.W, a.W);
-    const dim3 grid(groups, 2u, (unsigned)a.nblk);
+    const dim3 grid(share(2 * a.nblk, 9 * C * C, C == 64 ? 256 : 512), 2u, (unsigned)a.nblk);
+    const size_t lds = bb_wgrad_lds(C, P, a.W, w.sub, w.zspan);
     if (kind == 2) {
       if (C == 32) k_v1_wgrad<32><<<grid, rw_threads(32), lds, stream>>>(w);
       else k_v1_wgrad<64><<<grid, rw_threads(64), lds, stream>>>(w);
@@ -2629,11 +2667,20 @@ hipError_t launch_resident_wgrad(int kind, int g, int C, int MID, const ResArgs&
     else k_bb_wgrad<64><<<grid, rw_threads(64), lds, stream>>>(w);
     return hipGetLastError();
   }
-  const size_t lds = wgrad_lds(C, MID, a.H * a.W, a.W);
-  const dim3 grid(groups, (unsigned)(2 * (C / 64) + 1), (unsigned)a.nblk);
-  if (C == 128 && MID == 64) k_res_wgrad<128, 64><<<grid, rw_threads(64), lds, stream>>>(w);
-  else if (C == 128) k_res_wgrad<128, 32><<<grid, rw_threads(32), lds, stream>>>(w);
-  else k_res_wgrad<256, 64><<<grid, rw_threads(64), lds, stream>>>(w);
+  const unsigned n11 = 2 * (C / 64);
+  if (MID == 32) {
+    const dim3 grid(share((int)(n11 + 1) * a.nblk, 64 * MID, 1536), n11 + 1, (unsigned)a.nblk);
+    k_res_wgrad<128, 32, WG_ALL><<<grid, rw_threads(32), std::max(wgrad_1x1_lds(MID, P, w.sub, w.zspan), bb_wgrad_lds(MID, P, a.W, w.sub, w.zspan)), stream>>>(w);
+    return hipGetLastError();
+  }
+  const dim3 g1(share((int)n11 * a.nblk, 64 * MID, 1536), n11, (unsigned)a.nblk);
+  const size_t l1 = wgrad_1x1_lds(MID, P, w.sub, w.zspan);
+  if (C == 128) k_res_wgrad<128, 64, WG_1X1><<<g1, rw_threads(64), l1, stream>>>(w);
+  else k_res_wgrad<256, 64, WG_1X1><<<g1, rw_threads(64), l1, stream>>>(w);
+  const dim3 g3(share(a.nblk, 9 * MID * MID, 256), 1u, (unsigned)a.nblk);
+  const size_t l3 = bb_wgrad_lds(MID, P, a.W, w.sub, w.zspan);
+  if (C == 128) k_res_wgrad<128, 64, WG_3X3><<<g3, rw_threads(64), l3, stream>>>(w);
+  else k_res_wgrad<256, 64, WG_3X3><<<g3, rw_threads(64), l3, stream>>>(w);
   return hipGetLastError();
 }
 

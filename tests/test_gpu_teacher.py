@@ -152,6 +152,17 @@ def test_lds_tile_resident_runs_layerwise(gpu, oracle, kind, c, mid, h, w, image
     layerwise(oracle, spec, "bf16", blockwise=False)
 
 
+@pytest.mark.parametrize("kind,c,mid,h,w,images",
+                         [(W.BASIC, 64, 64, 12, 8, 5), (W.POSTACT, 64, 64, 8, 8, 6),             # two and four images at a time, the last batch not full
+                          (W.BASIC, 32, 32, 4, 16, 9), (W.BOTTLENECK, 128, 32, 4, 16, 3),        # fewer images than fit a batch
+                          (W.BOTTLENECK, 256, 64, 4, 8, 15), (W.BOTTLENECK, 128, 64, 8, 32, 3)])  # as many as fit the LDS; rows of 32 pixels
+def test_weight_gradients_of_small_images_layerwise(gpu, oracle, kind, c, mid, h, w, images):
+    """Weight gradients of resident runs that stage several images of a micro-batch at a time, in shares that cross micro-batches."""
+    spec = W.PartitionSpec(name=f"batches-{kind}-{c}-{mid}@{h}x{w}-b{images}", in_h=h, in_w=w, in_c=c, blocks=(W.Block(kind, c, mid, c, 1),) * 2,
+                           microbatch=images, num_microbatches=3, seed=67)
+    layerwise(oracle, spec, "bf16", blockwise=False)
+
+
 @pytest.mark.parametrize("images", [1, 31, 33])
 @pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 16, 32), (W.BASIC, 32, 32, 16), (W.BASIC, 64, 64, 8),
                                            (W.POSTACT, 16, 16, 32), (W.POSTACT, 32, 32, 16), (W.POSTACT, 64, 64, 8),
