@@ -12,6 +12,9 @@
 // contraction - statistics.  The form with LDS tiles measured 17.4 / 10.7 / 12 us per block forward.  A run of 9 blocks of 32 channels and one
 // of 3 blocks of 64 on 128 images: 139 -> 104 us forward, 154 -> 120 us backward; the three runs of ResNet-110 v1 (52 blocks):
 // 683 -> 477 and 820 -> 568 us.
+// Few images (4 or 8 of a batch) leave no other work-group to hide a wave that waits for the memory pipeline to take its loads:
+// at 64 channels 2.2 us of an inference block were spent asking for the next matrix in one go.  With the loads dealt out over the
+// contraction the same runs take 97 and 111 us (128 images), 440 and 541 us (v1), and inference of ResNet-110 on 4 images 317 -> 278 us.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -36,14 +39,21 @@ struct Geo {
 
 // 3x3 convolution from the canvas.  src: tap (0, 0) of the lane's pixel of the wave's first tile (+ fk; 16 channels: + (fq & 1)*8); FLIP: the
 // data gradient (taps mirrored).  w: the staged matrix at the wave's first channel tile, + lane*8.  zero: eight zeros (of the border).
-template <int C, bool FLIP>
-__device__ __forceinline__ void conv3x3(const bf16_t* src, const bf16_t* zero, const bf16_t* w, int fq, floatx4 (&acc)[Geo<C>::PTW][Geo<C>::NTW]) {
+// third(integral_constant 0 ... 2) runs at the start, after one and after two thirds of the contraction: the next matrix' loads.
+template <int C, bool FLIP, class THIRD>
+__device__ __forceinline__ void conv3x3(const bf16_t* src, const bf16_t* zero, const bf16_t* w, int fq, floatx4 (&acc)[Geo<C>::PTW][Geo<C>::NTW], THIRD&& third) {
+  auto thirds = [&](int i) {
+    if (i == 0) third(std::integral_constant<int, 0>{});
+    else if (i == 1) third(std::integral_constant<int, 1>{});
+    else third(std::integral_constant<int, 2>{});
+  };
   using G = Geo<C>;
   constexpr int MS = G::MS, CW = G::CW;
   if constexpr (C == 16) {   // packed weights [16][160], k = tap*16 + c, zero beyond tap 8: lane groups 0-1 take the even tap of a step, 2-3 the odd one.
     // The odd half of the last step has no tap: zeros, not another tap's values times the zero weights (0 * infinity)
 #pragma unroll
     for (int st = 0; st < 5; ++st) {
+      if (st % 2 == 0) thirds(st / 2);
       constexpr int last = 8;
       const int ta = 2 * st, tb = 2 * st + 1 > last ? last : 2 * st + 1;
       const int oa = FLIP ? (2 - ta / 3) * CW + 2 - ta % 3 : ta / 3 * CW + ta % 3, ob = FLIP ? (2 - tb / 3) * CW + 2 - tb % 3 : tb / 3 * CW + tb % 3;
@@ -58,6 +68,7 @@ __device__ __forceinline__ void conv3x3(const bf16_t* src, const bf16_t* zero, c
   } else if constexpr (C == 32) {   // the four input rows of a filter column serve both output rows
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
+      thirds(s);
       bf16x8 px[4];
 #pragma unroll
       for (int ir = 0; ir < 4; ++ir) px[ir] = *reinterpret_cast<const bf16x8*>(src + (ir * CW + s) * MS);
@@ -73,6 +84,7 @@ __device__ __forceinline__ void conv3x3(const bf16_t* src, const bf16_t* zero, c
   } else {
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
+      thirds(r);
 #pragma unroll
       for (int s = 0; s < 3; ++s)
 #pragma unroll
@@ -201,10 +213,10 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     if constexpr (!POST && !INFER)
       if (!exchange(X, B0, 0, coef1, [] {})) return;
   }
-  for (int bi = 0; bi < a.nblk; ++bi) {
-    const ResBlock B = a.blocks[bi];
+  ResBlock B = a.blocks[0], Bn = B;
+  for (int bi = 0; bi < a.nblk; ++bi, B = Bn) {
     const bool more = bi + 1 < a.nblk;
-    const ResBlock Bn = a.blocks[more ? bi + 1 : bi];
+    Bn = a.blocks[more ? bi + 1 : bi];   // a block ahead of its use
     // ---- conv1 on relu(bn1(x)) | x
     if constexpr (!POST) bn_pack(X, coef1);
     else {
@@ -214,7 +226,6 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
         for (int nt = 0; nt < NTW; ++nt) pk[j][nt] = pack4(X[j][nt]);
     }
     to_canvas();
-    if constexpr (INFER) w.issue(a.packed + B.wf_off[1], wave, fr, fq);
     __syncthreads();
     if constexpr (INFER)
       if (more) run_coef(Bn, 0, coef1);   // every wave has used this block's
@@ -223,14 +234,13 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     for (int j = 0; j < PTW; ++j)
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, acc);
+    conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, acc, [&](auto i) { w.template issue_third<i.value>(a.packed + B.wf_off[1], wave, fr, fq); });
     uint2 cp[PTW][NTW];
     round_to(acc, cp);
     if constexpr (INFER) {
       __syncthreads();   // the canvas and conv1's matrix have been read
       w.commit(sW, wave, lane);
     } else {
-      w.issue(a.packed + B.wf_off[1], wave, fr, fq);   // the exchange hides it
       if (!exchange(acc, B, POST ? 0 : 1, coef2, [&] {
             w.commit(sW, wave, lane);
             if constexpr (POST) { if (bi > 0) px_store(image(a.blocks[bi - 1].y_off), L.off, pk); }   // the block before's output
@@ -241,20 +251,18 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     // ---- conv2 on relu(bn2(c1)), onto x | on its own
     bn_pack(acc, coef2);
     to_canvas();
-    if constexpr (INFER)
-      if (more) w.issue(a.packed + Bn.wf_off[0], wave, fr, fq);
     __syncthreads();
+    auto next_matrix = [&](auto i) { if (more) w.template issue_third<i.value>(a.packed + Bn.wf_off[0], wave, fr, fq); };
     if constexpr (INFER)
       if (more) run_coef(Bn, 1, coef2);
     if constexpr (!POST) {
-      conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, X);
+      conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, X, next_matrix);
       round_to(X, cp);
       if constexpr (INFER) {
         if (!more) { px_store(image(B.y_off), L.off, cp); break; }
         __syncthreads();
         w.commit(sW, wave, lane);
       } else if (more) {
-        w.issue(a.packed + Bn.wf_off[0], wave, fr, fq);
         if (!exchange(X, Bn, 0, coef1, [&] {
               w.commit(sW, wave, lane);
               px_store(image(B.y_off), L.off, cp);
@@ -268,9 +276,8 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
       for (int j = 0; j < PTW; ++j)
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-      conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, acc);
+      conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, acc, next_matrix);
       round_to(acc, cp);
-      if (more) w.issue(a.packed + Bn.wf_off[0], wave, fr, fq);
       if (!exchange(acc, B, 1, coef1, [&] {
             if (more) w.commit(sW, wave, lane);
             px_store(image(B.c2_off), L.off, cp);
@@ -394,10 +401,10 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
     store_tables();
   }
   __syncthreads();
-  for (int bi = a.nblk - 1; bi >= 0; --bi) {
-    const ResBlock B = a.blocks[bi];
+  ResBlock B = a.blocks[a.nblk - 1], Bn = B;
+  for (int bi = a.nblk - 1; bi >= 0; --bi, B = Bn) {
     const bool more = bi > 0;
-    const ResBlock Bn = a.blocks[more ? bi - 1 : 0];
+    Bn = a.blocks[more ? bi - 1 : 0];   // a block ahead of its use
     floatx4 acc[PTW][NTW];
     auto store_gx = [&] { if (bi + 1 < a.nblk) px_store(image(a.blocks[bi + 1].gx_off), L.off, DY); };   // the gradient of the input of the block above
     if constexpr (!POST) {
@@ -405,8 +412,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
       to_canvas(DY);
       __syncthreads();
       zero(acc);
-      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc);
-      w.issue(a.packed + B.wd_off[0], wave, fr, fq);
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc, [&](auto i) { w.template issue_third<i.value>(a.packed + B.wd_off[0], wave, fr, fq); });
       px_arrange(xa);
       if (!exchange(Relu{}, acc, xa, cf2, B, 1, [&] {
             w.commit(sW, wave, lane);
@@ -419,8 +425,8 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
       __syncthreads();
       // ---- conv1 data gradient, BN1 + ReLU backward, plus the shortcut
       zero(acc);
-      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc);
-      if (more) { w.issue(a.packed + Bn.wd_off[1], wave, fr, fq); load_tables(bi - 1); }
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc, [&](auto i) { if (more) w.template issue_third<i.value>(a.packed + Bn.wd_off[1], wave, fr, fq); });
+      if (more) load_tables(bi - 1);
       px_arrange(xb);
       if (!exchange(Relu{}, acc, xb, cf1, B, 0, [&] {
             if (more) { w.commit(sW, wave, lane); store_tables(); px_load(xa, image(Bn.c1_off), L.off); }
@@ -455,8 +461,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
       __syncthreads();
       // ---- conv2 data gradient, BN1 + ReLU backward -> dc1
       zero(acc);
-      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc);
-      w.issue(a.packed + B.wd_off[0], wave, fr, fq);
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc, [&](auto i) { w.template issue_third<i.value>(a.packed + B.wd_off[0], wave, fr, fq); });
       if (more) load_tables(bi - 1);
       px_arrange(xb);
       if (!exchange(Relu{}, acc, xb, cf1, B, 0, [&] {
@@ -471,7 +476,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
       __syncthreads();
       px_store(image(B.dc1_off), L.off, dcp);
       // ---- conv1 data gradient plus the shortcut
-      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, dz);
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, dz, [](auto) {});
 #pragma unroll
       for (int j = 0; j < PTW; ++j)
 #pragma unroll
