@@ -171,11 +171,22 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) { p[j][nt] = pack4(v[j][nt]); v[j][nt] = unpack4(p[j][nt]); }
   };
-  auto run_coef = [&](const ResBlock& B, int q, float2* dst) {
-    if (tid < C) {
-      const float* run = a.running + B.run_off[q];
-      dst[tid] = bn_scale_shift(run[tid], 1.0f / sqrtf(run[C + tid] + a.eps), (a.params + B.gamma_off[q])[tid], (a.params + B.beta_off[q])[tid]);
+  // inference: the coefficients of a block, one channel per lane: wave 0 takes those of the first BatchNorm, wave 1 those of the second.  Read a
+  // block ahead of their use, as the loads of a wave that waits for them hold up the work-group
+  const bool t_on = wave < 2 && lane < C;
+  float rc_mean, rc_var, rc_gamma, rc_beta;
+  auto load_coef = [&](int b) {
+    const ResBlock* t = a.blocks + b;
+    if (t_on) {
+      const float* run = a.running + t->run_off[wave];
+      rc_mean = run[lane];
+      rc_var = run[C + lane];
+      rc_gamma = (a.params + t->gamma_off[wave])[lane];
+      rc_beta = (a.params + t->beta_off[wave])[lane];
     }
+  };
+  auto store_coef = [&](int q, float2* dst) {
+    if (t_on && wave == q) dst[lane] = bn_scale_shift(rc_mean, 1.0f / sqrtf(rc_var + a.eps), rc_gamma, rc_beta);
   };
   // statistics of v -> coef of BatchNorm q of block B; `late` runs behind the polls
   auto exchange = [&](const floatx4 (&v)[PTW][NTW], const ResBlock& B, int q, float2* coef, auto&& late) -> bool {
@@ -199,16 +210,17 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
   {
     const ResBlock B0 = a.blocks[0];
     w.issue(a.packed + B0.wf_off[0], wave, fr, fq);
+    if constexpr (INFER) load_coef(0);
     px_load(pk, image(B0.x_off), L.off);
     for (int i = tid; i < G::CANVAS / 16; i += RG_NT) reinterpret_cast<u32x4*>(canvas)[i] = u32x4{0u, 0u, 0u, 0u};
     if (tid == 0) *fail = 0;
-    if constexpr (INFER) { run_coef(B0, 0, coef1); run_coef(B0, 1, coef2); }
     px_arrange(pk);
 #pragma unroll
     for (int j = 0; j < PTW; ++j)
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) X[j][nt] = unpack4(pk[j][nt]);
     w.commit(sW, wave, lane);
+    if constexpr (INFER) { store_coef(0, coef1); store_coef(1, coef2); }
     __syncthreads();
     if constexpr (!POST && !INFER)
       if (!exchange(X, B0, 0, coef1, [] {})) return;
@@ -227,8 +239,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     }
     to_canvas();
     __syncthreads();
-    if constexpr (INFER)
-      if (more) run_coef(Bn, 0, coef1);   // every wave has used this block's
+    if constexpr (INFER) load_coef(more ? bi + 1 : bi);
     floatx4 acc[PTW][NTW];
 #pragma unroll
     for (int j = 0; j < PTW; ++j)
@@ -238,6 +249,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     uint2 cp[PTW][NTW];
     round_to(acc, cp);
     if constexpr (INFER) {
+      store_coef(0, coef1);   // every wave has used this block's
       __syncthreads();   // the canvas and conv1's matrix have been read
       w.commit(sW, wave, lane);
     } else {
@@ -253,13 +265,12 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     to_canvas();
     __syncthreads();
     auto next_matrix = [&](auto i) { if (more) w.template issue_third<i.value>(a.packed + Bn.wf_off[0], wave, fr, fq); };
-    if constexpr (INFER)
-      if (more) run_coef(Bn, 1, coef2);
     if constexpr (!POST) {
       conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, X, next_matrix);
       round_to(X, cp);
       if constexpr (INFER) {
         if (!more) { px_store(image(B.y_off), L.off, cp); break; }
+        store_coef(1, coef2);   // every wave has used this block's
         __syncthreads();
         w.commit(sW, wave, lane);
       } else if (more) {

@@ -69,6 +69,9 @@ constexpr int rg_fwd_lds() {
 // Barriers per block: 7 (training), 2 (inference).  The matrices of conv1 and conv3 take turns in one LDS area in training
 // (conv1's is dead when conv3's is staged, behind the barrier that ends conv1, and the other way round); conv2's of the next
 // block is staged behind the barrier that ends conv2.
+// Inference is bounded by latency (4.2 us per 128-32 block, of which the products take 0.9): every matrix and table is asked for as soon as the
+// registers of the one before are free, a whole block ahead of its use, and the tables of the three BatchNorms are read by waves of their
+// own.  Asked for within the block, the tables three dependent reads long in one wave: 22 blocks took 93 us, now 78.
 template <int C, int MID, bool INFER>
 __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
@@ -108,11 +111,45 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
 
   W1 w1; W2 w2; W3 w3;
   floatx4 X[RG_PTW][NC];
+  // Inference: the coefficients of a block, one channel per thread: waves 0 .. C/64 - 1 take the first BatchNorm, the next two waves the others.
+  static_assert(C / 64 + 2 <= RG_NW && MID <= 64, "a channel per lane");
+  float rc_mean, rc_var, rc_gamma, rc_beta;
+  const int tq = wave < C / 64 ? 0 : wave - C / 64 + 1, tc = tq == 0 ? tid : lane;
+  const bool t_on = tq == 0 || (tq < 3 && lane < MID);
+  float2* const t_dst = coefC + (tq == 0 ? 0 : tq == 1 ? C : C + MID);
+  const int last = a.nblk - 1;
+  struct { unsigned long long w1, w2, w3, run, gamma, beta; } nx;   // offsets of what is asked for next
+  auto next_offsets = [&](int b01, int b2) {   // matrices and tables of the first two convolutions of block b01, of the third of block b2
+    const ResBlock *t01 = a.blocks + (b01 < last ? b01 : last), *t2 = a.blocks + (b2 < last ? b2 : last);
+    nx.w1 = t01->wf_off[0];
+    nx.w2 = t01->wf_off[1];
+    nx.w3 = t2->wf_off[2];
+    const ResBlock* t = tq < 2 ? t01 : t2;
+    const int q = tq < 3 ? tq : 2;
+    nx.run = t->run_off[q];
+    nx.gamma = t->gamma_off[q];
+    nx.beta = t->beta_off[q];
+  };
+  auto load_coef = [&] {
+    if (!t_on) return;
+    const float* run = a.running + nx.run;
+    rc_mean = run[tc];
+    rc_var = run[(tq == 0 ? C : MID) + tc];
+    rc_gamma = (a.params + nx.gamma)[tc];
+    rc_beta = (a.params + nx.beta)[tc];
+  };
+  auto store_coef = [&] {
+    if (t_on) t_dst[tc] = bn_scale_shift(rc_mean, 1.0f / sqrtf(rc_var + a.eps), rc_gamma, rc_beta);
+  };
   {
     const ResBlock B0 = a.blocks[0];
     w1.issue(a.packed + B0.wf_off[0], wave, fr, fq);
-    if constexpr (INFER) w2.issue(a.packed + B0.wf_off[1], wave, fr, fq);
-    if constexpr (INFER) w3.issue(a.packed + B0.wf_off[2], wave, fr, fq);
+    if constexpr (INFER) {
+      next_offsets(0, 0);
+      w2.issue(a.packed + nx.w2, wave, fr, fq);
+      w3.issue(a.packed + nx.w3, wave, fr, fq);
+      load_coef();
+    }
     for (int i = tid; i < RG_CW * RG_CW * MS / 8; i += RG_NT) reinterpret_cast<u32x4*>(canvas)[i] = u32x4{0u, 0u, 0u, 0u};
     if (tid == 0) *fail = 0;
     uint2 q[RG_PTW][NC];
@@ -125,7 +162,11 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
     w1.commit(sW1, wave, lane);
     if constexpr (INFER) {
       w2.commit(sW2, wave, lane);
-      w3.commit(sW3, wave, lane);
+      store_coef();
+      next_offsets(1, 0);
+      w1.issue(a.packed + nx.w1, wave, fr, fq);   // w3 and the table of the third BatchNorm are kept for the first block, where they are staged
+      w2.issue(a.packed + nx.w2, wave, fr, fq);
+      load_coef();
     } else {
       const bf16_t* g = a.packed + B0.wf_off[1];
       w2.template issue<0>(g, wave, fr, fq); w2.template commit<0>(sW2, wave, lane);
@@ -133,13 +174,6 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
       w2.template issue<2>(g, wave, fr, fq); w2.template commit<2>(sW2, wave, lane);
     }
   }
-  // inference: the coefficients of BatchNorm q of a block; one channel per thread
-  auto run_coef = [&](const ResBlock& B, int q, int Cc, float2* dst) {
-    if (tid < Cc) {
-      const float* run = a.running + B.run_off[q];
-      dst[tid] = bn_scale_shift(run[tid], 1.0f / sqrtf(run[Cc + tid] + a.eps), (a.params + B.gamma_off[q])[tid], (a.params + B.beta_off[q])[tid]);
-    }
-  };
   const float inv_n = 1.f / (float)a.nmem;
   // training: statistics of the wave's values v -> coef of the BatchNorm q of block B; `late` runs behind the polls.  Returns false when a
   // partner did not show up.
@@ -164,30 +198,22 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   };
   using IC = std::integral_constant<int, C>;
   using IM = std::integral_constant<int, MID>;
-  {
-    const ResBlock B0 = a.blocks[0];
-    if constexpr (INFER) {
-      run_coef(B0, 0, C, coefC);
-      run_coef(B0, 1, MID, coefM);
-      run_coef(B0, 2, MID, coefM3);
-      __syncthreads();
-    } else {
-      __syncthreads();
-      if (!exchange(IC{}, X, B0, 0, coefC, [] {})) return;
-    }
+  __syncthreads();
+  if constexpr (!INFER) {
+    if (!exchange(IC{}, X, a.blocks[0], 0, coefC, [] {})) return;
   }
   for (int bi = 0; bi < a.nblk; ++bi) {
-    const ResBlock B = a.blocks[bi];
     const bool more = bi + 1 < a.nblk;
+    const ResBlock B = a.blocks[bi];
     const ResBlock Bn = a.blocks[more ? bi + 1 : bi];
+    if constexpr (INFER) next_offsets(bi + 2, bi + 1);
     // ---- conv1 (1x1, C -> MID) on relu(bn1(x))
     floatx4 acc[RG_PTW][NM];
 #pragma unroll
     for (int j = 0; j < RG_PTW; ++j)
 #pragma unroll
       for (int nt = 0; nt < NM; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (INFER) w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq);
-    else w3.issue(a.packed + B.wf_off[2], wave, fr, fq);
+    if constexpr (!INFER) w3.issue(a.packed + B.wf_off[2], wave, fr, fq);
 #pragma unroll
     for (int ks = 0; ks < C / 32; ++ks) {
       bf16x8 bf[RG_PTW];
@@ -219,13 +245,14 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
 #pragma unroll
       for (int nt = 0; nt < NM; ++nt)
         *reinterpret_cast<uint2*>(cv_w + j * RG_CW * MS + nt * 16) = bn_relu_pack(acc[j][nt], coefM + nt * 16 + fq * 4);
-    if (INFER && more) w2.issue(a.packed + Bn.wf_off[1], wave, fr, fq);
     __syncthreads();
-    if constexpr (INFER) {   // every wave is past conv1 and its tables
+    if constexpr (INFER) {   // every wave is past conv1 and its tables, and past conv3 of the block before
       w1.commit(sW1, wave, lane);
-      if (bi > 0) w3.commit(sW3, wave, lane);
-      if (more) { run_coef(Bn, 0, C, coefC); run_coef(Bn, 1, MID, coefM); }
-      if (bi > 0) run_coef(B, 2, MID, coefM3);
+      w3.commit(sW3, wave, lane);
+      store_coef();
+      load_coef();
+      w1.issue(a.packed + nx.w1, wave, fr, fq);   // a whole block ahead of their use
+      w3.issue(a.packed + nx.w3, wave, fr, fq);
     }
     // ---- conv2 (3x3, MID -> MID)
 #pragma unroll
@@ -239,7 +266,8 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
       for (int nt = 0; nt < NM; ++nt) { cp[j][nt] = pack4(acc[j][nt]); acc[j][nt] = unpack4(cp[j][nt]); }
     if constexpr (INFER) {
       __syncthreads();
-      if (more) { w2.commit(sW2, wave, lane); w3.issue(a.packed + Bn.wf_off[2], wave, fr, fq); }
+      w2.commit(sW2, wave, lane);
+      w2.issue(a.packed + nx.w2, wave, fr, fq);
     } else {
       if (more) { w2.template issue<0>(a.packed + Bn.wf_off[1], wave, fr, fq); w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq); }   // the exchange hides it
       if (!exchange(IM{}, acc, B, 2, coefM3, [&] {
