@@ -63,8 +63,9 @@ struct PackDesc {
 //               pixel-row tile and channel, for the BatchNorm that consumes this output;
 //   EPI_BNBWD : the output is the gradient da w.r.t. a BN+ReLU output: it is masked with the ReLU
 //               decision recomputed from the BN input x (dz = da*[z>0], stored instead of da) and the
-//               partial sums {sum dz, sum dz*xhat} are written, one row per pixel-row tile.
-enum : int { EPI_NONE = 0, EPI_STATS = 1, EPI_BNBWD = 2 };
+//               partial sums {sum dz, sum dz*xhat} are written, one row per pixel-row tile;
+//   EPI_BIAS  : bias and ReLU on the rounded output (forward convolutions and dense layers).
+enum : int { EPI_NONE = 0, EPI_STATS = 1, EPI_BNBWD = 2, EPI_BIAS = 3 };
 struct ConvEpi {
   int kind = EPI_NONE;
   PtrTab partials{};        // EPI_STATS: 4 floats, EPI_BNBWD: 2 floats per (tile row, channel)
@@ -72,7 +73,9 @@ struct ConvEpi {
   PtrTab stats{};           // EPI_BNBWD: {mean(N), invstd(N)} float
   const float* gamma = nullptr;
   const float* beta = nullptr;
-  // EPI_NONE without residual operand: room for a reduction split over several work-groups (long reductions
+  const float* bias = nullptr;   // EPI_BIAS
+  int relu = 0;
+  // EPI_NONE and EPI_BIAS without residual operand: room for a reduction split over several work-groups (long reductions
   // into few output tiles): per member a buffer of splitk_floats floats, slab s holds fp32 partial sums [M][N] at s*M*N;
   // 0 floats = none.  Per member, because calls for different micro-batches may overlap on different streams.
   PtrTab splitk_ws{};

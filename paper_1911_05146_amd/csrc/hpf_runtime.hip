@@ -854,7 +854,7 @@ struct Ctx {
   // pro_bn (bf16 mode): x is the input of that BatchNorm and the convolution normalises it while staging; src: its statistics.  Records are
   // finalised here, by the convolution or by a launch in front of it; src then names the finished statistics.
   int conv_fwd(const ConvPlan& cv, const PtrTab& x, const PtrTab& y, const PtrTab& add, bool want_stats = false,
-               const BnPlan* pro_bn = nullptr, BnSource* src = nullptr) {
+               const BnPlan* pro_bn = nullptr, BnSource* src = nullptr, const float* bias = nullptr, int relu = 0) {
     const ConvGeom q = geom_fwd(cv);
     if (h->P.dt == DT_BF16) {
       ConvEpi epi;
@@ -875,13 +875,16 @@ struct Ctx {
         const int bm = conv_mfma_tile_rows(g, q);
         rows = (q.M + bm - 1) / bm;
       }
+      if (bias && fused()) { epi.kind = EPI_BIAS; epi.bias = bias; epi.relu = relu; }
       if (h->P.splitk_floats) { epi.splitk_ws = mbp(h->P.splitk_off); epi.splitk_floats = h->P.splitk_floats; }
       const int back = conv_seg(PROF_CONV_FWD, q, add.p[0] != nullptr);
       chk(launch_conv_mfma(CONV_FWD, g, x, h->packed() + cv.wf_off, y, add, q, s, epi, pro), "conv_fwd");
       if (back != PROF_NONE) seg(back);
+      if (bias && !fused()) chk(launch_bias_act_fwd(DT_BF16, g, y, y, bias, q.M, q.N, relu, s), "bias_act");
       return rows;
     }
     chk(launch_conv_f32(CONV_FWD, g, x, h->params() + cv.w_off, y, add, q, s), "conv_fwd_f32");
+    if (bias) chk(launch_bias_act_fwd(h->P.dt, g, y, y, bias, q.M, q.N, relu, s), "bias_act");
     return 0;
   }
   // bn / bn_x: the BatchNorm (and its stashed input) whose backward consumes dx; returns partial rows.
@@ -1030,9 +1033,7 @@ void run_forward(Ctx& c, const PtrTab& labels, float* loss_accum) {
               "bn_add_relu");
       } else if (p.d.kind == K_CONV_RELU || p.d.kind == K_DENSE) {
         const PtrTab y0 = c.tab(p.y0);
-        c.conv_fwd(p.cv[0], x, y0, Ctx::none());
-        const int rows = p.d.kind == K_DENSE ? (int)b : (int)M_in;
-        c.chk(launch_bias_act_fwd(P.dt, c.g, y0, y0, bias, rows, p.d.c_out, p.d.kind == K_DENSE ? (p.d.c_mid != 0) : 1, c.s), "bias_act");
+        c.conv_fwd(p.cv[0], x, y0, Ctx::none(), false, nullptr, nullptr, bias, p.d.kind == K_DENSE ? (p.d.c_mid != 0) : 1);
         if (p.d.kind == K_CONV_RELU && p.d.stride == 2)
           c.chk(launch_maxpool2_fwd(P.dt, c.g, y0, y, (int)b, p.h_in, p.w_in, p.d.c_out, c.s), "maxpool");
       } else if (p.d.kind == K_BN_RELU) {

@@ -139,3 +139,26 @@ def test_pipelines_of_partitions_equal_the_unsplit_model(gpu, oracle, model, n_p
         rep = compare(whole, res, yard, mode, ref64=lambda: oracle.run_step(whole, to64(inp), np.float64, sgd=(0.1, 0.9)),
                       strict=(mode == "f32"), insensitive="skip")
         print(f"[parity] pipeline {whole.name} {mode}: " + fmt(rep), flush=True)
+
+
+@pytest.mark.parametrize("block,hw,c,b", [
+    (W.Block(W.CONV_RELU, 16, 16, 16, 1), 9, 16, 3),          # 64 x 16 tile, a last tile of 51 rows
+    (W.Block(W.CONV_RELU, 16, 32, 32, 2), 8, 16, 3),          # 64 x 32, with the max-pool behind it
+    (W.Block(W.CONV_RELU, 32, 64, 64, 1), 7, 32, 5),          # 64 x 64
+    (W.Block(W.CONV_RELU, 64, 128, 128, 2), 16, 64, 7),      # 128 x 128, whole reduction in one work-group
+    (W.Block(W.CONV_RELU, 128, 128, 128, 1), 3, 128, 4),      # 128 x 128, reduction split, 36 rows
+    (W.Block(W.DENSE, 1024, 1, 128, 1), 1, 1024, 5),           # split, with ReLU
+    (W.Block(W.DENSE, 64, 0, 48, 1), 1, 64, 5),               # no ReLU
+])
+def test_bias_and_relu_in_the_convolution(gpu, block, hw, c, b):
+    """Bias and ReLU where the convolution stores its output: the same values, rounding included, as in a pass of their own
+    (fusion level 0)."""
+    from parity import rel_err, run_gpu_step
+    spec = unit(f"bias-{block}", [block], hw, c, b=b, m=2)
+    print(f"\n[case] {spec.name} hw={hw} c={c} b={b}", flush=True)
+    inp = W.make_inputs(spec, randomize_affine=True)
+    _, apart = run_gpu_step(spec, inp, "bf16", fusion=0)
+    _, fused = run_gpu_step(spec, inp, "bf16", fusion=2)
+    for x, y in zip(apart["act_out"] + apart["err_out"], fused["act_out"] + fused["err_out"]):
+        assert np.array_equal(x, y)
+    assert rel_err(fused["grad"], apart["grad"]) < 1e-5      # gradient sums: fp32 atomics, order may differ
