@@ -276,10 +276,11 @@ hipError_t launch_bias_act_fwd(int dt, int g, const PtrTab& x, const PtrTab& y, 
 // dx = dy * [y > 0] (relu) or dy; g_bias[c] += sum of dx over the rows.  sums / partials: scratch as for the BatchNorm backward.
 hipError_t launch_bias_act_bwd(int dt, int g, const PtrTab& y, const PtrTab& dy, const PtrTab& dx, float* g_bias, int M, int C,
                                int relu, const PtrTab& sums, const PtrTab& partials, hipStream_t stream);
-// 2x2 max-pool of stride 2 (h, w even) and its backward pass (gradient to the first maximum in row-major order).
+// 2x2 max-pool of stride 2 (h, w even), and the backward pass of a ReLU layer with bias and such a pool behind it: y the layer's
+// output in front of the pool, dy the pooled gradient (which goes to the first maximum in row-major order).
 hipError_t launch_maxpool2_fwd(int dt, int g, const PtrTab& x, const PtrTab& y, int b, int h, int w, int C, hipStream_t stream);
-hipError_t launch_maxpool2_bwd(int dt, int g, const PtrTab& x, const PtrTab& dy, const PtrTab& dx, int b, int h, int w, int C,
-                               hipStream_t stream);
+hipError_t launch_pool_relu_bias_bwd(int dt, int g, const PtrTab& y, const PtrTab& dy, const PtrTab& dx, float* g_bias, int b, int h, int w, int C,
+                                     const PtrTab& sums, const PtrTab& partials, hipStream_t stream);
 // Residual join of a post-activation block, y = max(bn(x) + add, 0) (statistics given), and its backward pass:
 // dz = dy * [y > 0]; dadd = dz; dx through the BatchNorm; dgamma / dbeta added into g_gamma / g_beta.
 hipError_t launch_bn_add_relu_apply(int dt, int g, const PtrTab& x, const PtrTab& add, const PtrTab& y, const float* gamma,

@@ -1171,14 +1171,13 @@ void run_backward(Ctx& c) {
         }
       } else if (p.d.kind == K_CONV_RELU || p.d.kind == K_DENSE) {
         const PtrTab y0 = c.tab(p.y0);
-        PtrTab d0 = dy;
         if (p.d.kind == K_CONV_RELU && p.d.stride == 2) {
-          c.chk(launch_maxpool2_bwd(P.dt, c.g, y0, dy, t0, (int)b, p.h_in, p.w_in, p.d.c_out, c.s), "maxpool_bwd");
-          d0 = t0;
+          c.chk(launch_pool_relu_bias_bwd(P.dt, c.g, y0, dy, t1, g_bias, (int)b, p.h_in, p.w_in, p.d.c_out, sums, parts, c.s), "pool_relu_bias_bwd");
+        } else {
+          const int rows = p.d.kind == K_DENSE ? (int)b : (int)M_in;
+          c.chk(launch_bias_act_bwd(P.dt, c.g, y0, dy, t1, g_bias, rows, p.d.c_out, p.d.kind == K_DENSE ? (p.d.c_mid != 0) : 1, sums, parts, c.s),
+                "bias_act_bwd");
         }
-        const int rows = p.d.kind == K_DENSE ? (int)b : (int)M_in;
-        c.chk(launch_bias_act_bwd(P.dt, c.g, y0, d0, t1, g_bias, rows, p.d.c_out, p.d.kind == K_DENSE ? (p.d.c_mid != 0) : 1, sums, parts, c.s),
-              "bias_act_bwd");
         if (!deferred) c.conv_wgrad(p.cv[0], x, t1);
         c.conv_dgrad(p.cv[0], t1, gx, Ctx::none());
       } else if (p.d.kind == K_BN_RELU) {

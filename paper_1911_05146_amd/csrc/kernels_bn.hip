@@ -616,37 +616,56 @@ __global__ __launch_bounds__(256) void k_maxpool2_fwd(PtrTab xs, PtrTab ys, int 
     store8(y + px * C + cg * 8, best);
   }
 }
-// The gradient of a window goes to its maximum; among equal maxima to the first in row-major order.
-template <class T>
-__global__ __launch_bounds__(256) void k_maxpool2_bwd(PtrTab xs, PtrTab dys, PtrTab dxs, int b, int h, int w, int C) {
-  const T* __restrict__ x = (const T*)pick(xs, blockIdx.z);
+// Backward of ReLU, bias and the max-pool behind them: the gradient of a window goes to its maximum (among equal maxima to the first in
+// row-major order) where that is positive, and counts there for the bias.  In two passes the pooled gradient went through memory at four
+// times its size and the stages of VGG-16 took five launches more; rows are pixels of the pooled image.
+template <class T, class A>
+__global__ __launch_bounds__(BN_THREADS) void k_pool_relu_bias_bwd(PtrTab ys, PtrTab dys, PtrTab dxs, int b, int h, int w, int C, int rows_per_block,
+                                                                   PtrTab parts) {
+  const T* __restrict__ y = (const T*)pick(ys, blockIdx.z);
   const T* __restrict__ dy = (const T*)pick(dys, blockIdx.z);
   T* __restrict__ dx = (T*)pick(dxs, blockIdx.z);
-  const int ho = h / 2, wo = w / 2, CG = C / 8;
-  const size_t total = (size_t)b * ho * wo * CG;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const int cg = (int)(i % CG);
-    const size_t px = i / CG;
-    const int q = (int)(px % wo), p = (int)((px / wo) % ho), n = (int)(px / ((size_t)wo * ho));
-    float v[4][8], d[8], o[8];
-    int arg[8];
+  A* __restrict__ partials = (A*)pick(parts, blockIdx.z);
+  __shared__ A sh[16][BN_THREADS];
+  const BnMap m = bn_map(C);
+  A s[16];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) load8(x + (((size_t)n * h + 2 * p + (t >> 1)) * w + 2 * q + (t & 1)) * C + cg * 8, v[t]);
-    load8(dy + px * C + cg * 8, d);
+  for (int j = 0; j < 16; ++j) s[j] = 0;
+  if (m.active) {
+    const int ho = h / 2, wo = w / 2;
+    const int r0 = blockIdx.x * rows_per_block;
+    const int r1 = min(b * ho * wo, r0 + rows_per_block);
+    for (int r = r0 + m.rl; r < r1; r += m.rpp) {
+      const int q = r % wo, pn = r / wo, p = pn % ho, n = pn / ho;
+      const size_t o = (((size_t)n * h + 2 * p) * w + 2 * q) * C + m.c0;
+      float v[4][8], d[8], dz[8];
+      int arg[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      float best = v[0][j];
-      arg[j] = 0;
+      for (int t = 0; t < 4; ++t) load8(y + o + (size_t)((t >> 1) * w + (t & 1)) * C, v[t]);
+      load8(dy + (size_t)r * C + m.c0, d);
 #pragma unroll
-      for (int t = 1; t < 4; ++t)
-        if (v[t][j] > best) { best = v[t][j]; arg[j] = t; }
+      for (int j = 0; j < 8; ++j) {
+        float best = v[0][j];
+        arg[j] = 0;
+#pragma unroll
+        for (int t = 1; t < 4; ++t)
+          if (v[t][j] > best) { best = v[t][j]; arg[j] = t; }
+        if (!(best > 0.f)) d[j] = 0.f;
+        s[j] += (A)d[j];
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dz[j] = arg[j] == t ? d[j] : 0.f;
+        store8(dx + o + (size_t)((t >> 1) * w + (t & 1)) * C, dz);
+      }
     }
+  }
+  block_reduce16(s, m, C, sh);
+  if (m.active && m.rl == 0) {
+    A* p = partials + ((size_t)blockIdx.x * C + m.c0) * 2;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) o[j] = arg[j] == t ? d[j] : 0.f;
-      store8(dx + (((size_t)n * h + 2 * p + (t >> 1)) * w + 2 * q + (t & 1)) * C + cg * 8, o);
-    }
+    for (int j = 0; j < 8; ++j) { p[2 * j] = s[j]; p[2 * j + 1] = 0; }
   }
 }
 
@@ -917,12 +936,17 @@ hipError_t launch_maxpool2_fwd(int dt, int ng, const PtrTab& x, const PtrTab& y,
   return hipGetLastError();
 }
 
-hipError_t launch_maxpool2_bwd(int dt, int ng, const PtrTab& x, const PtrTab& dy, const PtrTab& dx, int b, int h, int w, int C,
-                               hipStream_t stream) {
-  const size_t total = (size_t)b * (h / 2) * (w / 2) * (C / 8);
-  const dim3 grid((unsigned)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096), 1, (unsigned)ng);
-  if (dt == DT_BF16) k_maxpool2_bwd<bf16_t><<<grid, 256, 0, stream>>>(x, dy, dx, b, h, w, C);
-  else k_maxpool2_bwd<float><<<grid, 256, 0, stream>>>(x, dy, dx, b, h, w, C);
+hipError_t launch_pool_relu_bias_bwd(int dt, int ng, const PtrTab& y, const PtrTab& dy, const PtrTab& dx, float* g_bias, int b, int h, int w, int C,
+                                     const PtrTab& sums, const PtrTab& partials, hipStream_t stream) {
+  const BnGrid g = reduce_grid(b * (h / 2) * (w / 2), C);
+  const dim3 grid(g.grid.x, g.grid.y, (unsigned)ng), fin((unsigned)((C + FIN_CH - 1) / FIN_CH), 1, (unsigned)ng);
+  if (dt == DT_BF16) {
+    k_pool_relu_bias_bwd<bf16_t, float><<<grid, BN_THREADS, 0, stream>>>(y, dy, dx, b, h, w, C, g.rows_per_block, partials);
+    k_bn_bwd_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(C, g.grid.x, partials, sums, nullptr, g_bias);
+  } else {
+    k_pool_relu_bias_bwd<float, double><<<grid, BN_THREADS, 0, stream>>>(y, dy, dx, b, h, w, C, g.rows_per_block, partials);
+    k_bn_bwd_finalize<double><<<fin, BN_THREADS, 0, stream>>>(C, g.grid.x, partials, sums, nullptr, g_bias);
+  }
   return hipGetLastError();
 }
 
