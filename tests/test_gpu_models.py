@@ -162,3 +162,11 @@ def test_bias_and_relu_in_the_convolution(gpu, block, hw, c, b):
     for x, y in zip(apart["act_out"] + apart["err_out"], fused["act_out"] + fused["err_out"]):
         assert np.array_equal(x, y)
     assert rel_err(fused["grad"], apart["grad"]) < 1e-5      # gradient sums: fp32 atomics, order may differ
+
+
+@pytest.mark.parametrize("in_c,h,w,b", [(1, 5, 3, 3), (2, 9, 7, 2), (3, 32, 32, 2), (5, 6, 11, 1), (17, 8, 8, 2)])
+def test_stem_columns(gpu, oracle, in_c, h, w, b):
+    """The stem's im2col columns: channel counts that divide nothing, images smaller than a work-group's share, odd edges."""
+    spec = W.PartitionSpec(name=f"stem-{in_c}x{h}x{w}", in_h=h, in_w=w, in_c=in_c, blocks=(W.Block(W.BN_RELU, 16, 16, 16, 1),), microbatch=b,
+                           num_microbatches=2, seed=71, has_stem=True, stem_c_out=16)
+    layerwise(oracle, spec, "bf16")
