@@ -69,9 +69,9 @@ constexpr int rg_fwd_lds() {
 // Barriers per block: 7 (training), 2 (inference).  The matrices of conv1 and conv3 take turns in one LDS area in training
 // (conv1's is dead when conv3's is staged, behind the barrier that ends conv1, and the other way round); conv2's of the next
 // block is staged behind the barrier that ends conv2.
-// Inference is bounded by latency (4.2 us per 128-32 block, of which the products take 0.9): every matrix and table is asked for as soon as the
+// Inference is bounded by latency (3.8 us per 128-32 block, of which the products take 0.9): every matrix and table is asked for as soon as the
 // registers of the one before are free, a whole block ahead of its use, and the tables of the three BatchNorms are read by waves of their
-// own.  Asked for within the block, the tables three dependent reads long in one wave: 22 blocks took 93 us, now 78.
+// own.  Asked for within the block, the tables three dependent reads in one wave, 21 blocks took 95 us, now 80.
 template <int C, int MID, bool INFER>
 __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
