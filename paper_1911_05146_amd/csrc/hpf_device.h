@@ -72,55 +72,97 @@ __device__ __forceinline__ float sum16(float v) { return row_sum<1>(v); }   // o
 
 // Where the consumer of a BatchNorm takes its {mean, invstd} from (bf16 mode).
 enum : int { BN_FROM_STATS = 0, BN_FROM_RECORDS = 1, BN_FROM_RUNNING = 2 };
+// Records of row blocks ([row][C]) are added up in one order wherever it is done, so a result does not depend on who does it: row b belongs
+// to group b % FIN_GROUPS, a group is added in ascending rows and the groups in ascending order.  A work-group of 256 threads takes nch <= 64
+// channels; FinMap: thread j * nch + cl has the rows j, j + rg, ... of channel cl, which are `vg` groups.  FIN_RECS records of a thread are in
+// flight together, so up to FIN_RECS * rg rows cost one round trip.
+constexpr int FIN_RECS = 8, FIN_GROUPS = 16, FIN_SH = FIN_GROUPS * 64;   // FIN_SH: floats of LDS, a row of 64 channels per group
+struct FinMap {
+  int nch, rg, vg, j, cl;
+  bool on;
+  __device__ __forceinline__ explicit FinMap(int nch_) : nch(nch_), rg(nch_ > 32 ? 4 : nch_ > 16 ? 8 : 16), vg(FIN_GROUPS / rg) {
+    j = (int)threadIdx.x / nch;
+    cl = (int)threadIdx.x - j * nch;
+    on = j < rg;
+  }
+};
+// Sums of a thread's groups
+struct FinAcc {
+  float a[4] = {0.f, 0.f, 0.f, 0.f};
+  template <class V>
+  __device__ __forceinline__ void add(const FinMap& m, V v) {   // v(i): value of the thread's record i in a round of FIN_RECS * rg rows
+    if (m.vg == 4) {
+#pragma unroll
+      for (int i = 0; i < FIN_RECS; ++i) a[i & 3] += v(i);
+    } else if (m.vg == 2) {
+#pragma unroll
+      for (int i = 0; i < FIN_RECS; ++i) a[i & 1] += v(i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < FIN_RECS; ++i) a[0] += v(i);
+    }
+  }
+  __device__ __forceinline__ void store(const FinMap& m, float* sh) const {
+    if (!m.on) return;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (k < m.vg) sh[(m.j + k * m.rg) * 64 + m.cl] = a[k];
+  }
+  static __device__ __forceinline__ float sum(const FinMap& m, const float* sh) {
+    float t = sh[m.cl];
+#pragma unroll
+    for (int g = 1; g < FIN_GROUPS; ++g) t += sh[g * 64 + m.cl];
+    return t;
+  }
+};
 // {mean, invstd} of channels [c_base, c_base + nch), nch <= 64, from the statistics records {K, S1, S2, n} of nrows row blocks
 // ([row][C], S1 / S2 sums about K), by a work-group of 256 threads; out(c, mean, invstd) is called by one thread per channel.
-// Two passes in a fixed order: the mean from the block sums, then the squared deviations about it, M2 = sum [S2 - S1^2/n + n (mean_b -
-// mean)^2]; FIN_RECS records of a thread stay in registers, so up to 8 * (256 / nch) rows cost one round trip.  sh: 256 floats of LDS.
-constexpr int FIN_RECS = 8;
+// Two passes: the mean from the block sums, then the squared deviations about it, M2 = sum [S2 - S1^2/n + n (mean_b - mean)^2].
+// sh: FIN_SH floats of LDS.
 template <class OUT>
 __device__ __forceinline__ void bn_finalize_records(const float4* __restrict__ rec, unsigned nrows, int C, int c_base, int nch, int M, float eps,
                                                     float* sh, OUT out) {
-  const int rg = 256 / nch, j = (int)threadIdx.x / nch, cl = (int)threadIdx.x - j * nch, c = c_base + cl;
-  const bool on = j < rg && c < C;
-  const float4* p = rec + (on ? c : 0);
+  const FinMap m(nch);
+  const int c = c_base + m.cl;
+  const bool on = m.on && c < C;
+  const char* p = (const char*)rec;
+  const unsigned row_bytes = (unsigned)C * 16, col = (unsigned)c * 16;
   float4 q[FIN_RECS];
   auto load = [&](unsigned b0) {   // all loads in flight together
 #pragma unroll
     for (int i = 0; i < FIN_RECS; ++i) {
-      const unsigned b = b0 + (unsigned)(j + i * rg);
-      q[i] = on && b < nrows ? p[(size_t)b * C] : make_float4(0.f, 0.f, 0.f, 0.f);
+      const unsigned b = b0 + (unsigned)(m.j + i * m.rg);
+      q[i] = on && b < nrows ? *(const float4*)(p + (b * row_bytes + col)) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
-  const unsigned step = (unsigned)(FIN_RECS * rg), b_last = (nrows - 1) / step * step;
-  float tot = 0.f;
-  for (unsigned b0 = 0; b0 <= b_last; b0 += step) {
+  const unsigned step = (unsigned)(FIN_RECS * m.rg);
+  FinAcc acc;
+  for (unsigned b0 = 0; b0 < nrows; b0 += step) {
     load(b0);
-#pragma unroll
-    for (int i = 0; i < FIN_RECS; ++i) tot += q[i].w * q[i].x + q[i].y;   // n*K + S1 = sum of the block's values
+    acc.add(m, [&](int i) { return q[i].w * q[i].x + q[i].y; });   // n*K + S1 = sum of the block's values
   }
-  auto total = [&](float v) {
+  if (nrows > step) load(0);   // on its way during the sum over the groups
+  auto publish = [&](const FinAcc& a) {
     __syncthreads();
-    sh[threadIdx.x] = v;
+    a.store(m, sh);
     __syncthreads();
-    float t = 0.f;
-    for (int r = 0; r < rg; ++r) t += sh[r * nch + cl];
-    return t;
   };
-  const float mean = total(tot) / (float)M;
-  float m2 = 0.f;
-  for (unsigned b0 = b_last;; b0 -= step) {   // the last ones are still in registers
-#pragma unroll
-    for (int i = 0; i < FIN_RECS; ++i)
-      if (q[i].w > 0.f) {                     // squared deviations of the block about the overall mean
-        const float s1n = q[i].y / q[i].w, d = q[i].x + s1n - mean;
-        m2 += q[i].z - q[i].y * s1n + q[i].w * d * d;
-      }
-    if (b0 == 0) break;
-    load(b0 - step);
+  publish(acc);
+  const float mean = FinAcc::sum(m, sh) / (float)M;
+  FinAcc dev;
+  for (unsigned b0 = 0;;) {
+    dev.add(m, [&](int i) {                   // squared deviations of the block about the overall mean
+      if (!(q[i].w > 0.f)) return 0.f;
+      const float s1n = q[i].y / q[i].w, d = q[i].x + s1n - mean;
+      return q[i].z - q[i].y * s1n + q[i].w * d * d;
+    });
+    b0 += step;
+    if (b0 >= nrows) break;
+    load(b0);
   }
-  m2 = total(m2);
-  if (on && j == 0) {
-    float var = m2 / (float)M;
+  publish(dev);
+  if (on && m.j == 0) {
+    float var = FinAcc::sum(m, sh) / (float)M;
     var = var > 0.f ? var : 0.f;
     out(c, mean, 1.0f / sqrtf(var + eps));
   }

@@ -11,8 +11,8 @@
 //           dx = gamma*invstd*(dz - dbeta/M - xhat*dgamma/M) (+ the skip gradient of an identity
 //           shortcut).
 // Reductions: per-thread partial sums -> cross-lane shuffles and LDS across the row groups of a
-// block -> one record per block in global memory.  The records are added up in a fixed order, so the result does not depend on
-// scheduling: in bf16 mode by every work-group of the kernel that consumes them, for its own 64 channels (one round trip
+// block -> one record per block in global memory.  The records are added up in a fixed order, the same one in every kernel that does it
+// (FinMap), so the result depends neither on scheduling nor on who adds: in bf16 mode by every work-group of the kernel that consumes them, for its own 64 channels (one round trip
 // instead of a launch of 4.7 us between two others; wide tensors with many records and the fp32 mode: by a launch of
 // its own).  A grid-wide "last block finishes" scheme was measured slower: its device-scope fence and atomic round
 // trips cost more than a kernel boundary.  The variance uses sums shifted by the first row's
@@ -208,6 +208,7 @@ __global__ __launch_bounds__(BN_THREADS) void k_bn_stats_finalize(int M, int C, 
 // second pass does not go back to memory (up to 128 tile rows: one memory round trip instead of a chain of them;
 // these launches sit between every convolution and its consumer, so their latency is on the critical path).
 constexpr int FINW_CH = 16, FINW_RG = BN_THREADS / FINW_CH, FIN_CACHE = 8;
+static_assert(FINW_RG == FIN_GROUPS, "records are added up in the same order as by the kernels that consume them");
 
 __device__ __forceinline__ float finw_sum(float v, float (*sh)[FINW_CH + 1], int cl, int j) {
   __syncthreads();
@@ -295,7 +296,7 @@ __global__ __launch_bounds__(BN_THREADS) void k_bn_bwd_finalize_wide(int C, unsi
   }
 }
 
-// The kernels that apply a BatchNorm on statistics of their own making: 64 channels per block (FIN_CG groups of 8), FIN_ROWS rows at a time
+// The kernels that apply a BatchNorm on statistics of their own making: 64 channels per block (FIN_CG groups of 8)
 constexpr int FIN_CG = 8;
 
 // {mean, invstd} of a thread's 8 channels.  BN_FROM_RECORDS: finalised by the block (all of its threads call this); the first block of its
@@ -306,7 +307,7 @@ struct BnStatsOf {
   __device__ __forceinline__ void load(const BnSource& src, int M, int C, const BnMap& m) {
     A* stats = (A*)pick(src.stats, blockIdx.z);
     if constexpr (SRC == BN_FROM_RECORDS) {
-      __shared__ float sh[BN_THREADS], fm[2][FIN_CG * 8];
+      __shared__ float sh[FIN_SH], fm[2][FIN_CG * 8];
       const int nch = C < FIN_CG * 8 ? C : FIN_CG * 8, c_base = blockIdx.y * FIN_CG * 8;
       bn_finalize_records((const float4*)pick(src.records, blockIdx.z), src.rows, C, c_base, nch, M, src.eps, sh, [&](int c, float mean, float is_) {
         fm[0][c - c_base] = mean;
@@ -334,29 +335,30 @@ struct BnSumsOf {
   A sb[8], sg[8];
   __device__ __forceinline__ void load(const BnBwdSums& src, int M, int C, int frozen, const BnMap& m) {
     if constexpr (FIN) {
-      __shared__ float sh[2][BN_THREADS], fs[2][FIN_CG * 8];
-      const int nch = C < FIN_CG * 8 ? C : FIN_CG * 8, c_base = blockIdx.y * FIN_CG * 8;
-      const int rg = BN_THREADS / nch, j = (int)threadIdx.x / nch, cl = (int)threadIdx.x - j * nch, c = c_base + cl;
+      __shared__ float sh[2][FIN_SH], fs[2][FIN_CG * 8];
+      const int c_base = blockIdx.y * FIN_CG * 8;
+      const FinMap f(C < FIN_CG * 8 ? C : FIN_CG * 8);
+      const int c = c_base + f.cl;
       const float2* __restrict__ p = (const float2*)pick(src.records, blockIdx.z);
-      float a1 = 0.f, a2 = 0.f;
-      const bool on = j < rg && c < C;
-      for (unsigned b0 = 0; b0 < src.rows; b0 += (unsigned)(FIN_RECS * rg)) {   // FIN_RECS records in flight together
+      FinAcc a1, a2;
+      const bool on = f.on && c < C;
+      for (unsigned b0 = 0; b0 < src.rows; b0 += (unsigned)(FIN_RECS * f.rg)) {   // FIN_RECS records in flight together
         float2 q[FIN_RECS];
 #pragma unroll
         for (int i = 0; i < FIN_RECS; ++i) {
-          const unsigned b = b0 + (unsigned)(j + i * rg);
+          const unsigned b = b0 + (unsigned)(f.j + i * f.rg);
           q[i] = on && b < src.rows ? p[(size_t)b * C + c] : make_float2(0.f, 0.f);
         }
-#pragma unroll
-        for (int i = 0; i < FIN_RECS; ++i) { a1 += q[i].x; a2 += q[i].y; }
+        a1.add(f, [&](int i) { return q[i].x; });
+        a2.add(f, [&](int i) { return q[i].y; });
       }
-      sh[0][threadIdx.x] = a1; sh[1][threadIdx.x] = a2;
+      a1.store(f, sh[0]);
+      a2.store(f, sh[1]);
       __syncthreads();
-      if ((int)threadIdx.x < nch && c < C) {
-        a1 = 0.f; a2 = 0.f;
-        for (int r = 0; r < rg; ++r) { a1 += sh[0][r * nch + cl]; a2 += sh[1][r * nch + cl]; }
-        fs[0][cl] = a1; fs[1][cl] = a2;
-        if (blockIdx.x == 0) { atomicAdd(&src.g_beta[c], a1); atomicAdd(&src.g_gamma[c], a2); }
+      if (f.j < 2 && c < C) {
+        const float t = FinAcc::sum(f, sh[f.j]);
+        fs[f.j][f.cl] = t;
+        if (blockIdx.x == 0) atomicAdd(&(f.j == 0 ? src.g_beta : src.g_gamma)[c], t);
       }
       __syncthreads();
       if (m.active) { load8a(fs[0] + m.c0 - c_base, sb); load8a(fs[1] + m.c0 - c_base, sg); }
@@ -789,17 +791,17 @@ dim3 apply_grid(int M, int C) {
 }
 
 // Whether the kernel that applies a BatchNorm adds up the records itself, which costs each of its blocks a round trip and up to 64 channels'
-// records, or a launch in front of it does (4.7 us, nearly all of it latency).  12 544 x 256, 25 rows of records: 8.1 against
-// 4.9 + 4.8 us (backward), 7.5 against 5.6 + 4.8 (forward); x 1024, 49 rows: 21.9 against 19.5 + 4.8; 13 images 32x32x64, 208 rows:
+// records, or a launch in front of it does (4.7 us, nearly all of it latency).  12 544 x 256, 25 rows of records: 6.9 against
+// 4.9 + 4.7 us (backward), 7.2 against 5.6 + 4.7 (forward); x 1024, 49 rows: 20.4 against 19.5 + 4.7; 13 images 32x32x64, 208 rows:
 // slower by 3 us.
 bool finalize_in_apply(unsigned rows, int C) { return (size_t)rows * (C < FIN_CG * 8 ? C : FIN_CG * 8) <= 4096; }
 
-// ... of the kernels that finalise the records themselves: 64 channels per block, and rows enough per block that a launch reads its
-// records about 2000 times
+// ... of the kernels that finalise the records themselves: 64 channels per block, and five blocks per CU, which is what their registers let
+// run together (at 2048 the last ones started on the records when the others were done with their rows: x 256 8.1, x 1024 21.7 us)
 dim3 finalize_grid(int M, int C, int ng) {
   const int CG = C / 8, CGB = CG < FIN_CG ? CG : FIN_CG, rpp = BN_THREADS / CGB, gy = (CG + CGB - 1) / CGB;
   int gx = (M + rpp - 1) / rpp;
-  const int cap = 2048 / (gy * ng);
+  const int cap = 1280 / (gy * ng);
   if (gx > cap) gx = cap < 1 ? 1 : cap;
   return dim3((unsigned)gx, (unsigned)gy, (unsigned)ng);
 }

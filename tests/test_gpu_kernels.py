@@ -191,3 +191,50 @@ def test_probe_mfma_loop_computes_the_product_it_claims(env, wide):
     assert np.abs(got - want).max() <= 1e-6 * np.abs(want).max()
     with pytest.raises(hpf.HpfError):
         hpf.hpf_probe_mfma_bf16(sink.data_ptr(), 0, 1)
+
+
+@pytest.mark.parametrize("c,h,w,b,fusion", [
+    (16, 32, 32, 4, 2), (16, 32, 32, 13, 2),       # 32 and 104 rows of records: 16 threads per channel
+    (32, 8, 8, 1, 2), (32, 32, 32, 8, 2),          # one row; as many as the consumer takes (two rounds of loads)
+    (48, 9, 7, 40, 2), (64, 32, 32, 2, 2),         # channels that divide no work-group; 64 rows, two rounds
+    (64, 32, 32, 3, 2),                            # 96 rows of 64 channels: a launch in front
+    (80, 16, 16, 4, 2), (256, 14, 14, 16, 2),      # a second slab of 16 channels; four slabs
+    (16, 32, 32, 4, 1), (32, 32, 32, 8, 1), (48, 16, 16, 4, 1), (80, 16, 16, 3, 1)])   # the convolution behind the BatchNorm finalises
+def test_records_are_added_up_in_one_order(env, c, h, w, b, fusion):
+    """The statistics and the backward sums of a BatchNorm do not depend on which kernel adds up the records: the same bits from
+    the kernel that consumes them as from a launch of its own (bn_relu_forward; the gradient of a unit's bias)."""
+    from paper_1911_05146_amd import workloads as W
+    hpf, torch = env
+    print(f"\n[case] {b}x{h}x{w}x{c} fusion={fusion}", flush=True)
+    gen = torch.Generator().manual_seed(c * h + b)
+    x = (torch.randn((b, h, w, c), generator=gen) + 0.5).to("cuda:0", torch.bfloat16)
+    dy = (0.1 * torch.randn((b, h, w, c), generator=gen)).to("cuda:0", torch.bfloat16)
+
+    def run(kind):
+        spec = W.PartitionSpec(name=f"unit-{kind}", in_h=h, in_w=w, in_c=c, blocks=(W.Block(kind, c, c, c, 1),), microbatch=b, num_microbatches=1)
+        params = np.random.default_rng(5).standard_normal(W.n_params(spec)).astype(np.float32) * 0.05
+        at = {}
+        for e in W.param_layout(spec):
+            at[e.name.split(".", 1)[1]] = slice(e.offset, e.offset + e.size)
+            if e.kind in ("gamma", "beta", "bias"):
+                params[e.offset:e.offset + e.size] = 1.0 if e.kind == "gamma" else 40.0   # every ReLU is active
+        part = hpf.Partition(spec, params)
+        try:
+            part.set_fusion(fusion)
+            y = part.forward_microbatch(0, x)
+            torch.cuda.synchronize()
+            st = part.stash_read(0, 0, hpf.HPF_T_STATS0) if kind != W.BIAS_RELU else None
+            part.backward_microbatch(0, dy)
+            g = part.grad_accum_read()
+        finally:
+            part.close()
+        return y, st, {k: g[v] for k, v in at.items()}
+
+    y, st, g = run(W.BN_RELU if fusion == 2 else W.BASIC)
+    one = torch.ones(c, device="cuda:0")
+    ref, ref_st = hpf.Ops().bn_relu_forward(x, one, 40.0 * one)
+    torch.cuda.synchronize()
+    assert np.array_equal(st, ref_st.double().cpu().numpy())
+    if fusion == 2:
+        assert torch.equal(y, ref)
+        assert np.array_equal(g["bn.beta"], run(W.BIAS_RELU)[2]["bias"])
