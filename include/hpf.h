@@ -201,11 +201,12 @@ hpf_status hpf_grad_accum_zero(hpf_partition* p, void* hip_stream);
  * refreshes the bf16 weight copies; clears G; starts the next batch.  Needs all backward calls. */
 hpf_status hpf_sgd_step(hpf_partition* p, float lr, float momentum, void* hip_stream);
 
-/* Long forward and backward kernel sequences of a call (96 launches and more) are captured into a HIP graph when the
- * call comes again with the caller pointers of the time before, and replayed as long as the pointers stay the same (the
- * default stream and streams that are already capturing always get plain launches).  Enabled by default; 0 switches
- * back to launching every kernel.  Shorter sequences always get plain launches: they leave the device no idle time and
- * need nothing prepared for new pointers. */
+/* HIP graphs of the kernel sequences of forward, backward and inference calls.  A sequence is captured when the call
+ * comes a second time in a row with the same caller pointers, and replayed as long as they stay the same; the default
+ * stream and streams that are already capturing always get plain launches.
+ * Without a call of this function a partition does so for sequences of 96 launches and more: shorter ones leave the
+ * device no idle time when launched plainly.  enable != 0: for every sequence of 8 launches and more, which costs the
+ * host less and the device a gap per call (for callers whose host is the limit).  enable == 0: never. */
 hpf_status hpf_partition_set_graphs(hpf_partition* p, int32_t enable);
 
 /* How far bf16 mode fuses the kernel schedule; the arithmetic is the same at every level, summation

@@ -677,11 +677,16 @@ struct GraphSlot {
 // Measured per batch, every call launched plainly / replayed: ResNet-110 partition 453 / 460 us, ResNet-1001 fine cut, ten
 // calls, 1382 / 1449, VGG-16 1668 / 1683, first batch on new buffers 1421 / 1581 and 1829 / 2038.  What a graph saves is
 // host time: ResNet-152 stage 3, 200 and 230 launches a call, 11.59 ms either way, of which the host is busy for 2.4 / 0.3 ms.
+// One thread that feeds several streams keeps ahead too: chains of four and eight partitions of ResNet-110, 64 and 128 calls a
+// batch, are done after 4.09 / 4.17 and 8.33 / 8.44 ms, the host after 2.8 / 2.4 and 4.7 / 4.4.
 constexpr int kMinGraphLaunches = 96;
+// Graphs asked for by hpf_partition_set_graphs(p, 1): for a caller whose host is what limits it (several streams fed by one thread, a host
+// with other work).  Below 8 launches a replay costs the host no less than the launches.
+constexpr int kMinGraphLaunchesAsked = 8;
 
 struct hpf_partition {
   Plan P;
-  bool use_graphs = true;
+  int min_graph_launches = kMinGraphLaunches;   // 0: no graphs
   // bf16 mode: 0 = every BatchNorm step a kernel of its own, 1 = BN reductions in the convolution epilogues and
   // normalisation in the consuming convolutions, 2 = additionally image-resident kernels for runs of identity
   // bottleneck blocks
@@ -1274,15 +1279,15 @@ hpf_status wait_all_backward(hpf_partition* p, hipStream_t s) {
 }
 
 // Runs `body` (kernel launches on stream s only), through a HIP graph where that is the better way: a long sequence that
-// is called again with the pointers of the call before (kMinGraphLaunches).  The sequences contain kernel nodes only.
+// is called again with the pointers of the call before (min_graph_launches).  The sequences contain kernel nodes only.
 // Launches go out one by one when graphs are off or the stream is already capturing.
 template <class Body>
 hpf_status run_graphed(hpf_partition* p, GraphSlot& slot, const std::vector<const void*>& key, hipStream_t s, Ctx& c, Body body) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   // the default (NULL) stream cannot be captured
-  const bool graphs = p->use_graphs && !p->profiling && s != nullptr && hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+  const bool graphs = p->min_graph_launches > 0 && !p->profiling && s != nullptr && hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
   const bool again = slot.key == key;
-  if (!graphs || !again || slot.launches < kMinGraphLaunches) {
+  if (!graphs || !again || slot.launches < p->min_graph_launches) {
     body();
     if (c.err != hipSuccess) return fail(HPF_EDEVICE, "%s: %s", c.where, hipGetErrorString(c.err));
     if (graphs && !again) {
@@ -1736,7 +1741,7 @@ hpf_status hpf_sgd_step(hpf_partition* p, float lr, float momentum, void* hip_st
 
 hpf_status hpf_partition_set_graphs(hpf_partition* p, int32_t enable) {
   if (!p) return fail(HPF_EINVAL, "null handle");
-  p->use_graphs = enable != 0;
+  p->min_graph_launches = enable ? kMinGraphLaunchesAsked : 0;
   return HPF_OK;
 }
 
