@@ -80,8 +80,8 @@ class Pipeline:
         self.streams = _streams_apart(torch, self.device, len(self.parts))
         self._keep = []
         # Boundary tensors of one batch, per partition and micro-batch: what it sends forward and the gradients it returns.
-        # Kept from batch to batch, so that a call meets the addresses its HIP graph was captured with.  A batch writes
-        # them again in the order of the streams: the forward of (p, i) follows p's backward of (p, i) in the batch
+        # Kept from batch to batch: nothing is allocated per batch, and no tensor is freed on one stream while another still
+        # works on it.  A batch writes them again in the order of the streams: the forward of (p, i) follows p's backward of (p, i) in the batch
         # before, which waited for every partition that had read the output; the backward of (p, i) follows p's forward,
         # which waited for those that had read its gradients and have gone on to this batch.
         def empty(shape, dtype):

@@ -62,3 +62,59 @@ def test_bottleneck_model_in_two_and_four_partitions(gpu, oracle):
     for n_parts, group in ((2, 1), (4, 2), (3, 4)):
         _run(oracle, "bottleneck-2stage", blocks, n_parts, 16, 64, 4, 4, 78, group=group)
     _run(oracle, "bottleneck-2stage-level1", blocks, 2, 16, 64, 4, 4, 78, group=1, fusion=1)
+
+
+def _pipe(kind):
+    from paper_1911_05146_amd import layer_cuts as LC
+    from paper_1911_05146_amd.pipeline import Pipeline, split_model
+    from test_gpu_layer_cuts import small_model
+    if kind == "cut":        # cuts inside blocks: shortcut values travel past the partitions in between
+        cm = LC.split_at_layers("cutnet", small_model(), [1, 2, 5, 7, 10, 13], 16, 16, 10, 4, 3, 91)
+        return Pipeline(cm.specs, W.make_inputs(cm.whole, randomize_affine=True).params, cut_model=cm), cm.whole
+    blocks = W.basic_resnet_blocks(3)
+    whole = W.partition_of("resnet20", list(blocks), 1, 0, 32, 16, 16, 10, 4, 4, 92)
+    return Pipeline(split_model("resnet20", blocks, 3, 32, 16, 10, 4, 4, 92), W.make_inputs(whole, randomize_affine=True).params, group=kind), whole
+
+
+def _batch_inputs(whole, seed):
+    import torch
+    gen = torch.Generator().manual_seed(seed)
+    shape = (whole.microbatch, whole.in_h, whole.in_w, whole.in_c)
+    return ([torch.randn(shape, generator=gen).to("cuda:0") for _ in range(whole.num_microbatches)],
+            [torch.randint(0, 10, (whole.microbatch,), generator=gen, dtype=torch.int32).to("cuda:0") for _ in range(whole.num_microbatches)])
+
+
+@pytest.mark.parametrize("late", [0, 1, -1])
+@pytest.mark.parametrize("kind", [1, 2, 4, "cut"])
+def test_batches_one_behind_the_other(gpu, kind, late):
+    """Four batches queued without waiting for the device, one partition's stream late: each has the loss and the gradients that it
+    has on a pipeline of its own, so no batch writes over a boundary tensor that the one before still reads."""
+    import torch
+    print(f"\n[case] {kind} late={late}", flush=True)
+    pipe, whole = _pipe(kind)
+    batches = [_batch_inputs(whole, 7 + k) for k in range(4)]
+    torch.cuda.synchronize()
+    got = []
+    for x, lab in batches:
+        with torch.cuda.stream(pipe.streams[late]):
+            torch.cuda._sleep(2_000_000)
+        pipe.run_batch(x, lab)
+        with torch.cuda.stream(pipe.streams[-1]):
+            loss = pipe.loss.clone()
+        g = []
+        for p, s in zip(pipe.parts, pipe.streams):
+            with torch.cuda.stream(s):
+                g.append(p.grad_accum_read(out=torch.empty(p.n_params, device="cuda:0"), stream=s))
+            p.grad_accum_zero(stream=s)
+        got.append((loss, g))
+    torch.cuda.synchronize()
+    pipe.close()
+    for (x, lab), (loss, g) in zip(batches, got):
+        one, _ = _pipe(kind)
+        one.run_batch(x, lab)
+        want = [p.grad_accum_read() for p in one.parts]
+        torch.cuda.synchronize()
+        assert abs(loss.item() - one.loss.item()) <= 1e-6 * abs(one.loss.item())
+        for a, b in zip(g, want):      # the same kernels on the same values: only the order of the fp32 atomics differs
+            assert np.linalg.norm(a.cpu().numpy() - b) <= 1e-5 * np.linalg.norm(b)
+        one.close()
