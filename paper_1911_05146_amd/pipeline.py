@@ -97,8 +97,9 @@ class Pipeline:
         return self.parts[-1].loss
 
     def run_batch(self, act_in, labels):
-        """Forward and backward of one batch: act_in / labels are lists of m device tensors.  Returns when all work
-        is queued; the gradients are complete after `synchronize()` / `grad_accum_read()`."""
+        """Forward and backward of one batch: act_in / labels are lists of m device tensors, written before or in the order
+        of `streams[0]` / `streams[-1]`.  Returns when all work is queued; the gradients are complete after
+        `synchronize()` / `grad_accum_read()`."""
         if self.cut is not None:
             return self._run_batch_cut(act_in, labels)
         torch, P, g = self.torch, len(self.parts), self.group
@@ -136,8 +137,14 @@ class Pipeline:
                 else:
                     part.backward_microbatches(unit[0], g, e_in, out, stream=s)
                 bwd_done[p][ui].record(s)
-        # the caller's tensors must outlive the queued work: those of the batch before are let go only now that this
-        # batch is queued behind it on the same streams
+        self._hold(act_in, labels)
+
+    def _hold(self, act_in, labels):
+        """The caller's tensors must outlive the queued work however far the host is ahead: torch's allocator is told which
+        streams use them.  Memory of another owner is at least referred to until the batch after next is queued."""
+        for tensors, s in ((act_in, self.streams[0]), (labels, self.streams[-1])):
+            for t in tensors:
+                t.record_stream(s)
         self._keep = [self._keep[-2:] if self._keep else None, act_in, labels]
 
     def _run_batch_cut(self, act_in, labels):
@@ -170,7 +177,7 @@ class Pipeline:
                     got[msg.tensor] = grads[msg.dst][i][msg.tensor]
                 part.backward_microbatch_cut(i, got["act"], got["skip"], grads[p][i]["act"], grads[p][i]["skip"], stream=s)
                 bwd_done[p][i].record(s)
-        self._keep = [self._keep[-2:] if self._keep else None, act_in, labels]
+        self._hold(act_in, labels)
 
     def synchronize(self):
         self.torch.cuda.synchronize(self.device)

@@ -118,3 +118,27 @@ def test_batches_one_behind_the_other(gpu, kind, late):
         for a, b in zip(g, want):      # the same kernels on the same values: only the order of the fp32 atomics differs
             assert np.linalg.norm(a.cpu().numpy() - b) <= 1e-5 * np.linalg.norm(b)
         one.close()
+
+
+@pytest.mark.parametrize("kind", [1, "cut"])
+def test_inputs_outlive_the_queued_work(gpu, kind):
+    """The caller's tensors are not given to anyone else while a queued batch may still read them."""
+    import torch
+    pipe, whole = _pipe(kind)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(pipe.streams[0]):
+        torch.cuda._sleep(300_000_000)
+        asleep = torch.cuda.Event()
+        asleep.record()
+    used = set()
+    for k in range(4):
+        x = [torch.empty((whole.microbatch, whole.in_h, whole.in_w, whole.in_c), device="cuda:0") for _ in range(whole.num_microbatches)]
+        lab = [torch.zeros(whole.microbatch, dtype=torch.int32, device="cuda:0") for _ in range(whole.num_microbatches)]
+        assert used.isdisjoint(t.data_ptr() for t in x + lab), f"batch {k} got memory of a queued batch"
+        used.update(t.data_ptr() for t in x + lab)
+        pipe.run_batch(x, lab)
+        for p, s in zip(pipe.parts, pipe.streams):
+            p.grad_accum_zero(stream=s)
+    assert not asleep.query(), "the device did not wait"
+    torch.cuda.synchronize()
+    pipe.close()
