@@ -267,3 +267,24 @@ def test_an_infinite_activation_reaches_its_neighbours_as_infinity(gpu, c, h, w)
             assert np.array_equal(np.isinf(y), np.broadcast_to(want[..., None], y.shape)), level
     finally:
         part.close()
+
+
+@pytest.mark.parametrize("mode", ["f32", "bf16"])
+@pytest.mark.parametrize("c,classes", [(12192, 24), (12208, 10), (16112, 16)])
+def test_logits_of_wide_heads(gpu, oracle, c, classes, mode):
+    """Channel counts around the one from which the kernel's LDS limit is raised, and the largest that is
+    taken.  Both sides add c products of fp32 values in different orders: rounding of 1e-7 times the square root of c."""
+    import torch
+    hpf = gpu
+    spec = W.PartitionSpec(name=f"head-{c}-{classes}", in_h=2, in_w=2, in_c=c, blocks=(), has_head=True, head_bn=False,
+                           num_classes=classes, microbatch=3, num_microbatches=1, seed=12)
+    inp = W.make_inputs(spec, randomize_affine=True)
+    act = parity.bf16_round(inp.act_in[0]) if mode == "bf16" else inp.act_in[0]
+    print(f"[case] {c} channels, {classes} classes, {mode}", flush=True)
+    part = hpf.Partition(spec, inp.params, hpf.HPF_BF16 if mode == "bf16" else hpf.HPF_F32)
+    opart = oracle.OraclePartition(spec, inp.params, np.float32, storage="bf16" if mode == "bf16" else "none")
+    got = part.forward_inference(torch.from_numpy(act).to("cuda:0", torch.bfloat16 if mode == "bf16" else torch.float32))
+    torch.cuda.synchronize()
+    assert parity.rel_err(got.cpu().numpy(), opart.infer(act)) <= 2e-5
+    part.close()
+    opart.close()

@@ -219,10 +219,12 @@ def test_head_only_and_stem_only_partitions(gpu, oracle, mode):
 
 
 @pytest.mark.parametrize("mode", ["f32", "bf16"])
-@pytest.mark.parametrize("kind,hw,c,classes", [(2, 1, 4096, 10), (2, 1, 2080, 16), (2, 3, 48, 17), (1, 32, 16, 2), (2, 1, 12000, 10)])
+@pytest.mark.parametrize("kind,hw,c,classes", [(2, 1, 4096, 10), (2, 1, 2080, 16), (2, 3, 48, 17), (1, 32, 16, 2), (2, 1, 12000, 10),
+                                               (2, 1, 12192, 24), (2, 1, 12208, 10), (2, 1, 16112, 16)])
 def test_head_shapes(gpu, oracle, mode, kind, hw, c, classes):
     """The pool's slices (more and fewer pixels than slices, channel groups that divide nothing, more than one pass over the
-    channels), both forms of the logits, and channel counts that take the kernels' LDS beyond 64 KiB."""
+    channels), both forms of the logits, and channel counts around the one from which the kernels' LDS (c + classes + 4168
+    floats) is more than 64 KiB: the last that is not, the first that is, and the largest that is taken."""
     spec = W.PartitionSpec(name=f"head-{kind}-{hw}-{c}-{classes}", in_h=hw, in_w=hw, in_c=c, blocks=(), has_head=True,
                            head_bn=kind == 1, num_classes=classes, microbatch=3, num_microbatches=2, seed=11)
     check(oracle, spec, mode, strict=True)
