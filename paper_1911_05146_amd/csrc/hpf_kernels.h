@@ -293,9 +293,9 @@ struct BnRunDesc { unsigned long long stats_off; int C; int run_off; };   // sta
 // After a training forward: for the group's members in order, r <- momentum*r + (1-momentum)*{mean, 1/invstd^2 - eps}.
 hipError_t launch_bn_running_update(int dt, int g, const PtrTab& bases, const BnRunDesc* table_dev, int n_bn, float* running,
                                     float momentum, float eps, hipStream_t stream);
-// Inference: stats = {running mean, 1/sqrt(running variance + eps)}.
-hipError_t launch_bn_running_stats(int dt, int g, const PtrTab& stats, const float* running_mean_var, int C, float eps,
-                                   hipStream_t stream);
+// Inference in fp32 mode: stats = {running mean, 1/sqrt(running variance + eps)} (double).  In bf16 mode the kernels that apply a BatchNorm read
+// the running statistics themselves.
+hipError_t launch_bn_running_stats(int g, const PtrTab& stats, const float* running_mean_var, int C, float eps, hipStream_t stream);
 
 // Stem: fp32 image [b,H,W,Cin] -> bf16 im2col columns [b*H*W, Kc], k = (r*3+s)*Cin + c, zero padded.
 hipError_t launch_im2col3x3(int g, const PtrTab& img, const PtrTab& col, int b, int H, int W, int Cin, int Kc,

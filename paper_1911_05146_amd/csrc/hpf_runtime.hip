@@ -810,7 +810,7 @@ struct Ctx {
     if (inference && P.dt == DT_BF16) {
       src.running = h->running() + bn.run_off;
     } else if (inference) {
-      chk(launch_bn_running_stats(P.dt, g, src.stats, h->running() + bn.run_off, bn.C, P.d.bn_eps, s), "bn_running_stats");
+      chk(launch_bn_running_stats(g, src.stats, h->running() + bn.run_off, bn.C, P.d.bn_eps, s), "bn_running_stats");
     } else if (P.d.bn_mode != 0) {
       chk(launch_bn_frozen_stats(P.dt, g, src.stats, bn.C, P.d.bn_eps, s), "bn_frozen_stats");
     } else if (P.dt == DT_BF16) {

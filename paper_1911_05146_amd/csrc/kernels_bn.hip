@@ -526,11 +526,10 @@ __global__ __launch_bounds__(256) void k_bn_running_update(PtrTab bases, const B
   }
 }
 
-template <class A>
 __global__ void k_bn_running_stats(PtrTab statss, const float* __restrict__ running, int C, float eps) {
-  A* stats = (A*)pick(statss, blockIdx.z);
+  double* stats = (double*)pick(statss, blockIdx.z);
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < C) { stats[c] = (A)running[c]; stats[C + c] = rsqrt_exact((A)running[C + c] + (A)eps); }
+  if (c < C) { stats[c] = (double)running[c]; stats[C + c] = rsqrt_exact((double)running[C + c] + (double)eps); }
 }
 
 
@@ -899,11 +898,9 @@ hipError_t launch_bn_running_update(int dt, int ng, const PtrTab& bases, const B
   return hipGetLastError();
 }
 
-hipError_t launch_bn_running_stats(int dt, int ng, const PtrTab& stats, const float* running_mean_var, int C, float eps,
-                                   hipStream_t stream) {
+hipError_t launch_bn_running_stats(int ng, const PtrTab& stats, const float* running_mean_var, int C, float eps, hipStream_t stream) {
   const dim3 grid((unsigned)((C + 255) / 256), 1, (unsigned)ng);
-  if (dt == DT_BF16) k_bn_running_stats<float><<<grid, 256, 0, stream>>>(stats, running_mean_var, C, eps);
-  else k_bn_running_stats<double><<<grid, 256, 0, stream>>>(stats, running_mean_var, C, eps);
+  k_bn_running_stats<<<grid, 256, 0, stream>>>(stats, running_mean_var, C, eps);
   return hipGetLastError();
 }
 
