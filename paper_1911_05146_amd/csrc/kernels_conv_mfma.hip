@@ -822,9 +822,11 @@ int conv_mfma_tile_rows(int ng, const ConvGeom& g) {
   return t == 0 || t == 4 ? 128 : 64;
 }
 
-// A launch of its own for the finalize step costs 4.5 us, all of it latency; every work-group doing it costs one round trip and
-// reads rows * Cs records, so up to 64 KiB per work-group (the transitions of the CIFAR ResNets: 4 to 52 KiB) it is the faster way.
-bool conv_takes_records(int ng, const ConvGeom& g, unsigned rows) { return pick_tile(ng, g) != 4 && rows * (size_t)g.Cs <= 4096; }
+// A launch of its own for the finalize step costs 4.7 us, nearly all of it latency.  Done by every work-group it costs the convolution a round trip
+// per 64 channels, one after the other, and rows * Cs records to read.  3x3, 16 / 32 / 64 channels: 1024 records + 1.2 / 1.0 / 1.0 us,
+// 4096 + 4.0 / 3.0 / 3.1, 8192 + 8.8 / 6.7 / 6.4 (64 to 512 work-groups); 1x1 out of 128 channels, 1024 + 2.8, 4096 + 3.6; out of 192 + 4.5
+// whatever the records, out of 256 + 5.6, 512 + 11, 1024 + 21.
+bool conv_takes_records(int ng, const ConvGeom& g, unsigned rows) { return pick_tile(ng, g) != 4 && g.Cs <= 128 && rows * (size_t)g.Cs <= 4096; }
 
 int conv_splitk(int ng, const ConvGeom& g) {
   if (g.N % 16 != 0 || g.Cs % 8 != 0 || g.Kpad % KC != 0) return 1;
