@@ -9,6 +9,7 @@ Host logic only: every tensor operation is a call into the C-ABI library through
 """
 from __future__ import annotations
 
+import os
 from typing import List, Optional, Sequence
 
 from . import hpf
@@ -23,21 +24,29 @@ def split_model(name: str, blocks: Sequence[W.Block], n_parts: int, in_hw: int, 
                            microbatch, num_microbatches, seed) for p in range(n_parts)]
 
 
-_HW_QUEUES = 4   # hardware queues that the runtime deals a process's streams to (its default)
+def _hw_queues():
+    """Hardware queues that the runtime deals a process's streams to: GPU_MAX_HW_QUEUES, by default 4."""
+    try:
+        return max(1, int(os.environ.get("GPU_MAX_HW_QUEUES", "")))
+    except ValueError:
+        return 4
 
 
 def _streams_apart(torch, device, n):
-    """n streams, each on a hardware queue of its own as long as there are enough of them.  Work of two streams that share a
-    queue runs one after the other: four partitions of ResNet-110 took 5.1 ms per batch on four queues and 7.5 to 12.5 ms
-    where two or more shared one.  The runtime gives a stream the queue that the fewest streams hold when it is first
-    used: after a few streams all queues are held by equally many, and from then on consecutive ones get different queues."""
-    streams = [torch.cuda.Stream(device) for _ in range(_HW_QUEUES + n)]
+    """n streams, placed so that they share hardware queues as little as can be had from here.  Work of two streams that
+    share a queue runs one after the other: four partitions of ResNet-110 took 5.1 ms per batch on four queues and 7.5 to
+    12.5 ms where two or more shared one; results are the same.  The runtime gives a stream the queue that the fewest
+    streams hold when it is first used: after as many streams as there are queues all are held by equally many, and from
+    then on consecutive ones get different queues.  Not guaranteed: torch deals streams out of a pool of 32, and those that
+    the program has used before keep the queue they have."""
+    first = _hw_queues()
+    streams = [torch.cuda.Stream(device) for _ in range(first + n)]
     word = torch.empty(1, device=device)
     for s in streams:
         with torch.cuda.stream(s):
             word.zero_()
     torch.cuda.synchronize(device)
-    return streams[_HW_QUEUES:]
+    return streams[first:]
 
 
 class Pipeline:

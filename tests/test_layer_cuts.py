@@ -206,3 +206,29 @@ def test_invalid_cut_descriptions_are_rejected(oracle):
                 replace(good, in_c=4)):
         with pytest.raises(ValueError):
             oracle.OraclePartition(bad, np.zeros(64, np.float32))
+
+
+@pytest.mark.parametrize("set_to, queues", [(None, 4), ("2", 2), ("8", 8), ("", 4), ("all", 4), ("0", 1)])
+def test_streams_of_a_pipeline_follow_as_many_used_ones_as_there_are_hardware_queues(monkeypatch, set_to, queues):
+    """A stream gets the queue that the fewest hold when it is first used: every queue is held before the pipeline's own are made."""
+    from contextlib import nullcontext
+    from types import SimpleNamespace
+    from paper_1911_05146_amd import pipeline
+    made, used = [], []
+
+    class Word:
+        def zero_(self):
+            used.append(current[-1])
+
+    current = []
+
+    def stream(s):
+        current.append(s)
+        return nullcontext()
+    cuda = SimpleNamespace(Stream=lambda device: made.append(len(made)) or made[-1], stream=stream, synchronize=lambda device: None)
+    if set_to is None:
+        monkeypatch.delenv("GPU_MAX_HW_QUEUES", raising=False)
+    else:
+        monkeypatch.setenv("GPU_MAX_HW_QUEUES", set_to)
+    got = pipeline._streams_apart(SimpleNamespace(cuda=cuda, empty=lambda n, device: Word()), "device", 3)
+    assert got == [queues, queues + 1, queues + 2] and used == made == list(range(queues + 3))
