@@ -798,9 +798,11 @@ hipError_t launch_tile(int mode, int ng, const PtrTab& src, const bf16_t* wpk, c
 
 // 0: 128x128, 1: 64x64, 2: 64x32, 3: 64x16, 4: 128x128 with 64-element steps on 8 waves
 constexpr int BIG_MIN_K = 256;        // reductions from here on count as wide for the choice of what is written to memory
-// The 8-wave tile pays a fixed 8 us per work-group (pipeline fill, epilogue through LDS) and runs one work-group
-// per CU: with four reduction steps (K = 256) the 64x64 tiles, five work-groups per CU, are faster (1x1 256 -> 1024
-// on 12 544 rows: 22.8 us against 27.8 us); from eight steps on the wide tile wins (K = 512: 11.6 against 14.7 us).
+// The 8-wave tile pays a fixed 8 us per work-group (pipeline fill, epilogue through LDS) and runs one work-group per CU; of the
+// 64x64 tile four share a CU (36 KiB of LDS each) and hide each other's.  1x1 convolutions, 64x64 / 8-wave tile, us: K = 256, 12 544 rows
+// into 1024 channels 24.0 / 29.3, into 128 7.0 / 8.4, 1568 rows into 1024 7.0 / 8.6; K = 512, 12 544 rows into 256 14.5 / 12.6, 3136 into
+// 1024 13.9 / 12.0.  This rule does not look at the number of tiles: with 100 of them and fewer the 64x64 tile is the faster one
+// at K = 512 too (12 544 rows into 128 9.6 / 11.1, 3136 into 256 7.9 / 10.6).
 constexpr int BIG_MIN_K_TILE = 512;
 int pick_tile(int ng, const ConvGeom& g) {
   if (big_tile_fits(g) && g.Kpad >= BIG_MIN_K_TILE) return 4;
