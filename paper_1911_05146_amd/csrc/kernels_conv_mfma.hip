@@ -15,7 +15,7 @@
 // lane groups of a wave cover 16 consecutive channels = 32 contiguous bytes per pixel.
 //
 // Work-group: 256 threads = 4 waves arranged WR x WC over a BM (pixels) x BN (channels) tile;
-// K advances 64 per step (32 in the 128-row tile), double-buffered in LDS with one barrier per step and the
+// K advances 64 per step (32 in the 128-row tile and where K is short), double-buffered in LDS with one barrier per step and the
 // next steps' global loads in flight during the MFMAs.
 #include <mutex>
 
@@ -218,7 +218,10 @@ __device__ __forceinline__ void conv_epilogue(floatx4 (&acc)[CT][PT], int wr, in
 // channels at 8x8 13.4 -> 10.0 us (two forms of it 13.2 -> 11.5 and 11.1 -> 7.9), 64 -> 32 gradient at 16x16 12.0 -> 10.7; 1x1
 // 256 -> 1024 on 12 544 rows 34.5 -> 30.9.  Four chunks in flight instead of two: no faster (ResNet-20 439 against 433 us per
 // batch), and a work-group less per CU (35.8).
-template <int BM, int BN, int WR, int WC, int MODE, int EPI, int PRO>
+// SHORT: reductions of up to SHORT_K elements are five steps of 32 at most, all of them in flight from the start, in 20 instead of 36 KiB of LDS (eight
+// instead of four work-groups per CU, and no half-empty last step).  1x1 on 50 176 rows, steps of 64 / SHORT, us: 32 -> 128 channels 9.7 / 8.1,
+// 128 -> 512 31.9 / 25.7, behind a BatchNorm 53 / 42, 160 -> 512 36.0 / 30.1; 3x3 16 -> 16 5.8 / 5.1; on 784 rows 64 -> 256 4.2 / 3.7, 16 -> 16 4.2 / 3.7.
+template <int BM, int BN, int WR, int WC, int KS, int MODE, int EPI, int PRO>
 __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __restrict__ wpk, PtrTab outs, PtrTab adds,
                                                    ConvGeom g, ConvEpi epi, ConvPro pro) {
   extern __shared__ float2 coef[];   // PRO: per source channel {scale, shift}
@@ -228,7 +231,8 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
   static_assert(WR * WC == 4, "4 waves");
   constexpr int WPX = BM / WR, WCH = BN / WC, PT = WPX / 16, CT = WCH / 16;
   static_assert(PT >= 1 && CT >= 1, "tile too small");
-  constexpr int KS = BM == 64 ? 64 : 32, UPR = KS / 8, RPP = 256 / UPR;   // reduction elements per step, 16-byte units per row, rows per pass of the threads
+  constexpr int UPR = KS / 8, RPP = 256 / UPR;   // KS: reduction elements per step; 16-byte units per row, rows per pass of the threads
+  constexpr bool SHORT = BM == 64 && KS == 32;   // the whole reduction, up to SHORT_K elements, is in flight at once
   constexpr int LSTR = KS + 8;       // LDS row stride in bf16 (144 or 80 bytes: conflict-free 16-byte reads)
   constexpr int A_UNITS = BM / RPP;
   static_assert(A_UNITS >= 1, "BM >= 64");
@@ -258,12 +262,12 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
     if (m >= g.M) a_h[u] = -(1 << 20);   // a row outside every image
   }
 
-  // NPRE chunks are kept in flight in registers.  Every load is issued unconditionally (outside the image, the tensor or the reduction
+  // NPRE chunks are kept in flight in registers (SHORT: all there are).  Every load of a chunk is issued unconditionally (outside the image, the tensor or the reduction
   // it reads a clamped address and is zeroed when it is stored to LDS; past the last chunk the last one is loaded again), so
   // the number of outstanding loads is known at every wait.
   constexpr int NPRE = 2;
   struct Slot { uint4 a[A_UNITS]; uint4 w[W_UNITS]; int c; bool av[A_UNITS], wv; };
-  Slot sl0, sl1;   // named, not an array: they must stay in registers
+  Slot sl0, sl1, sl2, sl3, sl4;   // named, not an array: they must stay in registers (SHORT: all five)
   if (PRO) {
     if (pro.rows) {
       float* stt = (float*)pick(pro.stats, blockIdx.z);
@@ -337,13 +341,16 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
     for (int j = 0; j < PT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   load_chunk(sl0);
-  load_chunk(sl1);
+  if (!SHORT || nk > 1) load_chunk(sl1);
+  if (SHORT && nk > 2) load_chunk(sl2);
+  if (SHORT && nk > 3) load_chunk(sl3);
+  if (SHORT && nk > 4) load_chunk(sl4);
   store_chunk(0, sl0);
   __syncthreads();
   const int frag_row = lane & 15, frag_k = (lane >> 4) * 8;
-  // one step: its chunk is in LDS buffer `buf` and its register slot `cur` is free again; `nxt` holds the chunk behind it
-  auto step = [&](int buf, Slot& cur, const Slot& nxt) {
-    load_chunk(cur);
+  // one step: its chunk is in LDS buffer `buf` and its register slot `cur` is free again; `nxt` holds the chunk behind it (more: there is one)
+  auto step = [&](int buf, Slot& cur, const Slot& nxt, bool more) {
+    if (!SHORT) load_chunk(cur);
     bf16x8 fa[KS / KC][PT], fw[KS / KC][CT];
 #pragma unroll
     for (int h = 0; h < KS / KC; ++h) {
@@ -354,7 +361,7 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
       for (int i = 0; i < CT; ++i)
         fw[h][i] = *reinterpret_cast<const bf16x8*>(&sW[buf][(wc * WCH + i * 16 + frag_row) * LSTR + h * KC + frag_k]);
     }
-    store_chunk(buf ^ 1, nxt);
+    if (!SHORT || more) store_chunk(buf ^ 1, nxt);
 #pragma unroll
     for (int h = 0; h < KS / KC; ++h)
 #pragma unroll
@@ -364,12 +371,20 @@ __global__ __launch_bounds__(256) void k_conv_mfma(PtrTab srcs, const bf16_t* __
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[h][i], fa[h][j], acc[i][j], 0, 0, 0);
     __syncthreads();
   };
-  int kc0 = 0;
-  for (; kc0 + NPRE <= nk; kc0 += NPRE) {
-    step(0, sl0, sl1);
-    step(1, sl1, sl0);
+  if (SHORT) {
+    step(0, sl0, sl1, nk > 1);
+    if (nk > 1) step(1, sl1, sl2, nk > 2);
+    if (nk > 2) step(0, sl2, sl3, nk > 3);
+    if (nk > 3) step(1, sl3, sl4, nk > 4);
+    if (nk > 4) step(0, sl4, sl4, false);
+  } else {
+    int kc0 = 0;
+    for (; kc0 + NPRE <= nk; kc0 += NPRE) {
+      step(0, sl0, sl1, true);
+      step(1, sl1, sl0, true);
+    }
+    if (kc0 < nk) step(0, sl0, sl1, true);
   }
-  if (kc0 < nk) step(0, sl0, sl1);
 
   static_assert((BN + WR * BN * 2) * 4 <= (int)sizeof(sA), "epilogue scratch fits the staging buffer");
   conv_epilogue<BM, BN, WR, WC, PT, CT, EPI>(acc, wr, wc, blockIdx.x, row0, ch0, reinterpret_cast<float*>(&sA[0][0]), g, epi, add, out);
@@ -774,13 +789,13 @@ hipError_t launch_big(int mode, int ng, const PtrTab& src, const bf16_t* wpk, co
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WR, int WC>
+template <int BM, int BN, int WR, int WC, int KS>
 hipError_t launch_tile(int mode, int ng, const PtrTab& src, const bf16_t* wpk, const PtrTab& out, const PtrTab& add,
                        const ConvGeom& g, hipStream_t stream, const ConvEpi& epi, const ConvPro& pro) {
   const dim3 grid((unsigned)((g.M + BM - 1) / BM), (unsigned)(g.N / BN), (unsigned)ng);
   const size_t dyn = pro.on ? (size_t)g.Cs * sizeof(float2) : 0;
 #define HPF_CONV(MODE_, EPI_, PRO_) \
-  k_conv_mfma<BM, BN, WR, WC, MODE_, EPI_, PRO_><<<grid, 256, dyn, stream>>>(src, wpk, out, add, g, epi, pro)
+  k_conv_mfma<BM, BN, WR, WC, KS, MODE_, EPI_, PRO_><<<grid, 256, dyn, stream>>>(src, wpk, out, add, g, epi, pro)
   if (mode == CONV_FWD) {
     if (epi.kind == EPI_STATS) { if (pro.on) HPF_CONV(CONV_FWD, EPI_STATS, 1); else HPF_CONV(CONV_FWD, EPI_STATS, 0); }
     else if (epi.kind == EPI_NONE) { if (pro.on) HPF_CONV(CONV_FWD, EPI_NONE, 1); else HPF_CONV(CONV_FWD, EPI_NONE, 0); }
@@ -804,6 +819,7 @@ constexpr int BIG_MIN_K = 256;        // reductions from here on count as wide f
 // 1024 13.9 / 12.0.  This rule does not look at the number of tiles: with 100 of them and fewer the 64x64 tile is the faster one
 // at K = 512 too (12 544 rows into 128 9.6 / 11.1, 3136 into 256 7.9 / 10.6).
 constexpr int BIG_MIN_K_TILE = 512;
+constexpr int SHORT_K = 160;
 int pick_tile(int ng, const ConvGeom& g) {
   if (big_tile_fits(g) && g.Kpad >= BIG_MIN_K_TILE) return 4;
   // the 128x128 tile pays off through operand reuse over a long reduction; short reductions are
@@ -874,10 +890,16 @@ hipError_t launch_conv_mfma(int mode, int ng, const PtrTab& src, const bf16_t* w
   if (g.N % 16 != 0 || g.Cs % 8 != 0 || g.Kpad % KC != 0 || (g.stride != 1 && g.stride != 2)) return hipErrorInvalidValue;
   switch (pick_tile(ng, g)) {
     case 4: return launch_big(mode, ng, src, wpk, out, add, g, stream, epi, pro);
-    case 0: return launch_tile<128, 128, 2, 2>(mode, ng, src, wpk, out, add, g, stream, epi, pro);
-    case 1: return launch_tile<64, 64, 2, 2>(mode, ng, src, wpk, out, add, g, stream, epi, pro);
-    case 2: return launch_tile<64, 32, 4, 1>(mode, ng, src, wpk, out, add, g, stream, epi, pro);
-    default: return launch_tile<64, 16, 4, 1>(mode, ng, src, wpk, out, add, g, stream, epi, pro);
+    case 0: return launch_tile<128, 128, 2, 2, 32>(mode, ng, src, wpk, out, add, g, stream, epi, pro);
+    case 1:
+      return g.Kpad <= SHORT_K ? launch_tile<64, 64, 2, 2, 32>(mode, ng, src, wpk, out, add, g, stream, epi, pro)
+                               : launch_tile<64, 64, 2, 2, 64>(mode, ng, src, wpk, out, add, g, stream, epi, pro);
+    case 2:
+      return g.Kpad <= SHORT_K ? launch_tile<64, 32, 4, 1, 32>(mode, ng, src, wpk, out, add, g, stream, epi, pro)
+                               : launch_tile<64, 32, 4, 1, 64>(mode, ng, src, wpk, out, add, g, stream, epi, pro);
+    default:
+      return g.Kpad <= SHORT_K ? launch_tile<64, 16, 4, 1, 32>(mode, ng, src, wpk, out, add, g, stream, epi, pro)
+                               : launch_tile<64, 16, 4, 1, 64>(mode, ng, src, wpk, out, add, g, stream, epi, pro);
   }
 }
 

@@ -239,3 +239,29 @@ def test_records_are_added_up_in_one_order(env, c, h, w, b, fusion):
     if fusion == 2:
         assert torch.equal(y, ref)
         assert np.array_equal(g["bn.beta"], run(W.BIAS_RELU)[2]["bias"])
+
+
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("cin,R", [(c, 1) for c in (16, 32, 48, 64, 96, 128, 144, 160, 176, 192)] + [(16, 3), (32, 3)])
+def test_reductions_of_a_few_steps(env, cin, R, stride):
+    """Every number of steps on both sides of the one up to which a reduction is in flight as a whole, all three channel tiles, forward and
+    data gradient, against float64 on the same bf16 values: fp32 sums, rounded to bf16 once."""
+    hpf, torch = env
+    ops = ops_for(hpf, "bf16")
+    gen = torch.Generator().manual_seed(cin + R)
+    for cout in (16, 32, 64, 80, 128):
+        for b, h, w in ((1, 2, 2), (3, 6, 10)):
+            print(f"\n[case] {b}x{h}x{w} {cin} -> {cout} R={R} stride={stride}", flush=True)
+            x = torch.randn((b, h, w, cin), generator=gen).to(torch.bfloat16)
+            wt = (torch.randn((R, R, cin, cout), generator=gen) * 0.1).to(torch.bfloat16).float()
+            dy = torch.randn((b, h // stride, w // stride, cout), generator=gen).to(torch.bfloat16)
+            y = ops.conv_forward(x.cuda(), wt.cuda(), stride=stride)
+            dx = ops.conv_dgrad(dy.cuda(), wt.cuda(), (h, w), stride=stride)
+            torch.cuda.synchronize()
+            xr = x.double().permute(0, 3, 1, 2).requires_grad_()
+            yr = torch.nn.functional.conv2d(xr, wt.double().permute(3, 2, 0, 1), stride=stride, padding=R // 2)
+            yr.backward(dy.double().permute(0, 3, 1, 2))
+            for got, ref in ((y, yr.detach()), (dx, xr.grad)):
+                got, ref = got.double().cpu(), ref.permute(0, 2, 3, 1)
+                # half a bf16 step, and the fp32 sum of at most 1152 products
+                assert bool(((got - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-5 * ref.abs().max()).all())

@@ -145,6 +145,7 @@ def test_pipelines_of_partitions_equal_the_unsplit_model(gpu, oracle, model, n_p
     (W.Block(W.CONV_RELU, 16, 16, 16, 1), 9, 16, 3),          # 64 x 16 tile, a last tile of 51 rows
     (W.Block(W.CONV_RELU, 16, 32, 32, 2), 8, 16, 3),          # 64 x 32, with the max-pool behind it
     (W.Block(W.CONV_RELU, 32, 64, 64, 1), 7, 32, 5),          # 64 x 64
+    (W.Block(W.CONV_RELU, 16, 64, 64, 1), 7, 16, 5),          # 64 x 64, five steps of 32
     (W.Block(W.CONV_RELU, 64, 128, 128, 2), 16, 64, 7),      # 128 x 128, whole reduction in one work-group
     (W.Block(W.CONV_RELU, 128, 128, 128, 1), 3, 128, 4),      # 128 x 128, reduction split, 36 rows
     (W.Block(W.DENSE, 1024, 1, 128, 1), 1, 1024, 5),           # split, with ReLU

@@ -75,6 +75,18 @@ def test_statistics_from_records_layerwise(gpu, oracle, blk, hw, fusion, images,
     layerwise(oracle, spec, "bf16", grouped=grouped, fusion=fusion, blockwise=False)
 
 
+@pytest.mark.parametrize("fusion", [0, 1])
+@pytest.mark.parametrize("blk,hw", [(W.Block(W.BOTTLENECK, 160, 128, 64, 1), 10),    # five and four steps of 32 behind a BatchNorm, with and without statistics behind
+                                    (W.Block(W.BOTTLENECK, 96, 48, 192, 2), 14),     # three, two; a projection of three
+                                    (W.Block(W.BOTTLENECK, 192, 160, 192, 1), 6),    # six (steps of 64) and five, identity shortcut
+                                    (W.Block(W.BASIC, 16, 16, 16, 1), 12)])          # 3x3 in five
+def test_short_reductions_layerwise(gpu, oracle, blk, hw, fusion):
+    """Reductions that are in flight as a whole, with the BatchNorm in front, the statistics, the sums of a backward pass and the residual."""
+    spec = W.PartitionSpec(name=f"short-{blk.c_in}-{blk.c_mid}-{blk.c_out}", in_h=hw, in_w=hw, in_c=blk.c_in, blocks=(blk,),
+                           microbatch=3, num_microbatches=2, seed=37)
+    layerwise(oracle, spec, "bf16", grouped=True, fusion=fusion, blockwise=False)
+
+
 @pytest.mark.parametrize("images,micro", [(1, 1), (3, 3), (1, 8), (4, 7)])
 def test_weight_gradients_of_several_classes_in_one_launch_layerwise(gpu, oracle, images, micro):
     """Five tile classes and the whole-image one, few items each: one launch whose micro-batches go to work-groups in even and odd shares."""
