@@ -843,8 +843,12 @@ int conv_mfma_tile_rows(int ng, const ConvGeom& g) {
 // A launch of its own for the finalize step costs 4.7 us, nearly all of it latency.  Done by every work-group it costs the convolution a round trip
 // per 64 channels, one after the other, and rows * Cs records to read.  3x3, 16 / 32 / 64 channels: 1024 records + 1.2 / 1.0 / 1.0 us,
 // 4096 + 4.0 / 3.0 / 3.1, 8192 + 8.8 / 6.7 / 6.4 (64 to 512 work-groups); 1x1 out of 128 channels, 1024 + 2.8, 4096 + 3.6; out of 192 + 4.5
-// whatever the records, out of 256 + 5.6, 512 + 11, 1024 + 21.
-bool conv_takes_records(int ng, const ConvGeom& g, unsigned rows) { return pick_tile(ng, g) != 4 && g.Cs <= 128 && rows * (size_t)g.Cs <= 4096; }
+// whatever the records, out of 256 + 5.6, 512 + 11, 1024 + 21.  More work-groups than a chip holds at four per CU pay for it one after the
+// other: 1x1 out of 32 / 64 / 128 channels, 1024 of them + 0.9 / 1.5 / 3.4, 2048 + 3.5 / 4.5 / 8.3; 1568 of them out of 128 + 7.9.
+bool conv_takes_records(int ng, const ConvGeom& g, unsigned rows) {
+  const int t = pick_tile(ng, g), bm = t == 0 ? 128 : 64, bn = t == 0 ? 128 : t == 1 ? 64 : t == 2 ? 32 : 16;
+  return t != 4 && g.Cs <= 128 && rows * (size_t)g.Cs <= 4096 && (size_t)((g.M + bm - 1) / bm) * (g.N / bn) * ng <= 1024;
+}
 
 int conv_splitk(int ng, const ConvGeom& g) {
   if (g.N % 16 != 0 || g.Cs % 8 != 0 || g.Kpad % KC != 0) return 1;

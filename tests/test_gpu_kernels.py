@@ -200,7 +200,8 @@ def test_probe_mfma_loop_computes_the_product_it_claims(env, wide):
     (64, 32, 32, 3, 2),                            # 96 rows of 64 channels: a launch in front
     (80, 16, 16, 4, 2), (256, 14, 14, 16, 2),      # a second slab of 16 channels; four slabs
     (16, 32, 32, 4, 1), (32, 32, 32, 8, 1), (48, 16, 16, 4, 1), (80, 16, 16, 3, 1),   # the convolution behind the BatchNorm finalises
-    (112, 8, 8, 8, 1), (128, 8, 8, 32, 1), (144, 8, 8, 4, 1), (256, 8, 8, 4, 1)])   # in two slabs; more than 128 channels: a launch in front
+    (112, 8, 8, 8, 1), (128, 8, 8, 32, 1), (144, 8, 8, 4, 1), (256, 8, 8, 4, 1),   # in two slabs; more than 128 channels: a launch in front
+    (16, 32, 32, 64, 1), (16, 32, 32, 65, 1)])   # 1024 work-groups, and more
 def test_records_are_added_up_in_one_order(env, c, h, w, b, fusion):
     """The statistics and the backward sums of a BatchNorm do not depend on which kernel adds up the records: the same bits from
     the kernel that consumes them as from a launch of its own (bn_relu_forward; the gradient of a unit's bias)."""
