@@ -789,6 +789,17 @@ dim3 apply_grid(int M, int C) {
   return dim3((unsigned)gx, (unsigned)((CG + CGB - 1) / CGB));
 }
 
+// ... of the kernels that take running statistics: every thread computes the invstd of its channels (the square roots and divisions of eight are
+// the work of about seven rows), so five blocks per CU, each with many rows.  A block per BN_THREADS units took 53 us for 1024 channels x 50 176
+// rows and 19.6 for 64 x 262 144, now 32 and 13.2 (a launch in front of it that writes invstd: 33.4 and 14.5, and 4.2 for the launch).
+dim3 running_grid(int M, int C, int ng) {
+  dim3 g = apply_grid(M, C);
+  const unsigned cap = 1280u / (g.y * (unsigned)ng);
+  if (g.x > cap) g.x = cap < 1 ? 1 : cap;
+  g.z = (unsigned)ng;
+  return g;
+}
+
 // Whether the kernel that applies a BatchNorm adds up the records itself, which costs each of its blocks a round trip and up to 64 channels'
 // records, or a launch in front of it does (4.7 us, nearly all of it latency).  12 544 x 256, 25 rows of records: 6.9 against
 // 4.9 + 4.7 us (backward), 7.2 against 5.6 + 4.7 (forward); x 1024, 49 rows: 20.4 against 19.5 + 4.7; 13 images 32x32x64, 208 rows:
@@ -845,7 +856,7 @@ hipError_t launch_bn_apply_relu(int dt, int ng, const PtrTab& x, const PtrTab& a
   dim3 grid = apply_grid(M, C);
   grid.z = (unsigned)ng;
   if (dt != DT_BF16) k_bn_apply_relu<float, double, BN_FROM_STATS><<<grid, BN_THREADS, 0, stream>>>(x, a, gamma, beta, src, M, C);
-  else if (src.running) k_bn_apply_relu<bf16_t, float, BN_FROM_RUNNING><<<grid, BN_THREADS, 0, stream>>>(x, a, gamma, beta, src, M, C);
+  else if (src.running) k_bn_apply_relu<bf16_t, float, BN_FROM_RUNNING><<<running_grid(M, C, ng), BN_THREADS, 0, stream>>>(x, a, gamma, beta, src, M, C);
   else if (src.rows && finalize_in_apply(src.rows, C)) k_bn_apply_relu<bf16_t, float, BN_FROM_RECORDS><<<finalize_grid(M, C, ng), BN_THREADS, 0, stream>>>(x, a, gamma, beta, src, M, C);
   else {
     if (src.rows) k_bn_stats_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(M, C, src.rows, src.eps, src.records, src.stats);
@@ -954,7 +965,7 @@ hipError_t launch_bn_add_relu_apply(int dt, int ng, const PtrTab& x, const PtrTa
   dim3 grid = apply_grid(M, C);
   grid.z = (unsigned)ng;
   if (dt != DT_BF16) k_bn_add_relu_apply<float, double, BN_FROM_STATS><<<grid, BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, src, M, C);
-  else if (src.running) k_bn_add_relu_apply<bf16_t, float, BN_FROM_RUNNING><<<grid, BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, src, M, C);
+  else if (src.running) k_bn_add_relu_apply<bf16_t, float, BN_FROM_RUNNING><<<running_grid(M, C, ng), BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, src, M, C);
   else if (src.rows && finalize_in_apply(src.rows, C)) k_bn_add_relu_apply<bf16_t, float, BN_FROM_RECORDS><<<finalize_grid(M, C, ng), BN_THREADS, 0, stream>>>(x, add, y, gamma, beta, src, M, C);
   else {
     if (src.rows) k_bn_stats_finalize_wide<<<finw(C, ng), BN_THREADS, 0, stream>>>(M, C, src.rows, src.eps, src.records, src.stats);

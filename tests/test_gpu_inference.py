@@ -288,3 +288,28 @@ def test_logits_of_wide_heads(gpu, oracle, c, classes, mode):
     assert parity.rel_err(got.cpu().numpy(), opart.infer(act)) <= 2e-5
     part.close()
     opart.close()
+
+
+@pytest.mark.parametrize("c,hw,b,m", [(16, 5, 3, 2), (16, 64, 41, 1), (64, 32, 11, 3), (272, 16, 37, 2), (1024, 14, 16, 8)])
+def test_running_statistics_applied_in_a_pass_of_their_own(gpu, c, hw, b, m):
+    """Fewer blocks than the chip holds and more rows than they take at a time, channels that divide no block: relu(bn(x)) against float64,
+    rounded to bf16 once."""
+    import torch
+    hpf = gpu
+    spec = W.PartitionSpec(name=f"bn-{c}", in_h=hw, in_w=hw, in_c=c, blocks=(W.Block(W.BN_RELU, c, c, c, 1),), microbatch=b, num_microbatches=m, seed=5)
+    rng = np.random.default_rng(c)
+    params = rng.standard_normal(W.n_params(spec)).astype(np.float32)
+    run = np.concatenate([rng.standard_normal(c), rng.uniform(0.1, 4.0, c)]).astype(np.float32)
+    print(f"[case] {m} x {b}x{hw}x{hw}x{c}", flush=True)
+    part = hpf.Partition(spec, params)
+    part.bn_running_write(run)
+    x = [torch.randn((b, hw, hw, c), device="cuda:0").to(torch.bfloat16) for _ in range(m)]
+    y = part.forward_inference_group(x)
+    torch.cuda.synchronize()
+    at = {e.kind: torch.from_numpy(params[e.offset:e.offset + e.size]).double().cuda() for e in W.param_layout(spec)}
+    mean, var = (torch.from_numpy(v).double().cuda() for v in (run[:c], run[c:]))
+    for a, got in zip(x, y):
+        pre = at["gamma"] * ((a.double() - mean) / torch.sqrt(var + spec.bn_eps)) + at["beta"]
+        # half a bf16 step of the result, and the roundings of the fp32 terms
+        assert bool(((got.double() - pre.clamp(min=0)).abs() <= pre.abs() * 2.0 ** -8 + 1e-5).all())
+    part.close()
