@@ -109,6 +109,7 @@ struct Plan {
   Loc g_stem;                          // gradient w.r.t. the stem output
   int t9_h = 0, t9_w = 0;                          // image shape of the whole-convolution weight-gradient items (class 10)
   std::vector<WgradItem> items[WGRAD_CLASSES];     // deferred weight-gradient work, per tile class (bf16 mode)
+  int wg_rows[WGRAD_CLASSES] = {}, wg_nr_rows[WGRAD_CLASSES] = {};   // pixel rows of the longest item; nr: without resident runs
   std::vector<WgradItem> items_nr[WGRAD_CLASSES];  // the same without the blocks of image-resident runs (those have a launch of their own)
   size_t items_nr_off[WGRAD_CLASSES] = {};
   double wg_nr_bytes[WGRAD_CLASSES] = {}, wg_nr_flops[WGRAD_CLASSES] = {};
@@ -612,6 +613,8 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
         it.g = q; it.tap = tap; it.c0 = c0; it.n0 = n0;
         it.m_begin = m_begin; it.m_end = m_end;
         (pass ? P.items_nr : P.items)[cls].push_back(it);
+        int& longest = (pass ? P.wg_nr_rows : P.wg_rows)[cls];
+        if (m_end - m_begin > longest) longest = m_end - m_begin;
       };
       if (cls == WGRAD_CLASS_T9) {   // whole images per item; about 1000 work-groups (two per CU at 67 KiB of LDS, twice over)
         int parts = (int)((1024 + tiles_in_class[cls] - 1) / tiles_in_class[cls]);
@@ -1242,6 +1245,7 @@ void run_backward(Ctx& c) {
     for (int k = 0; k < WGRAD_CLASSES; ++k) {
       l.n[k] = (int)(res ? P.items_nr : P.items)[k].size();
       if (l.n[k] == 0) continue;
+      l.rows[k] = (res ? P.wg_nr_rows : P.wg_rows)[k];
       l.items[k] = (const WgradItem*)(c.h->arena + (res ? P.items_nr_off : P.items_off)[k]);
       bytes += (res ? P.wg_nr_bytes : P.wg_bytes)[k];
       flops += (res ? P.wg_nr_flops : P.wg_flops)[k];

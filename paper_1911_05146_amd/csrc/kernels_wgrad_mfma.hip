@@ -606,6 +606,20 @@ int wgrad_class_lds(int cls, int t9_lds) {
   return cls < 9 ? generic[cls] : cls == 9 ? WgradTile<128, 128, 64>::QUAD_BYTES : t9_lds;
 }
 
+// What a launch of few items is made of: a work-group takes wgrad_item_us for its item and each of its micro-batches (the latency of the
+// steps; a 64-row step of the quadrant kernel, a 128-row step of the others, an image), and every share of the micro-batches adds all
+// output elements with atomics, ATOMICS_PER_US of them (256 per ns, from launches of 63 and 252 items).  More shares end the first sooner and pay
+// the second more often.  63 items of 64 x 64 over 8 micro-batches: 14.1 us in one share, 9.4 in four (taken), 13.3 in eight; of 128 x 128
+// over 8 31, 22.2 in two (taken), 40; over 4 19.2, 16.5 in two (taken), 23; 252 of them over 4 25.4 in one (taken), 32 in two.
+constexpr double ATOMICS_PER_US = 256e3;
+double wgrad_item_us(int cls, int rows) {
+  if (cls == WGRAD_CLASS_T9) return 4.0 * ((rows + T9_P - 1) / T9_P);
+  if (cls == 9) return 1.5 * ((rows + 63) / 64);
+  const int bc = 16 << cls / 3, bn = 16 << cls % 3;
+  return (bc == 64 || bn == 64 ? 1.25 : 0.9) * ((rows + 127) / 128);
+}
+int wgrad_item_sums(int cls) { return cls == WGRAD_CLASS_T9 ? 9 * 256 : cls == 9 ? 128 * 128 : (16 << cls / 3) * (16 << cls % 3); }
+
 template <int BC, int BN>
 hipError_t launch_tile(int ng, const PtrTab& a, const PtrTab& dy, float* dw, const WgradGeom& g, hipStream_t stream) {
   const int tiles = g.R * g.R * (g.Cin / BC) * (g.N / BN);
@@ -684,27 +698,36 @@ hipError_t launch_wgrad_grouped(const WgradLaunch& l, int ng, const PtrTab& regi
   static const int order[WGRAD_CLASSES] = {WGRAD_CLASS_T9, 9, 8, 7, 5, 6, 2, 4, 3, 1, 0};
   WgradClassList list{};
   int total = 0, lds = 0;
+  double longest = 0, sums = 0;   // us of the longest item for a micro-batch; output elements of all items
   for (int k : order)
     if (l.n[k] > 0 && l.n[k] <= MERGE_ITEMS) {
       list.items[list.n] = l.items[k]; list.first[list.n] = total; list.cls[list.n] = k;
       ++list.n;
       total += l.n[k];
       lds = std::max(lds, wgrad_class_lds(k, l.t9_lds));
+      longest = std::max(longest, wgrad_item_us(k, l.rows[k]));
+      sums += (double)l.n[k] * wgrad_item_sums(k);
     }
-  if (list.n > 0) {
-    // micro-batches to work-groups of their own as long as the launch does not fill the chip (two work-groups per CU)
-    const int gy = std::min(ng, std::max(1, MERGE_WGS / total));
+  int gy = 1;   // shares of the micro-batches: work-groups of their own as long as the launch does not fill the chip (two work-groups per CU)
+  for (int t = 2; t <= std::min(ng, MERGE_WGS / std::max(total, 1)); ++t) {
+    auto us = [&](int shares) { return (ng + shares - 1) / shares * longest + shares * sums / ATOMICS_PER_US; };
+    if (us(t) < us(gy)) gy = t;
+  }
+  // in the kernel of its class, below: 72 items of 128 x 128 11.7 against 12.8 us
+  const bool alone = list.n == 1 && gy == 1;
+  if (list.n > 0 && !alone) {
     k_wgrad_merged<<<dim3((unsigned)total, (unsigned)gy), 256, (size_t)lds, stream>>>(list, w);
     ++*n_launches;
   }
+  auto own = [&](int k) { return l.n[k] > MERGE_ITEMS || (alone && list.cls[0] == k); };
 #define HPF_WG(CLS, BC, BN) \
-  if (l.n[CLS] > MERGE_ITEMS) { k_wgrad_grouped<BC, BN><<<l.n[CLS], 256, 0, stream>>>(l.items[CLS], w); ++*n_launches; }
+  if (own(CLS)) { k_wgrad_grouped<BC, BN><<<l.n[CLS], 256, 0, stream>>>(l.items[CLS], w); ++*n_launches; }
   HPF_WG(0, 16, 16) HPF_WG(1, 16, 32) HPF_WG(2, 16, 64)
   HPF_WG(3, 32, 16) HPF_WG(4, 32, 32) HPF_WG(5, 32, 64)
   HPF_WG(6, 64, 16) HPF_WG(7, 64, 32) HPF_WG(8, 64, 64)
 #undef HPF_WG
-  if (l.n[9] > MERGE_ITEMS) { k_wgrad_grouped_quad<<<l.n[9], 256, WgradTile<128, 128, 64>::QUAD_BYTES, stream>>>(l.items[9], w); ++*n_launches; }
-  if (l.n[WGRAD_CLASS_T9] > MERGE_ITEMS) {   // all items of the class have one image shape (checked by the planner): the LDS size comes with the call
+  if (own(9)) { k_wgrad_grouped_quad<<<l.n[9], 256, WgradTile<128, 128, 64>::QUAD_BYTES, stream>>>(l.items[9], w); ++*n_launches; }
+  if (own(WGRAD_CLASS_T9)) {   // all items of the class have one image shape (checked by the planner): the LDS size comes with the call
     k_wgrad_grouped_t9<<<l.n[WGRAD_CLASS_T9], 256, (size_t)l.t9_lds, stream>>>(l.items[WGRAD_CLASS_T9], w);
     ++*n_launches;
   }

@@ -164,6 +164,15 @@ def test_lds_tile_resident_runs_layerwise(gpu, oracle, kind, c, mid, h, w, image
     layerwise(oracle, spec, "bf16", blockwise=False)
 
 
+@pytest.mark.parametrize("kind,c,hw,images,micro", [(W.CONV_RELU, 256, 7, 4, 2), (W.CONV_RELU, 64, 10, 2, 1), (W.CONV_RELU, 16, 32, 2, 1),   # a class in its own kernel
+                                                    (W.CONV_RELU, 128, 7, 4, 7), (W.CONV_RELU, 64, 10, 2, 7), (W.DENSE, 512, 1, 5, 8)])   # in two, four shares
+def test_weight_gradients_of_one_class_layerwise(gpu, oracle, kind, c, hw, images, micro):
+    """One tile class with few items: in the kernel of the class, or its micro-batches dealt to work-groups in shares that do not divide them."""
+    spec = W.PartitionSpec(name=f"class-{kind}-{c}", in_h=hw, in_w=hw, in_c=c, blocks=(W.Block(kind, c, c if kind != W.DENSE else 1, c, 1),),
+                           microbatch=images, num_microbatches=micro, seed=31)
+    layerwise(oracle, spec, "bf16", grouped=True, fusion=1, blockwise=False)
+
+
 @pytest.mark.parametrize("kind,c,mid,h,w,images",
                          [(W.BASIC, 64, 64, 12, 8, 5), (W.POSTACT, 64, 64, 8, 8, 6),             # two and four images at a time, the last batch not full
                           (W.BASIC, 32, 32, 4, 16, 9), (W.BOTTLENECK, 128, 32, 4, 16, 3),        # fewer images than fit a batch
