@@ -273,24 +273,26 @@ __global__ __launch_bounds__(256) void k_copy16(u32x4* __restrict__ dst, const u
 }
 
 // bf16 operand copies of the convolution weights; STEP: behind the SGD step, which then needs no pass of its own (28 bytes per weight
-// instead of 24 + 12, and one launch).  grid (n_convs, Y): the Y blocks of a convolution share its 64 x 64 tiles of the fp32 master
+// instead of 24 + 12, and one launch).  grid (Y, n_convs): the Y blocks of a convolution share its 64 x 64 tiles of the fp32 master
 // [k = tap*Cin + c][n] round-robin.  A tile is updated as it is loaded, and both copies are written from LDS with 16-byte stores: the
 // forward one is its transpose, the data-gradient one takes its rows.  Channel counts and offsets are multiples of 16 (the stem's Cin
 // excepted).  Parameters that are no convolution weights follow the convolution in front of them (rest_*; the first also the ones before it).
-// ResNet-20 (0.27 M parameters): 4.5 + 25 us as two launches with a serial data-gradient copy, now 5.8; VGG-16 (33.6 M): 129 + 77, now 155.
+// The blocks of a convolution are consecutive, so they go to all dies: with the convolutions in x a matrix stayed on the dies that x mod 8 gave it
+// (the last quarter of VGG-16, 16.8 of 23.6 M weights in one of four matrices: 197 us, now 95).
+// ResNet-20 (0.27 M parameters): 4.5 + 25 us as two launches with a serial data-gradient copy, now 5.8; VGG-16 (33.6 M): 129 + 77, now 143.
 template <bool STEP>
 __global__ __launch_bounds__(256) void k_sgd_pack(float* __restrict__ params, float* __restrict__ mom, float* __restrict__ grads,
                                                   bf16_t* __restrict__ packed, const PackDesc* __restrict__ table, float lr, float mu,
                                                   const int* __restrict__ invalid) {
   if (STEP && invalid && *invalid) return;
   __shared__ float tile[64][65];
-  const PackDesc d = table[blockIdx.x];
+  const PackDesc d = table[blockIdx.y];
   const int tid = threadIdx.x;
   if (STEP) {
     for (int part = 0; part < 2; ++part) {
       const size_t off = part ? d.rest_off : 0;
       const int len = part ? d.rest_len : d.first_len;
-      for (int i = blockIdx.y * 256 + tid; i < len; i += gridDim.y * 256) {
+      for (int i = blockIdx.x * 256 + tid; i < len; i += gridDim.x * 256) {
         const float vel = fmaf(mu, mom[off + i], grads[off + i]);
         mom[off + i] = vel;
         params[off + i] = fmaf(-lr, vel, params[off + i]);
@@ -300,7 +302,7 @@ __global__ __launch_bounds__(256) void k_sgd_pack(float* __restrict__ params, fl
   }
   const int ktot = d.T * d.Cin, tk = (d.Kf + 63) / 64, tn = (d.Cout + 63) / 64;
   bf16_t* wf = packed + d.wf_off;  // [Cout][Kf], k = tap*Cin + c
-  for (int t = blockIdx.y; t < tk * tn; t += gridDim.y) {
+  for (int t = blockIdx.x; t < tk * tn; t += gridDim.x) {
     const int k0 = (t / tn) * 64, n0 = (t % tn) * 64;
     __syncthreads();
     {
@@ -438,23 +440,26 @@ hipError_t launch_zero_f32(float* p, size_t n, hipStream_t stream) {
 }
 
 namespace {
+constexpr int MAX_GRID_Y = 65535;
 // blocks per convolution: one per tile of the largest one (blocks with nothing to do leave at once)
 dim3 pack_grid(int n_convs, size_t max_elems) {
   const size_t y = (max_elems + 4095) / 4096;
-  return dim3((unsigned)n_convs, (unsigned)(y < 8 ? 8 : (y > 1024 ? 1024 : y)));
+  return dim3((unsigned)(y < 8 ? 8 : (y > 1024 ? 1024 : y)), (unsigned)(n_convs < MAX_GRID_Y ? n_convs : MAX_GRID_Y));
 }
 }  // namespace
 
 hipError_t launch_pack_weights(const float* params, bf16_t* packed, const PackDesc* table_dev, int n_convs, size_t max_elems,
                                hipStream_t stream) {
   if (n_convs <= 0) return hipSuccess;
-  k_sgd_pack<false><<<pack_grid(n_convs, max_elems), 256, 0, stream>>>(const_cast<float*>(params), nullptr, nullptr, packed, table_dev, 0.f, 0.f, nullptr);
+  for (int c = 0; c < n_convs; c += MAX_GRID_Y)
+    k_sgd_pack<false><<<pack_grid(n_convs - c, max_elems), 256, 0, stream>>>(const_cast<float*>(params), nullptr, nullptr, packed, table_dev + c, 0.f, 0.f, nullptr);
   return hipGetLastError();
 }
 
 hipError_t launch_sgd_pack(float* params, float* mom, float* grads, bf16_t* packed, const PackDesc* table_dev, int n_convs, size_t max_elems,
                            float lr, float mu, const int* invalid, hipStream_t stream) {
-  k_sgd_pack<true><<<pack_grid(n_convs, max_elems), 256, 0, stream>>>(params, mom, grads, packed, table_dev, lr, mu, invalid);
+  for (int c = 0; c < n_convs; c += MAX_GRID_Y)
+    k_sgd_pack<true><<<pack_grid(n_convs - c, max_elems), 256, 0, stream>>>(params, mom, grads, packed, table_dev + c, lr, mu, invalid);
   return hipGetLastError();
 }
 

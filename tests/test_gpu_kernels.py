@@ -266,3 +266,35 @@ def test_reductions_of_a_few_steps(env, cin, R, stride):
                 got, ref = got.double().cpu(), ref.permute(0, 2, 3, 1)
                 # half a bf16 step, and the fp32 sum of at most 1152 products
                 assert bool(((got - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-5 * ref.abs().max()).all())
+
+
+@pytest.mark.parametrize("blocks", [((512, 16, 1),), ((16, 528, 9), (528, 16, 9), (16, 48, 9)), ((64, 64, 9),) * 5 + ((64, 1040, 9),)])
+def test_update_and_packed_copies_of_matrices_of_different_sizes(env, blocks):
+    """The step with momentum against its formula, and the copies that the convolutions read: a batch on the updated partition gives what one
+    made from the updated parameters gives."""
+    from paper_1911_05146_amd import workloads as W
+    hpf, torch = env
+    print(f"\n[case] {blocks}", flush=True)
+    hw = 1 if blocks[0][2] == 1 else 4
+    spec = W.PartitionSpec(name="sgd", in_h=hw, in_w=hw, in_c=blocks[0][0], microbatch=2, num_microbatches=1,
+                           blocks=tuple(W.Block(W.DENSE, i, 1, o, 1) if t == 1 else W.Block(W.CONV_RELU, i, o, o, 1) for i, o, t in blocks))
+    rng = np.random.default_rng(3)
+    params = (0.1 * rng.standard_normal(W.n_params(spec))).astype(np.float32)
+    gen = torch.Generator().manual_seed(1)
+    part = hpf.Partition(spec, params)
+    x = torch.randn(part.in_shape, generator=gen).to("cuda:0", torch.bfloat16)
+    dy = torch.randn(part.out_shape, generator=gen).to("cuda:0", torch.bfloat16)
+    p, v = params.copy(), np.zeros_like(params)
+    for _ in range(2):
+        part.forward_microbatch(0, x)
+        part.backward_microbatch(0, dy)
+        v = np.float32(0.9) * v + part.grad_accum_read()
+        p = p - np.float32(1e-3) * v
+        part.sgd_step(1e-3, 0.9)
+    got = part.params_read()
+    assert np.abs(got - p).max() <= 1e-6 * np.abs(p).max()          # fused multiply-adds: a rounding each
+    fresh = hpf.Partition(spec, got)
+    assert torch.equal(part.forward_microbatch(0, x), fresh.forward_microbatch(0, x))
+    assert torch.equal(part.backward_microbatch(0, dy), fresh.backward_microbatch(0, dy))
+    part.close()
+    fresh.close()
