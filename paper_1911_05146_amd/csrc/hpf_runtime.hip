@@ -9,6 +9,7 @@
 // the previous partition.  Units: [stem conv] + pre-activation residual blocks + [head].
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -109,7 +110,8 @@ struct Plan {
   Loc g_stem;                          // gradient w.r.t. the stem output
   int t9_h = 0, t9_w = 0;                          // image shape of the whole-convolution weight-gradient items (class 10)
   std::vector<WgradItem> items[WGRAD_CLASSES];     // deferred weight-gradient work, per tile class (bf16 mode)
-  int wg_rows[WGRAD_CLASSES] = {}, wg_nr_rows[WGRAD_CLASSES] = {};   // pixel rows of the longest item; nr: without resident runs
+  // pixel rows of the longest item and most items that add to one output element; nr: without resident runs
+  int wg_rows[WGRAD_CLASSES] = {}, wg_nr_rows[WGRAD_CLASSES] = {}, wg_adds[WGRAD_CLASSES] = {}, wg_nr_adds[WGRAD_CLASSES] = {};
   std::vector<WgradItem> items_nr[WGRAD_CLASSES];  // the same without the blocks of image-resident runs (those have a launch of their own)
   size_t items_nr_off[WGRAD_CLASSES] = {};
   double wg_nr_bytes[WGRAD_CLASSES] = {}, wg_nr_flops[WGRAD_CLASSES] = {};
@@ -616,11 +618,13 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
         int& longest = (pass ? P.wg_nr_rows : P.wg_rows)[cls];
         if (m_end - m_begin > longest) longest = m_end - m_begin;
       };
+      int& adds = (pass ? P.wg_nr_adds : P.wg_adds)[cls];
       if (cls == WGRAD_CLASS_T9) {   // whole images per item; about 1000 work-groups (two per CU at 67 KiB of LDS, twice over)
         int parts = (int)((1024 + tiles_in_class[cls] - 1) / tiles_in_class[cls]);
         if (parts > q.b) parts = q.b;
         const int imgs = (q.b + parts - 1) / parts, px = q.H * q.W;
         for (int i0 = 0; i0 < q.b; i0 += imgs) item(0, 0, 0, i0 * px, (i0 + imgs < q.b ? i0 + imgs : q.b) * px);
+        adds = std::max(adds, (q.b + imgs - 1) / imgs);
         continue;
       }
       // Items of equal length: a class may mix convolutions with few tiles over many pixel rows and ones with many
@@ -634,6 +638,7 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
       if (splits < 1) splits = 1;
       const int rows = ((q.M + splits - 1) / splits + 127) / 128 * 128;
       splits = (q.M + rows - 1) / rows;
+      adds = std::max(adds, splits);
       for (int tap = 0; tap < w.R * w.R; ++tap)
         for (int c0 = 0; c0 < w.cin_run; c0 += bc)
           for (int n0 = 0; n0 < cv.cout; n0 += bn)
@@ -1246,6 +1251,7 @@ void run_backward(Ctx& c) {
       l.n[k] = (int)(res ? P.items_nr : P.items)[k].size();
       if (l.n[k] == 0) continue;
       l.rows[k] = (res ? P.wg_nr_rows : P.wg_rows)[k];
+      l.adds[k] = (res ? P.wg_nr_adds : P.wg_adds)[k];
       l.items[k] = (const WgradItem*)(c.h->arena + (res ? P.items_nr_off : P.items_off)[k]);
       bytes += (res ? P.wg_nr_bytes : P.wg_bytes)[k];
       flops += (res ? P.wg_nr_flops : P.wg_flops)[k];

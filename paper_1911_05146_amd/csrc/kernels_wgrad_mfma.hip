@@ -611,7 +611,8 @@ int wgrad_class_lds(int cls, int t9_lds) {
 // output elements with atomics, ATOMICS_PER_US of them (256 per ns, from launches of 63 and 252 items).  More shares end the first sooner and pay
 // the second more often.  63 items of 64 x 64 over 8 micro-batches: 14.1 us in one share, 9.4 in four (taken), 13.3 in eight; of 128 x 128
 // over 8 31, 22.2 in two (taken), 40; over 4 19.2, 16.5 in two (taken), 23; 252 of them over 4 25.4 in one (taken), 32 in two.
-constexpr double ATOMICS_PER_US = 256e3;
+// Additions to one element follow each other (18 ns): the stem of 64 images, 128 items that add to the same 27 x 16, 8.1 us in one share (taken), 15.4 in four.
+constexpr double ATOMICS_PER_US = 256e3, SAME_ADDRESS_US = 0.018;
 double wgrad_item_us(int cls, int rows) {
   if (cls == WGRAD_CLASS_T9) return 4.0 * ((rows + T9_P - 1) / T9_P);
   if (cls == 9) return 1.5 * ((rows + 63) / 64);
@@ -699,6 +700,7 @@ hipError_t launch_wgrad_grouped(const WgradLaunch& l, int ng, const PtrTab& regi
   WgradClassList list{};
   int total = 0, lds = 0;
   double longest = 0, sums = 0;   // us of the longest item for a micro-batch; output elements of all items
+  int adds = 0;
   for (int k : order)
     if (l.n[k] > 0 && l.n[k] <= MERGE_ITEMS) {
       list.items[list.n] = l.items[k]; list.first[list.n] = total; list.cls[list.n] = k;
@@ -707,10 +709,11 @@ hipError_t launch_wgrad_grouped(const WgradLaunch& l, int ng, const PtrTab& regi
       lds = std::max(lds, wgrad_class_lds(k, l.t9_lds));
       longest = std::max(longest, wgrad_item_us(k, l.rows[k]));
       sums += (double)l.n[k] * wgrad_item_sums(k);
+      adds = std::max(adds, l.adds[k]);
     }
   int gy = 1;   // shares of the micro-batches: work-groups of their own as long as the launch does not fill the chip (two work-groups per CU)
   for (int t = 2; t <= std::min(ng, MERGE_WGS / std::max(total, 1)); ++t) {
-    auto us = [&](int shares) { return (ng + shares - 1) / shares * longest + shares * sums / ATOMICS_PER_US; };
+    auto us = [&](int shares) { return (ng + shares - 1) / shares * longest + shares * (sums / ATOMICS_PER_US + adds * SAME_ADDRESS_US); };
     if (us(t) < us(gy)) gy = t;
   }
   // in the kernel of its class, below: 72 items of 128 x 128 11.7 against 12.8 us

@@ -165,7 +165,8 @@ def test_lds_tile_resident_runs_layerwise(gpu, oracle, kind, c, mid, h, w, image
 
 
 @pytest.mark.parametrize("kind,c,hw,images,micro", [(W.CONV_RELU, 256, 7, 4, 2), (W.CONV_RELU, 64, 10, 2, 1), (W.CONV_RELU, 16, 32, 2, 1),   # a class in its own kernel
-                                                    (W.CONV_RELU, 128, 7, 4, 7), (W.CONV_RELU, 64, 10, 2, 7), (W.DENSE, 512, 1, 5, 8)])   # in two, four shares
+                                                    (W.CONV_RELU, 128, 7, 4, 7), (W.CONV_RELU, 64, 10, 2, 7), (W.DENSE, 512, 1, 5, 8),   # in two, four shares
+                                                    (W.CONV_RELU, 16, 24, 16, 3)])   # many items that add to one tile
 def test_weight_gradients_of_one_class_layerwise(gpu, oracle, kind, c, hw, images, micro):
     """One tile class with few items: in the kernel of the class, or its micro-batches dealt to work-groups in shares that do not divide them."""
     spec = W.PartitionSpec(name=f"class-{kind}-{c}", in_h=hw, in_w=hw, in_c=c, blocks=(W.Block(kind, c, c if kind != W.DENSE else 1, c, 1),),
