@@ -1156,7 +1156,7 @@ __device__ __forceinline__ void add_bn_param_grads(const ResWgArgs& a, unsigned 
 
 // grid: (image groups, items, blocks of the run).  Items: conv1 in chunks of 64 input channels, conv3 in chunks of 64 output channels (1x1);
 // conv2 (3x3).  One launch for both where MID is 32; with 64 the 3x3 item holds 72 sums per lane, and in a launch of their own the 1x1 items
-// run two work-groups per CU instead of one (21 blocks 128-64, 256 images: 455 us together, 233 + 134 apart).
+// run two work-groups per CU instead of one (21 blocks 128-64, 256 images: 455 us together, 233 + 134 apart; few images: launch_resident_wgrad).
 enum : int { WG_ALL = 0, WG_1X1 = 1, WG_3X3 = 2 };
 template <int C, int MID, int PART>
 __global__ void __launch_bounds__(rw_threads(MID), PART == WG_1X1 ? 4 : 2) k_res_wgrad(const ResWgArgs a) {
@@ -2551,7 +2551,8 @@ hipError_t resident_prepare() {
   for (const void* f : bb)
     if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_wgrad<128, 32, WG_ALL>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  for (const void* f : {reinterpret_cast<const void*>(k_res_wgrad<256, 64, WG_1X1>), reinterpret_cast<const void*>(k_res_wgrad<256, 64, WG_3X3>),
+  for (const void* f : {reinterpret_cast<const void*>(k_res_wgrad<128, 64, WG_ALL>), reinterpret_cast<const void*>(k_res_wgrad<256, 64, WG_ALL>),
+                        reinterpret_cast<const void*>(k_res_wgrad<256, 64, WG_1X1>), reinterpret_cast<const void*>(k_res_wgrad<256, 64, WG_3X3>),
                         reinterpret_cast<const void*>(k_res_wgrad<128, 64, WG_1X1>), reinterpret_cast<const void*>(k_res_wgrad<128, 64, WG_3X3>)})
     if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   const void* wide[] = {reinterpret_cast<const void*>(k_res_forward<128, 64, 2, false>), reinterpret_cast<const void*>(k_res_backward<128, 64, 2, false>)};
@@ -2671,6 +2672,17 @@ hipError_t launch_resident_wgrad(int kind, int g, int C, int MID, const ResArgs&
   if (MID == 32) {
     const dim3 grid(share((int)(n11 + 1) * a.nblk, 64 * MID, 1536), n11 + 1, (unsigned)a.nblk);
     k_res_wgrad<128, 32, WG_ALL><<<grid, rw_threads(32), std::max(wgrad_1x1_lds(MID, P, w.sub, w.zspan), bb_wgrad_lds(MID, P, a.W, w.sub, w.zspan)), stream>>>(w);
+    return hipGetLastError();
+  }
+  // Few images: all items in one launch, a work-group per CU.  us of one / two launches, 16x16 128-64: 7 blocks, 5 images 17 / 24, 64 images 53 / 71;
+  // 21 blocks, 16 images 46 / 60; 8x8 256-64: 7 blocks, 5 images 12 / 19, 21 blocks, 32 images 46 / 47.  From about 512 work-groups worth of
+  // them on the occupancy of the 1x1 items counts for more (21 blocks 128-64, 256 images: see k_res_wgrad).
+  const int items = (int)(n11 + 1) * a.nblk, sums = (int)(n11 * 64 * MID + 9 * MID * MID) / (int)(n11 + 1);
+  if (wgrad_groups(batches, items, sums, items * batches) * items <= 512) {
+    const dim3 grid(share(items, sums, 256), n11 + 1, (unsigned)a.nblk);
+    const size_t lds = std::max(wgrad_1x1_lds(MID, P, w.sub, w.zspan), bb_wgrad_lds(MID, P, a.W, w.sub, w.zspan));
+    if (C == 128) k_res_wgrad<128, 64, WG_ALL><<<grid, rw_threads(64), lds, stream>>>(w);
+    else k_res_wgrad<256, 64, WG_ALL><<<grid, rw_threads(64), lds, stream>>>(w);
     return hipGetLastError();
   }
   const dim3 g1(share((int)n11 * a.nblk, 64 * MID, 1536), n11, (unsigned)a.nblk);

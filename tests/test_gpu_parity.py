@@ -198,6 +198,20 @@ def test_image_resident_runs_edge_cases(gpu, oracle):
     assert rel_err(r1["act_out"][0], r2["act_out"][0]) < 2e-2   # the other schedule: another bf16 evaluation
 
 
+@pytest.mark.parametrize("c,hw", [(128, 16), (256, 8)])
+def test_weight_gradients_of_wide_runs_in_one_launch_and_in_two(gpu, c, hw):
+    """A call for each micro-batch has few enough images for one launch of all items, a group call takes two: the same gradients."""
+    from parity import rel_err, run_gpu_step
+    spec = W.PartitionSpec(name=f"launches-{c}", in_h=hw, in_w=hw, in_c=c, blocks=(W.Block(W.BOTTLENECK, c, 64, c, 1),) * 4, microbatch=64,
+                           num_microbatches=4, seed=41)
+    inp = W.make_inputs(spec, randomize_affine=True)
+    _, one = run_gpu_step(spec, inp, "bf16")
+    _, two = run_gpu_step(spec, inp, "bf16", grouped=True)
+    for x, y in zip(one["act_out"] + one["err_out"], two["act_out"] + two["err_out"]):
+        assert np.array_equal(x, y)
+    assert rel_err(two["grad"], one["grad"]) < 1e-5         # fp32 sums in another order
+
+
 def test_fusion_levels_agree_on_the_benchmark_partition(gpu, oracle):
     """The three kernel schedules are three bf16 evaluations of the same batch."""
     spec = W.with_microbatching(W.config(3), 32, 2, loss_divisor=256)
