@@ -144,6 +144,7 @@ struct WgradLaunch {
   const WgradItem* items[WGRAD_CLASSES] = {};
   int n[WGRAD_CLASSES] = {};
   int rows[WGRAD_CLASSES] = {}, adds[WGRAD_CLASSES] = {};   // pixel rows of the longest item; most items that add to one output element
+  bool bn[WGRAD_CLASSES] = {};    // an item recomputes relu(bn(x))
   int t9_lds = 0;            // wgrad_t9_lds_bytes of the class's image shape
 };
 hipError_t launch_wgrad_grouped(const WgradLaunch& l, int g, const PtrTab& region_base, const PtrTab& caller_dy, const PtrTab& caller_a,

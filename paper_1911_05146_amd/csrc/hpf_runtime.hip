@@ -112,6 +112,7 @@ struct Plan {
   std::vector<WgradItem> items[WGRAD_CLASSES];     // deferred weight-gradient work, per tile class (bf16 mode)
   // pixel rows of the longest item and most items that add to one output element; nr: without resident runs
   int wg_rows[WGRAD_CLASSES] = {}, wg_nr_rows[WGRAD_CLASSES] = {}, wg_adds[WGRAD_CLASSES] = {}, wg_nr_adds[WGRAD_CLASSES] = {};
+  bool wg_bn[WGRAD_CLASSES] = {}, wg_nr_bn[WGRAD_CLASSES] = {};   // an item recomputes its operand
   std::vector<WgradItem> items_nr[WGRAD_CLASSES];  // the same without the blocks of image-resident runs (those have a launch of their own)
   size_t items_nr_off[WGRAD_CLASSES] = {};
   double wg_nr_bytes[WGRAD_CLASSES] = {}, wg_nr_flops[WGRAD_CLASSES] = {};
@@ -619,6 +620,7 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
         if (m_end - m_begin > longest) longest = m_end - m_begin;
       };
       int& adds = (pass ? P.wg_nr_adds : P.wg_adds)[cls];
+      if (w.bn) (pass ? P.wg_nr_bn : P.wg_bn)[cls] = true;
       if (cls == WGRAD_CLASS_T9) {   // whole images per item; about 1000 work-groups (two per CU at 67 KiB of LDS, twice over)
         int parts = (int)((1024 + tiles_in_class[cls] - 1) / tiles_in_class[cls]);
         if (parts > q.b) parts = q.b;
@@ -1252,6 +1254,7 @@ void run_backward(Ctx& c) {
       if (l.n[k] == 0) continue;
       l.rows[k] = (res ? P.wg_nr_rows : P.wg_rows)[k];
       l.adds[k] = (res ? P.wg_nr_adds : P.wg_adds)[k];
+      l.bn[k] = (res ? P.wg_nr_bn : P.wg_bn)[k];
       l.items[k] = (const WgradItem*)(c.h->arena + (res ? P.items_nr_off : P.items_off)[k]);
       bytes += (res ? P.wg_nr_bytes : P.wg_bytes)[k];
       flops += (res ? P.wg_nr_flops : P.wg_flops)[k];

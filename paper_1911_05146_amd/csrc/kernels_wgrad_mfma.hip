@@ -607,17 +607,17 @@ int wgrad_class_lds(int cls, int t9_lds) {
 }
 
 // What a launch of few items is made of: a work-group takes wgrad_item_us for its item and each of its micro-batches (the latency of the
-// steps; a 64-row step of the quadrant kernel, a 128-row step of the others, an image), and every share of the micro-batches adds all
+// steps; a 64-row step of the quadrant kernel, a 128-row step of the others, twice that where relu(bn(x)) is recomputed, an image), and every share of the micro-batches adds all
 // output elements with atomics, ATOMICS_PER_US of them (256 per ns, from launches of 63 and 252 items).  More shares end the first sooner and pay
 // the second more often.  63 items of 64 x 64 over 8 micro-batches: 14.1 us in one share, 9.4 in four (taken), 13.3 in eight; of 128 x 128
 // over 8 31, 22.2 in two (taken), 40; over 4 19.2, 16.5 in two (taken), 23; 252 of them over 4 25.4 in one (taken), 32 in two.
 // Additions to one element follow each other (18 ns): the stem of 64 images, 128 items that add to the same 27 x 16, 8.1 us in one share (taken), 15.4 in four.
 constexpr double ATOMICS_PER_US = 256e3, SAME_ADDRESS_US = 0.018;
-double wgrad_item_us(int cls, int rows) {
+double wgrad_item_us(int cls, int rows, bool bn_operand) {
   if (cls == WGRAD_CLASS_T9) return 4.0 * ((rows + T9_P - 1) / T9_P);
   if (cls == 9) return 1.5 * ((rows + 63) / 64);
   const int bc = 16 << cls / 3, bn = 16 << cls % 3;
-  return (bc == 64 || bn == 64 ? 1.25 : 0.9) * ((rows + 127) / 128);
+  return (bc == 64 || bn == 64 ? 1.25 : 0.9) * (bn_operand ? 2 : 1) * ((rows + 127) / 128);
 }
 int wgrad_item_sums(int cls) { return cls == WGRAD_CLASS_T9 ? 9 * 256 : cls == 9 ? 128 * 128 : (16 << cls / 3) * (16 << cls % 3); }
 
@@ -707,7 +707,7 @@ hipError_t launch_wgrad_grouped(const WgradLaunch& l, int ng, const PtrTab& regi
       ++list.n;
       total += l.n[k];
       lds = std::max(lds, wgrad_class_lds(k, l.t9_lds));
-      longest = std::max(longest, wgrad_item_us(k, l.rows[k]));
+      longest = std::max(longest, wgrad_item_us(k, l.rows[k], l.bn[k]));
       sums += (double)l.n[k] * wgrad_item_sums(k);
       adds = std::max(adds, l.adds[k]);
     }
