@@ -174,13 +174,17 @@ struct ResBlock {
   // written by the backward launch, added into the gradients of beta and gamma by the weight-gradient launch
   unsigned long long dgb_off[3];
   unsigned long long run_off[3];             // running {mean(C), variance(C)} of the three BatchNorms (floats)
+  // a block that leads a run in: its projection's packed weights; post-activation ones also write the projected shortcut, relu(bn1(c1)) and
+  // the gradient w.r.t. the shortcut
+  unsigned long long pf_off, pd_off, sc_off, a1_off, dsc_off;
 };
 struct ResArgs {
   const ResBlock* blocks;   // device table of the run
   int nblk;
+  int lead;                 // the first block of the table halves the image and doubles the channels (resident_lead_shape)
   int nmem;                 // images per micro-batch = work-groups per exchange group
   int ngroup;               // micro-batches in the launch (set by the launchers)
-  int H, W;
+  int H, W;                 // of the identity blocks
   float eps;
   PtrTab base;              // micro-batch regions of the group members (grid z)
   PtrTab act_in, act_out, err_in, err_out;   // caller buffers per member (null where the pass does not use them)
@@ -198,6 +202,8 @@ bool resident_shape_ok(int kind, int C, int MID, int H, int W, int nmem);   // k
 // the grouped per-layer launch); banded runs and all runs of kind 2 go through the per-layer kernels at inference.
 inline bool resident_has_wgrad_launch(int kind, int C, int bands) { (void)kind; return bands == 1 && C != 16; }
 inline bool resident_has_inference_launch(int kind, int bands) { return bands == 1 && kind != 2; }
+// The block in front of a run of basic blocks (kinds 0 and 2) of c_out channels on h_out x w_out pixels can lead it in: stride 2, c_in = c_out / 2.
+bool resident_lead_shape(int kind, int c_in, int c_out, int h_out, int w_out);
 // Largest number of micro-batches of nmem images one launch may hold on the current device (0: none):
 // every work-group takes a CU of its own and all of them must be resident together.
 int resident_max_group(int nmem);   // nmem: work-groups per micro-batch (images x bands)

@@ -130,7 +130,12 @@ struct Plan {
     return m;
   }
   // image-resident runs of identity bottleneck blocks (bf16 mode, micro-batch statistics)
-  struct ResRun { int first = 0, count = 0, kind = 1, C = 0, MID = 0, bands = 1; size_t table_off = 0; /* bytes from the arena base */ };
+  struct ResRun {
+    int first = 0, count = 0, kind = 1, C = 0, MID = 0, bands = 1;
+    int lead = 0;           // 1: block `first` is the one that changes the shape (resident_lead_shape), the identity blocks come behind it
+    size_t table_off = 0;   // bytes from the arena base
+    bool identity(int i) const { return i >= first + lead && i < first + count; }
+  };
   std::vector<ResRun> runs;
   std::vector<int> run_at;             // per block: index of the run that starts (forward) at this block, else -1
   std::vector<int> run_end_at;         // per block: index of the run that ends at this block, else -1
@@ -470,17 +475,29 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
         return p.d.stride == 1 && !p.proj && p.d.c_in == p.d.c_mid && resident_shape_ok(2, p.d.c_in, p.d.c_mid, p.h_in, p.w_in, d.microbatch);
       return p.residual() && p.whole() && p.d.stride == 1 && !p.proj && resident_shape_ok(p.d.kind, p.d.c_in, p.d.c_mid, p.h_in, p.w_in, d.microbatch);
     };
+    // Blocks that lead a run in, with or without identity blocks behind them.  Only where the partition has resident runs anyway: calls with
+    // image-resident launches are refused on a stream that the caller captures, and a partition of such a block alone is accepted there.
+    bool any = false;
+    for (int i = 0; i < d.n_blocks && !any; ++i) any = eligible(i);
+    auto leads = [&](int i) {
+      const BlockPlan& p = P.bp[i];
+      return any && (p.d.kind == 0 || p.d.kind == K_POSTACT) && p.whole() && p.proj && p.d.stride == 2 && p.d.c_mid == p.d.c_out &&
+             resident_lead_shape(p.d.kind, p.d.c_in, p.d.c_out, p.h_out, p.w_out) &&
+             resident_shape_ok(p.d.kind, p.d.c_out, p.d.c_out, p.h_out, p.w_out, d.microbatch);
+    };
     int cmax_run = 0;
     size_t xchg_bytes = 0;
     for (int i = 0; i < d.n_blocks;) {
-      if (!eligible(i)) { ++i; continue; }
+      const int lead = leads(i);
+      if (!lead && !eligible(i)) { ++i; continue; }
+      const hpf_block_desc& bd = P.bp[i].d;
       int j = i + 1;
-      while (j < d.n_blocks && eligible(j) && P.bp[j].d.kind == P.bp[i].d.kind && P.bp[j].d.c_in == P.bp[i].d.c_in &&
-             P.bp[j].d.c_mid == P.bp[i].d.c_mid)
+      while (j < d.n_blocks && eligible(j) && P.bp[j].d.kind == bd.kind && P.bp[j].d.c_in == bd.c_out && P.bp[j].d.c_mid == bd.c_mid &&
+             P.bp[j].h_in == P.bp[i].h_out && P.bp[j].w_in == P.bp[i].w_out)
         ++j;
       Plan::ResRun r;
-      r.first = i; r.count = j - i; r.kind = P.bp[i].d.kind; r.C = P.bp[i].d.c_in; r.MID = P.bp[i].d.c_mid;
-      r.bands = resident_bands(r.kind, r.C, r.MID, P.bp[i].h_in, P.bp[i].w_in);
+      r.first = i; r.count = j - i; r.kind = bd.kind; r.C = bd.c_out; r.MID = bd.c_mid; r.lead = lead;
+      r.bands = resident_bands(r.kind, r.C, r.MID, P.bp[i].h_out, P.bp[i].w_out);
       r.table_off = P.res_blocks.size() * sizeof(ResBlock);   // made absolute below
       auto res_loc = [](const Loc& l) -> unsigned long long {
         switch (l.kind) {
@@ -506,6 +523,10 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
           rb.gamma_off[q] = p.bn[q].g_off; rb.beta_off[q] = p.bn[q].b_off;
           rb.dgb_off[q] = alloc(2 * (size_t)p.bn[q].C * sizeof(float)).off;
           rb.run_off[q] = p.bn[q].run_off;
+        }
+        if (p.proj) {
+          rb.pf_off = p.pj.wf_off; rb.pd_off = p.pj.wd_off;
+          if (p.d.kind == K_POSTACT) { rb.sc_off = res_loc(p.sc); rb.a1_off = res_loc(p.a[0]); rb.dsc_off = res_loc(p.dc[2]); }
         }
         P.res_blocks.push_back(rb);
       }
@@ -550,7 +571,7 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
       const BlockPlan& p = P.bp[i];
       bool in_run = false;
       for (const Plan::ResRun& r : P.runs)   // runs without a weight-gradient launch of their own stay in the grouped launch
-        in_run = in_run || (resident_has_wgrad_launch(r.kind, r.C, r.bands) && i >= r.first && i < r.first + r.count);
+        in_run = in_run || (resident_has_wgrad_launch(r.kind, r.C, r.bands) && r.identity(i));
       if (!p.residual()) {   // the operands are stored activations (no BatchNorm to recompute)
         if (p.d.kind == K_POSTACT) {
           wc.push_back(WConv{&p.cv[0], p.cv[0].cin, p.cv[0].cin, p.cv[0].R, p.x_in, p.dc[0], nullptr, in_run});
@@ -929,7 +950,7 @@ struct Ctx {
     const BlockPlan& p0 = P.bp[r.first];
     ResArgs a{};
     a.blocks = (const ResBlock*)(h->arena + r.table_off);
-    a.nblk = r.count; a.nmem = P.d.microbatch; a.H = p0.h_in; a.W = p0.w_in; a.eps = P.d.bn_eps;
+    a.nblk = r.count; a.lead = r.lead; a.nmem = P.d.microbatch; a.H = p0.h_out; a.W = p0.w_out; a.eps = P.d.bn_eps;
     for (int i = 0; i < g; ++i) {
       a.base.p[i] = h->mb_base(mb0 + i);
       a.act_in.p[i] = const_cast<void*>(act_in[i]); a.act_out.p[i] = act_out[i];
@@ -947,7 +968,7 @@ struct Ctx {
   }
   void res_forward(const Plan::ResRun& r) {
     const BlockPlan& p0 = h->P.bp[r.first];
-    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_in * p0.w_in;
+    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_out * p0.w_out;
     double st, fl;
     res_figures(r, px, &st, &fl);
     seg(PROF_RES_FWD, img * 2.0 * (px * r.C + r.count * st), img * r.count * fl);
@@ -956,7 +977,7 @@ struct Ctx {
   }
   void res_inference(const Plan::ResRun& r) {
     const BlockPlan& p0 = h->P.bp[r.first];
-    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_in * p0.w_in;
+    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_out * p0.w_out;
     double st, fl;
     res_figures(r, px, &st, &fl);
     seg(PROF_RES_FWD, img * 2.0 * 2.0 * px * r.C, img * r.count * fl);   // run input read, run output written
@@ -965,7 +986,7 @@ struct Ctx {
   }
   void res_backward(const Plan::ResRun& r) {
     const BlockPlan& p0 = h->P.bp[r.first];
-    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_in * p0.w_in;
+    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_out * p0.w_out;
     double st, fl;
     res_figures(r, px, &st, &fl);
     seg(PROF_RES_BWD, img * 2.0 * (px * r.C + r.count * 2.0 * st), img * r.count * fl);
@@ -974,11 +995,15 @@ struct Ctx {
   }
   void res_wgrad(const Plan::ResRun& r) {
     const BlockPlan& p0 = h->P.bp[r.first];
-    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_in * p0.w_in;
+    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_out * p0.w_out;
     double st, fl;
     res_figures(r, px, &st, &fl);
-    seg(PROF_RES_WGRAD, img * r.count * 2.0 * 2.0 * st, img * r.count * fl);
-    chk(launch_resident_wgrad(r.kind, g, r.C, r.MID, res_args(r), s), "resident_wgrad");
+    const int n = r.count - r.lead;
+    if (n == 0) return;
+    ResArgs a = res_args(r);
+    a.blocks += r.lead; a.nblk = n; a.lead = 0;   // the lead's weight gradients go with the grouped ones
+    seg(PROF_RES_WGRAD, img * n * 2.0 * 2.0 * st, img * n * fl);
+    chk(launch_resident_wgrad(r.kind, g, r.C, r.MID, a, s), "resident_wgrad");
     seg_end();
   }
   void conv_wgrad(const ConvPlan& cv, const PtrTab& a, const PtrTab& dy) {
@@ -1935,7 +1960,7 @@ hpf_status hpf_stash_read(hpf_partition* p, int32_t mb, int32_t unit, int32_t te
     auto held = [&](int j) { return j >= q.j0 && j < q.j1; };
     auto in_run = [&](int i) {
       for (const Plan::ResRun& r : P.runs)
-        if (i >= r.first && i < r.first + r.count) return true;
+        if (r.identity(i)) return true;
       return false;
     };
     if (!q.residual()) {   // units of VGG-16 / ResNet-v1: input, output, the tensors in between, the boundary gradients
@@ -1948,7 +1973,7 @@ hpf_status hpf_stash_read(hpf_partition* p, int32_t mb, int32_t unit, int32_t te
         case HPF_T_GX: loc = grad_in(unit); need = n_in * P.esz; break;
         case HPF_T_C1: if (q.d.kind == K_POSTACT) { loc = q.c[0]; need = M_out * q.d.c_mid * P.esz; } break;
         case HPF_T_A0:   // inside an image-resident run relu(bn1(c1)) never reaches memory
-          if (q.d.kind == K_POSTACT && !(p->resident() && (P.run_at[unit] >= 0 || in_run(unit)))) { loc = q.a[0]; need = M_out * q.d.c_mid * P.esz; }
+          if (q.d.kind == K_POSTACT && !(p->resident() && in_run(unit))) { loc = q.a[0]; need = M_out * q.d.c_mid * P.esz; }
           break;
         case HPF_T_C2: if (q.d.kind == K_POSTACT) { loc = q.c[1]; need = M_out * q.d.c_out * P.esz; } break;
         case HPF_T_SC: if (q.d.kind == K_POSTACT) { loc = q.sc; need = M_out * q.d.c_out * P.esz; } break;

@@ -15,114 +15,39 @@
 // Few images (4 or 8 of a batch) leave no other work-group to hide a wave that waits for the memory pipeline to take its loads:
 // at 64 channels 2.2 us of an inference block were spent asking for the next matrix in one go.  With the loads dealt out over the
 // contraction the same runs take 97 and 111 us (128 images), 440 and 541 us (v1), and inference of ResNet-110 on 4 images 317 -> 278 us.
+//
+// The block in front of a run of 32 or 64 channels halves the image and doubles the channels; it leads the run in (LEAD): the same launch starts, or
+// in the backward pass ends, with it.  Layer by layer it took five launches forward and five backward of 4 to 13 us each, which a few images leave
+// nearly empty; as part of the run it takes two exchanges and four contractions a direction, and its output never comes back from memory.  ResNet-20
+// on 4 images (two such blocks) 336 -> 260 us a batch, a quarter of ResNet-110 on 128 images (one) 359 -> 309, ResNet-110 v1 1437 -> 1333,
+// inference of ResNet-110 on 4 images 271 -> 242.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
 
-#include "hpf_resident_reg.h"
+#include "hpf_resident_basic.h"
 
 namespace hpf {
 namespace {
 
-template <int C>
-struct Geo {
-  static constexpr int IMG = C == 16 ? 32 : C == 32 ? 16 : 8, P = IMG * IMG;
-  static constexpr int CG = C == 64 ? 2 : 1, NPW = RG_NW / CG;          // waves per tile, waves along the pixels
-  static constexpr int PTW = P / 16 / NPW, NTW = C / 16 / CG;           // pixel tiles and channel tiles per wave
-  static constexpr int CW = IMG + 2, MS = C + 8;                        // canvas row and pixel pitch (elements)
-  static constexpr int NPX = PTW * 16;
-  // tile j of a wave in the canvas, from its first one
-  static constexpr int tile_off(int j) { return C == 16 ? ((j >> 1) * CW + (j & 1) * 16) * MS : j * CW * MS; }
-  using W = WStage<C, (9 * C + 31) / 32 * 32, false>;
-  static constexpr int CANVAS = CW * CW * MS * 2;                       // bytes
-};
-
-// 3x3 convolution from the canvas.  src: tap (0, 0) of the lane's pixel of the wave's first tile (+ fk; 16 channels: + (fq & 1)*8); FLIP: the
-// data gradient (taps mirrored).  w: the staged matrix at the wave's first channel tile, + lane*8.  zero: eight zeros (of the border).
-// third(integral_constant 0 ... 2) runs at the start, after one and after two thirds of the contraction: the next matrix' loads.
-template <int C, bool FLIP, class THIRD>
-__device__ __forceinline__ void conv3x3(const bf16_t* src, const bf16_t* zero, const bf16_t* w, int fq, floatx4 (&acc)[Geo<C>::PTW][Geo<C>::NTW], THIRD&& third) {
-  auto thirds = [&](int i) {
-    if (i == 0) third(std::integral_constant<int, 0>{});
-    else if (i == 1) third(std::integral_constant<int, 1>{});
-    else third(std::integral_constant<int, 2>{});
-  };
-  using G = Geo<C>;
-  constexpr int MS = G::MS, CW = G::CW;
-  if constexpr (C == 16) {   // packed weights [16][160], k = tap*16 + c, zero beyond tap 8: lane groups 0-1 take the even tap of a step, 2-3 the odd one.
-    // The odd half of the last step has no tap: zeros, not another tap's values times the zero weights (0 * infinity)
-#pragma unroll
-    for (int st = 0; st < 5; ++st) {
-      if (st % 2 == 0) thirds(st / 2);
-      constexpr int last = 8;
-      const int ta = 2 * st, tb = 2 * st + 1 > last ? last : 2 * st + 1;
-      const int oa = FLIP ? (2 - ta / 3) * CW + 2 - ta % 3 : ta / 3 * CW + ta % 3, ob = FLIP ? (2 - tb / 3) * CW + 2 - tb % 3 : tb / 3 * CW + tb % 3;
-      const bf16_t* q = src + (fq < 2 ? oa : ob) * MS;
-      const bf16x8 wf = G::W::get(w, st, 0);
-#pragma unroll
-      for (int j = 0; j < G::PTW; ++j) {
-        const bf16_t* px = 2 * st == last && fq >= 2 ? zero : q + G::tile_off(j);
-        acc[j][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, *reinterpret_cast<const bf16x8*>(px), acc[j][0], 0, 0, 0);
-      }
-    }
-  } else if constexpr (C == 32) {   // the four input rows of a filter column serve both output rows
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      thirds(s);
-      bf16x8 px[4];
-#pragma unroll
-      for (int ir = 0; ir < 4; ++ir) px[ir] = *reinterpret_cast<const bf16x8*>(src + (ir * CW + s) * MS);
-#pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int nt = 0; nt < G::NTW; ++nt) {
-          const bf16x8 wf = G::W::get(w, FLIP ? (2 - r) * 3 + 2 - s : r * 3 + s, nt);
-#pragma unroll
-          for (int j = 0; j < G::PTW; ++j) acc[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, px[j + r], acc[j][nt], 0, 0, 0);
-        }
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      thirds(r);
-#pragma unroll
-      for (int s = 0; s < 3; ++s)
-#pragma unroll
-        for (int ks = 0; ks < C / 32; ++ks) {
-          const bf16x8 px = *reinterpret_cast<const bf16x8*>(src + (r * CW + s) * MS + ks * 32);
-#pragma unroll
-          for (int nt = 0; nt < G::NTW; ++nt)
-            acc[0][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(G::W::get(w, (FLIP ? (2 - r) * 3 + 2 - s : r * 3 + s) * (C / 32) + ks, nt), px, acc[0][nt], 0, 0, 0);
-        }
-      keep_order();
-    }
-  }
+template <int C, bool LEAD>
+constexpr int lead_lds(bool fwd) {
+  if constexpr (LEAD) return fwd ? Lead<C>::FWD_LDS : Lead<C>::BWD_LDS;
+  return 0;
 }
-
-// what every kernel of a lane's place needs
-template <int C>
-struct Lane {
-  int tid, lane, wave, fr, fq, pw, cg;
-  unsigned off;                 // of its channels in an image
-  int cw, cr;                   // canvas: where it writes (its pixel, its channels) and tap (0, 0) of its reads
-  __device__ __forceinline__ Lane() {
-    using G = Geo<C>;
-    tid = threadIdx.x; lane = tid & 63; wave = wave_index(); fr = lane & 15; fq = lane >> 4;
-    pw = G::CG == 1 ? wave : wave % G::NPW; cg = G::CG == 1 ? 0 : wave / G::NPW;
-    const int p = pw * G::NPX + fr, row = p / G::IMG, col = p % G::IMG, c0 = cg * G::NTW * 16;
-    off = C == 16 ? (unsigned)(p * C + fq * 4) : px_offset(p, C, fq) + (unsigned)c0;
-    cw = ((row + 1) * G::CW + col + 1) * G::MS + c0 + fq * 4;
-    cr = (row * G::CW + col) * G::MS + (C == 16 ? (fq & 1) * 8 : fq * 8);
-  }
-};
-
-template <int C, bool INFER>
+template <int C, bool LEAD>
+constexpr int lead_proj_bytes() {
+  if constexpr (LEAD) return Lead<C>::DP::BYTES;
+  return 0;
+}
+template <int C, bool INFER, bool LEAD>
 constexpr int basic_fwd_lds() {
   using G = Geo<C>;
-  return G::CANVAS + G::W::BYTES + 2 * C * 8 + (INFER ? 0 : G::NPW * 2 * C * 4) + 16;
+  return G::CANVAS + G::W::BYTES + 2 * C * 8 + (INFER ? 0 : G::NPW * 2 * C * 4) + 16 + lead_lds<C, LEAD>(true);
 }
 
-template <int C, bool POST, bool INFER>
+// LEAD: the run's first block is the one that halves the image and doubles the channels (Lead).
+template <int C, bool POST, bool INFER, bool LEAD>
 __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
   static_assert(!(POST && INFER), "post-activation runs: training only");
   using G = Geo<C>;
@@ -171,16 +96,28 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) { p[j][nt] = pack4(v[j][nt]); v[j][nt] = unpack4(p[j][nt]); }
   };
+  auto join = [&](const floatx4 (&v)[PTW][NTW], const float2* cf) {   // X = relu(bn(v) + X)
+#pragma unroll
+    for (int nt = 0; nt < NTW; ++nt) {
+      const float4 p = reinterpret_cast<const float4*>(cf + c_at + nt * 16)[0], q = reinterpret_cast<const float4*>(cf + c_at + nt * 16)[1];
+      const float sc[4] = {p.x, p.z, q.x, q.z}, sh[4] = {p.y, p.w, q.y, q.w};
+#pragma unroll
+      for (int j = 0; j < PTW; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) X[j][nt][e] = fmaxf(fmaf(v[j][nt][e], sc[e], sh[e]) + X[j][nt][e], 0.f);
+    }
+  };
   // inference: the coefficients of a block, one channel per lane: wave 0 takes those of the first BatchNorm, wave 1 those of the second.  Read a
   // block ahead of their use, as the loads of a wave that waits for them hold up the work-group
   const bool t_on = wave < 2 && lane < C;
   float rc_mean, rc_var, rc_gamma, rc_beta;
   auto load_coef = [&](int b) {
     const ResBlock* t = a.blocks + b;
-    if (t_on) {
+    const int n = LEAD && b == 0 && wave == 0 ? C / 2 : C;
+    if (t_on && lane < n) {
       const float* run = a.running + t->run_off[wave];
       rc_mean = run[lane];
-      rc_var = run[C + lane];
+      rc_var = run[n + lane];
       rc_gamma = (a.params + t->gamma_off[wave])[lane];
       rc_beta = (a.params + t->beta_off[wave])[lane];
     }
@@ -188,16 +125,18 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
   auto store_coef = [&](int q, float2* dst) {
     if (t_on && wave == q) dst[lane] = bn_scale_shift(rc_mean, 1.0f / sqrtf(rc_var + a.eps), rc_gamma, rc_beta);
   };
-  // statistics of v -> coef of BatchNorm q of block B; `late` runs behind the polls
-  auto exchange = [&](const floatx4 (&v)[PTW][NTW], const ResBlock& B, int q, float2* coef, auto&& late) -> bool {
-    const int gc = gather_channel<C>(wave, lane);
+  // statistics of v, a tensor of geometry GV -> coef of BatchNorm q of block B; `late` runs behind the polls
+  auto exchange_of = [&](auto gv, const auto& v, float* row, const ResBlock& B, int q, float2* coef, auto&& late) -> bool {
+    using GV = decltype(gv);
+    constexpr int Cc = GV::NC;
+    const int gc = gather_channel<Cc>(wave, lane);
     const float gamma = (a.params + B.gamma_off[q])[gc], beta = (a.params + B.beta_off[q])[gc];
-    stats_wave(v, red_w, C, fr, fq);
+    stats_wave(v, row, Cc, fr, fq);
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
-    stats_publish_waves<C, G::NPX, G::NPW>(red, slot(), me, tag);
+    stats_publish_waves<Cc, GV::NPX, GV::NPW>(red, slot(), me, tag);
     const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
-    collect_stats<C>(slot(), a.nmem, tag, inv_n, (float)G::P, a.eps, gamma, beta, o, wave, lane, fail);
+    collect_stats<Cc>(slot(), a.nmem, tag, inv_n, (float)GV::P, a.eps, gamma, beta, o, wave, lane, fail);
     ++phase;
     late();
     __syncthreads();
@@ -207,7 +146,120 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     }
     return true;
   };
-  {
+  auto exchange = [&](const floatx4 (&v)[PTW][NTW], const ResBlock& B, int q, float2* coef, auto&& late) -> bool {
+    return exchange_of(G{}, v, red_w, B, q, coef, late);
+  };
+  constexpr int FIRST = LEAD ? 1 : 0;   // the run's first identity block
+  if constexpr (LEAD) {
+    using LD = Lead<C>;
+    using I = typename LD::I;
+    constexpr int CI = LD::CI;
+    const Lane<CI> LI;
+    unsigned char* base = smem + basic_fwd_lds<C, INFER, false>();
+    bf16_t* canvas_x = reinterpret_cast<bf16_t*>(base);
+    bf16_t* sW1 = reinterpret_cast<bf16_t*>(base + I::CANVAS);
+    bf16_t* sWP = reinterpret_cast<bf16_t*>(base + I::CANVAS + LD::W1::BYTES);
+    float2* coef_x = reinterpret_cast<float2*>(base + I::CANVAS + LD::W1::BYTES + LD::WP::BYTES);
+    const ResBlock T = a.blocks[0];
+    const bool more = a.nblk > 1;
+    const ResBlock Tn = a.blocks[more ? 1 : 0];
+    uint2 px[I::PTW][I::NTW];
+    px_load(px, cx.tensor(T.x_off) + (size_t)me * (I::P * CI), LI.off);
+    typename LD::W1 w1;
+    typename LD::WP wp;
+    w1.issue(a.packed + T.wf_off[0], wave, fr, fq);
+    wp.issue(a.packed + T.pf_off, wave, fr, fq);
+    w.issue(a.packed + T.wf_off[1], wave, fr, fq);
+    if constexpr (INFER) load_coef(0);
+    for (int i = tid; i < G::CANVAS / 16; i += RG_NT) reinterpret_cast<u32x4*>(canvas)[i] = u32x4{0u, 0u, 0u, 0u};
+    for (int i = tid; i < I::CANVAS / 16; i += RG_NT) reinterpret_cast<u32x4*>(canvas_x)[i] = u32x4{0u, 0u, 0u, 0u};
+    if (tid == 0) *fail = 0;
+    px_arrange(px);
+    w1.commit(sW1, wave, lane);
+    wp.commit(sWP, wave, lane);
+    w.commit(sW, wave, lane);
+    if constexpr (INFER) { if (lane < CI) store_coef(0, coef_x); store_coef(1, coef2); }
+    __syncthreads();
+    // ---- conv1 and the projection on relu(bn1(x)) | x
+    if constexpr (!POST) {
+      floatx4 xf[I::PTW][I::NTW];
+#pragma unroll
+      for (int j = 0; j < I::PTW; ++j)
+#pragma unroll
+        for (int nt = 0; nt < I::NTW; ++nt) xf[j][nt] = unpack4(px[j][nt]);
+      if constexpr (!INFER)
+        if (!exchange_of(I{}, xf, red + wave * 2 * CI, T, 0, coef_x, [] {})) return;
+#pragma unroll
+      for (int nt = 0; nt < I::NTW; ++nt)
+#pragma unroll
+        for (int j = 0; j < I::PTW; ++j) px[j][nt] = bn_relu_pack(xf[j][nt], coef_x + nt * 16 + fq * 4);
+    }
+#pragma unroll
+    for (int j = 0; j < I::PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < I::NTW; ++nt) *reinterpret_cast<uint2*>(canvas_x + LI.cw + I::tile_off(j) + nt * 16) = px[j][nt];
+    __syncthreads();
+    if constexpr (INFER) { if (more) load_coef(1); }
+    floatx4 acc[PTW][NTW];
+#pragma unroll
+    for (int j = 0; j < PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NTW; ++nt) acc[j][nt] = X[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int p = L.pw * G::NPX + fr, row = p / G::IMG, col = p % G::IMG, at = L.cg * NTW * 512 + lane * 8;
+    const bf16_t* src = canvas_x + (2 * row * I::CW + 2 * col) * I::MS + (CI == 16 ? (fq & 1) * 8 : fq * 8);
+    conv3x3_s2<C>(src, canvas_x, sW1 + at, fq, acc);
+    proj_s2<C>(src, canvas_x, sWP + at, fq, X);
+    uint2 cp[PTW][NTW], sp[PTW][NTW];
+    round_to(acc, cp);
+    round_to(X, sp);   // the shortcut is a tensor of its own
+    if constexpr (INFER) {
+      if (more) store_coef(0, coef1);
+    } else {
+      if (!exchange(acc, T, POST ? 0 : 1, coef2, [&] {
+            px_store(image(T.c1_off), L.off, cp);
+            if constexpr (POST) px_store(image(T.sc_off), L.off, sp);
+          }))
+        return;
+    }
+    // ---- conv2 on relu(bn2(c1)), onto the shortcut | on its own
+    bn_pack(acc, coef2);
+    to_canvas();
+    if constexpr (POST) px_store(image(T.a1_off), L.off, pk);
+    __syncthreads();
+    auto next_matrix = [&](auto i) { if (more) w.template issue_third<i.value>(a.packed + Tn.wf_off[0], wave, fr, fq); };
+    if constexpr (!POST) {
+      conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, X, next_matrix);
+      round_to(X, cp);
+      if (!more) {
+        px_store(image(T.y_off), L.off, cp);
+      } else if constexpr (INFER) {
+        store_coef(1, coef2);   // every wave has used the lead's
+        __syncthreads();
+        w.commit(sW, wave, lane);
+      } else {
+        if (!exchange(X, Tn, 0, coef1, [&] {
+              w.commit(sW, wave, lane);
+              px_store(image(T.y_off), L.off, cp);
+            }))
+          return;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < PTW; ++j)
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+      conv3x3<C, false>(canvas + L.cr, canvas, wr, fq, acc, next_matrix);
+      round_to(acc, cp);
+      if (!exchange(acc, T, 1, coef1, [&] {
+            if (more) w.commit(sW, wave, lane);
+            px_store(image(T.c2_off), L.off, cp);
+          }))
+        return;
+      join(acc, coef1);
+      round_to(X, cp);
+      if (!more) px_store(image(T.y_off), L.off, cp);   // else stored by the next block
+    }
+  } else {
     const ResBlock B0 = a.blocks[0];
     w.issue(a.packed + B0.wf_off[0], wave, fr, fq);
     if constexpr (INFER) load_coef(0);
@@ -225,8 +277,8 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     if constexpr (!POST && !INFER)
       if (!exchange(X, B0, 0, coef1, [] {})) return;
   }
-  ResBlock B = a.blocks[0], Bn = B;
-  for (int bi = 0; bi < a.nblk; ++bi, B = Bn) {
+  ResBlock B = a.blocks[FIRST < a.nblk ? FIRST : 0], Bn = B;
+  for (int bi = FIRST; bi < a.nblk; ++bi, B = Bn) {
     const bool more = bi + 1 < a.nblk;
     Bn = a.blocks[more ? bi + 1 : bi];   // a block ahead of its use
     // ---- conv1 on relu(bn1(x)) | x
@@ -255,7 +307,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     } else {
       if (!exchange(acc, B, POST ? 0 : 1, coef2, [&] {
             w.commit(sW, wave, lane);
-            if constexpr (POST) { if (bi > 0) px_store(image(a.blocks[bi - 1].y_off), L.off, pk); }   // the block before's output
+            if constexpr (POST) { if (bi > 0) px_store(image(a.blocks[bi - 1].y_off), L.off, pk); }   // the output of the block before
             px_store(image(B.c1_off), L.off, cp);
           }))
         return;
@@ -294,15 +346,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
             px_store(image(B.c2_off), L.off, cp);
           }))
         return;
-#pragma unroll
-      for (int nt = 0; nt < NTW; ++nt) {
-        const float4 p = reinterpret_cast<const float4*>(coef1 + c_at + nt * 16)[0], q = reinterpret_cast<const float4*>(coef1 + c_at + nt * 16)[1];
-        const float sc[4] = {p.x, p.z, q.x, q.z}, sh[4] = {p.y, p.w, q.y, q.w};
-#pragma unroll
-        for (int j = 0; j < PTW; ++j)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) X[j][nt][e] = fmaxf(fmaf(acc[j][nt][e], sc[e], sh[e]) + X[j][nt][e], 0.f);
-      }
+      join(acc, coef1);
       round_to(X, cp);
       if (!more) px_store(image(B.y_off), L.off, cp);
     }
@@ -311,13 +355,13 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
   if (!INFER && me == 0 && tid == 0) *tagp = tag0 + phase;
 }
 
-template <int C>
+template <int C, bool LEAD>
 constexpr int basic_bwd_lds() {
   using G = Geo<C>;
-  return G::CANVAS + G::W::BYTES + (2 * 4 * C + 3 * C + G::NPW * 2 * C) * 4 + 16;
+  return G::CANVAS + G::W::BYTES + (2 * 4 * C + 3 * C + G::NPW * 2 * C) * 4 + 16 + lead_lds<C, LEAD>(false);
 }
 
-template <int C, bool POST>
+template <int C, bool POST, bool LEAD>
 __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
   using G = Geo<C>;
   constexpr int PTW = G::PTW, NTW = G::NTW;
@@ -347,34 +391,42 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
   const bf16_t* const wr = sW + L.cg * NTW * 512 + lane * 8;
   const float inv_M = 1.f / ((float)a.nmem * (float)G::P);
 
+  bf16_t* const sD1 = reinterpret_cast<bf16_t*>(smem + basic_bwd_lds<C, false>());   // the lead's conv1 and projection
+  bf16_t* const sDP = reinterpret_cast<bf16_t*>(smem + basic_bwd_lds<C, false>() + (LEAD ? lead_lds<C, LEAD>(false) - lead_proj_bytes<C, LEAD>() : 0));
   typename G::W w;
   uint2 DY[PTW][NTW], xa[PTW][NTW], xb[PTW][NTW], yv[PTW][NTW], dcp[PTW][NTW];
   // tables: wave 0 the channels of the first BatchNorm, wave 1 those of the second
   CfRegs tb;
   float* const t_dst = wave == 0 ? cf1 : cf2;
-  const bool t_on = wave < 2 && lane < C;
+  int t_n = C;   // channels of this wave's BatchNorm (the lead's first one has C/2)
+  auto t_on = [&] { return wave < 2 && lane < t_n; };
   auto load_tables = [&](int bi) {
-    if (t_on) {
+    if (LEAD && !POST && bi == 0 && wave == 0) t_n = C / 2;
+    if (t_on()) {
       const ResBlock* t = a.blocks + bi;
-      tb.load(reinterpret_cast<const float*>(cx.base + t->stats_off[wave]), a.params + t->gamma_off[wave], a.params + t->beta_off[wave], lane, C);
+      tb.load(reinterpret_cast<const float*>(cx.base + t->stats_off[wave]), a.params + t->gamma_off[wave], a.params + t->beta_off[wave], lane, t_n);
     }
   };
-  auto store_tables = [&] { if (t_on) tb.store(t_dst, lane, C); };
+  auto store_tables = [&] { if (t_on()) tb.store(t_dst, lane, t_n); };
   auto to_canvas = [&](const uint2 (&v)[PTW][NTW]) {
 #pragma unroll
     for (int j = 0; j < PTW; ++j)
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) *reinterpret_cast<uint2*>(canvas + L.cw + G::tile_off(j) + nt * 16) = v[j][nt];
   };
-  // sums of a BatchNorm backward -> tab; `late` runs behind the polls
-  auto exchange = [&](auto relu, floatx4 (&dz)[PTW][NTW], const uint2 (&x)[PTW][NTW], const float* cf, const ResBlock& B, int q, auto&& late) -> bool {
-    const CfChannel ck(cf, gather_channel<C>(wave, lane), C);
-    bwd_sums_wave<decltype(relu)::value>(dz, x, cf + c0, red_w, C, fr, fq);
+  // sums of a BatchNorm backward over a tensor of geometry GV -> tab; `late` runs behind the polls.  at: the wave's first channel, row: its row of
+  // red there; direct: DIRECT for this block
+  auto exchange_of = [&](auto gv, auto relu, auto direct, auto& dz, const auto& x, const float* cf, int at, float* row, const ResBlock& B, int q, auto&& late) -> bool {
+    using GV = decltype(gv);
+    constexpr int Cc = GV::NC;
+    constexpr bool D = decltype(direct)::value;
+    const CfChannel ck(cf, gather_channel<Cc>(wave, lane), Cc);
+    bwd_sums_wave<decltype(relu)::value>(dz, x, cf + at, row, Cc, fr, fq);
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
-    sums_publish_waves<C, G::NPW>(red, slot(), me, tag);
-    collect_bwd<C, 32>(slot(), a.nmem, tag, inv_M, ck, tab, !DIRECT && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave, lane, fail,
-                       DIRECT && me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
+    sums_publish_waves<Cc, GV::NPW>(red, slot(), me, tag);
+    collect_bwd<Cc, 32>(slot(), a.nmem, tag, inv_M * (float)G::P / (float)GV::P, ck, tab, !D && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave,
+                        lane, fail, D && me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
     ++phase;
     late();
     __syncthreads();
@@ -383,6 +435,9 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
       return false;
     }
     return true;
+  };
+  auto exchange = [&](auto relu, floatx4 (&dz)[PTW][NTW], const uint2 (&x)[PTW][NTW], const float* cf, const ResBlock& B, int q, auto&& late) -> bool {
+    return exchange_of(G{}, relu, std::integral_constant<bool, DIRECT>{}, dz, x, cf, c0, red_w, B, q, late);
   };
   auto apply = [&](const floatx4 (&dz)[PTW][NTW], const uint2 (&x)[PTW][NTW]) {   // -> dcp
 #pragma unroll
@@ -410,10 +465,20 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
     px_arrange(DY);
     w.commit(sW, wave, lane);
     store_tables();
+    if constexpr (LEAD) {
+      const ResBlock T = a.blocks[0];
+      typename Lead<C>::D1 d1;
+      typename Lead<C>::DP dp;
+      d1.issue(a.packed + T.wd_off[0], wave, fr, fq);
+      dp.issue(a.packed + T.pd_off, wave, fr, fq);
+      d1.commit(sD1, wave, lane);
+      dp.commit(sDP, wave, lane);
+    }
   }
   __syncthreads();
+  constexpr int FIRST = LEAD ? 1 : 0;   // the run's first identity block
   ResBlock B = a.blocks[a.nblk - 1], Bn = B;
-  for (int bi = a.nblk - 1; bi >= 0; --bi, B = Bn) {
+  for (int bi = a.nblk - 1; bi >= FIRST; --bi, B = Bn) {
     const bool more = bi > 0;
     Bn = a.blocks[more ? bi - 1 : 0];   // a block ahead of its use
     floatx4 acc[PTW][NTW];
@@ -494,7 +559,155 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
         for (int nt = 0; nt < NTW; ++nt) DY[j][nt] = pack4(dz[j][nt]);
     }
   }
-  px_store(image(a.blocks[0].gx_off), L.off, DY);
+  if constexpr (!LEAD) {
+    px_store(image(a.blocks[0].gx_off), L.off, DY);
+  } else {
+    using LD = Lead<C>;
+    constexpr int CI = LD::CI, TI = LD::TI, NTI = LD::NTI;
+    B = a.blocks[0];
+    auto store_gx = [&] { if (a.nblk > 1) px_store(image(a.blocks[1].gx_off), L.off, DY); };
+    // the lane's output pixel of its first tile, in the canvas, and the input pixel of class (0, 0) below it
+    const int t0 = C == 32 ? wave * 2 : wave & 3, ro = C == 32 ? t0 : 2 * t0 + (fr >> 3), co = C == 32 ? fr : fr & 7;
+    const bf16_t* const src = canvas + ((ro + 1) * G::CW + co + 1) * G::MS + fq * 8;
+    const bf16_t* const d1r = sD1 + lane * 8;
+    const bf16_t* const dpr = sDP + lane * 8;
+    const unsigned px0 = (unsigned)(2 * ro * (2 * G::IMG) + 2 * co);
+    const bool hi = C == 64 && wave >= 4;
+    auto px_at = [&](int j) -> unsigned {   // input pixel of tile j
+      const int pr = C == 32 ? (j >> 1) & 1 : j, pc = C == 32 ? j & 1 : hi ? 1 - j : j;
+      return px0 + (unsigned)((pr + (C == 32 ? 2 * (j >> 2) : 0)) * (2 * G::IMG) + pc);
+    };
+    bf16_t* const gx = cx.tensor(B.gx_off) + (size_t)me * (4 * G::P * CI);
+    floatx4 da[TI][NTI];
+#pragma unroll
+    for (int j = 0; j < TI; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NTI; ++nt) da[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto proj = [&] {   // its data gradient reaches the pixels of class (0, 0)
+      if (C == 64 && hi) return;
+#pragma unroll
+      for (int j = 0; j < TI; j += 4)
+#pragma unroll
+        for (int ks = 0; ks < C / 32; ++ks) {
+          const bf16x8 v = *reinterpret_cast<const bf16x8*>(src + (j >> 2) * G::CW * G::MS + ks * 32);
+#pragma unroll
+          for (int nt = 0; nt < NTI; ++nt) da[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(LD::DP::get(dpr, ks, nt), v, da[j][nt], 0, 0, 0);
+        }
+    };
+    auto conv1 = [&] {
+      if constexpr (C == 32) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          const bf16_t* q = src + r * G::CW * G::MS;
+          dgrad_s2<C, 0, 0>(q, d1r, da[4 * r]);
+          dgrad_s2<C, 0, 1>(q, d1r, da[4 * r + 1]);
+          dgrad_s2<C, 1, 0>(q, d1r, da[4 * r + 2]);
+          dgrad_s2<C, 1, 1>(q, d1r, da[4 * r + 3]);
+        }
+      } else if (!hi) {
+        dgrad_s2<C, 0, 0>(src, d1r, da[0]);
+        dgrad_s2<C, 1, 1>(src, d1r, da[1]);
+      } else {
+        dgrad_s2<C, 0, 1>(src, d1r, da[0]);
+        dgrad_s2<C, 1, 0>(src, d1r, da[1]);
+      }
+    };
+    auto store = [&](const uint2 (&v)[TI][NTI]) {
+#pragma unroll
+      for (int j = 0; j < TI; ++j) {
+        if constexpr (CI == 16) {
+          *reinterpret_cast<uint2*>(gx + px_at(j) * CI + fq * 4) = v[j][0];
+        } else {
+          uint2 e = v[j][0], o = v[j][1];
+          pair_swap(e, o);
+          *reinterpret_cast<uint4*>(gx + px_offset((int)px_at(j), CI, fq)) = make_uint4(e.x, e.y, o.x, o.y);
+        }
+      }
+    };
+    uint2 out[TI][NTI];
+    floatx4 acc[PTW][NTW];
+    if constexpr (!POST) {
+      // ---- conv2 data gradient, BN2 + ReLU backward -> dc1; the projection's data gradient from the same canvas
+      to_canvas(DY);
+      __syncthreads();
+      zero(acc);
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc, [](auto) {});
+      proj();
+      px_arrange(xa);
+      uint2 xi[TI][NTI];
+      if (!exchange_of(G{}, Relu{}, std::true_type{}, acc, xa, cf2, c0, red_w, B, 1, [&] {
+            store_gx();
+            const bf16_t* x = cx.tensor(B.x_off) + (size_t)me * (4 * G::P * CI);
+#pragma unroll
+            for (int j = 0; j < TI; ++j) {
+              if constexpr (CI == 16) {
+                xi[j][0] = *reinterpret_cast<const uint2*>(x + px_at(j) * CI + fq * 4);
+              } else {
+                const uint4 q = *reinterpret_cast<const uint4*>(x + px_offset((int)px_at(j), CI, fq));
+                xi[j][0] = make_uint2(q.x, q.y);
+                xi[j][1] = make_uint2(q.z, q.w);
+              }
+            }
+          }))
+        return;
+      apply(acc, xa);
+      to_canvas(dcp);
+      __syncthreads();
+      // ---- conv1 data gradient, BN1 + ReLU backward
+      conv1();
+      px_arrange(xi);
+      if (!exchange_of(typename LD::I{}, Relu{}, std::true_type{}, da, xi, cf1, 0, red + wave * 2 * CI, B, 0, [&] { px_store(image(B.dc1_off), L.off, dcp); })) return;
+#pragma unroll
+      for (int nt = 0; nt < NTI; ++nt)
+#pragma unroll
+        for (int j = 0; j < TI; ++j) out[j][nt] = pack4(bwd_apply<CI>(da[j][nt], xi[j][nt], tab + nt * 16 + fq * 4));
+    } else {
+      // ---- through the join and BN2: dz = dy*[y > 0] -> dc2; the projection's data gradient of dz
+      floatx4 dz[PTW][NTW];
+      px_arrange(yv);
+      px_arrange(xa);
+      uint2 dzp[PTW][NTW];
+#pragma unroll
+      for (int j = 0; j < PTW; ++j)
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dz[j][nt][e] = elem4(yv[j][nt], e) > 0.f ? elem4(DY[j][nt], e) : 0.f;
+          dzp[j][nt] = pack4(dz[j][nt]);
+        }
+      if (a.nblk > 1) w.issue(a.packed + B.wd_off[1], wave, fr, fq);
+      if (a.nblk > 1) __syncthreads();   // conv1's data gradient of the block above reads the canvas
+      to_canvas(dzp);
+      if (!exchange_of(G{}, NoRelu{}, std::true_type{}, dz, xa, cf2, c0, red_w, B, 1, [&] {
+            if (a.nblk > 1) w.commit(sW, wave, lane);
+            store_gx();
+            px_store(image(B.dsc_off), L.off, dzp);
+            px_load(xb, image(B.c1_off), L.off);
+          }))
+        return;
+      proj();
+      apply(dz, xa);
+      __syncthreads();
+      to_canvas(dcp);
+      __syncthreads();
+      // ---- conv2 data gradient, BN1 + ReLU backward -> dc1
+      zero(acc);
+      conv3x3<C, true>(canvas + L.cr, canvas, wr, fq, acc, [](auto) {});
+      px_arrange(xb);
+      if (!exchange_of(G{}, Relu{}, std::true_type{}, acc, xb, cf1, c0, red_w, B, 0, [&] { px_store(image(B.dc2_off), L.off, dcp); })) return;
+      apply(acc, xb);
+      to_canvas(dcp);
+      __syncthreads();
+      px_store(image(B.dc1_off), L.off, dcp);
+      // ---- conv1 data gradient
+      conv1();
+#pragma unroll
+      for (int nt = 0; nt < NTI; ++nt)
+#pragma unroll
+        for (int j = 0; j < TI; ++j) out[j][nt] = pack4(da[j][nt]);
+    }
+    store(out);
+  }
   if (me == 0 && tid == 0) *tagp = tag0 + phase;
 }
 
@@ -505,45 +718,56 @@ hipError_t launch_basic(K kernel, int lds, int g, const ResArgs& a, hipStream_t 
   kernel<<<dim3((unsigned)(a.nmem * g)), RG_NT, (size_t)lds, stream>>>(b);
   return hipGetLastError();
 }
-
-}  // namespace
-
-bool resident_basic_shape(int kind, int C, int H, int W) {
-  return (kind == 0 || kind == 2) && ((C == 16 && H == 32 && W == 32) || (C == 32 && H == 16 && W == 16) || (C == 64 && H == 8 && W == 8));
+template <int C, bool LEAD>
+hipError_t fwd_c(int kind, int g, const ResArgs& a, bool infer, hipStream_t stream) {
+  if (infer) return launch_basic(k_basic_forward<C, false, true, LEAD>, basic_fwd_lds<C, true, LEAD>(), g, a, stream);
+  return kind == 2 ? launch_basic(k_basic_forward<C, true, false, LEAD>, basic_fwd_lds<C, false, LEAD>(), g, a, stream)
+                   : launch_basic(k_basic_forward<C, false, false, LEAD>, basic_fwd_lds<C, false, LEAD>(), g, a, stream);
 }
-hipError_t resident_basic_prepare() {
+template <int C, bool LEAD>
+hipError_t bwd_c(int kind, int g, const ResArgs& a, hipStream_t stream) {
+  return kind == 2 ? launch_basic(k_basic_backward<C, true, LEAD>, basic_bwd_lds<C, LEAD>(), g, a, stream)
+                   : launch_basic(k_basic_backward<C, false, LEAD>, basic_bwd_lds<C, LEAD>(), g, a, stream);
+}
+template <int C, bool LEAD>
+hipError_t prepare_c() {
   const void* const kernels[] = {
-      reinterpret_cast<const void*>(k_basic_forward<16, false, false>), reinterpret_cast<const void*>(k_basic_forward<32, false, false>),
-      reinterpret_cast<const void*>(k_basic_forward<64, false, false>), reinterpret_cast<const void*>(k_basic_forward<16, false, true>),
-      reinterpret_cast<const void*>(k_basic_forward<32, false, true>),  reinterpret_cast<const void*>(k_basic_forward<64, false, true>),
-      reinterpret_cast<const void*>(k_basic_forward<16, true, false>),  reinterpret_cast<const void*>(k_basic_forward<32, true, false>),
-      reinterpret_cast<const void*>(k_basic_forward<64, true, false>),  reinterpret_cast<const void*>(k_basic_backward<16, false>),
-      reinterpret_cast<const void*>(k_basic_backward<32, false>),       reinterpret_cast<const void*>(k_basic_backward<64, false>),
-      reinterpret_cast<const void*>(k_basic_backward<16, true>),        reinterpret_cast<const void*>(k_basic_backward<32, true>),
-      reinterpret_cast<const void*>(k_basic_backward<64, true>)};
+      reinterpret_cast<const void*>(k_basic_forward<C, false, false, LEAD>), reinterpret_cast<const void*>(k_basic_forward<C, false, true, LEAD>),
+      reinterpret_cast<const void*>(k_basic_forward<C, true, false, LEAD>), reinterpret_cast<const void*>(k_basic_backward<C, false, LEAD>),
+      reinterpret_cast<const void*>(k_basic_backward<C, true, LEAD>)};
   for (const void* f : kernels) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
-template <int C>
-static hipError_t fwd_c(int kind, int g, const ResArgs& a, bool infer, hipStream_t stream) {
-  if (infer) return launch_basic(k_basic_forward<C, false, true>, basic_fwd_lds<C, true>(), g, a, stream);
-  return kind == 2 ? launch_basic(k_basic_forward<C, true, false>, basic_fwd_lds<C, false>(), g, a, stream)
-                   : launch_basic(k_basic_forward<C, false, false>, basic_fwd_lds<C, false>(), g, a, stream);
+static_assert(basic_fwd_lds<64, false, true>() <= 160 * 1024 && basic_fwd_lds<32, false, true>() <= 160 * 1024 && basic_bwd_lds<64, true>() <= 160 * 1024, "LDS of a CU");
+
+}  // namespace
+
+bool resident_basic_shape(int kind, int C, int H, int W) {
+  return (kind == 0 || kind == 2) && ((C == 16 && H == 32 && W == 32) || (C == 32 && H == 16 && W == 16) || (C == 64 && H == 8 && W == 8));
 }
-template <int C>
-static hipError_t bwd_c(int kind, int g, const ResArgs& a, hipStream_t stream) {
-  return kind == 2 ? launch_basic(k_basic_backward<C, true>, basic_bwd_lds<C>(), g, a, stream)
-                   : launch_basic(k_basic_backward<C, false>, basic_bwd_lds<C>(), g, a, stream);
+bool resident_lead_shape(int kind, int c_in, int c_out, int h_out, int w_out) {
+  return c_out >= 32 && c_in * 2 == c_out && resident_basic_shape(kind, c_out, h_out, w_out);
+}
+hipError_t resident_basic_prepare() {
+  hipError_t e = prepare_c<16, false>();
+  if (e == hipSuccess) e = prepare_c<32, false>();
+  if (e == hipSuccess) e = prepare_c<64, false>();
+  if (e == hipSuccess) e = prepare_c<32, true>();
+  if (e == hipSuccess) e = prepare_c<64, true>();
+  return e;
 }
 hipError_t launch_basic_forward(int kind, int g, int C, const ResArgs& a, bool infer, hipStream_t stream) {
-  if (kind == 2 && infer) return hipErrorInvalidValue;
-  return C == 16 ? fwd_c<16>(kind, g, a, infer, stream) : C == 32 ? fwd_c<32>(kind, g, a, infer, stream) : fwd_c<64>(kind, g, a, infer, stream);
+  if ((kind == 2 && infer) || (a.lead && C == 16)) return hipErrorInvalidValue;
+  if (a.lead) return C == 32 ? fwd_c<32, true>(kind, g, a, infer, stream) : fwd_c<64, true>(kind, g, a, infer, stream);
+  return C == 16 ? fwd_c<16, false>(kind, g, a, infer, stream) : C == 32 ? fwd_c<32, false>(kind, g, a, infer, stream) : fwd_c<64, false>(kind, g, a, infer, stream);
 }
 hipError_t launch_basic_backward(int kind, int g, int C, const ResArgs& a, hipStream_t stream) {
-  return C == 16 ? bwd_c<16>(kind, g, a, stream) : C == 32 ? bwd_c<32>(kind, g, a, stream) : bwd_c<64>(kind, g, a, stream);
+  if (a.lead && C == 16) return hipErrorInvalidValue;
+  if (a.lead) return C == 32 ? bwd_c<32, true>(kind, g, a, stream) : bwd_c<64, true>(kind, g, a, stream);
+  return C == 16 ? bwd_c<16, false>(kind, g, a, stream) : C == 32 ? bwd_c<32, false>(kind, g, a, stream) : bwd_c<64, false>(kind, g, a, stream);
 }
 
 }  // namespace hpf
