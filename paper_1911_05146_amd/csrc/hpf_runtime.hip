@@ -36,6 +36,9 @@ hpf_status fail(hpf_status st, const char* fmt, ...) {
 }
 
 constexpr size_t ALIGN = 256;
+// Regions of the micro-batches: 64 KiB, so that their place does not depend on the sizes of the tables in front of them.  ResNet-1001 partition, 8 regions
+// from offsets of 256 bytes / 4 KiB / 64 KiB / 2 MiB (the kernels the same): 951.6 / 954 / 947.9 / 961 us.
+constexpr size_t REGION_ALIGN = 64 * 1024;
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 int round_up32(int v) { return (v + 31) / 32 * 32; }
 
@@ -558,7 +561,7 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
     }
     if (P.splitk_floats) P.splitk_off = alloc(P.splitk_floats * sizeof(float)).off;
   }
-  P.mb_bytes = mo;
+  P.mb_bytes = (mo + REGION_ALIGN - 1) / REGION_ALIGN * REGION_ALIGN;
 
   // ---- deferred weight-gradient items (bf16 mode)
   if (P.dt == DT_BF16) {
@@ -684,6 +687,7 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
   P.abort_off = g;  g += align_up(sizeof(int));
   P.running_off = g; g += align_up(P.n_running * sizeof(float));
   P.bn_table_off = g; g += align_up(P.bn_table.size() * sizeof(BnRunDesc));
+  g = (g + REGION_ALIGN - 1) / REGION_ALIGN * REGION_ALIGN;
   P.mb_off = g;     g += P.mb_bytes * (size_t)d.num_microbatches;
   P.arena_bytes = g;
   return HPF_OK;
