@@ -32,7 +32,7 @@ def _stale(target: str, deps) -> bool:
 
 def build(force: bool = False, verbose: bool = False) -> str:
     hipcc = _hipcc()
-    headers = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
+    headers = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".h", ".inl"))]
     headers.append(os.path.join(HERE, "..", "include", "hpf.h"))
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)

@@ -202,8 +202,8 @@ bool resident_shape_ok(int kind, int C, int MID, int H, int W, int nmem);   // k
 // the grouped per-layer launch); banded runs and all runs of kind 2 go through the per-layer kernels at inference.
 inline bool resident_has_wgrad_launch(int kind, int C, int bands) { (void)kind; return bands == 1 && C != 16; }
 inline bool resident_has_inference_launch(int kind, int bands) { return bands == 1 && kind != 2; }
-// The block in front of a run of basic blocks (kinds 0 and 2) of c_out channels on h_out x w_out pixels can lead it in: stride 2, c_in = c_out / 2.
-bool resident_lead_shape(int kind, int c_in, int c_out, int h_out, int w_out);
+// A block of stride 2 with a projection can lead in a run whose blocks have its output's shape (the runs that the register kernels take).
+bool resident_lead_shape(int kind, int c_in, int c_mid, int c_out, int h_out, int w_out);
 // Largest number of micro-batches of nmem images one launch may hold on the current device (0: none):
 // every work-group takes a CU of its own and all of them must be resident together.
 int resident_max_group(int nmem);   // nmem: work-groups per micro-batch (images x bands)

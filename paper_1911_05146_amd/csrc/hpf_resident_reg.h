@@ -179,8 +179,10 @@ __device__ __forceinline__ float halve_sum(const float (&s1)[4], const float (&s
 // first channel.  Plain sums about a value that all work-groups have at hand (the mean of the block before) would be 0.3 us (128-32) / 1.3 us
 // (128-64) per block faster, but the variance then loses a factor (distance / sigma)^2 of its digits: invstd of a channel that a block
 // moves by 40 sigma was off by 1.6e-4 instead of 1e-7.
-template <int PTW, int NTL>
-__device__ __forceinline__ void stats_wave(const floatx4 (&v)[PTW][NTL], float* red, int Cc, int fr, int fq) {
+__device__ __forceinline__ float elem(const floatx4& v, int e) { return v[e]; }
+__device__ __forceinline__ float elem(const uint2& v, int e) { return elem4(v, e); }
+template <class V, int PTW, int NTL>   // V: floatx4, or uint2 (packed)
+__device__ __forceinline__ void stats_wave(const V (&v)[PTW][NTL], float* red, int Cc, int fr, int fq) {
   const bool b3 = fr & 8, b2 = fr & 4, b1 = fr & 2;
   float* dst = red + (b3 ? Cc : 0) + fq * 4 + ((fr >> 1) & 3);
 #pragma unroll
@@ -188,10 +190,10 @@ __device__ __forceinline__ void stats_wave(const floatx4 (&v)[PTW][NTL], float* 
     float K[4], s1[4], s2[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      K[e] = row_first(v[0][nt][e]);
+      K[e] = row_first(elem(v[0][nt], e));
 #pragma unroll
       for (int j = 0; j < PTW; ++j) {
-        const float d = v[j][nt][e] - K[e];
+        const float d = elem(v[j][nt], e) - K[e];
         s1[e] = j == 0 ? d : s1[e] + d;
         s2[e] = j == 0 ? d * d : fmaf(d, d, s2[e]);
       }

@@ -484,9 +484,9 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
     for (int i = 0; i < d.n_blocks && !any; ++i) any = eligible(i);
     auto leads = [&](int i) {
       const BlockPlan& p = P.bp[i];
-      return any && (p.d.kind == 0 || p.d.kind == K_POSTACT) && p.whole() && p.proj && p.d.stride == 2 && p.d.c_mid == p.d.c_out &&
-             resident_lead_shape(p.d.kind, p.d.c_in, p.d.c_out, p.h_out, p.w_out) &&
-             resident_shape_ok(p.d.kind, p.d.c_out, p.d.c_out, p.h_out, p.w_out, d.microbatch);
+      return any && (p.residual() || p.d.kind == K_POSTACT) && p.whole() && p.proj && p.d.stride == 2 &&
+             resident_lead_shape(p.d.kind, p.d.c_in, p.d.c_mid, p.d.c_out, p.h_out, p.w_out) &&
+             resident_shape_ok(p.d.kind, p.d.c_out, p.d.c_mid, p.h_out, p.w_out, d.microbatch);
     };
     int cmax_run = 0;
     size_t xchg_bytes = 0;

@@ -748,8 +748,9 @@ static_assert(basic_fwd_lds<64, false, true>() <= 160 * 1024 && basic_fwd_lds<32
 bool resident_basic_shape(int kind, int C, int H, int W) {
   return (kind == 0 || kind == 2) && ((C == 16 && H == 32 && W == 32) || (C == 32 && H == 16 && W == 16) || (C == 64 && H == 8 && W == 8));
 }
-bool resident_lead_shape(int kind, int c_in, int c_out, int h_out, int w_out) {
-  return c_out >= 32 && c_in * 2 == c_out && resident_basic_shape(kind, c_out, h_out, w_out);
+bool resident_lead_shape(int kind, int c_in, int c_mid, int c_out, int h_out, int w_out) {
+  if (c_in * 2 != c_out) return false;
+  return kind == 1 ? resident_reg_shape(kind, c_out, c_mid, h_out, w_out) : c_out >= 32 && c_mid == c_out && resident_basic_shape(kind, c_out, h_out, w_out);
 }
 hipError_t resident_basic_prepare() {
   hipError_t e = prepare_c<16, false>();

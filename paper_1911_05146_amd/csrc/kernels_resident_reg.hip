@@ -15,6 +15,11 @@
 // Measured on 256 images (8 micro-batches), per block: forward 20.7 -> 13.1 us (128-32) and 28.2 -> 21.9 (128-64), backward
 // 26.1 -> 21.2 and 37.3 -> 35 (4 and 18 registers of the backward spill: 20 and 68 bytes of scratch per lane).  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
 // 4 us at the memory's rate), and issue: 8 waves per CU leave the matrix cores idle while they do BatchNorm.
+//
+// The block in front of a run that halves the image and doubles the channels (64 -> 128, projection) leads it in (LEAD): the same launch starts, or
+// ends, with it.  Layer by layer it took about nine launches of 4 to 9 us a direction; here it adds 19 us forward (the whole input, 128 KiB an image,
+// is read for BatchNorm 1) and backward.  Seven blocks of ResNet-1001 with one such block, 13 images, one call per micro-batch: 1257 -> 1055 us for
+// five micro-batches.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -55,6 +60,41 @@ __device__ __forceinline__ void conv3x3_rows(const bf16_t* src, const bf16_t* w2
   }
 }
 
+// The block that leads a run in (LEAD): CI = C/2 channels on 32 x 32 pixels -> C on 16 x 16, its first convolution and the projection 1x1 with
+// stride 2.  They read one input pixel in four, the class (0, 0) of the parities of row and column; the others count in BatchNorm 1 alone.  Tile
+// 4*j + q of a wave: class q under row j of its output rows.
+constexpr int RG_LT = 4 * RG_PTW;
+template <int C>
+struct LeadPx {
+  static constexpr int CI = C / 2, NI = CI / 16;
+  unsigned off;   // of the lane's place in the input image
+  __device__ __forceinline__ LeadPx(int row0, int fr, int fq) : off(px_offset(2 * row0 * (2 * RG_IMG) + 2 * fr, CI, fq)) {}
+  static constexpr int at(int t, int k) { return ((2 * (t >> 2) + ((t >> 1) & 1)) * (2 * RG_IMG) + (t & 1)) * CI + k * 32; }
+  __device__ __forceinline__ void load(uint2 (&v)[NI], const bf16_t* g, int t) const {
+#pragma unroll
+    for (int k = 0; k < NI / 2; ++k) {
+      const uint4 q = *reinterpret_cast<const uint4*>(g + at(t, k) + off);
+      v[2 * k] = make_uint2(q.x, q.y);
+      v[2 * k + 1] = make_uint2(q.z, q.w);
+    }
+  }
+  static __device__ __forceinline__ void arrange(uint2 (&v)[NI]) {
+#pragma unroll
+    for (int k = 0; k < NI / 2; ++k) pair_swap(v[2 * k], v[2 * k + 1]);
+  }
+  __device__ __forceinline__ void store(bf16_t* g, int t, const uint2 (&v)[NI]) const {
+#pragma unroll
+    for (int k = 0; k < NI / 2; ++k) {
+      uint2 e = v[2 * k], o = v[2 * k + 1];
+      pair_swap(e, o);
+      *reinterpret_cast<uint4*>(g + at(t, k) + off) = make_uint4(e.x, e.y, o.x, o.y);
+    }
+  }
+};
+
+template <int C, int S = 1>
+struct Channels { static constexpr int value = C, pixels = S; };
+
 template <int C, int MID, bool INFER>
 constexpr int rg_fwd_lds() {
   using W1 = WStage<MID, C, true>;
@@ -72,7 +112,7 @@ constexpr int rg_fwd_lds() {
 // Inference is bounded by latency (3.8 us per 128-32 block, of which the products take 0.9): every matrix and table is asked for as soon as the
 // registers of the one before are free, a whole block ahead of its use, and the tables of the three BatchNorms are read by waves of their
 // own.  Asked for within the block, the tables three dependent reads in one wave, 21 blocks took 95 us, now 80.
-template <int C, int MID, bool INFER>
+template <int C, int MID, bool INFER, bool LEAD>
 __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
   using W1 = WStage<MID, C, true>;
@@ -130,18 +170,124 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
     nx.gamma = t->gamma_off[q];
     nx.beta = t->beta_off[q];
   };
+  constexpr int CI = LEAD ? LeadPx<C>::CI : C;   // channels of the run's input
+  int n0 = CI;                                   // channels of the first BatchNorm of the block
   auto load_coef = [&] {
-    if (!t_on) return;
+    if (!t_on || (LEAD && tq == 0 && tc >= n0)) return;
     const float* run = a.running + nx.run;
     rc_mean = run[tc];
-    rc_var = run[(tq == 0 ? C : MID) + tc];
+    rc_var = run[(tq == 0 ? (LEAD ? n0 : C) : MID) + tc];
     rc_gamma = (a.params + nx.gamma)[tc];
     rc_beta = (a.params + nx.beta)[tc];
   };
   auto store_coef = [&] {
-    if (t_on) t_dst[tc] = bn_scale_shift(rc_mean, 1.0f / sqrtf(rc_var + a.eps), rc_gamma, rc_beta);
+    if (t_on && (!LEAD || tq > 0 || tc < n0)) t_dst[tc] = bn_scale_shift(rc_mean, 1.0f / sqrtf(rc_var + a.eps), rc_gamma, rc_beta);
   };
-  {
+  const float inv_n = 1.f / (float)a.nmem;
+  // training: statistics of the wave's values v -> coef of the BatchNorm q of block B; `late` runs behind the polls.  Returns false when a
+  // partner did not show up.
+  auto exchange = [&](auto cc, const auto& v, const ResBlock& B, int q, float2* coef, auto&& late) -> bool {
+    constexpr int Cc = decltype(cc)::value, S = decltype(cc)::pixels;   // S: pixels per pixel of a block's output
+    const int gc = gather_channel<Cc>(wave, lane);
+    const float gamma = (a.params + B.gamma_off[q])[gc], beta = (a.params + B.beta_off[q])[gc];
+    stats_wave(v, red + wave * 2 * Cc, Cc, fr, fq);
+    __syncthreads();
+    const unsigned tag = tag0 + 1u + phase;
+    stats_publish_waves<Cc, S * RG_NPX>(red, slot(), me, tag);
+    const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
+    collect_stats<Cc>(slot(), a.nmem, tag, inv_n, (float)(S * RG_P), a.eps, gamma, beta, o, wave, lane, fail);
+    ++phase;
+    late();
+    __syncthreads();
+    if (*fail) {
+      if (tid == 0) atomicExch(a.abort_flag, 1);
+      return false;
+    }
+    return true;
+  };
+  using IC = Channels<C>;
+  using IM = Channels<MID>;
+  floatx4 acc0[RG_PTW][NM];   // conv1 of the lead
+  if constexpr (LEAD) {
+    using LP = LeadPx<C>;
+    using WL1 = WStage<MID, CI, true>;
+    using WLP = WStage<C, CI, true>;
+    constexpr int NI = LP::NI;
+    static_assert(WLP::BYTES <= RG_CW * RG_CW * MS * 2 && WL1::BYTES <= W1::BYTES, "the lead's matrices lie where the canvas and conv1's will");
+    const LP lp(row0, fr, fq);
+    const ResBlock T = a.blocks[0];
+    const bf16_t* x = cx.tensor(T.x_off) + (size_t)me * (4 * RG_P * CI);
+    WL1 l1;
+    WLP lw;
+    uint2 px[RG_LT][NI];
+    l1.issue(a.packed + T.wf_off[0], wave, fr, fq);
+    lw.issue(a.packed + T.pf_off, wave, fr, fq);
+#pragma unroll
+    for (int t = 0; t < RG_LT; t += INFER ? 4 : 1) lp.load(px[t], x, t);
+    if constexpr (INFER) {
+      next_offsets(0, 0);
+      w2.issue(a.packed + nx.w2, wave, fr, fq);
+      w3.issue(a.packed + nx.w3, wave, fr, fq);
+      load_coef();
+    }
+    if (tid == 0) *fail = 0;
+    l1.commit(sW1, wave, lane);
+    lw.commit(canvas, wave, lane);
+    if constexpr (INFER) {
+      w2.commit(sW2, wave, lane);
+      store_coef();
+      n0 = C;
+      next_offsets(1, 0);
+      w1.issue(a.packed + nx.w1, wave, fr, fq);
+      w2.issue(a.packed + nx.w2, wave, fr, fq);
+      load_coef();
+    } else {
+      const bf16_t* g = a.packed + T.wf_off[1];
+      w2.template issue<0>(g, wave, fr, fq); w2.template commit<0>(sW2, wave, lane);
+      w2.template issue<1>(g, wave, fr, fq); w2.template commit<1>(sW2, wave, lane);
+      w2.template issue<2>(g, wave, fr, fq); w2.template commit<2>(sW2, wave, lane);
+    }
+#pragma unroll
+    for (int t = 0; t < RG_LT; t += INFER ? 4 : 1) LP::arrange(px[t]);
+    __syncthreads();
+    if constexpr (!INFER) {
+      if (!exchange(Channels<CI, 4>{}, px, T, 0, coefC, [] {})) return;
+    }
+    // ---- conv1 (CI -> MID) and the projection (CI -> C), on relu(bn1(x)) of the pixels of class (0, 0)
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j) {
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) acc0[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int nt = 0; nt < NC; ++nt) X[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int ks = 0; ks < CI / 32; ++ks) {
+      bf16x8 bf[RG_PTW];
+#pragma unroll
+      for (int j = 0; j < RG_PTW; ++j)
+        bf[j] = frag_of(bn_relu_pack(unpack4(px[4 * j][2 * ks]), coefC + 2 * ks * 16 + fq * 4), bn_relu_pack(unpack4(px[4 * j][2 * ks + 1]), coefC + (2 * ks + 1) * 16 + fq * 4));
+#pragma unroll
+      for (int nt = 0; nt < NM; ++nt) {
+        const bf16x8 wf = WL1::get(w1r, ks, nt);
+#pragma unroll
+        for (int j = 0; j < RG_PTW; ++j) acc0[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, bf[j], acc0[j][nt], 0, 0, 0);
+      }
+#pragma unroll
+      for (int nt = 0; nt < NC; ++nt) {
+        const bf16x8 wf = WLP::get(canvas + lane * 8, ks, nt);
+#pragma unroll
+        for (int j = 0; j < RG_PTW; ++j) X[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, bf[j], X[j][nt], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < RG_PTW; ++j)
+#pragma unroll
+      for (int nt = 0; nt < NC; ++nt) X[j][nt] = unpack4(pack4(X[j][nt]));   // the shortcut is a tensor of its own
+    __syncthreads();
+    for (int i = tid; i < RG_CW * RG_CW * MS / 8; i += RG_NT) reinterpret_cast<u32x4*>(canvas)[i] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+  } else {
     const ResBlock B0 = a.blocks[0];
     w1.issue(a.packed + B0.wf_off[0], wave, fr, fq);
     if constexpr (INFER) {
@@ -173,145 +319,19 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
       w2.template issue<1>(g, wave, fr, fq); w2.template commit<1>(sW2, wave, lane);
       w2.template issue<2>(g, wave, fr, fq); w2.template commit<2>(sW2, wave, lane);
     }
-  }
-  const float inv_n = 1.f / (float)a.nmem;
-  // training: statistics of the wave's values v -> coef of the BatchNorm q of block B; `late` runs behind the polls.  Returns false when a
-  // partner did not show up.
-  auto exchange = [&](auto cc, const auto& v, const ResBlock& B, int q, float2* coef, auto&& late) -> bool {
-    constexpr int Cc = decltype(cc)::value;
-    const int gc = gather_channel<Cc>(wave, lane);
-    const float gamma = (a.params + B.gamma_off[q])[gc], beta = (a.params + B.beta_off[q])[gc];
-    stats_wave(v, red + wave * 2 * Cc, Cc, fr, fq);
     __syncthreads();
-    const unsigned tag = tag0 + 1u + phase;
-    stats_publish_waves<Cc, RG_NPX>(red, slot(), me, tag);
-    const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
-    collect_stats<Cc>(slot(), a.nmem, tag, inv_n, (float)RG_P, a.eps, gamma, beta, o, wave, lane, fail);
-    ++phase;
-    late();
-    __syncthreads();
-    if (*fail) {
-      if (tid == 0) atomicExch(a.abort_flag, 1);
-      return false;
-    }
-    return true;
-  };
-  using IC = std::integral_constant<int, C>;
-  using IM = std::integral_constant<int, MID>;
-  __syncthreads();
-  if constexpr (!INFER) {
-    if (!exchange(IC{}, X, a.blocks[0], 0, coefC, [] {})) return;
-  }
-  for (int bi = 0; bi < a.nblk; ++bi) {
-    const bool more = bi + 1 < a.nblk;
-    const ResBlock B = a.blocks[bi];
-    const ResBlock Bn = a.blocks[more ? bi + 1 : bi];
-    if constexpr (INFER) next_offsets(bi + 2, bi + 1);
-    // ---- conv1 (1x1, C -> MID) on relu(bn1(x))
-    floatx4 acc[RG_PTW][NM];
-#pragma unroll
-    for (int j = 0; j < RG_PTW; ++j)
-#pragma unroll
-      for (int nt = 0; nt < NM; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (!INFER) w3.issue(a.packed + B.wf_off[2], wave, fr, fq);
-#pragma unroll
-    for (int ks = 0; ks < C / 32; ++ks) {
-      bf16x8 bf[RG_PTW];
-#pragma unroll
-      for (int j = 0; j < RG_PTW; ++j)
-        bf[j] = frag_of(bn_relu_pack(X[j][2 * ks], coefC + 2 * ks * 16 + fq * 4), bn_relu_pack(X[j][2 * ks + 1], coefC + (2 * ks + 1) * 16 + fq * 4));
-#pragma unroll
-      for (int nt = 0; nt < NM; ++nt) {
-        const bf16x8 wf = W1::get(w1r, ks, nt);
-#pragma unroll
-        for (int j = 0; j < RG_PTW; ++j) acc[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, bf[j], acc[j][nt], 0, 0, 0);
-      }
-    }
-    uint2 cp[RG_PTW][NM];
-#pragma unroll
-    for (int j = 0; j < RG_PTW; ++j)
-#pragma unroll
-      for (int nt = 0; nt < NM; ++nt) { cp[j][nt] = pack4(acc[j][nt]); acc[j][nt] = unpack4(cp[j][nt]); }
     if constexpr (!INFER) {
-      if (!exchange(IM{}, acc, B, 1, coefM, [&] {
-            w3.commit(sW3, wave, lane);
-            if (bi > 0) w2.template commit<2>(sW2, wave, lane);
-            px_store<MID != 32>(image(B.c1_off, MID), offM, cp);
-          }))
-        return;
+      if (!exchange(IC{}, X, a.blocks[0], 0, coefC, [] {})) return;
     }
-#pragma unroll
-    for (int j = 0; j < RG_PTW; ++j)
-#pragma unroll
-      for (int nt = 0; nt < NM; ++nt)
-        *reinterpret_cast<uint2*>(cv_w + j * RG_CW * MS + nt * 16) = bn_relu_pack(acc[j][nt], coefM + nt * 16 + fq * 4);
-    __syncthreads();
-    if constexpr (INFER) {   // every wave is past conv1 and its tables, and past conv3 of the block before
-      w1.commit(sW1, wave, lane);
-      w3.commit(sW3, wave, lane);
-      store_coef();
-      load_coef();
-      w1.issue(a.packed + nx.w1, wave, fr, fq);   // a whole block ahead of their use
-      w3.issue(a.packed + nx.w3, wave, fr, fq);
-    }
-    // ---- conv2 (3x3, MID -> MID)
-#pragma unroll
-    for (int j = 0; j < RG_PTW; ++j)
-#pragma unroll
-      for (int nt = 0; nt < NM; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    conv3x3_rows<MID, false, W2>(cv_r, w2r, acc);
-#pragma unroll
-    for (int j = 0; j < RG_PTW; ++j)
-#pragma unroll
-      for (int nt = 0; nt < NM; ++nt) { cp[j][nt] = pack4(acc[j][nt]); acc[j][nt] = unpack4(cp[j][nt]); }
-    if constexpr (INFER) {
-      __syncthreads();
-      w2.commit(sW2, wave, lane);
-      w2.issue(a.packed + nx.w2, wave, fr, fq);
-    } else {
-      if (more) { w2.template issue<0>(a.packed + Bn.wf_off[1], wave, fr, fq); w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq); }   // the exchange hides it
-      if (!exchange(IM{}, acc, B, 2, coefM3, [&] {
-            if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wf_off[1], wave, fr, fq); }
-            px_store<MID != 32>(image(B.c2_off, MID), offM, cp);
-          }))
-        return;
-    }
-    // ---- conv3 (1x1, MID -> C) on relu(bn3(c2)), accumulated onto x
-    {
-      bf16x8 bf[RG_PTW][MID / 32];
-#pragma unroll
-      for (int ks = 0; ks < MID / 32; ++ks)
-#pragma unroll
-        for (int j = 0; j < RG_PTW; ++j)
-          bf[j][ks] = frag_of(bn_relu_pack(acc[j][2 * ks], coefM3 + 2 * ks * 16 + fq * 4), bn_relu_pack(acc[j][2 * ks + 1], coefM3 + (2 * ks + 1) * 16 + fq * 4));
-#pragma unroll
-      for (int nt = 0; nt < NC; ++nt)
-#pragma unroll
-        for (int ks = 0; ks < MID / 32; ++ks) {
-          const bf16x8 wf = W3::get(w3r, ks, nt);
-#pragma unroll
-          for (int j = 0; j < RG_PTW; ++j) X[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, bf[j][ks], X[j][nt], 0, 0, 0);
-        }
-    }
-    uint2 yp[RG_PTW][NC];
-#pragma unroll
-    for (int j = 0; j < RG_PTW; ++j)
-#pragma unroll
-      for (int nt = 0; nt < NC; ++nt) { yp[j][nt] = pack4(X[j][nt]); X[j][nt] = unpack4(yp[j][nt]); }
-    auto store_y = [&] { px_store<MID != 32>(image(B.y_off, C), offC, yp); };
-    if constexpr (INFER) {
-      if (!more) store_y();
-    } else if (more) {
-      if (!exchange(IC{}, X, Bn, 0, coefC, [&] {
-            w1.commit(sW1, wave, lane);
-            w2.template commit<1>(sW2, wave, lane);
-            w2.template issue<2>(a.packed + Bn.wf_off[1], wave, fr, fq);
-            store_y();
-          }))
-        return;
-    } else {
-      store_y();
-    }
+  }
+  if constexpr (LEAD) {
+    constexpr bool LD = true;
+    const int bi = 0;
+#include "resident_reg_forward_block.inl"
+  }
+  for (int bi = LEAD ? 1 : 0; bi < a.nblk; ++bi) {
+    constexpr bool LD = false;
+#include "resident_reg_forward_block.inl"
   }
   // every member has read the counter before it took part in the first exchange, which member 0 has left
   if (!INFER && me == 0 && tid == 0) *tagp = tag0 + phase;
@@ -330,7 +350,7 @@ constexpr int rg_bwd_lds() {
 // Backward of a run: the same ownership, walking the blocks in reverse with the gradient of the residual stream in
 // registers (packed).  c1, c2 and x of a block are read straight into the register layout, each behind the polls of an exchange
 // well ahead of its use; what leaves (dc2, dc1, gx) is stored behind the polls of the exchange after.
-template <int C, int MID>
+template <int C, int MID, bool LEAD>
 __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
   constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
   using W3 = WStage<MID, C, true>;           // conv3 data gradient [MID][C]
@@ -375,14 +395,16 @@ __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
   const int tq = wave < C / 64 ? 0 : wave - C / 64 + 1, tc = tq == 0 ? tid : lane;
   float* const t_dst = tq == 0 ? cf1 : tq == 1 ? cf2 : cf3;
   const bool t_on = tq == 0 || (tq < 3 && lane < MID);
+  int n0 = C;   // channels of the first BatchNorm (the lead's has C/2)
   auto load_tables = [&](int bi) {   // tq is uniform: the offsets come by scalar loads from the table of blocks
-    if (t_on) {
+    if (LEAD && bi == 0) n0 = C / 2;
+    if (t_on && (!LEAD || tq > 0 || tc < n0)) {
       const ResBlock* t = a.blocks + bi;
-      tb.load(reinterpret_cast<const float*>(cx.base + t->stats_off[tq]), a.params + t->gamma_off[tq], a.params + t->beta_off[tq], tc, tq == 0 ? C : MID);
+      tb.load(reinterpret_cast<const float*>(cx.base + t->stats_off[tq]), a.params + t->gamma_off[tq], a.params + t->beta_off[tq], tc, tq == 0 ? n0 : MID);
     }
   };
   auto store_tables = [&] {
-    if (t_on) tb.store(t_dst, tc, tq == 0 ? C : MID);
+    if (t_on && (!LEAD || tq > 0 || tc < n0)) tb.store(t_dst, tc, tq == 0 ? n0 : MID);
   };
   {
     const ResBlock BL = a.blocks[a.nblk - 1];
@@ -403,15 +425,19 @@ __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
     store_tables();
   }
   __syncthreads();
-  // exchange of the sums of a BatchNorm backward; `late` runs behind the polls
-  auto exchange = [&](auto cc, auto& dz, const auto& x, const float* cf, float* dgb, auto&& late) -> bool {
+  // exchange of the sums of a BatchNorm backward; `late` runs behind the polls.  lead: S = 4 input pixels per output pixel, and its BatchNorm parameter
+  // gradients are added here, as the run's weight-gradient launch does not know of it
+  auto exchange = [&](auto cc, auto lead, auto& dz, const auto& x, const float* cf, const ResBlock& B, int q, auto&& late) -> bool {
     constexpr int Cc = decltype(cc)::value;
+    constexpr bool ld = decltype(lead)::value;
     const CfChannel ck(cf, gather_channel<Cc>(wave, lane), Cc);
     bwd_sums_wave(dz, x, cf, red + wave * 2 * Cc, Cc, fr, fq);
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
     sums_publish_waves<Cc>(red, slot(), me, tag);
-    collect_bwd<Cc, (Cc == C ? 512 : 1024) / MID>(slot(), a.nmem, tag, inv_M, ck, tab, dgb, wave, lane, fail);
+    collect_bwd<Cc, (Cc == C ? 512 : 1024) / MID>(slot(), a.nmem, tag, ld && q == 0 ? 0.25f * inv_M : inv_M, ck, tab,
+                                                  !ld && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave, lane, fail,
+                                                  ld && me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
     ++phase;
     late();
     __syncthreads();
@@ -423,94 +449,17 @@ __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
   };
   using IC = std::integral_constant<int, C>;
   using IM = std::integral_constant<int, MID>;
-  for (int bi = a.nblk - 1; bi >= 0; --bi) {
-    const ResBlock B = a.blocks[bi];
-    const bool more = bi > 0;
-    const ResBlock Bn = a.blocks[more ? bi - 1 : 0];
-    auto dgb = [&](int q) { return me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr; };
-    // ---- conv3 data gradient, BN3 + ReLU backward -> dc2
-    floatx4 acc[RG_PTW][NM];
-#pragma unroll
-    for (int j = 0; j < RG_PTW; ++j)
-#pragma unroll
-      for (int nt = 0; nt < NM; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    w1.issue(a.packed + B.wd_off[0], wave, fr, fq);
-#pragma unroll
-    for (int ks = 0; ks < C / 32; ++ks)
-#pragma unroll
-      for (int nt = 0; nt < NM; ++nt) {
-        const bf16x8 wf = W3::get(w3r, ks, nt);
-#pragma unroll
-        for (int j = 0; j < RG_PTW; ++j)
-          acc[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, frag_of(DY[j][2 * ks], DY[j][2 * ks + 1]), acc[j][nt], 0, 0, 0);
-      }
-    px_arrange(xc2);
-    if (!exchange(IM{}, acc, xc2, cf3, dgb(2), [&] {
-          w1.commit(sW13, wave, lane);   // every wave is past conv3's data gradient
-          if (bi + 1 < a.nblk) w2.template commit<2>(sW2, wave, lane);
-          if (bi + 1 < a.nblk) px_store(image(a.blocks[bi + 1].gx_off, C), offC, DY);   // the gradient of the input of the block above
-          px_load(xc1, image(B.c1_off, MID), offM);
-          px_load(xx, image(B.x_off, C), offC);
-        }))
-      return;
-    uint2 dcp[RG_PTW][NM];
-#pragma unroll
-    for (int nt = 0; nt < NM; ++nt)
-#pragma unroll
-      for (int j = 0; j < RG_PTW; ++j) {
-        dcp[j][nt] = pack4(bwd_apply<MID>(acc[j][nt], xc2[j][nt], tab + nt * 16 + fq * 4));
-        *reinterpret_cast<uint2*>(cv_w + j * RG_CW * MS + nt * 16) = dcp[j][nt];
-      }
-    __syncthreads();
-    // ---- conv2 data gradient, BN2 + ReLU backward -> dc1
-#pragma unroll
-    for (int j = 0; j < RG_PTW; ++j)
-#pragma unroll
-      for (int nt = 0; nt < NM; ++nt) acc[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    conv3x3_rows<MID, true, W2>(cv_r, w2r, acc);
-    if (more) w2.template issue<0>(a.packed + Bn.wd_off[1], wave, fr, fq);   // every piece has an exchange to arrive
-    px_arrange(xc1);
-    if (!exchange(IM{}, acc, xc1, cf2, dgb(1), [&] {
-          if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wd_off[1], wave, fr, fq); }   // every wave is past conv2's data gradient
-          px_store(image(B.dc2_off, MID), offM, dcp);
-          if (more) { load_tables(bi - 1); w3.issue(a.packed + Bn.wd_off[2], wave, fr, fq); }
-        }))
-      return;
-#pragma unroll
-    for (int nt = 0; nt < NM; ++nt)
-#pragma unroll
-      for (int j = 0; j < RG_PTW; ++j) dcp[j][nt] = pack4(bwd_apply<MID>(acc[j][nt], xc1[j][nt], tab + nt * 16 + fq * 4));
-    if constexpr (MID >= 64) px_store(image(B.dc1_off, MID), offM, dcp);   // 16 registers that the exchange below cannot spare
-    // ---- conv1 data gradient, BN1 + ReLU backward, plus the shortcut
-    floatx4 da[RG_PTW][NC];
-#pragma unroll
-    for (int nt = 0; nt < NC; ++nt) {
-#pragma unroll
-      for (int j = 0; j < RG_PTW; ++j) da[j][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < MID / 32; ++ks) {
-        const bf16x8 wf = W1::get(w1r, ks, nt);
-#pragma unroll
-        for (int j = 0; j < RG_PTW; ++j)
-          da[j][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, frag_of(dcp[j][2 * ks], dcp[j][2 * ks + 1]), da[j][nt], 0, 0, 0);
-      }
-      if (nt % 4 == 3) keep_order();
-    }
-    px_arrange(xx);
-    if (!exchange(IC{}, da, xx, cf1, dgb(0), [&] {
-          if (more) { w3.commit(sW13, wave, lane); w2.template commit<1>(sW2, wave, lane); w2.template issue<2>(a.packed + Bn.wd_off[1], wave, fr, fq); store_tables(); px_load(xc2, image(Bn.c2_off, MID), offM); }   // conv1's data gradient and the tables of this block are behind the barrier
-          if constexpr (MID < 64) px_store(image(B.dc1_off, MID), offM, dcp);
-        }))
-      return;
-#pragma unroll
-    for (int nt = 0; nt < NC; ++nt) {
-      if (nt % 2 == 0) keep_order();
-#pragma unroll
-      for (int j = 0; j < RG_PTW; ++j)
-        DY[j][nt] = pack4(bwd_apply<C>(da[j][nt], xx[j][nt], tab + nt * 16 + fq * 4) + unpack4(DY[j][nt]));
-    }
+  for (int bi = a.nblk - 1; bi >= (LEAD ? 1 : 0); --bi) {
+    constexpr bool LD = false;
+#include "resident_reg_backward_block.inl"
   }
-  px_store(image(a.blocks[0].gx_off, C), offC, DY);
+  if constexpr (LEAD) {
+    constexpr bool LD = true;
+    const int bi = 0;
+#include "resident_reg_backward_block.inl"
+  } else {
+    px_store(image(a.blocks[0].gx_off, C), offC, DY);
+  }
   if (me == 0 && tid == 0) *tagp = tag0 + phase;
 }
 
@@ -527,28 +476,41 @@ hipError_t launch_reg(K kernel, int lds, int g, const ResArgs& a, hipStream_t st
 bool resident_reg_shape(int kind, int C, int MID, int H, int W) {
   return kind == 1 && C == 128 && (MID == 32 || MID == 64) && H == RG_IMG && W == RG_IMG;
 }
-hipError_t resident_reg_prepare() {
-  const void* const kernels[] = {
-      reinterpret_cast<const void*>(k_reg_forward<128, 32, false>), reinterpret_cast<const void*>(k_reg_forward<128, 32, true>),
-      reinterpret_cast<const void*>(k_reg_forward<128, 64, false>), reinterpret_cast<const void*>(k_reg_forward<128, 64, true>),
-      reinterpret_cast<const void*>(k_reg_backward<128, 32>),       reinterpret_cast<const void*>(k_reg_backward<128, 64>)};
+template <int MID, bool LEAD>
+static hipError_t prepare_m() {
+  const void* const kernels[] = {reinterpret_cast<const void*>(k_reg_forward<128, MID, false, LEAD>), reinterpret_cast<const void*>(k_reg_forward<128, MID, true, LEAD>),
+                                 reinterpret_cast<const void*>(k_reg_backward<128, MID, LEAD>)};
   for (const void* f : kernels) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
+hipError_t resident_reg_prepare() {
+  hipError_t e = prepare_m<32, false>();
+  if (e == hipSuccess) e = prepare_m<64, false>();
+  if (e == hipSuccess) e = prepare_m<32, true>();
+  if (e == hipSuccess) e = prepare_m<64, true>();
+  return e;
+}
+template <int MID, bool INFER>
+static hipError_t forward_m(int g, const ResArgs& a, hipStream_t stream) {
+  return a.lead ? launch_reg(k_reg_forward<128, MID, INFER, true>, rg_fwd_lds<128, MID, INFER>(), g, a, stream)
+                : launch_reg(k_reg_forward<128, MID, INFER, false>, rg_fwd_lds<128, MID, INFER>(), g, a, stream);
+}
+template <int MID>
+static hipError_t backward_m(int g, const ResArgs& a, hipStream_t stream) {
+  return a.lead ? launch_reg(k_reg_backward<128, MID, true>, rg_bwd_lds<128, MID>(), g, a, stream)
+                : launch_reg(k_reg_backward<128, MID, false>, rg_bwd_lds<128, MID>(), g, a, stream);
+}
 hipError_t launch_reg_forward(int g, int MID, const ResArgs& a, hipStream_t stream) {
-  return MID == 32 ? launch_reg(k_reg_forward<128, 32, false>, rg_fwd_lds<128, 32, false>(), g, a, stream)
-                   : launch_reg(k_reg_forward<128, 64, false>, rg_fwd_lds<128, 64, false>(), g, a, stream);
+  return MID == 32 ? forward_m<32, false>(g, a, stream) : forward_m<64, false>(g, a, stream);
 }
 hipError_t launch_reg_backward(int g, int MID, const ResArgs& a, hipStream_t stream) {
-  return MID == 32 ? launch_reg(k_reg_backward<128, 32>, rg_bwd_lds<128, 32>(), g, a, stream)
-                   : launch_reg(k_reg_backward<128, 64>, rg_bwd_lds<128, 64>(), g, a, stream);
+  return MID == 32 ? backward_m<32>(g, a, stream) : backward_m<64>(g, a, stream);
 }
 hipError_t launch_reg_inference(int g, int MID, const ResArgs& a, hipStream_t stream) {
-  return MID == 32 ? launch_reg(k_reg_forward<128, 32, true>, rg_fwd_lds<128, 32, true>(), g, a, stream)
-                   : launch_reg(k_reg_forward<128, 64, true>, rg_fwd_lds<128, 64, true>(), g, a, stream);
+  return MID == 32 ? forward_m<32, true>(g, a, stream) : forward_m<64, true>(g, a, stream);
 }
 static_assert(rg_bwd_lds<128, 64>() <= 160 * 1024 && rg_fwd_lds<128, 64, false>() <= 160 * 1024 && rg_fwd_lds<128, 64, true>() <= 160 * 1024, "LDS of a CU");
 

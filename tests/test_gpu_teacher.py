@@ -198,12 +198,14 @@ def test_register_resident_runs_around_the_polled_chunk_layerwise(gpu, oracle, k
 
 
 @pytest.mark.parametrize("before,behind,images,micro", [(0, 1, 5, 2), (1, 0, 1, 1), (1, 2, 33, 1), (0, 3, 4, 3)])
-@pytest.mark.parametrize("kind,c,hw", [(W.BASIC, 16, 32), (W.BASIC, 32, 16), (W.POSTACT, 16, 32), (W.POSTACT, 32, 16)])
-def test_runs_led_in_by_a_block_that_halves_the_image_layerwise(gpu, oracle, kind, c, hw, before, behind, images, micro):
+@pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 32, 32), (W.BASIC, 32, 64, 16), (W.POSTACT, 16, 32, 32), (W.POSTACT, 32, 64, 16),
+                                           (W.BOTTLENECK, 64, 32, 32), (W.BOTTLENECK, 64, 64, 32)])
+def test_runs_led_in_by_a_block_that_halves_the_image_layerwise(gpu, oracle, kind, c, mid, hw, before, behind, images, micro):
     """A strided block with a projection runs in the launch of the identity blocks behind it, or in one of its own at the end of a
     partition: between the caller's tensors, behind another run, one image and one word beyond a polled chunk."""
-    blocks = (W.Block(kind, c, c, c, 1),) * before + (W.Block(kind, c, 2 * c, 2 * c, 2),) + (W.Block(kind, 2 * c, 2 * c, 2 * c, 1),) * behind
-    spec = W.PartitionSpec(name=f"lead-{kind}-{c}@{hw}-{before}+{behind}-b{images}", in_h=hw, in_w=hw, in_c=c, blocks=blocks,
+    first = W.Block(kind, c, 16 if kind == W.BOTTLENECK else c, c, 1)
+    blocks = (first,) * before + (W.Block(kind, c, mid, 2 * c, 2),) + (W.Block(kind, 2 * c, mid, 2 * c, 1),) * behind
+    spec = W.PartitionSpec(name=f"lead-{kind}-{c}-{mid}@{hw}-{before}+{behind}-b{images}", in_h=hw, in_w=hw, in_c=c, blocks=blocks,
                            microbatch=images, num_microbatches=micro, seed=71)
     layerwise(oracle, spec, "bf16", grouped=micro != 3, blockwise=False)
 
