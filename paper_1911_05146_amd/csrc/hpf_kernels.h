@@ -51,6 +51,9 @@ struct PackDesc {
   unsigned long long w_off;   // fp32 master [T][Cin][Cout] in the parameter vector
   unsigned long long wf_off;  // bf16 [Cout][Kf]  k = tap*Cin + c     (forward operand)
   unsigned long long wd_off;  // bf16 [Cin][Kd]   k = tap*Cout + n    (data-gradient operand); ~0 = none
+  // The same operands once more in the order that the register-resident kernels read (fragment_at); ~0 = none
+  unsigned long long ff_off = ~0ull, fd_off = ~0ull;
+  int f_perm = 0, d_perm = 0;
   int T, Cin, Cout, Kf, Kd;
   // parameters that are no convolution weights: those between this convolution's and the next's, and (first convolution of the
   // table) first_len ones from the start of the vector
@@ -223,6 +226,19 @@ hipError_t launch_resident_wgrad(int kind, int g, int C, int MID, const ResArgs&
 // Inference forward of a run (BatchNorm by the running statistics in a.running): only the output of the last block
 // is written; no exchange, so there is no limit on the work-groups of a launch (g <= MAX_GROUP micro-batches).
 hipError_t launch_resident_inference(int kind, int g, int C, int MID, const ResArgs& a, hipStream_t stream);
+// Runs whose kernels read their packed weights in fragment order; and whether the columns of a convolution's operand are permuted
+bool resident_reads_fragments(int kind, int C, int MID, int H, int W);
+inline bool resident_permutes(int kind, int C, int R) { return kind == 1 && C == 128 && R == 1; }
+// The order of MFMA fragments: a [rows][len] matrix (rows a multiple of 16, len of 32) as pieces of 16 rows x 32 columns, 1 KiB each, step of the
+// reduction by step; in a piece the 16 bytes of lane (fr, fq), row fr and columns fq*8 ... + 7, lie at (fq*16 + fr)*8.  Permuted: columns {0, 16} +
+// fq*4 ... + 3.  So the loads of a wave are whole cache lines.  With the rows of the matrix, 16 segments of 64 bytes a load, a load held the CU's memory
+// pipeline, and the words of the exchanges behind it, for about 50 cycles instead of 16: four images through ResNet-110 (inference) 241 -> 220 us,
+// four chained partitions of it 3870 -> 3657, ResNet-110 v1 whole 1333 -> 1276, a sixteenth of ResNet-1001 951 -> 939.
+// The element of (row, col); col a multiple of 4 (permuted) or 8.
+__host__ __device__ inline size_t fragment_at(int row, int col, int rows, bool permuted) {
+  const int k = col & 31, fq = permuted ? (k & 15) >> 2 : k >> 3, e = permuted ? (k >> 4) * 4 : 0;
+  return ((size_t)(col >> 5) * (rows >> 4) + (row >> 4)) * 512 + (fq * 16 + (row & 15)) * 8 + e;
+}
 // The register form of the same launches (kernels_resident_reg.hip), called by the launchers above for the shapes it covers.
 bool resident_reg_shape(int kind, int C, int MID, int H, int W);
 hipError_t resident_reg_prepare();

@@ -17,7 +17,7 @@ struct Geo {
   static constexpr int NPX = PTW * 16;
   // tile j of a wave in the canvas, from its first one
   static constexpr int tile_off(int j) { return C == 16 ? ((j >> 1) * CW + (j & 1) * 16) * MS : j * CW * MS; }
-  using W = WStage<C, (9 * C + 31) / 32 * 32, false>;
+  using W = WStage<C, (9 * C + 31) / 32 * 32>;
   static constexpr int CANVAS = CW * CW * MS * 2;                       // bytes
 };
 
@@ -88,10 +88,10 @@ template <int C>
 struct Lead {
   static constexpr int CI = C / 2;
   using I = Geo<CI>;                                             // of the block's input
-  using W1 = WStage<C, (9 * CI + 31) / 32 * 32, false>;          // forward: conv1 and projection (packed: zero beyond CI)
-  using WP = WStage<C, 32, false>;
-  using D1 = WStage<CI, 9 * C, false>;                           // their data gradients
-  using DP = WStage<CI, C, false>;
+  using W1 = WStage<C, (9 * CI + 31) / 32 * 32>;          // forward: conv1 and projection (packed: zero beyond CI)
+  using WP = WStage<C, 32>;
+  using D1 = WStage<CI, 9 * C>;                           // their data gradients
+  using DP = WStage<CI, C>;
   static constexpr int FWD_LDS = I::CANVAS + W1::BYTES + WP::BYTES + CI * 8, BWD_LDS = D1::BYTES + DP::BYTES;
   // Input pixels by the parity (pr, pc) of their row and column: a class has the shape of the output image, so its tiles of 16 pixels are the
   // output's.  A tile of class (pr, pc) takes (1 + pr)*(1 + pc) filter taps.  A wave's tiles j: C = 32: both its output rows, all four classes;

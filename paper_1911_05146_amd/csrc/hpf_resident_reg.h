@@ -98,11 +98,11 @@ __device__ __forceinline__ void px_store(bf16_t* g, unsigned off, const uint2 (&
 __device__ __forceinline__ floatx4 unpack4(const uint2& q) { return floatx4{bf_lo(q.x), bf_hi(q.x), bf_lo(q.y), bf_hi(q.y)}; }
 
 // ---- weights: a [ROWS][LEN] bf16 matrix staged in LDS by the whole work-group, MFMA fragment by fragment (64 lanes x 16 bytes, so a
-// fragment read is one conflict-free 1 KiB access at a constant offset and staging needs no per-unit addresses).  issue()
-// asks for this wave's fragments, commit() stores them.  PERM: the reduction order of a register operand, i.e. lane (fr, fq) of
-// step kt holds columns kt*32 + {0, 16} + fq*4 + 0..3 of its row.
+// fragment read is one conflict-free 1 KiB access at a constant offset and staging needs no per-unit addresses), as it lies in memory
+// (fragment_at).  issue() asks for this wave's fragments, commit() stores them.  The operand of a convolution that reduces over the channels of a
+// register tensor is packed permuted: lane (fr, fq) of step kt holds columns kt*32 + {0, 16} + fq*4 + 0..3 of its row.
 // PARTS: the matrix travels in that many pieces, so that fewer registers hold what is on its way.
-template <int ROWS, int LEN, bool PERM, int PARTS = 1>
+template <int ROWS, int LEN, int PARTS = 1>
 struct WStage {
   static constexpr int KT = LEN / 32, NT = ROWS / 16, FR = KT * NT, FP = FR / PARTS, NU = (FP + RG_NW - 1) / RG_NW;
   static constexpr int BYTES = FR * 1024;
@@ -114,19 +114,13 @@ struct WStage {
   __device__ __forceinline__ void issue_third(const bf16_t* w, int wave, int fr, int fq) { issue<0>(w, wave, fr, fq, NU * I / 3, NU * (I + 1) / 3); }
   template <int PART = 0>
   __device__ __forceinline__ void issue(const bf16_t* w, int wave, int fr, int fq, int i0 = 0, int i1 = NU) {
-    const unsigned off = (unsigned)(fr * LEN + fq * (PERM ? 4 : 8));
+    const unsigned off = (unsigned)((fq * 16 + fr) * 8);
 #pragma unroll
     for (int i = 0; i < NU; ++i) {
       if (i < i0 || i >= i1) continue;
       const int f = PART * FP + wave + i * RG_NW;
       if (FP % RG_NW == 0 || f < (PART + 1) * FP) {
-        const bf16_t* g = w + (f % NT) * 16 * LEN + (f / NT) * 32;
-        if constexpr (PERM) {
-          const u32x2 lo = *reinterpret_cast<const u32x2*>(g + off), hi = *reinterpret_cast<const u32x2*>(g + 16 + off);
-          st[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
-        } else {
-          st[i] = *reinterpret_cast<const u32x4*>(g + off);
-        }
+        st[i] = *reinterpret_cast<const u32x4*>(w + f * 512 + off);
       }
     }
   }

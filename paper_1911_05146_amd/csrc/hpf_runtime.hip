@@ -51,6 +51,7 @@ struct ConvPlan {
   int cin = 0, cout = 0, R = 1, stride = 1, h_in = 0, w_in = 0, h_out = 0, w_out = 0;
   size_t w_off = 0;                 // fp32 master / gradient offset (floats)
   size_t wf_off = 0, wd_off = 0;    // packed bf16 offsets (elements)
+  int pack = -1;                    // its entry in the table of packed weights
   int Kf = 0, Kd = 0;
 };
 
@@ -229,6 +230,7 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
       cv.wd_off = pk; pk += (size_t)cv.cin * cv.Kd; pk = (pk + 7) / 8 * 8;
       pd.wd_off = cv.wd_off; pd.Kd = cv.Kd;
     }
+    cv.pack = (int)P.table.size();
     P.table.push_back(pd);
   };
   auto mk_conv = [&](int ci, int co, int R, int st, int hi, int wi) {
@@ -312,7 +314,7 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
     P.bfc_off = off; off += d.num_classes;
   }
   P.n_params = off;
-  P.packed_elems = pk;
+  P.packed_elems = pk;   // and behind them the copies in fragment order (resident runs)
   for (size_t i = 0; i < P.table.size(); ++i) {   // in the order of the parameter vector
     PackDesc& e = P.table[i];
     e.first_len = i == 0 ? (int)e.w_off : 0;
@@ -511,6 +513,17 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
           default: return RES_ERR_OUT;
         }
       };
+      // packed weights as the run's kernels read them: a copy of their own in the order of MFMA fragments for the register kernels
+      const bool frag = resident_reads_fragments(r.kind, r.C, r.MID, P.bp[i].h_out, P.bp[i].w_out);
+      auto operands = [&](const ConvPlan& cv, unsigned long long& f, unsigned long long& b) {
+        f = cv.wf_off; b = cv.wd_off;
+        if (!frag) return;
+        P.packed_elems = (P.packed_elems + 511) / 512 * 512;   // whole pieces
+        PackDesc& pd = P.table[cv.pack];
+        pd.f_perm = pd.d_perm = resident_permutes(r.kind, r.C, cv.R);
+        f = pd.ff_off = P.packed_elems; P.packed_elems += (size_t)cv.cout * cv.Kf;
+        b = pd.fd_off = P.packed_elems; P.packed_elems += (size_t)cv.cin * cv.Kd;
+      };
       for (int k = i; k < j; ++k) {
         const BlockPlan& p = P.bp[k];
         ResBlock rb{};
@@ -522,13 +535,14 @@ hpf_status build_plan(const hpf_partition_desc* desc, Plan& P) {
         rb.gx_off = res_loc(gx);
         for (int q = 0; q < p.nconv; ++q) {
           rb.stats_off[q] = p.bn[q].stats_off;
-          rb.wf_off[q] = p.cv[q].wf_off; rb.wd_off[q] = p.cv[q].wd_off; rb.w_off[q] = p.cv[q].w_off;
+          operands(p.cv[q], rb.wf_off[q], rb.wd_off[q]);
+          rb.w_off[q] = p.cv[q].w_off;
           rb.gamma_off[q] = p.bn[q].g_off; rb.beta_off[q] = p.bn[q].b_off;
           rb.dgb_off[q] = alloc(2 * (size_t)p.bn[q].C * sizeof(float)).off;
           rb.run_off[q] = p.bn[q].run_off;
         }
         if (p.proj) {
-          rb.pf_off = p.pj.wf_off; rb.pd_off = p.pj.wd_off;
+          operands(p.pj, rb.pf_off, rb.pd_off);
           if (p.d.kind == K_POSTACT) { rb.sc_off = res_loc(p.sc); rb.a1_off = res_loc(p.a[0]); rb.dsc_off = res_loc(p.dc[2]); }
         }
         P.res_blocks.push_back(rb);

@@ -272,6 +272,16 @@ __global__ __launch_bounds__(256) void k_copy16(u32x4* __restrict__ dst, const u
   if (blockIdx.x == 0 && (int)threadIdx.x < ntail) dtail[threadIdx.x] = stail[threadIdx.x];
 }
 
+// eight consecutive columns of a row, in the fragment order
+__device__ __forceinline__ void store_fragment(bf16_t* m, int row, int col, int rows, bool permuted, const uint4& v) {
+  if (permuted) {
+    *reinterpret_cast<uint2*>(m + fragment_at(row, col, rows, true)) = make_uint2(v.x, v.y);
+    *reinterpret_cast<uint2*>(m + fragment_at(row, col + 4, rows, true)) = make_uint2(v.z, v.w);
+  } else {
+    *reinterpret_cast<uint4*>(m + fragment_at(row, col, rows, false)) = v;
+  }
+}
+
 // bf16 operand copies of the convolution weights; STEP: behind the SGD step, which then needs no pass of its own (28 bytes per weight
 // instead of 24 + 12, and one launch).  grid (Y, n_convs): the Y blocks of a convolution share its 64 x 64 tiles of the fp32 master
 // [k = tap*Cin + c][n] round-robin.  A tile is updated as it is loaded, and both copies are written from LDS with 16-byte stores: the
@@ -346,6 +356,7 @@ __global__ __launch_bounds__(256) void k_sgd_pack(float* __restrict__ params, fl
         st.x = pack_bf16x2(tile[e8][r], tile[e8 + 1][r]); st.y = pack_bf16x2(tile[e8 + 2][r], tile[e8 + 3][r]);
         st.z = pack_bf16x2(tile[e8 + 4][r], tile[e8 + 5][r]); st.w = pack_bf16x2(tile[e8 + 6][r], tile[e8 + 7][r]);
         *reinterpret_cast<uint4*>(wf + (size_t)n * d.Kf + k) = st;
+        if (d.ff_off != ~0ull) store_fragment(packed + d.ff_off, n, k, d.Cout, d.f_perm, st);
       }
     }
     if (d.wd_off == ~0ull) continue;
@@ -360,9 +371,13 @@ __global__ __launch_bounds__(256) void k_sgd_pack(float* __restrict__ params, fl
         uint4 st;
         st.x = pack_bf16x2(q[0], q[1]); st.y = pack_bf16x2(q[2], q[3]); st.z = pack_bf16x2(q[4], q[5]); st.w = pack_bf16x2(q[6], q[7]);
         *reinterpret_cast<uint4*>(row + tap * d.Cout + n) = st;
+        if (d.fd_off != ~0ull) store_fragment(packed + d.fd_off, c, tap * d.Cout + n, d.Cin, d.d_perm, st);
       }
       if (tap == d.T - 1 && n0 + 64 >= d.Cout)              // padding
-        for (int p = d.T * d.Cout + e8; p < d.Kd; p += 64) *reinterpret_cast<uint4*>(row + p) = make_uint4(0u, 0u, 0u, 0u);
+        for (int p = d.T * d.Cout + e8; p < d.Kd; p += 64) {
+          *reinterpret_cast<uint4*>(row + p) = make_uint4(0u, 0u, 0u, 0u);
+          if (d.fd_off != ~0ull) store_fragment(packed + d.fd_off, c, p, d.Cin, d.d_perm, make_uint4(0u, 0u, 0u, 0u));
+        }
     }
   }
 }

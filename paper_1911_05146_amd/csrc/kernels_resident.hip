@@ -2527,6 +2527,8 @@ bool resident_shape_ok(int kind, int C, int MID, int H, int W, int nmem) {
   return fwd_lds(C, MID, P, nmem, &own) <= RES_LDS_BYTES && bwd_lds(C, MID, P, nmem, &own) <= RES_LDS_BYTES;
 }
 
+bool resident_reads_fragments(int kind, int C, int MID, int H, int W) { return resident_reg_shape(kind, C, MID, H, W) || resident_basic_shape(kind, C, H, W); }
+
 int resident_max_group(int nmem) {
   int dev = 0, cus = 0;
   if (nmem < 1 || hipGetDevice(&dev) != hipSuccess ||

@@ -97,9 +97,9 @@ struct Channels { static constexpr int value = C, pixels = S; };
 
 template <int C, int MID, bool INFER>
 constexpr int rg_fwd_lds() {
-  using W1 = WStage<MID, C, true>;
-  using W2 = WStage<MID, 9 * MID, false, 3>;
-  using W3 = WStage<C, MID, true>;
+  using W1 = WStage<MID, C>;
+  using W2 = WStage<MID, 9 * MID, 3>;
+  using W3 = WStage<C, MID>;
   const int w13 = INFER ? W1::BYTES + W3::BYTES : (W1::BYTES > W3::BYTES ? W1::BYTES : W3::BYTES);
   return RG_CW * RG_CW * (MID + 8) * 2 + W2::BYTES + w13 + (C + 2 * MID) * 8 + (INFER ? 0 : RG_NW * 2 * C * 4) + 16;
 }
@@ -115,9 +115,9 @@ constexpr int rg_fwd_lds() {
 template <int C, int MID, bool INFER, bool LEAD>
 __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
-  using W1 = WStage<MID, C, true>;
-  using W2 = WStage<MID, 9 * MID, false, INFER ? 1 : 3>;
-  using W3 = WStage<C, MID, true>;
+  using W1 = WStage<MID, C>;
+  using W2 = WStage<MID, 9 * MID, INFER ? 1 : 3>;
+  using W3 = WStage<C, MID>;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
   const int z = blockIdx.x % a.ngroup, me = blockIdx.x / a.ngroup;   // with g == 8 micro-batch z lives on XCD z
@@ -210,8 +210,8 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   floatx4 acc0[RG_PTW][NM];   // conv1 of the lead
   if constexpr (LEAD) {
     using LP = LeadPx<C>;
-    using WL1 = WStage<MID, CI, true>;
-    using WLP = WStage<C, CI, true>;
+    using WL1 = WStage<MID, CI>;
+    using WLP = WStage<C, CI>;
     constexpr int NI = LP::NI;
     static_assert(WLP::BYTES <= RG_CW * RG_CW * MS * 2 && WL1::BYTES <= W1::BYTES, "the lead's matrices lie where the canvas and conv1's will");
     const LP lp(row0, fr, fq);
@@ -340,9 +340,9 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
 // ------------------------------------------------------------------------------------------ backward
 template <int C, int MID>
 constexpr int rg_bwd_lds() {
-  using W3 = WStage<MID, C, true>;
-  using W2 = WStage<MID, 9 * MID, false, 3>;
-  using W1 = WStage<C, MID, true>;
+  using W3 = WStage<MID, C>;
+  using W2 = WStage<MID, 9 * MID, 3>;
+  using W1 = WStage<C, MID>;
   return RG_CW * RG_CW * (MID + 8) * 2 + W2::BYTES + (W1::BYTES > W3::BYTES ? W1::BYTES : W3::BYTES) + (4 * (C + 2 * MID) + 3 * C) * 4 +
          RG_NW * 2 * C * 4 + 16;
 }
@@ -353,9 +353,9 @@ constexpr int rg_bwd_lds() {
 template <int C, int MID, bool LEAD>
 __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
   constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
-  using W3 = WStage<MID, C, true>;           // conv3 data gradient [MID][C]
-  using W2 = WStage<MID, 9 * MID, false, 3>;    // conv2 data gradient [MID][9*MID]
-  using W1 = WStage<C, MID, true>;           // conv1 data gradient [C][MID]
+  using W3 = WStage<MID, C>;           // conv3 data gradient [MID][C]
+  using W2 = WStage<MID, 9 * MID, 3>;    // conv2 data gradient [MID][9*MID]
+  using W1 = WStage<C, MID>;           // conv1 data gradient [C][MID]
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
   const int z = blockIdx.x % a.ngroup, me = blockIdx.x / a.ngroup;   // with g == 8 micro-batch z lives on XCD z

@@ -2,8 +2,8 @@
 // run in (resident_reg_forward_block.inl).
 using LP = LeadPx<C>;
 constexpr int CI = LP::CI, NI = LP::NI;
-using WL1 = WStage<CI, MID, true>;   // conv1 data gradient [CI][MID]
-using WLP = WStage<CI, C, true>;     // projection data gradient [CI][C], staged where the canvas was
+using WL1 = WStage<CI, MID>;   // conv1 data gradient [CI][MID]
+using WLP = WStage<CI, C>;     // projection data gradient [CI][C], staged where the canvas was
 static_assert(WLP::BYTES <= RG_CW * RG_CW * MS * 2 && WL1::BYTES <= W1::BYTES, "the lead's matrices lie where the canvas and conv1's were");
 const LP lp(row0, fr, fq);
 WL1 l1;
