@@ -136,7 +136,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     const unsigned tag = tag0 + 1u + phase;
     stats_publish_waves<Cc, GV::NPX, GV::NPW>(red, slot(), me, tag);
     const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
-    collect_stats<Cc>(slot(), a.nmem, tag, inv_n, (float)GV::P, a.eps, gamma, beta, o, wave, lane, fail);
+    collect_stats<Cc, true>(slot(), a.nmem, tag, inv_n, (float)GV::P, a.eps, gamma, beta, o, wave, lane, fail);
     ++phase;
     late();
     __syncthreads();
@@ -425,7 +425,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
     sums_publish_waves<Cc, GV::NPW>(red, slot(), me, tag);
-    collect_bwd<Cc, 32>(slot(), a.nmem, tag, inv_M * (float)G::P / (float)GV::P, ck, tab, !D && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave,
+    collect_bwd<Cc, true, 32>(slot(), a.nmem, tag, inv_M * (float)G::P / (float)GV::P, ck, tab, !D && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave,
                         lane, fail, D && me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
     ++phase;
     late();
