@@ -242,9 +242,14 @@ __host__ __device__ inline size_t fragment_at(int row, int col, int rows, bool p
 // The register form of the same launches (kernels_resident_reg.hip), called by the launchers above for the shapes it covers.
 bool resident_reg_shape(int kind, int C, int MID, int H, int W);
 hipError_t resident_reg_prepare();
-hipError_t launch_reg_forward(int g, int MID, const ResArgs& a, hipStream_t stream);
-hipError_t launch_reg_backward(int g, int MID, const ResArgs& a, hipStream_t stream);
-hipError_t launch_reg_inference(int g, int MID, const ResArgs& a, hipStream_t stream);
+hipError_t launch_reg_forward(int g, int C, int MID, const ResArgs& a, hipStream_t stream);
+hipError_t launch_reg_backward(int g, int C, int MID, const ResArgs& a, hipStream_t stream);
+hipError_t launch_reg_inference(int g, int C, int MID, const ResArgs& a, hipStream_t stream);
+// ... of 256-64 bottlenecks on 8x8 (kernels_resident_reg8.hip), called by these
+hipError_t resident_reg8_prepare();
+hipError_t launch_reg8_forward(int g, const ResArgs& a, hipStream_t stream);
+hipError_t launch_reg8_backward(int g, const ResArgs& a, hipStream_t stream);
+hipError_t launch_reg8_inference(int g, const ResArgs& a, hipStream_t stream);
 // ... and for runs of basic blocks (kernels_resident_basic.hip); infer: kind 0 only
 bool resident_basic_shape(int kind, int C, int H, int W);
 hipError_t resident_basic_prepare();

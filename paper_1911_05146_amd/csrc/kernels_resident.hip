@@ -2589,7 +2589,7 @@ hipError_t launch_resident_forward(int kind, int g, int C, int MID, const ResArg
     return hipGetLastError();
   }
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > resident_max_group(a.nmem)) return hipErrorInvalidValue;
-  if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_forward(g, MID, a, stream);
+  if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_forward(g, C, MID, a, stream);
   if (resident_basic_shape(kind, C, a.H, a.W)) return launch_basic_forward(kind, g, C, a, false, stream);
   int own = 0;
   if (kind == 2) {
@@ -2618,7 +2618,7 @@ hipError_t launch_resident_inference(int kind, int g, int C, int MID, const ResA
   if (resident_bands(kind, C, MID, a.H, a.W) > 1) return hipErrorInvalidValue;   // bands: forward and backward launches only
   if (kind == 2) return hipErrorInvalidValue;   // post-activation runs: forward and backward launches only
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > MAX_GROUP || !a.running) return hipErrorInvalidValue;
-  if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_inference(g, MID, a, stream);
+  if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_inference(g, C, MID, a, stream);
   if (resident_basic_shape(kind, C, a.H, a.W)) return launch_basic_forward(kind, g, C, a, true, stream);
   int own = 0;
   if (kind == 0) {
@@ -2708,7 +2708,7 @@ hipError_t launch_resident_backward(int kind, int g, int C, int MID, const ResAr
     return hipGetLastError();
   }
   if (!resident_shape_ok(kind, C, MID, a.H, a.W, a.nmem) || a.nblk < 1 || g < 1 || g > resident_max_group(a.nmem)) return hipErrorInvalidValue;
-  if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_backward(g, MID, a, stream);
+  if (resident_reg_shape(kind, C, MID, a.H, a.W)) return launch_reg_backward(g, C, MID, a, stream);
   if (resident_basic_shape(kind, C, a.H, a.W)) return launch_basic_backward(kind, g, C, a, stream);
   int own = 0;
   if (kind == 2) {

@@ -750,7 +750,7 @@ bool resident_basic_shape(int kind, int C, int H, int W) {
 }
 bool resident_lead_shape(int kind, int c_in, int c_mid, int c_out, int h_out, int w_out) {
   if (c_in * 2 != c_out) return false;
-  return kind == 1 ? resident_reg_shape(kind, c_out, c_mid, h_out, w_out) : c_out >= 32 && c_mid == c_out && resident_basic_shape(kind, c_out, h_out, w_out);
+  return kind == 1 ? c_out == 128 && resident_reg_shape(kind, c_out, c_mid, h_out, w_out) : c_out >= 32 && c_mid == c_out && resident_basic_shape(kind, c_out, h_out, w_out);
 }
 hipError_t resident_basic_prepare() {
   hipError_t e = prepare_c<16, false>();

@@ -474,7 +474,7 @@ hipError_t launch_reg(K kernel, int lds, int g, const ResArgs& a, hipStream_t st
 }  // namespace
 
 bool resident_reg_shape(int kind, int C, int MID, int H, int W) {
-  return kind == 1 && C == 128 && (MID == 32 || MID == 64) && H == RG_IMG && W == RG_IMG;
+  return kind == 1 && ((C == 128 && (MID == 32 || MID == 64) && H == RG_IMG && W == RG_IMG) || (C == 256 && MID == 64 && H == 8 && W == 8));
 }
 template <int MID, bool LEAD>
 static hipError_t prepare_m() {
@@ -491,6 +491,7 @@ hipError_t resident_reg_prepare() {
   if (e == hipSuccess) e = prepare_m<64, false>();
   if (e == hipSuccess) e = prepare_m<32, true>();
   if (e == hipSuccess) e = prepare_m<64, true>();
+  if (e == hipSuccess) e = resident_reg8_prepare();
   return e;
 }
 template <int MID, bool INFER>
@@ -503,13 +504,16 @@ static hipError_t backward_m(int g, const ResArgs& a, hipStream_t stream) {
   return a.lead ? launch_reg(k_reg_backward<128, MID, true>, rg_bwd_lds<128, MID>(), g, a, stream)
                 : launch_reg(k_reg_backward<128, MID, false>, rg_bwd_lds<128, MID>(), g, a, stream);
 }
-hipError_t launch_reg_forward(int g, int MID, const ResArgs& a, hipStream_t stream) {
+hipError_t launch_reg_forward(int g, int C, int MID, const ResArgs& a, hipStream_t stream) {
+  if (C == 256) return launch_reg8_forward(g, a, stream);
   return MID == 32 ? forward_m<32, false>(g, a, stream) : forward_m<64, false>(g, a, stream);
 }
-hipError_t launch_reg_backward(int g, int MID, const ResArgs& a, hipStream_t stream) {
+hipError_t launch_reg_backward(int g, int C, int MID, const ResArgs& a, hipStream_t stream) {
+  if (C == 256) return launch_reg8_backward(g, a, stream);
   return MID == 32 ? backward_m<32>(g, a, stream) : backward_m<64>(g, a, stream);
 }
-hipError_t launch_reg_inference(int g, int MID, const ResArgs& a, hipStream_t stream) {
+hipError_t launch_reg_inference(int g, int C, int MID, const ResArgs& a, hipStream_t stream) {
+  if (C == 256) return launch_reg8_inference(g, a, stream);
   return MID == 32 ? forward_m<32, true>(g, a, stream) : forward_m<64, true>(g, a, stream);
 }
 static_assert(rg_bwd_lds<128, 64>() <= 160 * 1024 && rg_fwd_lds<128, 64, false>() <= 160 * 1024 && rg_fwd_lds<128, 64, true>() <= 160 * 1024, "LDS of a CU");

@@ -197,6 +197,15 @@ def test_register_resident_runs_around_the_polled_chunk_layerwise(gpu, oracle, k
     layerwise(oracle, spec, "bf16", blockwise=False)
 
 
+@pytest.mark.parametrize("images,micro,grouped", [(1, 1, True), (8, 3, True), (9, 2, False), (16, 1, True), (17, 1, True), (33, 2, True)])
+def test_register_resident_runs_of_8x8_bottlenecks_layerwise(gpu, oracle, images, micro, grouped):
+    """256-64 bottlenecks on 8x8: words of 8, 16 or 32 images at a time, full chunks and one image beyond.  Three blocks: the first, a following
+    one and the last."""
+    spec = W.PartitionSpec(name=f"reg8-256-64@8x8-b{images}", in_h=8, in_w=8, in_c=256, blocks=(W.Block(W.BOTTLENECK, 256, 64, 256, 1),) * 3,
+                           microbatch=images, num_microbatches=micro, seed=73)
+    layerwise(oracle, spec, "bf16", grouped=grouped, blockwise=False)
+
+
 @pytest.mark.parametrize("before,behind,images,micro", [(0, 1, 5, 2), (1, 0, 1, 1), (1, 2, 33, 1), (0, 3, 4, 3)])
 @pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 32, 32), (W.BASIC, 32, 64, 16), (W.POSTACT, 16, 32, 32), (W.POSTACT, 32, 64, 16),
                                            (W.BOTTLENECK, 64, 32, 32), (W.BOTTLENECK, 64, 64, 32)])
@@ -211,7 +220,7 @@ def test_runs_led_in_by_a_block_that_halves_the_image_layerwise(gpu, oracle, kin
 
 
 @pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 16, 32), (W.BASIC, 32, 32, 16), (W.BASIC, 64, 64, 8),
-                                           (W.BOTTLENECK, 128, 32, 16), (W.BOTTLENECK, 128, 64, 16)])
+                                           (W.BOTTLENECK, 128, 32, 16), (W.BOTTLENECK, 128, 64, 16), (W.BOTTLENECK, 256, 64, 8)])
 def test_statistics_of_channels_whose_mean_jumps_between_blocks(gpu, oracle, kind, c, mid, hw):
     """The first block of a run moves every fourth channel of the residual stream by 40 standard deviations.  The next block's
     statistics must not feel it: squares summed about any value d standard deviations from the mean lose a factor d^2 = 1600
@@ -241,7 +250,7 @@ def test_statistics_of_channels_whose_mean_jumps_between_blocks(gpu, oracle, kin
 
 
 @pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 16, 32), (W.BASIC, 32, 32, 16), (W.BASIC, 64, 64, 8),
-                                           (W.BOTTLENECK, 128, 32, 16), (W.BOTTLENECK, 128, 64, 16)])
+                                           (W.BOTTLENECK, 128, 32, 16), (W.BOTTLENECK, 128, 64, 16), (W.BOTTLENECK, 256, 64, 8)])
 def test_a_channel_whose_variance_overflows_is_switched_off(gpu, kind, c, mid, hw):
     """Values of +-3e18 have a sum of squares beyond float32: the variance is infinite, 1 / sqrt of it is 0 (not NaN), the channel's
     BatchNorm gives beta and every other channel is as without it."""
