@@ -228,7 +228,7 @@ hipError_t launch_resident_wgrad(int kind, int g, int C, int MID, const ResArgs&
 hipError_t launch_resident_inference(int kind, int g, int C, int MID, const ResArgs& a, hipStream_t stream);
 // Runs whose kernels read their packed weights in fragment order; and whether the columns of a convolution's operand are permuted
 bool resident_reads_fragments(int kind, int C, int MID, int H, int W);
-inline bool resident_permutes(int kind, int C, int R) { return kind == 1 && C == 128 && R == 1; }
+inline bool resident_permutes(int kind, int C, int R) { return kind == 1 && (C == 128 || C == 64) && R == 1; }
 // The order of MFMA fragments: a [rows][len] matrix (rows a multiple of 16, len of 32) as pieces of 16 rows x 32 columns, 1 KiB each, step of the
 // reduction by step; in a piece the 16 bytes of lane (fr, fq), row fr and columns fq*8 ... + 7, lie at (fq*16 + fr)*8.  Permuted: columns {0, 16} +
 // fq*4 ... + 3.  So the loads of a wave are whole cache lines.  With the rows of the matrix, 16 segments of 64 bytes a load, a load held the CU's memory
@@ -250,6 +250,10 @@ hipError_t resident_reg8_prepare();
 hipError_t launch_reg8_forward(int g, const ResArgs& a, hipStream_t stream);
 hipError_t launch_reg8_backward(int g, const ResArgs& a, hipStream_t stream);
 hipError_t launch_reg8_inference(int g, const ResArgs& a, hipStream_t stream);
+// ... of bottlenecks whose images are cut into row bands (kernels_resident_band.hip; resident_bands); members: bands of a micro-batch
+size_t band_xchg_bytes(int members);
+hipError_t launch_band_forward(int g, const ResArgs& a, hipStream_t stream);
+hipError_t launch_band_backward(int g, const ResArgs& a, hipStream_t stream);
 // ... and for runs of basic blocks (kernels_resident_basic.hip); infer: kind 0 only
 bool resident_basic_shape(int kind, int C, int H, int W);
 hipError_t resident_basic_prepare();

@@ -206,6 +206,15 @@ def test_register_resident_runs_of_8x8_bottlenecks_layerwise(gpu, oracle, images
     layerwise(oracle, spec, "bf16", grouped=grouped, blockwise=False)
 
 
+@pytest.mark.parametrize("images,blocks", [(1, 1), (1, 3), (9, 2), (16, 2)])
+def test_row_bands_around_the_polled_chunk_layerwise(gpu, oracle, images, blocks):
+    """64-16 bottlenecks at 32x32 collect the words of 32 bands at a time: the four bands of one image alone, one block alone, more than one chunk
+    (36 bands) and whole chunks (64)."""
+    spec = W.PartitionSpec(name=f"bands-{blocks}-b{images}", in_h=32, in_w=32, in_c=64, blocks=(W.Block(W.BOTTLENECK, 64, 16, 64, 1),) * blocks,
+                           microbatch=images, num_microbatches=1, seed=79)
+    layerwise(oracle, spec, "bf16", blockwise=False)
+
+
 @pytest.mark.parametrize("before,behind,images,micro", [(0, 1, 5, 2), (1, 0, 1, 1), (1, 2, 33, 1), (0, 3, 4, 3)])
 @pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 32, 32), (W.BASIC, 32, 64, 16), (W.POSTACT, 16, 32, 32), (W.POSTACT, 32, 64, 16),
                                            (W.BOTTLENECK, 64, 32, 32), (W.BOTTLENECK, 64, 64, 32)])
