@@ -240,7 +240,8 @@ struct Gather {
   // words of members m0 + mg + i*MG, i < INFL.  The first poll waits: loads that reach the
   // words before the partners' stores do delay those stores, by more than a microsecond (the record exchange of a 32-channel
   // tensor among 32 work-groups: 2.6 us from publish to coefficients when polled at once, 1.4-1.6 us with the pause; 128-32 blocks
-  // forward 357 -> 286 us per launch of 21 blocks; pauses of 8 to 40 measured 303 ... 286 ... 305).
+  // forward 357 -> 286 us per launch of 21 blocks; pauses of 8 to 40 measured 303 ... 286 ... 305).  By the second chunk the words are there: with a
+  // pause ahead of it too, the sixteenth of the wide ResNet-1001 took 1538 us, now 1512.
   // The slot has room for a multiple of CHUNK members, so all addresses are one lane offset from uniform bases.
   // SKIP: loads for members that there are not are left out, eight members at a time (16 images: 1 % of a step of ResNet-110).  Not in the
   // 128-channel kernels, where the branches cost registers (128-32, 32 images: 952 -> 969 us).
@@ -249,7 +250,7 @@ struct Gather {
     const unsigned off = (unsigned)((lane / WPW) * W + wave * WPW + (lane & (WPW - 1)));
     const int mine = lane_members(m0, nmem, lane);
     const u64* base = slot + (size_t)m0 * W;
-    __builtin_amdgcn_s_sleep(Cc < 128 ? 16 : 8);
+    if (m0 == 0) __builtin_amdgcn_s_sleep(Cc < 128 ? 16 : 8);
     for (;;) {
       bool ok = true;
 #pragma unroll
@@ -290,10 +291,10 @@ __device__ __forceinline__ void stats_out(const StatsOut& o, float mean, float v
   }
 }
 // {mean, M2} records of equal pixel counts -> coef[c] = {scale, shift}, the mean, and (member 0) stats = {mean(Cc), invstd(Cc)}
-template <int Cc, bool SKIP>
+template <int Cc, bool SKIP, int CH = 32>
 __device__ __forceinline__ void collect_stats(const u64* slot, int nmem, unsigned tag, float inv_n, float P, float eps, float gamma, float beta,
                                               const StatsOut& o, int wave, int lane, int* fail) {
-  using G = Gather<Cc>;
+  using G = Gather<Cc, CH>;
   u64 v[G::INFL];
   SpinBudget budget;
   float m0 = 0.f, s1 = 0.f, s2 = 0.f, sw = 0.f;   // sw: plain sum of the words (the M2 of the odd lanes)

@@ -104,6 +104,10 @@ constexpr int rg_fwd_lds() {
   return RG_CW * RG_CW * (MID + 8) * 2 + W2::BYTES + w13 + (C + 2 * MID) * 8 + (INFER ? 0 : RG_NW * 2 * C * 4) + 16;
 }
 
+// FEW: micro-batches of up to eight images, which take one chunk of eight records (111 blocks of ResNet-1001, 8 images: 3.1 -> 2.9 ms both ways).  A branch
+// for them in the one kernel cost the others 1 % in registers.
+constexpr int RG_FEW = 8;
+
 // Forward of a run.  INFER: BatchNorm by running statistics; nothing is exchanged or stashed, only the output of the last
 // block is written.
 // Barriers per block: 7 (training), 2 (inference).  The matrices of conv1 and conv3 take turns in one LDS area in training
@@ -112,7 +116,7 @@ constexpr int rg_fwd_lds() {
 // Inference is bounded by latency (3.8 us per 128-32 block, of which the products take 0.9): every matrix and table is asked for as soon as the
 // registers of the one before are free, a whole block ahead of its use, and the tables of the three BatchNorms are read by waves of their
 // own.  Asked for within the block, the tables three dependent reads in one wave, 21 blocks took 95 us, now 80.
-template <int C, int MID, bool INFER, bool LEAD>
+template <int C, int MID, bool INFER, bool LEAD, bool FEW>
 __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
   using W1 = WStage<MID, C>;
@@ -195,7 +199,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
     const unsigned tag = tag0 + 1u + phase;
     stats_publish_waves<Cc, S * RG_NPX>(red, slot(), me, tag);
     const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
-    collect_stats<Cc, false>(slot(), a.nmem, tag, inv_n, (float)(S * RG_P), a.eps, gamma, beta, o, wave, lane, fail);
+    collect_stats<Cc, false, FEW ? 8 : 32>(slot(), a.nmem, tag, inv_n, (float)(S * RG_P), a.eps, gamma, beta, o, wave, lane, fail);
     ++phase;
     late();
     __syncthreads();
@@ -350,7 +354,7 @@ constexpr int rg_bwd_lds() {
 // Backward of a run: the same ownership, walking the blocks in reverse with the gradient of the residual stream in
 // registers (packed).  c1, c2 and x of a block are read straight into the register layout, each behind the polls of an exchange
 // well ahead of its use; what leaves (dc2, dc1, gx) is stored behind the polls of the exchange after.
-template <int C, int MID, bool LEAD>
+template <int C, int MID, bool LEAD, bool FEW>
 __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
   constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
   using W3 = WStage<MID, C>;           // conv3 data gradient [MID][C]
@@ -435,7 +439,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
     sums_publish_waves<Cc>(red, slot(), me, tag);
-    collect_bwd<Cc, false, (Cc == C ? 512 : 1024) / MID>(slot(), a.nmem, tag, ld && q == 0 ? 0.25f * inv_M : inv_M, ck, tab,
+    collect_bwd<Cc, false, FEW ? 8 : (Cc == C ? 512 : 1024) / MID>(slot(), a.nmem, tag, ld && q == 0 ? 0.25f * inv_M : inv_M, ck, tab,
                                                   !ld && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave, lane, fail,
                                                   ld && me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
     ++phase;
@@ -478,8 +482,9 @@ bool resident_reg_shape(int kind, int C, int MID, int H, int W) {
 }
 template <int MID, bool LEAD>
 static hipError_t prepare_m() {
-  const void* const kernels[] = {reinterpret_cast<const void*>(k_reg_forward<128, MID, false, LEAD>), reinterpret_cast<const void*>(k_reg_forward<128, MID, true, LEAD>),
-                                 reinterpret_cast<const void*>(k_reg_backward<128, MID, LEAD>)};
+  const void* const kernels[] = {reinterpret_cast<const void*>(k_reg_forward<128, MID, false, LEAD, false>), reinterpret_cast<const void*>(k_reg_forward<128, MID, false, LEAD, true>),
+                                 reinterpret_cast<const void*>(k_reg_forward<128, MID, true, LEAD, false>),
+                                 reinterpret_cast<const void*>(k_reg_backward<128, MID, LEAD, false>), reinterpret_cast<const void*>(k_reg_backward<128, MID, LEAD, true>)};
   for (const void* f : kernels) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
@@ -494,15 +499,25 @@ hipError_t resident_reg_prepare() {
   if (e == hipSuccess) e = resident_reg8_prepare();
   return e;
 }
+template <int MID, bool INFER, bool LEAD>
+static hipError_t forward_l(int g, const ResArgs& a, hipStream_t stream) {
+  constexpr int lds = rg_fwd_lds<128, MID, INFER>();
+  if constexpr (!INFER)
+    if (a.nmem <= RG_FEW) return launch_reg(k_reg_forward<128, MID, false, LEAD, true>, lds, g, a, stream);
+  return launch_reg(k_reg_forward<128, MID, INFER, LEAD, false>, lds, g, a, stream);
+}
 template <int MID, bool INFER>
 static hipError_t forward_m(int g, const ResArgs& a, hipStream_t stream) {
-  return a.lead ? launch_reg(k_reg_forward<128, MID, INFER, true>, rg_fwd_lds<128, MID, INFER>(), g, a, stream)
-                : launch_reg(k_reg_forward<128, MID, INFER, false>, rg_fwd_lds<128, MID, INFER>(), g, a, stream);
+  return a.lead ? forward_l<MID, INFER, true>(g, a, stream) : forward_l<MID, INFER, false>(g, a, stream);
+}
+template <int MID, bool LEAD>
+static hipError_t backward_l(int g, const ResArgs& a, hipStream_t stream) {
+  return a.nmem <= RG_FEW ? launch_reg(k_reg_backward<128, MID, LEAD, true>, rg_bwd_lds<128, MID>(), g, a, stream)
+                          : launch_reg(k_reg_backward<128, MID, LEAD, false>, rg_bwd_lds<128, MID>(), g, a, stream);
 }
 template <int MID>
 static hipError_t backward_m(int g, const ResArgs& a, hipStream_t stream) {
-  return a.lead ? launch_reg(k_reg_backward<128, MID, true>, rg_bwd_lds<128, MID>(), g, a, stream)
-                : launch_reg(k_reg_backward<128, MID, false>, rg_bwd_lds<128, MID>(), g, a, stream);
+  return a.lead ? backward_l<MID, true>(g, a, stream) : backward_l<MID, false>(g, a, stream);
 }
 hipError_t launch_reg_forward(int g, int C, int MID, const ResArgs& a, hipStream_t stream) {
   if (C == 256) return launch_reg8_forward(g, a, stream);
