@@ -64,7 +64,8 @@ __device__ __forceinline__ void px_arrange(uint2 (&v)[PTW][NTL]) {
     for (int k = 0; k < NTL / 2; ++k) pair_swap(v[j][2 * k], v[j][2 * k + 1]);
 }
 // NT: streaming stores.  They keep the tensors (read again only much later) out of the caches, but bursts of them reach
-// the memory's rate; the forward of 128-32 blocks runs 8 % faster with stores that the L2 takes.
+// the memory's rate; the forward of 128-32 blocks runs 8 % faster with stores that the L2 takes.  In the backward kernels it is the other way round: 128-32 950 us a
+// step without and 930 with them, 128-64 1504 and 1522.
 template <bool NT = true, int PTW, int NTL>
 __device__ __forceinline__ void px_store(bf16_t* g, unsigned off, const uint2 (&v)[PTW][NTL]) {
 #pragma unroll
@@ -240,7 +241,8 @@ struct Gather {
   // words of members m0 + mg + i*MG, i < INFL.  The first poll waits: loads that reach the
   // words before the partners' stores do delay those stores, by more than a microsecond (the record exchange of a 32-channel
   // tensor among 32 work-groups: 2.6 us from publish to coefficients when polled at once, 1.4-1.6 us with the pause; 128-32 blocks
-  // forward 357 -> 286 us per launch of 21 blocks; pauses of 8 to 40 measured 303 ... 286 ... 305).  By the second chunk the words are there: with a
+  // forward 357 -> 286 us per launch of 21 blocks; pauses of 8 to 40 measured 303 ... 286 ... 305; with the
+  // present weight loads 12 instead of 16: ResNet-110 v1 1262 -> 1251, quarter of ResNet-110 294 -> 290; 8: 1260, 291).  By the second chunk the words are there: with a
   // pause ahead of it too, the sixteenth of the wide ResNet-1001 took 1538 us, now 1512.
   // The slot has room for a multiple of CHUNK members, so all addresses are one lane offset from uniform bases.
   // SKIP: loads for members that there are not are left out, eight members at a time (16 images: 1 % of a step of ResNet-110).  Not in the
@@ -250,7 +252,7 @@ struct Gather {
     const unsigned off = (unsigned)((lane / WPW) * W + wave * WPW + (lane & (WPW - 1)));
     const int mine = lane_members(m0, nmem, lane);
     const u64* base = slot + (size_t)m0 * W;
-    if (m0 == 0) __builtin_amdgcn_s_sleep(Cc < 128 ? 16 : 8);
+    if (m0 == 0) __builtin_amdgcn_s_sleep(Cc < 128 ? 12 : 8);
     for (;;) {
       bool ok = true;
 #pragma unroll

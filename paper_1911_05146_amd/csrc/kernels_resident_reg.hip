@@ -462,7 +462,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
     const int bi = 0;
 #include "resident_reg_backward_block.inl"
   } else {
-    px_store(image(a.blocks[0].gx_off, C), offC, DY);
+    px_store<MID == 32>(image(a.blocks[0].gx_off, C), offC, DY);
   }
   if (me == 0 && tid == 0) *tagp = tag0 + phase;
 }

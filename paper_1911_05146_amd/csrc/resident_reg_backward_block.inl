@@ -34,7 +34,7 @@ if (!exchange(IM{}, std::bool_constant<LD>{}, acc, xc2, cf3, B, 2, [&] {
       if constexpr (LD) l1.commit(sW13, wave, lane);
       else w1.commit(sW13, wave, lane);   // every wave is past conv3's data gradient
       if (bi + 1 < a.nblk) w2.template commit<2>(sW2, wave, lane);
-      if (bi + 1 < a.nblk) px_store(image(a.blocks[bi + 1].gx_off, C), offC, DY);   // the gradient of the input of the block above
+      if (bi + 1 < a.nblk) px_store<MID == 32>(image(a.blocks[bi + 1].gx_off, C), offC, DY);   // the gradient of the input of the block above
       px_load(xc1, image(B.c1_off, MID), offM);
       if constexpr (!LD) px_load(xx, image(B.x_off, C), offC);
     }))
@@ -57,7 +57,7 @@ if (more) w2.template issue<0>(a.packed + Bn.wd_off[1], wave, fr, fq);   // ever
 px_arrange(xc1);
 if (!exchange(IM{}, std::bool_constant<LD>{}, acc, xc1, cf2, B, 1, [&] {
       if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wd_off[1], wave, fr, fq); }   // every wave is past conv2's data gradient
-      px_store(image(B.dc2_off, MID), offM, dcp);
+      px_store<MID == 32>(image(B.dc2_off, MID), offM, dcp);
       if (more) { load_tables(bi - 1); w3.issue(a.packed + Bn.wd_off[2], wave, fr, fq); }
       if constexpr (LD) {
         lw.commit(canvas, wave, lane);   // every wave is past conv2's data gradient
@@ -96,7 +96,7 @@ if constexpr (LD) {
 #pragma unroll
   for (int j = 0; j < RG_PTW; ++j) LP::arrange(xe[j]);
   if (!exchange(std::integral_constant<int, CI>{}, std::bool_constant<LD>{}, da, xe, cf1, B, 0, [&] {
-        px_store(image(B.dc1_off, MID), offM, dcp);
+        px_store<MID == 32>(image(B.dc1_off, MID), offM, dcp);
 #pragma unroll
         for (int t = 0; t < 3 * RG_PTW; ++t) LP::arrange(xo[t]);
       }))
@@ -111,7 +111,7 @@ if constexpr (LD) {
     lp.store(gx, t, o);
   }
 } else {
-  if constexpr (MID >= 64) px_store(image(B.dc1_off, MID), offM, dcp);   // 16 registers that the exchange below cannot spare
+  if constexpr (MID >= 64) px_store<MID == 32>(image(B.dc1_off, MID), offM, dcp);   // 16 registers that the exchange below cannot spare
   // ---- conv1 data gradient, BN1 + ReLU backward, plus the shortcut
   floatx4 da[RG_PTW][NC];
 #pragma unroll
@@ -130,7 +130,7 @@ if constexpr (LD) {
   px_arrange(xx);
   if (!exchange(IC{}, std::bool_constant<LD>{}, da, xx, cf1, B, 0, [&] {
         if (more) { w3.commit(sW13, wave, lane); w2.template commit<1>(sW2, wave, lane); w2.template issue<2>(a.packed + Bn.wd_off[1], wave, fr, fq); store_tables(); px_load(xc2, image(Bn.c2_off, MID), offM); }   // conv1's data gradient and the tables of this block are behind the barrier
-        if constexpr (MID < 64) px_store(image(B.dc1_off, MID), offM, dcp);
+        if constexpr (MID < 64) px_store<MID == 32>(image(B.dc1_off, MID), offM, dcp);
       }))
     return;
 #pragma unroll
