@@ -13,7 +13,7 @@
 // What bounds the LDS-tile form (20.8 us per 128-32 block forward on 256 images): 2 500 VALU and 200 LDS instructions per wave and
 // block, 25 barriers, and exchanges whose records went through LDS twice.
 // Measured on 256 images (8 micro-batches), per block: forward 20.7 -> 13.1 us (128-32) and 28.2 -> 21.9 (128-64), backward
-// 26.1 -> 21.2 and 37.3 -> 35 (4 and 18 registers of the backward spill: 20 and 68 bytes of scratch per lane).  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
+// 26.1 -> 21.2 and 37.3 -> 35 (28 registers of the 128-64 backward spill: 92 bytes of scratch per lane).  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
 // 4 us at the memory's rate), and issue: 8 waves per CU leave the matrix cores idle while they do BatchNorm.
 //
 // The block in front of a run that halves the image and doubles the channels (64 -> 128, projection) leads it in (LEAD): the same launch starts, or
@@ -104,7 +104,7 @@ constexpr int rg_fwd_lds() {
   return RG_CW * RG_CW * (MID + 8) * 2 + W2::BYTES + w13 + (C + 2 * MID) * 8 + (INFER ? 0 : RG_NW * 2 * C * 4) + 16;
 }
 
-// FEW: micro-batches of up to eight images, which take one chunk of eight records (111 blocks of ResNet-1001, 8 images: 3.1 -> 2.9 ms both ways).  A branch
+// FEW: micro-batches of up to eight images, which take one chunk of eight records (111 blocks of ResNet-1001, 8 images: 3.1 -> 2.85 ms both ways).  A branch
 // for them in the one kernel cost the others 1 % in registers.
 constexpr int RG_FEW = 8;
 
