@@ -13,7 +13,7 @@
 // What bounds the LDS-tile form (20.8 us per 128-32 block forward on 256 images): 2 500 VALU and 200 LDS instructions per wave and
 // block, 25 barriers, and exchanges whose records went through LDS twice.
 // Measured on 256 images (8 micro-batches), per block: forward 20.7 -> 13.1 us (128-32) and 28.2 -> 21.9 (128-64), backward
-// 26.1 -> 21.2 and 37.3 -> 35 (28 registers of the 128-64 backward spill: 92 bytes of scratch per lane).  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
+// 26.1 -> 21.2 and 37.3 -> 35 (30 registers of the 128-64 backward spill: 92 bytes of scratch per lane).  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
 // 4 us at the memory's rate), and issue: 8 waves per CU leave the matrix cores idle while they do BatchNorm.
 //
 // The block in front of a run that halves the image and doubles the channels (64 -> 128, projection) leads it in (LEAD): the same launch starts, or
@@ -439,7 +439,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
     sums_publish_waves<Cc>(red, slot(), me, tag);
-    collect_bwd<Cc, false, FEW ? 8 : (Cc == C ? 512 : 1024) / MID>(slot(), a.nmem, tag, ld && q == 0 ? 0.25f * inv_M : inv_M, ck, tab,
+    collect_bwd<Cc, false, FEW ? 8 : (Cc == C ? 16 : 1024 / MID)>(slot(), a.nmem, tag, ld && q == 0 ? 0.25f * inv_M : inv_M, ck, tab,
                                                   !ld && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave, lane, fail,
                                                   ld && me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
     ++phase;
