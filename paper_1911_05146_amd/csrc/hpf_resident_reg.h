@@ -237,17 +237,18 @@ __device__ __forceinline__ void stats_publish_waves(const float* red, u64* slot,
 // CH: members polled at a time (a slot has room for a multiple of 32)
 template <int Cc, int CH = 32>
 struct Gather {
-  static constexpr int W = 2 * Cc, WPW = W / RG_NW, MG = 64 / WPW, CHUNK = CH, INFL = CHUNK / MG, STEP = MG < 8 ? 8 / MG : 1;
+  static constexpr int W = 2 * Cc, WPW = W / RG_NW, MG = 64 / WPW, CHUNK = CH, INFL = CHUNK / MG;
+  static_assert(INFL >= 1, "a member for every group of lanes");
   // words of members m0 + mg + i*MG, i < INFL.  The first poll waits: loads that reach the
   // words before the partners' stores do delay those stores, by more than a microsecond (the record exchange of a 32-channel
   // tensor among 32 work-groups: 2.6 us from publish to coefficients when polled at once, 1.4-1.6 us with the pause; 128-32 blocks
   // forward 357 -> 286 us per launch of 21 blocks; pauses of 8 to 40 measured 303 ... 286 ... 305; with the
   // present weight loads 12 instead of 16: ResNet-110 v1 1262 -> 1251, quarter of ResNet-110 294 -> 290; 8: 1260, 291).  By the second chunk the words are there: with a
   // pause ahead of it too, the sixteenth of the wide ResNet-1001 took 1538 us, now 1512.
-  // The slot has room for a multiple of CHUNK members, so all addresses are one lane offset from uniform bases.
-  // SKIP: loads for members that there are not are left out, eight members at a time (16 images: 1 % of a step of ResNet-110).  Not in the
-  // 128-channel kernels, where the branches cost registers (128-32, 32 images: 952 -> 969 us).
-  template <bool SKIP>
+  // The slot has room for a multiple of CHUNK members, so all addresses are one lane offset from uniform bases, and words of members that there are
+  // not are asked for as well.  A branch around them ends a group of loads, whose words are waited for before the next group is asked for: with
+  // one for every eight members, eight blocks of 64 channels on 20 images took 182 us a step and on 32 images 200, without 168 and 174.  Kernels for
+  // few members poll a smaller chunk instead.
   static __device__ __forceinline__ void poll(u64 (&v)[INFL], const u64* slot, int m0, int nmem, unsigned tag, int wave, int lane, int* fail, SpinBudget& budget) {
     const unsigned off = (unsigned)((lane / WPW) * W + wave * WPW + (lane & (WPW - 1)));
     const int mine = lane_members(m0, nmem, lane);
@@ -256,15 +257,7 @@ struct Gather {
     for (;;) {
       bool ok = true;
 #pragma unroll
-      for (int g = 0; g < INFL / STEP; ++g) {
-        if (!SKIP || g == 0 || nmem - m0 > g * STEP * MG) {
-#pragma unroll
-          for (int i = g * STEP; i < (g + 1) * STEP; ++i) v[i] = __hip_atomic_load(base + i * (MG * W) + off, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-#pragma unroll
-          for (int i = g * STEP; i < (g + 1) * STEP; ++i) v[i] = 0;
-        }
-      }
+      for (int i = 0; i < INFL; ++i) v[i] = __hip_atomic_load(base + i * (MG * W) + off, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
       for (int i = 0; i < INFL; ++i) ok = ok && ((unsigned)(v[i] >> 32) == tag || i >= mine);
       if (__all(ok)) break;
@@ -293,7 +286,7 @@ __device__ __forceinline__ void stats_out(const StatsOut& o, float mean, float v
   }
 }
 // {mean, M2} records of equal pixel counts -> coef[c] = {scale, shift}, the mean, and (member 0) stats = {mean(Cc), invstd(Cc)}
-template <int Cc, bool SKIP, int CH = 32>
+template <int Cc, int CH>
 __device__ __forceinline__ void collect_stats(const u64* slot, int nmem, unsigned tag, float inv_n, float P, float eps, float gamma, float beta,
                                               const StatsOut& o, int wave, int lane, int* fail) {
   using G = Gather<Cc, CH>;
@@ -301,7 +294,7 @@ __device__ __forceinline__ void collect_stats(const u64* slot, int nmem, unsigne
   SpinBudget budget;
   float m0 = 0.f, s1 = 0.f, s2 = 0.f, sw = 0.f;   // sw: plain sum of the words (the M2 of the odd lanes)
   for (int b = 0; more_chunks(b, nmem, budget); b += G::CHUNK) {
-    G::template poll<SKIP>(v, slot, b, nmem, tag, wave, lane, fail, budget);
+    G::poll(v, slot, b, nmem, tag, wave, lane, fail, budget);
     const int mine = G::lane_members(b, nmem, lane);
     float f[G::INFL], d[G::INFL];
 #pragma unroll
@@ -378,7 +371,7 @@ struct CfChannel {
 };
 // {sum dz, sum dz*xhat} of all members -> tab; dgb (member 0 only, else null): the two sums
 // CH: fewer words in flight than the forward collects, or they spill next to the gradients of a wide tensor
-template <int Cc, bool SKIP, int CH>
+template <int Cc, int CH>
 __device__ __forceinline__ void collect_bwd(const u64* slot, int nmem, unsigned tag, float inv_M, const CfChannel& k, float* tab, float* dgb, int wave,
                                             int lane, int* fail, float* g_beta = nullptr, float* g_gamma = nullptr) {
   using G = Gather<Cc, CH>;
@@ -387,7 +380,7 @@ __device__ __forceinline__ void collect_bwd(const u64* slot, int nmem, unsigned 
   SpinBudget budget;
   float sw = 0.f;
   for (int b = 0; more_chunks(b, nmem, budget); b += G::CHUNK) {
-    G::template poll<SKIP>(v, slot, b, nmem, tag, wave, lane, fail, budget);
+    G::poll(v, slot, b, nmem, tag, wave, lane, fail, budget);
     const int mine = G::lane_members(b, nmem, lane);
     float f[G::INFL];
 #pragma unroll

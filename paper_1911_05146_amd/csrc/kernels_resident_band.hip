@@ -103,6 +103,11 @@ struct BandLane {
   }
 };
 
+// FEW: micro-batches of up to four images, whose 16 bands are one chunk of records.  Eight blocks, us a step, chunks of 32 / 16: one image 172 / 164, four
+// images 185 / 180.
+constexpr int BAND_FEW = 16;
+
+template <bool FEW>
 __global__ void __launch_bounds__(RG_NT) k_band_forward(const ResArgs a) {
   constexpr int C = RB_C, MID = RB_MID;
   const BandLane L(a);
@@ -139,7 +144,7 @@ __global__ void __launch_bounds__(RG_NT) k_band_forward(const ResArgs a) {
     const unsigned tag = tag0 + 1u + phase;
     stats_publish_waves<Cc, RB_NPX>(red, slot(), me, tag);
     const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
-    collect_stats<Cc, true>(slot(), L.nwg, tag, inv_n, (float)RB_P, a.eps, gamma, beta, o, wave, lane, fail);
+    collect_stats<Cc, FEW ? BAND_FEW : 32>(slot(), L.nwg, tag, inv_n, (float)RB_P, a.eps, gamma, beta, o, wave, lane, fail);
     late(tag);
     ++phase;
     __syncthreads();
@@ -254,6 +259,7 @@ __global__ void __launch_bounds__(RG_NT) k_band_forward(const ResArgs a) {
 
 // The same ownership, walking the blocks in reverse with the gradient of the residual stream in registers (packed).  BatchNorm parameter gradients are
 // added here: the run has no weight-gradient launch that knows of them.
+template <bool FEW>
 __global__ void __launch_bounds__(RG_NT) k_band_backward(const ResArgs a) {
   constexpr int C = RB_C, MID = RB_MID;
   const BandLane L(a);
@@ -308,7 +314,7 @@ __global__ void __launch_bounds__(RG_NT) k_band_backward(const ResArgs a) {
     mid(tag);
     __syncthreads();
     sums_publish_waves<Cc>(red, slot(), me, tag);
-    collect_bwd<Cc, true, 32>(slot(), L.nwg, tag, inv_M, ck, tab, nullptr, wave, lane, fail, me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
+    collect_bwd<Cc, FEW ? BAND_FEW : 32>(slot(), L.nwg, tag, inv_M, ck, tab, nullptr, wave, lane, fail, me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
     late(tag);
     ++phase;
     __syncthreads();
@@ -431,7 +437,11 @@ int resident_bands(int kind, int C, int MID, int H, int W) {
   return kind == 1 && C == RB_C && MID == RB_MID && H == RB_BANDS * RB_ROWS && W == RB_W ? RB_BANDS : 1;
 }
 size_t band_xchg_bytes(int members) { return 2 * band_slot_words(members) * sizeof(u64); }
-hipError_t launch_band_forward(int g, const ResArgs& a, hipStream_t stream) { return launch_band(k_band_forward, RB_FWD_LDS, g, a, stream); }
-hipError_t launch_band_backward(int g, const ResArgs& a, hipStream_t stream) { return launch_band(k_band_backward, RB_BWD_LDS, g, a, stream); }
+hipError_t launch_band_forward(int g, const ResArgs& a, hipStream_t stream) {
+  return launch_band(a.nmem * RB_BANDS <= BAND_FEW ? k_band_forward<true> : k_band_forward<false>, RB_FWD_LDS, g, a, stream);
+}
+hipError_t launch_band_backward(int g, const ResArgs& a, hipStream_t stream) {
+  return launch_band(a.nmem * RB_BANDS <= BAND_FEW ? k_band_backward<true> : k_band_backward<false>, RB_BWD_LDS, g, a, stream);
+}
 
 }  // namespace hpf

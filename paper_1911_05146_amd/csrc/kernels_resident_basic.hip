@@ -46,8 +46,12 @@ constexpr int basic_fwd_lds() {
   return G::CANVAS + G::W::BYTES + 2 * C * 8 + (INFER ? 0 : G::NPW * 2 * C * 4) + 16 + lead_lds<C, LEAD>(true);
 }
 
+// FEW: micro-batches of up to 16 images, which take one chunk of 16 records.  Eight blocks of 64 channels, us a step, chunks of 32 / 16: 16 images
+// 168 / 160, 4 images 156 / 152; of 32 channels 140 / 135 and 128 / 131.  With 16 channels a lane asks for one record or for two, and it makes no difference.
+constexpr int BASIC_FEW = 16;
+
 // LEAD: the run's first block is the one that halves the image and doubles the channels (Lead).
-template <int C, bool POST, bool INFER, bool LEAD>
+template <int C, bool POST, bool INFER, bool LEAD, bool FEW>
 __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
   static_assert(!(POST && INFER), "post-activation runs: training only");
   using G = Geo<C>;
@@ -136,7 +140,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     const unsigned tag = tag0 + 1u + phase;
     stats_publish_waves<Cc, GV::NPX, GV::NPW>(red, slot(), me, tag);
     const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
-    collect_stats<Cc, true>(slot(), a.nmem, tag, inv_n, (float)GV::P, a.eps, gamma, beta, o, wave, lane, fail);
+    collect_stats<Cc, FEW ? BASIC_FEW : 32>(slot(), a.nmem, tag, inv_n, (float)GV::P, a.eps, gamma, beta, o, wave, lane, fail);
     ++phase;
     late();
     __syncthreads();
@@ -361,7 +365,7 @@ constexpr int basic_bwd_lds() {
   return G::CANVAS + G::W::BYTES + (2 * 4 * C + 3 * C + G::NPW * 2 * C) * 4 + 16 + lead_lds<C, LEAD>(false);
 }
 
-template <int C, bool POST, bool LEAD>
+template <int C, bool POST, bool LEAD, bool FEW>
 __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
   using G = Geo<C>;
   constexpr int PTW = G::PTW, NTW = G::NTW;
@@ -425,7 +429,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_backward(const ResArgs a) {
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
     sums_publish_waves<Cc, GV::NPW>(red, slot(), me, tag);
-    collect_bwd<Cc, true, 32>(slot(), a.nmem, tag, inv_M * (float)G::P / (float)GV::P, ck, tab, !D && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave,
+    collect_bwd<Cc, FEW ? BASIC_FEW : 32>(slot(), a.nmem, tag, inv_M * (float)G::P / (float)GV::P, ck, tab, !D && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave,
                         lane, fail, D && me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
     ++phase;
     late();
@@ -718,28 +722,44 @@ hipError_t launch_basic(K kernel, int lds, int g, const ResArgs& a, hipStream_t 
   kernel<<<dim3((unsigned)(a.nmem * g)), RG_NT, (size_t)lds, stream>>>(b);
   return hipGetLastError();
 }
+template <int C, bool POST, bool LEAD>
+hipError_t fwd_p(int g, const ResArgs& a, hipStream_t stream) {
+  if constexpr (C > 16)
+    if (a.nmem <= BASIC_FEW) return launch_basic(k_basic_forward<C, POST, false, LEAD, true>, basic_fwd_lds<C, false, LEAD>(), g, a, stream);
+  return launch_basic(k_basic_forward<C, POST, false, LEAD, false>, basic_fwd_lds<C, false, LEAD>(), g, a, stream);
+}
 template <int C, bool LEAD>
 hipError_t fwd_c(int kind, int g, const ResArgs& a, bool infer, hipStream_t stream) {
-  if (infer) return launch_basic(k_basic_forward<C, false, true, LEAD>, basic_fwd_lds<C, true, LEAD>(), g, a, stream);
-  return kind == 2 ? launch_basic(k_basic_forward<C, true, false, LEAD>, basic_fwd_lds<C, false, LEAD>(), g, a, stream)
-                   : launch_basic(k_basic_forward<C, false, false, LEAD>, basic_fwd_lds<C, false, LEAD>(), g, a, stream);
+  if (infer) return launch_basic(k_basic_forward<C, false, true, LEAD, false>, basic_fwd_lds<C, true, LEAD>(), g, a, stream);
+  return kind == 2 ? fwd_p<C, true, LEAD>(g, a, stream) : fwd_p<C, false, LEAD>(g, a, stream);
+}
+template <int C, bool POST, bool LEAD>
+hipError_t bwd_p(int g, const ResArgs& a, hipStream_t stream) {
+  if constexpr (C > 16)
+    if (a.nmem <= BASIC_FEW) return launch_basic(k_basic_backward<C, POST, LEAD, true>, basic_bwd_lds<C, LEAD>(), g, a, stream);
+  return launch_basic(k_basic_backward<C, POST, LEAD, false>, basic_bwd_lds<C, LEAD>(), g, a, stream);
 }
 template <int C, bool LEAD>
 hipError_t bwd_c(int kind, int g, const ResArgs& a, hipStream_t stream) {
-  return kind == 2 ? launch_basic(k_basic_backward<C, true, LEAD>, basic_bwd_lds<C, LEAD>(), g, a, stream)
-                   : launch_basic(k_basic_backward<C, false, LEAD>, basic_bwd_lds<C, LEAD>(), g, a, stream);
+  return kind == 2 ? bwd_p<C, true, LEAD>(g, a, stream) : bwd_p<C, false, LEAD>(g, a, stream);
+}
+template <class K>
+hipError_t raise_limit(K kernel) { return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); }
+template <int C, bool LEAD, bool FEW>
+hipError_t prepare_f() {
+  hipError_t e = raise_limit(k_basic_forward<C, false, false, LEAD, FEW>);
+  if (e == hipSuccess) e = raise_limit(k_basic_forward<C, true, false, LEAD, FEW>);
+  if (e == hipSuccess) e = raise_limit(k_basic_backward<C, false, LEAD, FEW>);
+  if (e == hipSuccess) e = raise_limit(k_basic_backward<C, true, LEAD, FEW>);
+  return e;
 }
 template <int C, bool LEAD>
 hipError_t prepare_c() {
-  const void* const kernels[] = {
-      reinterpret_cast<const void*>(k_basic_forward<C, false, false, LEAD>), reinterpret_cast<const void*>(k_basic_forward<C, false, true, LEAD>),
-      reinterpret_cast<const void*>(k_basic_forward<C, true, false, LEAD>), reinterpret_cast<const void*>(k_basic_backward<C, false, LEAD>),
-      reinterpret_cast<const void*>(k_basic_backward<C, true, LEAD>)};
-  for (const void* f : kernels) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  hipError_t e = raise_limit(k_basic_forward<C, false, true, LEAD, false>);
+  if (e == hipSuccess) e = prepare_f<C, LEAD, false>();
+  if constexpr (C > 16)
+    if (e == hipSuccess) e = prepare_f<C, LEAD, true>();
+  return e;
 }
 static_assert(basic_fwd_lds<64, false, true>() <= 160 * 1024 && basic_fwd_lds<32, false, true>() <= 160 * 1024 && basic_bwd_lds<64, true>() <= 160 * 1024, "LDS of a CU");
 

@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
     const unsigned tag = tag0 + 1u + phase;
     stats_publish_waves<Cc, S * RG_NPX>(red, slot(), me, tag);
     const StatsOut o{coef, me == 0 ? reinterpret_cast<float*>(cx.base + B.stats_off[q]) : nullptr};
-    collect_stats<Cc, false, FEW ? 8 : 32>(slot(), a.nmem, tag, inv_n, (float)(S * RG_P), a.eps, gamma, beta, o, wave, lane, fail);
+    collect_stats<Cc, FEW ? 8 : 32>(slot(), a.nmem, tag, inv_n, (float)(S * RG_P), a.eps, gamma, beta, o, wave, lane, fail);
     ++phase;
     late();
     __syncthreads();
@@ -439,7 +439,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_backward(const ResArgs a) {
     __syncthreads();
     const unsigned tag = tag0 + 1u + phase;
     sums_publish_waves<Cc>(red, slot(), me, tag);
-    collect_bwd<Cc, false, FEW ? 8 : (Cc == C ? 16 : 1024 / MID)>(slot(), a.nmem, tag, ld && q == 0 ? 0.25f * inv_M : inv_M, ck, tab,
+    collect_bwd<Cc, FEW ? 8 : (Cc == C ? 16 : 1024 / MID)>(slot(), a.nmem, tag, ld && q == 0 ? 0.25f * inv_M : inv_M, ck, tab,
                                                   !ld && me == 0 ? reinterpret_cast<float*>(cx.base + B.dgb_off[q]) : nullptr, wave, lane, fail,
                                                   ld && me == 0 ? a.grads + B.beta_off[q] : nullptr, a.grads + B.gamma_off[q]);
     ++phase;

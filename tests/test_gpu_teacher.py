@@ -185,13 +185,14 @@ def test_weight_gradients_of_small_images_layerwise(gpu, oracle, kind, c, mid, h
     layerwise(oracle, spec, "bf16", blockwise=False)
 
 
-@pytest.mark.parametrize("images", [1, 31, 33])
+@pytest.mark.parametrize("images", [1, 8, 9, 16, 17, 31, 33])
 @pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 16, 32), (W.BASIC, 32, 32, 16), (W.BASIC, 64, 64, 8),
                                            (W.POSTACT, 16, 16, 32), (W.POSTACT, 32, 32, 16), (W.POSTACT, 64, 64, 8),
                                            (W.BOTTLENECK, 128, 32, 16), (W.BOTTLENECK, 128, 64, 16)])
 def test_register_resident_runs_around_the_polled_chunk_layerwise(gpu, oracle, kind, c, mid, hw, images):
-    """Image-resident runs with the residual stream in registers collect the BatchNorm words of 32 images at a time: one image (no
-    partner), a chunk that is not full and one word beyond a chunk.  Two blocks: the first and the last."""
+    """Image-resident runs with the residual stream in registers collect the BatchNorm words of 32 images at a time, basic blocks of 32 and 64 channels
+    those of 16 where there are no more, bottlenecks of eight: one image (no partner), full chunks, chunks that are not full, one word beyond a chunk,
+    either side of each change of kernel.  Two blocks: the first and the last."""
     spec = W.PartitionSpec(name=f"reg-{kind}-{c}@{hw}x{hw}-b{images}", in_h=hw, in_w=hw, in_c=c,
                            blocks=(W.Block(kind, c, mid, c, 1),) * 2, microbatch=images, num_microbatches=1, seed=43)
     layerwise(oracle, spec, "bf16", blockwise=False)
@@ -206,16 +207,16 @@ def test_register_resident_runs_of_8x8_bottlenecks_layerwise(gpu, oracle, images
     layerwise(oracle, spec, "bf16", grouped=grouped, blockwise=False)
 
 
-@pytest.mark.parametrize("images,blocks", [(1, 1), (1, 3), (9, 2), (16, 2)])
+@pytest.mark.parametrize("images,blocks", [(1, 1), (1, 3), (4, 2), (5, 2), (8, 2), (9, 2), (16, 2)])
 def test_row_bands_around_the_polled_chunk_layerwise(gpu, oracle, images, blocks):
-    """64-16 bottlenecks at 32x32 collect the words of 32 bands at a time: the four bands of one image alone, one block alone, more than one chunk
-    (36 bands) and whole chunks (64)."""
+    """64-16 bottlenecks at 32x32 collect the words of 32 bands at a time, of 16 where there are no more: the four bands of one image alone, one block
+    alone, the last image of the one kernel and the first of the other, more than one chunk (36 bands) and whole chunks (32, 64)."""
     spec = W.PartitionSpec(name=f"bands-{blocks}-b{images}", in_h=32, in_w=32, in_c=64, blocks=(W.Block(W.BOTTLENECK, 64, 16, 64, 1),) * blocks,
                            microbatch=images, num_microbatches=1, seed=79)
     layerwise(oracle, spec, "bf16", blockwise=False)
 
 
-@pytest.mark.parametrize("before,behind,images,micro", [(0, 1, 5, 2), (1, 0, 1, 1), (1, 2, 33, 1), (0, 3, 4, 3)])
+@pytest.mark.parametrize("before,behind,images,micro", [(0, 1, 5, 2), (1, 0, 1, 1), (1, 2, 33, 1), (0, 3, 4, 3), (1, 1, 16, 1), (0, 1, 17, 1)])
 @pytest.mark.parametrize("kind,c,mid,hw", [(W.BASIC, 16, 32, 32), (W.BASIC, 32, 64, 16), (W.POSTACT, 16, 32, 32), (W.POSTACT, 32, 64, 16),
                                            (W.BOTTLENECK, 64, 32, 32), (W.BOTTLENECK, 64, 64, 32)])
 def test_runs_led_in_by_a_block_that_halves_the_image_layerwise(gpu, oracle, kind, c, mid, hw, before, behind, images, micro):
