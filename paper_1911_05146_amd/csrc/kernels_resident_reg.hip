@@ -24,6 +24,7 @@
 
 #include <type_traits>
 
+#include "hpf_ahead.h"
 #include "hpf_resident_reg.h"
 
 namespace hpf {
@@ -164,7 +165,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   const int last = a.nblk - 1;
   struct { unsigned long long w1, w2, w3, run, gamma, beta; } nx;   // offsets of what is asked for next
   auto next_offsets = [&](int b01, int b2) {   // matrices and tables of the first two convolutions of block b01, of the third of block b2
-    const ResBlock *t01 = a.blocks + (b01 < last ? b01 : last), *t2 = a.blocks + (b2 < last ? b2 : last);
+    const ResBlock *t01 = a.blocks + b01, *t2 = a.blocks + (b2 < last ? b2 : last);
     nx.w1 = t01->wf_off[0];
     nx.w2 = t01->wf_off[1];
     nx.w3 = t2->wf_off[2];
@@ -241,10 +242,12 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
       w2.commit(sW2, wave, lane);
       store_coef();
       n0 = C;
-      next_offsets(1, 0);
-      w1.issue(a.packed + nx.w1, wave, fr, fq);
-      w2.issue(a.packed + nx.w2, wave, fr, fq);
-      load_coef();
+      if (const int b = block_ahead(true, 0, 1, a.nblk); b > 0) {
+        next_offsets(b, 0);
+        w1.issue(a.packed + nx.w1, wave, fr, fq);
+        w2.issue(a.packed + nx.w2, wave, fr, fq);
+        load_coef();
+      }
     } else {
       const bf16_t* g = a.packed + T.wf_off[1];
       w2.template issue<0>(g, wave, fr, fq); w2.template commit<0>(sW2, wave, lane);
@@ -313,7 +316,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
     if constexpr (INFER) {
       w2.commit(sW2, wave, lane);
       store_coef();
-      next_offsets(1, 0);
+      next_offsets(block_ahead(false, 0, 1, a.nblk), 0);
       w1.issue(a.packed + nx.w1, wave, fr, fq);   // w3 and the table of the third BatchNorm are kept for the first block, where they are staged
       w2.issue(a.packed + nx.w2, wave, fr, fq);
       load_coef();

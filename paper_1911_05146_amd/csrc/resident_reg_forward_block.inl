@@ -3,7 +3,8 @@
 const bool more = bi + 1 < a.nblk;
 const ResBlock B = a.blocks[bi];
 const ResBlock Bn = a.blocks[more ? bi + 1 : bi];
-if constexpr (INFER) next_offsets(bi + 2, bi + 1);
+const int ahead = INFER ? block_ahead(LD, bi, 2, a.nblk) : 0;
+if constexpr (INFER) { if (!LD || ahead >= 0) next_offsets(ahead, bi + 1); }
 // ---- conv1 (1x1, C -> MID) on relu(bn1(x))
 floatx4 acc[RG_PTW][NM];
 if constexpr (!INFER) w3.issue(a.packed + B.wf_off[2], wave, fr, fq);
@@ -51,12 +52,14 @@ for (int j = 0; j < RG_PTW; ++j)
     *reinterpret_cast<uint2*>(cv_w + j * RG_CW * MS + nt * 16) = bn_relu_pack(acc[j][nt], coefM + nt * 16 + fq * 4);
 __syncthreads();
 if constexpr (INFER) {   // every wave is past conv1 and its tables, and past conv3 of the block before
-  w1.commit(sW1, wave, lane);
   w3.commit(sW3, wave, lane);
-  store_coef();
-  load_coef();
-  w1.issue(a.packed + nx.w1, wave, fr, fq);   // a whole block ahead of their use
-  w3.issue(a.packed + nx.w3, wave, fr, fq);
+  if (!LD || ahead >= 0) {
+    w1.commit(sW1, wave, lane);
+    store_coef();
+    load_coef();
+    w1.issue(a.packed + nx.w1, wave, fr, fq);   // a whole block ahead of their use
+    w3.issue(a.packed + nx.w3, wave, fr, fq);
+  }
 }
 // ---- conv2 (3x3, MID -> MID)
 #pragma unroll
@@ -70,8 +73,10 @@ for (int j = 0; j < RG_PTW; ++j)
   for (int nt = 0; nt < NM; ++nt) { cp[j][nt] = pack4(acc[j][nt]); acc[j][nt] = unpack4(cp[j][nt]); }
 if constexpr (INFER) {
   __syncthreads();
-  w2.commit(sW2, wave, lane);
-  w2.issue(a.packed + nx.w2, wave, fr, fq);
+  if (!LD || ahead >= 0) {
+    w2.commit(sW2, wave, lane);
+    w2.issue(a.packed + nx.w2, wave, fr, fq);
+  }
 } else {
   if (more) { w2.template issue<0>(a.packed + Bn.wf_off[1], wave, fr, fq); w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq); }   // the exchange hides it
   if (!exchange(IM{}, acc, B, 2, coefM3, [&] {

@@ -34,6 +34,8 @@ def small_specs():
     led = W.PartitionSpec(name="led", in_h=32, in_w=32, in_c=64,                            # the strided block in the run's launch, and on its own
                           blocks=(W.Block(W.BOTTLENECK, 64, 32, 128, 2),) + (W.Block(W.BOTTLENECK, 128, 32, 128, 1),) * 2, microbatch=3,
                           num_microbatches=2, seed=12)
+    led_alone = W.PartitionSpec(name="led-alone", in_h=32, in_w=32, in_c=64, blocks=(W.Block(W.BOTTLENECK, 64, 16, 64, 1), W.Block(W.BOTTLENECK, 64, 32, 128, 2)),
+                                microbatch=3, num_microbatches=2, seed=12)
     led_wide = W.PartitionSpec(name="led-wide", in_h=32, in_w=32, in_c=64, blocks=(W.Block(W.BOTTLENECK, 64, 16, 64, 1), W.Block(W.BOTTLENECK, 64, 64, 128, 2)),
                                microbatch=3, num_microbatches=2, seed=12)
     # runs of the sizes that the LDS-tile kernels take
@@ -45,7 +47,7 @@ def small_specs():
                                       blocks=(W.Block(W.BOTTLENECK, 128, 32, 128, 1),) * 2 + (W.Block(W.BOTTLENECK, 128, 64, 128, 1),) * 2 +
                                              (W.Block(W.BOTTLENECK, 128, 64, 256, 2),) + (W.Block(W.BOTTLENECK, 256, 64, 256, 1),) * 2,
                                       microbatch=3, num_microbatches=2, seed=14)
-    return {"resnet20": r20, "bottleneck_run": bott, "cut_partition": cut, "wide_runs": wide, "led_run": led, "led_wide_alone": led_wide, "tile_basic_runs": tile_basic,
+    return {"resnet20": r20, "bottleneck_run": bott, "cut_partition": cut, "wide_runs": wide, "led_run": led, "led_alone": led_alone, "led_wide_alone": led_wide, "tile_basic_runs": tile_basic,
             "tile_bottleneck_runs": tile_bottleneck}
 
 
@@ -65,7 +67,7 @@ def train_batch(part, spec, t, grouped):
 
 @pytest.mark.parametrize("mode", ["f32", "bf16"])
 @pytest.mark.parametrize("grouped", [False, True])
-@pytest.mark.parametrize("name", ["resnet20", "bottleneck_run", "cut_partition", "wide_runs", "led_run", "led_wide_alone", "tile_basic_runs", "tile_bottleneck_runs"])
+@pytest.mark.parametrize("name", ["resnet20", "bottleneck_run", "cut_partition", "wide_runs", "led_run", "led_alone", "led_wide_alone", "tile_basic_runs", "tile_bottleneck_runs"])
 def test_running_statistics_and_inference_against_oracle(gpu, oracle, name, grouped, mode):
     import torch
     hpf = gpu

@@ -42,6 +42,25 @@ int main() { std::printf("%%u %%u %%u\\n", looks(8 * %d, ~0u), looks(8 * %d, 3),
     assert late == 4 * chunks
 
 
+def test_operands_asked_for_ahead_have_the_shape_of_the_run(tmp_path):
+    """What block bi of an inference run asks for ahead belongs to a block of that run, and never to the lead, whose first matrix and table are half as large."""
+    run_cpp(tmp_path, '''
+#include <cstdio>
+#include "hpf_ahead.h"
+int main() {
+  for (int lead = 0; lead < 2; ++lead)
+    for (int nblk = 1; nblk < 6; ++nblk)
+      for (int bi = 0; bi < nblk; ++bi)
+        for (int distance = 1; distance < 3; ++distance) {
+          const int b = hpf::block_ahead(lead, bi, distance, nblk);
+          const bool alone = lead && nblk == 1;
+          if (alone ? b != -1 : b < lead || b >= nblk || (bi + distance < nblk && b != bi + distance)) { std::printf("%d %d %d %d: %d\\n", lead, nblk, bi, distance, b); return 1; }
+        }
+  return 0;
+}
+''')
+
+
 FAKE_GPU = '''
 #include <cstdio>
 #include <cstdlib>
