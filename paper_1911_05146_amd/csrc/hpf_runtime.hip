@@ -19,6 +19,7 @@
 
 #include "../../include/hpf.h"
 #include "hpf_admission.h"
+#include "hpf_figures.h"
 #include "hpf_kernels.h"
 
 using namespace hpf;
@@ -978,49 +979,35 @@ struct Ctx {
     a.xchg_off = P.xchg_off; a.tag_off = P.tag_off; a.abort_flag = h->abort_flag();
     return a;
   }
-  // algorithmic figures of a run per image: every stashed tensor once (elements), contraction flop of one direction
-  static void res_figures(const Plan::ResRun& r, double px, double* stash_elems, double* flops) {
-    if (r.kind == 2) { *stash_elems = px * 3.0 * r.C; *flops = 2.0 * px * 2.0 * 9.0 * r.C * r.C; }
-    else if (r.kind == 0) { *stash_elems = px * 2.0 * r.C; *flops = 2.0 * px * 2.0 * 9.0 * r.C * r.C; }
-    else { *stash_elems = px * (2.0 * r.MID + r.C); *flops = 2.0 * px * (2.0 * r.C * r.MID + 9.0 * r.MID * r.MID); }
-  }
-  void res_forward(const Plan::ResRun& r) {
+  RunFigures res_figures(const Plan::ResRun& r) const {
     const BlockPlan& p0 = h->P.bp[r.first];
-    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_out * p0.w_out;
-    double st, fl;
-    res_figures(r, px, &st, &fl);
-    seg(PROF_RES_FWD, img * 2.0 * (px * r.C + r.count * st), img * r.count * fl);
+    return run_figures(r.kind, r.C, r.MID, (double)p0.h_out * p0.w_out, r.count, r.lead);
+  }
+  double res_images() const { return (double)g * h->P.d.microbatch; }
+  void res_forward(const Plan::ResRun& r) {
+    const RunFigures f = res_figures(r);
+    seg(PROF_RES_FWD, res_images() * 2.0 * f.forward, res_images() * f.flops);
     chk(launch_resident_forward(r.kind, g, r.C, r.MID, res_args(r), s), "resident_forward");
     seg_end();
   }
   void res_inference(const Plan::ResRun& r) {
-    const BlockPlan& p0 = h->P.bp[r.first];
-    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_out * p0.w_out;
-    double st, fl;
-    res_figures(r, px, &st, &fl);
-    seg(PROF_RES_FWD, img * 2.0 * 2.0 * px * r.C, img * r.count * fl);   // run input read, run output written
+    const RunFigures f = res_figures(r);
+    seg(PROF_RES_FWD, res_images() * 2.0 * f.inference, res_images() * f.flops);
     chk(launch_resident_inference(r.kind, g, r.C, r.MID, res_args(r), s), "resident_inference");
     seg_end();
   }
   void res_backward(const Plan::ResRun& r) {
-    const BlockPlan& p0 = h->P.bp[r.first];
-    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_out * p0.w_out;
-    double st, fl;
-    res_figures(r, px, &st, &fl);
-    seg(PROF_RES_BWD, img * 2.0 * (px * r.C + r.count * 2.0 * st), img * r.count * fl);
+    const RunFigures f = res_figures(r);
+    seg(PROF_RES_BWD, res_images() * 2.0 * f.backward, res_images() * f.flops);
     chk(launch_resident_backward(r.kind, g, r.C, r.MID, res_args(r), s), "resident_backward");
     seg_end();
   }
   void res_wgrad(const Plan::ResRun& r) {
-    const BlockPlan& p0 = h->P.bp[r.first];
-    const double img = (double)g * h->P.d.microbatch, px = (double)p0.h_out * p0.w_out;
-    double st, fl;
-    res_figures(r, px, &st, &fl);
-    const int n = r.count - r.lead;
-    if (n == 0) return;
+    if (r.count == r.lead) return;
+    const RunFigures f = res_figures(r);
     ResArgs a = res_args(r);
-    a.blocks += r.lead; a.nblk = n; a.lead = 0;   // the lead's weight gradients go with the grouped ones
-    seg(PROF_RES_WGRAD, img * n * 2.0 * 2.0 * st, img * n * fl);
+    a.blocks += r.lead; a.nblk = r.count - r.lead; a.lead = 0;   // the lead's weight gradients go with the grouped ones
+    seg(PROF_RES_WGRAD, res_images() * 2.0 * f.wgrad, res_images() * f.wgrad_flops);
     chk(launch_resident_wgrad(r.kind, g, r.C, r.MID, a, s), "resident_wgrad");
     seg_end();
   }

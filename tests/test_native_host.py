@@ -61,6 +61,48 @@ int main() {
 ''')
 
 
+def _figures(tmp_path, kind, c, mid, px, count, lead):
+    out = run_cpp(tmp_path, '''
+#include <cstdio>
+#include "hpf_figures.h"
+int main() {
+  const hpf::RunFigures f = hpf::run_figures(%d, %d, %d, %d, %d, %d);
+  std::printf("%%.0f %%.0f %%.0f %%.0f %%.0f %%.0f\\n", f.forward, f.inference, f.backward, f.flops, f.wgrad, f.wgrad_flops);
+}
+''' % (kind, c, mid, px, count, lead))
+    return [int(v) for v in out]
+
+
+LED_RUNS = [(0, 32, 32, 16, 18), (0, 64, 64, 8, 1), (1, 128, 32, 16, 7), (1, 128, 64, 16, 1), (2, 64, 64, 8, 3)]
+
+
+@pytest.mark.parametrize("kind,c,mid,hw,blocks,lead", [(*r, lead) for lead in (0, 1) for r in LED_RUNS] + [(1, 256, 64, 8, 4, 0)])
+def test_algorithmic_figures_of_a_run(tmp_path, kind, c, mid, hw, blocks, lead):
+    """Every tensor of the run once, block by block, and 2*M*K*N per contraction; the block that leads a run in has twice the image edge and half the channels in front."""
+    px = hw * hw
+    fwd = bwd = flops = wgrad = wflops = 0
+    for i in range(blocks):
+        led = lead and i == 0
+        x = 4 * px * c // 2 if led else px * c            # the block's input, and its gradient
+        ci, y = (c // 2 if led else c), px * c
+        inner = [px * mid] * 2 if kind == 1 else [y] * (2 if kind == 2 else 1)     # outputs of the convolutions but the block's last (post-activation: all)
+        extra = [y, y] if kind == 2 and led else []                               # the shortcut and relu(bn1(c1))
+        if i == 0:
+            fwd, bwd, infer = x, y, x + y                 # the run's input; the gradient of its output
+        fwd += sum(inner) + sum(extra) + y
+        if kind == 2:
+            bwd += sum(inner) + y + sum(inner) + x + (y if led else 0)             # c1, c2, y read; their gradients, the input's and the shortcut's written
+        else:
+            bwd += x + sum(inner) + sum(inner) + x
+        pairs = [(ci, mid, 1), (mid, mid, 9), (mid, c, 1)] if kind == 1 else [(ci, c, 9), (c, c, 9)]
+        k = sum(a * b * t for a, b, t in pairs) + (ci * c if led else 0)
+        flops += 2 * px * k
+        if not led:
+            wgrad += 2 * (y + sum(inner))
+            wflops += 2 * px * k
+    assert _figures(tmp_path, kind, c, mid, px, blocks, lead) == [fwd, infer, bwd, flops, wgrad, wflops]
+
+
 FAKE_GPU = '''
 #include <cstdio>
 #include <cstdlib>
