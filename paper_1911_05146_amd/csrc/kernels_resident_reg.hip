@@ -121,7 +121,11 @@ template <int C, int MID, bool INFER, bool LEAD, bool FEW>
 __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
   constexpr int MS = MID + 8, NC = C / 16, NM = MID / 16;
   using W1 = WStage<MID, C>;
-  using W2 = WStage<MID, 9 * MID, INFER ? 1 : 3>;
+  // Training of 128-32 blocks: conv2's matrix travels in one piece (12 registers), and the next block's matrices are asked for behind the polls of an exchange.
+  // Ahead of them, in fragment order, they hold up its words: 21 blocks, 8 micro-batches of 32 / 16 images, 302 / 288 us, behind them 297 / 281 (with matrices in
+  // row order, ahead of the polls, 294 / 283); 13 images, one micro-batch, 285 / 281; 8 micro-batches of 8 images 257 / 252.
+  constexpr bool WHOLE = !INFER && MID == 32;
+  using W2 = WStage<MID, 9 * MID, INFER || WHOLE ? 1 : 3>;
   using W3 = WStage<C, MID>;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int fr = lane & 15, fq = lane >> 4, fk = fq * 8;
@@ -156,6 +160,13 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
 
   W1 w1; W2 w2; W3 w3;
   floatx4 X[RG_PTW][NC];
+  auto stage_w2 = [&](const bf16_t* g) {   // training: of the first block
+    w2.template issue<0>(g, wave, fr, fq); w2.template commit<0>(sW2, wave, lane);
+    if constexpr (!WHOLE) {
+      w2.template issue<1>(g, wave, fr, fq); w2.template commit<1>(sW2, wave, lane);
+      w2.template issue<2>(g, wave, fr, fq); w2.template commit<2>(sW2, wave, lane);
+    }
+  };
   // Inference: the coefficients of a block, one channel per thread: waves 0 .. C/64 - 1 take the first BatchNorm, the next two waves the others.
   static_assert(C / 64 + 2 <= RG_NW && MID <= 64, "a channel per lane");
   float rc_mean, rc_var, rc_gamma, rc_beta;
@@ -249,10 +260,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
         load_coef();
       }
     } else {
-      const bf16_t* g = a.packed + T.wf_off[1];
-      w2.template issue<0>(g, wave, fr, fq); w2.template commit<0>(sW2, wave, lane);
-      w2.template issue<1>(g, wave, fr, fq); w2.template commit<1>(sW2, wave, lane);
-      w2.template issue<2>(g, wave, fr, fq); w2.template commit<2>(sW2, wave, lane);
+      stage_w2(a.packed + T.wf_off[1]);
     }
 #pragma unroll
     for (int t = 0; t < RG_LT; t += INFER ? 4 : 1) LP::arrange(px[t]);
@@ -321,10 +329,7 @@ __global__ void __launch_bounds__(RG_NT) k_reg_forward(const ResArgs a) {
       w2.issue(a.packed + nx.w2, wave, fr, fq);
       load_coef();
     } else {
-      const bf16_t* g = a.packed + B0.wf_off[1];
-      w2.template issue<0>(g, wave, fr, fq); w2.template commit<0>(sW2, wave, lane);
-      w2.template issue<1>(g, wave, fr, fq); w2.template commit<1>(sW2, wave, lane);
-      w2.template issue<2>(g, wave, fr, fq); w2.template commit<2>(sW2, wave, lane);
+      stage_w2(a.packed + B0.wf_off[1]);
     }
     __syncthreads();
     if constexpr (!INFER) {

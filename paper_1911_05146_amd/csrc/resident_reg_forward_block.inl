@@ -40,7 +40,7 @@ for (int j = 0; j < RG_PTW; ++j)
 if constexpr (!INFER) {
   if (!exchange(IM{}, acc, B, 1, coefM, [&] {
         w3.commit(sW3, wave, lane);
-        if (bi > 0) w2.template commit<2>(sW2, wave, lane);
+        if constexpr (!WHOLE) { if (bi > 0) w2.template commit<2>(sW2, wave, lane); }
         px_store<MID != 32>(image(B.c1_off, MID), offM, cp);
       }))
     return;
@@ -78,9 +78,11 @@ if constexpr (INFER) {
     w2.issue(a.packed + nx.w2, wave, fr, fq);
   }
 } else {
-  if (more) { w2.template issue<0>(a.packed + Bn.wf_off[1], wave, fr, fq); w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq); }   // the exchange hides it
+  auto next_w12 = [&] { w2.template issue<0>(a.packed + Bn.wf_off[1], wave, fr, fq); w1.issue(a.packed + Bn.wf_off[0], wave, fr, fq); };
+  if constexpr (!WHOLE) { if (more) next_w12(); }   // the exchange hides it
   if (!exchange(IM{}, acc, B, 2, coefM3, [&] {
-        if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wf_off[1], wave, fr, fq); }
+        if constexpr (WHOLE) { if (more) next_w12(); }
+        else if (more) { w2.template commit<0>(sW2, wave, lane); w2.template issue<1>(a.packed + Bn.wf_off[1], wave, fr, fq); }
         px_store<MID != 32>(image(B.c2_off, MID), offM, cp);
       }))
     return;
@@ -113,8 +115,8 @@ if constexpr (INFER) {
 } else if (more) {
   if (!exchange(IC{}, X, Bn, 0, coefC, [&] {
         w1.commit(sW1, wave, lane);
-        w2.template commit<1>(sW2, wave, lane);
-        w2.template issue<2>(a.packed + Bn.wf_off[1], wave, fr, fq);
+        if constexpr (WHOLE) w2.template commit<0>(sW2, wave, lane);
+        else { w2.template commit<1>(sW2, wave, lane); w2.template issue<2>(a.packed + Bn.wf_off[1], wave, fr, fq); }
         store_y();
       }))
     return;
