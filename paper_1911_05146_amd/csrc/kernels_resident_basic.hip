@@ -46,8 +46,8 @@ constexpr int basic_fwd_lds() {
   return G::CANVAS + G::W::BYTES + 2 * C * 8 + (INFER ? 0 : G::NPW * 2 * C * 4) + 16 + lead_lds<C, LEAD>(true);
 }
 
-// FEW: micro-batches of up to 16 images, which take one chunk of 16 records.  Eight blocks of 64 channels, us a step, chunks of 32 / 16: 16 images
-// 168 / 160, 4 images 156 / 152; of 32 channels 140 / 135 and 128 / 131.  With 16 channels a lane asks for one record or for two, and it makes no difference.
+// FEW: micro-batches of up to 16 images, which take one chunk of 16 records.  17 blocks, 16 images, us forward and backward, chunks of 32 / 16: 64 channels
+// 150 and 186 / 143 and 176, 32 channels 127 and 151 / 124 and 147, 16 channels 149 and 189 / 146 and 186; 4 images of 64 channels 146 and 170 / 145 and 168.
 constexpr int BASIC_FEW = 16;
 
 // LEAD: the run's first block is the one that halves the image and doubles the channels (Lead).
@@ -724,8 +724,7 @@ hipError_t launch_basic(K kernel, int lds, int g, const ResArgs& a, hipStream_t 
 }
 template <int C, bool POST, bool LEAD>
 hipError_t fwd_p(int g, const ResArgs& a, hipStream_t stream) {
-  if constexpr (C > 16)
-    if (a.nmem <= BASIC_FEW) return launch_basic(k_basic_forward<C, POST, false, LEAD, true>, basic_fwd_lds<C, false, LEAD>(), g, a, stream);
+  if (a.nmem <= BASIC_FEW) return launch_basic(k_basic_forward<C, POST, false, LEAD, true>, basic_fwd_lds<C, false, LEAD>(), g, a, stream);
   return launch_basic(k_basic_forward<C, POST, false, LEAD, false>, basic_fwd_lds<C, false, LEAD>(), g, a, stream);
 }
 template <int C, bool LEAD>
@@ -735,8 +734,7 @@ hipError_t fwd_c(int kind, int g, const ResArgs& a, bool infer, hipStream_t stre
 }
 template <int C, bool POST, bool LEAD>
 hipError_t bwd_p(int g, const ResArgs& a, hipStream_t stream) {
-  if constexpr (C > 16)
-    if (a.nmem <= BASIC_FEW) return launch_basic(k_basic_backward<C, POST, LEAD, true>, basic_bwd_lds<C, LEAD>(), g, a, stream);
+  if (a.nmem <= BASIC_FEW) return launch_basic(k_basic_backward<C, POST, LEAD, true>, basic_bwd_lds<C, LEAD>(), g, a, stream);
   return launch_basic(k_basic_backward<C, POST, LEAD, false>, basic_bwd_lds<C, LEAD>(), g, a, stream);
 }
 template <int C, bool LEAD>
@@ -757,8 +755,7 @@ template <int C, bool LEAD>
 hipError_t prepare_c() {
   hipError_t e = raise_limit(k_basic_forward<C, false, true, LEAD, false>);
   if (e == hipSuccess) e = prepare_f<C, LEAD, false>();
-  if constexpr (C > 16)
-    if (e == hipSuccess) e = prepare_f<C, LEAD, true>();
+  if (e == hipSuccess) e = prepare_f<C, LEAD, true>();
   return e;
 }
 static_assert(basic_fwd_lds<64, false, true>() <= 160 * 1024 && basic_fwd_lds<32, false, true>() <= 160 * 1024 && basic_bwd_lds<64, true>() <= 160 * 1024, "LDS of a CU");

@@ -190,8 +190,8 @@ def test_weight_gradients_of_small_images_layerwise(gpu, oracle, kind, c, mid, h
                                            (W.POSTACT, 16, 16, 32), (W.POSTACT, 32, 32, 16), (W.POSTACT, 64, 64, 8),
                                            (W.BOTTLENECK, 128, 32, 16), (W.BOTTLENECK, 128, 64, 16)])
 def test_register_resident_runs_around_the_polled_chunk_layerwise(gpu, oracle, kind, c, mid, hw, images):
-    """Image-resident runs with the residual stream in registers collect the BatchNorm words of 32 images at a time, basic blocks of 32 and 64 channels
-    those of 16 where there are no more, bottlenecks of eight: one image (no partner), full chunks, chunks that are not full, one word beyond a chunk,
+    """Image-resident runs with the residual stream in registers collect the BatchNorm words of 32 images at a time, basic blocks those of 16 where there
+    are no more, bottlenecks of eight: one image (no partner), full chunks, chunks that are not full, one word beyond a chunk,
     either side of each change of kernel.  Two blocks: the first and the last."""
     spec = W.PartitionSpec(name=f"reg-{kind}-{c}@{hw}x{hw}-b{images}", in_h=hw, in_w=hw, in_c=c,
                            blocks=(W.Block(kind, c, mid, c, 1),) * 2, microbatch=images, num_microbatches=1, seed=43)
