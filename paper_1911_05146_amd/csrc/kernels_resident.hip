@@ -1875,13 +1875,9 @@ size_t bwd_lds(int C, int MID, int P, int nmem, int* own) {
 
 constexpr size_t RES_LDS_BYTES = 160 * 1024 - 1024;   // LDS of a gfx950 CU, less room for the kernels' static allocations
 
-// What the row-band kernels' records took in LDS when they lay there (64-16 bottlenecks at 32x32: 256 pixels a band): it still says how many images they
-// accept (resident_shape_ok)
-size_t band_lds_limit(int nwg) {
-  const int C = 64, MID = 16, P = 256, W = 32;
-  return (size_t)P * (C + 8) * 2 + (size_t)(2 * P + 2 * W) * (MID + 8) * 2 + (size_t)(C + 2 * MID) * 16 + (size_t)RES_NWV * 2 * C * 4 + (size_t)C * 16 +
-         (size_t)nwg * 2 * C * 4 + (size_t)2 * W * MID * 4;
-}
+// Row-band runs (64-16 bottlenecks at 32x32) end here.  Their records lie in LDS no longer; the limit is that of the form in which they did, for the reason at
+// resident_shape_ok.
+constexpr int BAND_MAX_IMAGES = 42;
 
 template <class K>
 hipError_t launch_res(K kernel, size_t lds, int own, int g, const ResArgs& a, hipStream_t stream) {
@@ -1911,8 +1907,7 @@ bool resident_shape_ok(int kind, int C, int MID, int H, int W, int nmem) {
   if (H <= 0 || (W != 8 && W != 16 && W != 32) || P % 32) return false;
   if (nmem < 1 || nmem > 1024) return false;
   int own = 0;
-  if (const int nb = resident_bands(kind, C, MID, H, W); nb > 1)
-    return band_lds_limit(nmem * nb) <= RES_LDS_BYTES;
+  if (resident_bands(kind, C, MID, H, W) > 1) return nmem <= BAND_MAX_IMAGES;
   if (kind == 0 || kind == 2) {   // basic blocks: C -> C -> C, before / after the activation
     if (MID != C) return false;
     if (C == 16) return resident_basic_shape(kind, C, H, W);   // the register kernels alone
@@ -2003,7 +1998,7 @@ hipError_t launch_resident_forward(int kind, int g, int C, int MID, const ResArg
   const size_t lds = fwd_lds(C, MID, a.H * a.W, a.nmem, &own);
   if (C == 128 && MID == 64) return launch_res(k_res_forward<128, 64, 2, false>, lds, own, g, a, stream);
   if (C == 128) return launch_res(k_res_forward<128, 32, 2, true>, lds, own, g, a, stream);
-  // one pixel tile per wave: the weights through LDS where the tiles leave room for them (8x8 images)
+  // one pixel tile per wave: the weights through LDS where the tiles leave room for them (64 pixels and fewer)
   if (lds + wl_bytes(C, MID) <= RES_LDS_BYTES)
     return launch_res(k_res_forward<256, 64, 1, false, false, true>, lds + wl_bytes(C, MID), own, g, a, stream);
   return launch_res(k_res_forward<256, 64, 1, false>, lds, own, g, a, stream);
