@@ -231,9 +231,11 @@ bool resident_reads_fragments(int kind, int C, int MID, int H, int W);
 inline bool resident_permutes(int kind, int C, int R) { return kind == 1 && (C == 128 || C == 64) && R == 1; }
 // The order of MFMA fragments: a [rows][len] matrix (rows a multiple of 16, len of 32) as pieces of 16 rows x 32 columns, 1 KiB each, step of the
 // reduction by step; in a piece the 16 bytes of lane (fr, fq), row fr and columns fq*8 ... + 7, lie at (fq*16 + fr)*8.  Permuted: columns {0, 16} +
-// fq*4 ... + 3.  So the loads of a wave are whole cache lines.  With the rows of the matrix, 16 segments of 64 bytes a load, a load held the CU's memory
-// pipeline, and the words of the exchanges behind it, for about 50 cycles instead of 16: four images through ResNet-110 (inference) 241 -> 220 us,
-// four chained partitions of it 3870 -> 3657, ResNet-110 v1 whole 1333 -> 1276, a sixteenth of ResNet-1001 951 -> 939.
+// fq*4 ... + 3.  So the loads of a wave are whole cache lines.  A CU takes such a load from the L2 in 16 cycles; 16 row segments of 64 bytes take it 64
+// cycles, 32 of 32 bytes (permuted columns in row order) 128, and the words of an exchange wait behind them (a loop of such loads, eight waves, a matrix of
+// 128 KiB).  Four images through ResNet-110 (inference) 241 -> 220 us, four chained partitions of it 3870 -> 3657, ResNet-110 v1 whole 1333 -> 1276, a sixteenth of
+// ResNet-1001 951 -> 939.  What it costs: the update writes these matrices twice (k_sgd_pack), as fusion levels 0 and 1 and the
+// inference of post-activation and banded runs read them by rows: ResNet-1001 whole 50 -> 57 us, ResNet-110 v1 12.6 -> 14.6.
 // The element of (row, col); col a multiple of 4 (permuted) or 8.
 __host__ __device__ inline size_t fragment_at(int row, int col, int rows, bool permuted) {
   const int k = col & 31, fq = permuted ? (k & 15) >> 2 : k >> 3, e = permuted ? (k >> 4) * 4 : 0;

@@ -7,7 +7,7 @@ namespace hpf {
 constexpr unsigned RES_SPIN_LIMIT = 1u << 19;
 
 // Looks in vain that one collection has left, over all its chunks of members together: with a limit per chunk a work-group
-// without partners would hold its CU for as many limits as there are chunks (eight for 64 images in the backward of 128-64 blocks).
+// without partners would hold its CU for as many limits as there are chunks (four for 64 images in the backward of 128-64 blocks).
 struct SpinBudget {
   unsigned spins = 0;
   constexpr bool spent() const { return spins > RES_SPIN_LIMIT; }

@@ -283,13 +283,13 @@ __device__ __forceinline__ void store_fragment(bf16_t* m, int row, int col, int 
 }
 
 // bf16 operand copies of the convolution weights; STEP: behind the SGD step, which then needs no pass of its own (28 bytes per weight
-// instead of 24 + 12, and one launch).  grid (Y, n_convs): the Y blocks of a convolution share its 64 x 64 tiles of the fp32 master
-// [k = tap*Cin + c][n] round-robin.  A tile is updated as it is loaded, and both copies are written from LDS with 16-byte stores: the
+// instead of 24 + 12, and one launch; 32 where register-resident kernels read the weights, whose fragment order is written beside the rows).  grid (Y, n_convs): the Y blocks of a convolution share its 64 x 64 tiles of the fp32 master
+// [k = tap*Cin + c][n] round-robin.  A tile is updated as it is loaded, and the copies are written from LDS with 16-byte stores: the
 // forward one is its transpose, the data-gradient one takes its rows.  Channel counts and offsets are multiples of 16 (the stem's Cin
 // excepted).  Parameters that are no convolution weights follow the convolution in front of them (rest_*; the first also the ones before it).
 // The blocks of a convolution are consecutive, so they go to all dies: with the convolutions in x a matrix stayed on the dies that x mod 8 gave it
 // (the last quarter of VGG-16, 16.8 of 23.6 M weights in one of four matrices: 197 us, now 95).
-// ResNet-20 (0.27 M parameters): 4.5 + 25 us as two launches with a serial data-gradient copy, now 5.8; VGG-16 (33.6 M): 129 + 77, now 143.
+// ResNet-20 (0.27 M parameters): 4.5 + 25 us as two launches with a serial data-gradient copy, now 6.2; VGG-16 (33.6 M): 129 + 77, now 143.
 template <bool STEP>
 __global__ __launch_bounds__(256) void k_sgd_pack(float* __restrict__ params, float* __restrict__ mom, float* __restrict__ grads,
                                                   bf16_t* __restrict__ packed, const PackDesc* __restrict__ table, float lr, float mu,

@@ -12,7 +12,7 @@
 // against columns of zeros.
 //
 // Bound by the exchanges: the products of a block are under 0.2 us.  111 blocks of ResNet-1001, 8 micro-batches of 8 images, us per block, before (bands
-// in LDS tiles, records gathered there) and now: forward 15.0 / 10.1, backward 18.2 / 13.0.
+// in LDS tiles, records gathered there) and now: forward 15.0 / 10.1, backward 18.2 / 12.8.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(RG_NT) k_basic_forward(const ResArgs a) {
     // ---- conv2 on relu(bn2(c1)), onto the shortcut | on its own
     bn_pack(acc, coef2);
     to_canvas();
-    if constexpr (POST) px_store(image(T.a1_off), L.off, pk);
+    if constexpr (POST) px_store(image(T.a1_off), L.off, pk);   // no kernel reads it, but hpf_stash_read has always given it out for these blocks
     __syncthreads();
     auto next_matrix = [&](auto i) { if (more) w.template issue_third<i.value>(a.packed + Tn.wf_off[0], wave, fr, fq); };
     if constexpr (!POST) {

@@ -12,9 +12,10 @@
 //
 // What bounds the LDS-tile form (20.8 us per 128-32 block forward on 256 images): 2 500 VALU and 200 LDS instructions per wave and
 // block, 25 barriers, and exchanges whose records went through LDS twice.
-// Measured on 256 images (8 micro-batches), per block: forward 20.7 -> 13.1 us (128-32) and 28.2 -> 21.9 (128-64), backward
-// 26.1 -> 21.2 and 37.3 -> 35 (30 registers of the 128-64 backward spill: 92 bytes of scratch per lane).  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
-// 4 us at the memory's rate), and issue: 8 waves per CU leave the matrix cores idle while they do BatchNorm.
+// Measured on 256 images (8 micro-batches), per block, images in LDS tiles / now: forward 20.7 / 13.5 us (128-32) and 28.2 / 22.1 (128-64), backward
+// 26.1 / 20.1 and 37.3 / 32.9.  What is left: three exchanges per direction (1.5 us each), the stores of the stash (24 MiB per block,
+// 4 us at the memory's rate), and issue: 8 waves per CU leave the matrix cores idle while they do BatchNorm.  The backward of 128-64 blocks spills: 30 registers
+// (92 bytes of scratch a lane), 34 (100) with few images, 74 (284) and 72 (280) with a lead.
 //
 // The block in front of a run that halves the image and doubles the channels (64 -> 128, projection) leads it in (LEAD): the same launch starts, or
 // ends, with it.  Layer by layer it took about nine launches of 4 to 9 us a direction; here it adds 19 us forward (the whole input, 128 KiB an image,
@@ -113,7 +114,7 @@ constexpr int RG_FEW = 8;
 // block is written.
 // Barriers per block: 7 (training), 2 (inference).  The matrices of conv1 and conv3 take turns in one LDS area in training
 // (conv1's is dead when conv3's is staged, behind the barrier that ends conv1, and the other way round); conv2's of the next
-// block is staged behind the barrier that ends conv2.
+// block is staged behind the barrier that ends conv2, in one piece (WHOLE) or in three, which 64 inner channels need to stay within the registers.
 // Inference is bounded by latency (3.8 us per 128-32 block, of which the products take 0.9): every matrix and table is asked for as soon as the
 // registers of the one before are free, a whole block ahead of its use, and the tables of the three BatchNorms are read by waves of their
 // own.  Asked for within the block, the tables three dependent reads in one wave, 21 blocks took 95 us, now 80.

@@ -10,8 +10,9 @@
 //
 // Measured, 111 blocks of ResNet-1001, 8 micro-batches of 8 images, us per block, before (images in LDS tiles) and now: forward 15.2 / 10.7, backward
 // 22.5 / 12.9.  A form after kernels_resident_reg.hip, waves dividing the pixels, with the sums and the weights of all through LDS, took 13.2 and 16.1.
-// What bounds it now: the memory pipeline of a CU takes about 45 cycles for each KiB of weights (240 a block; none of them at all: 8.5 and 12.5 us),
-// and every exchange about 1.1 us from its records' leaving to the last one's arrival.
+// What bounds it now: 240 KiB of weights a block and work-group (1.6 us at the 16 cycles a KiB that a CU takes at best; none of them at all: 8.5 and 12.5 us),
+// and every exchange about 1.1 us from its records' leaving to the last one's arrival.  On more than eight images the kernels spill: 7 registers forward
+// (32 bytes of scratch a lane), 8 backward (36).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
