@@ -112,7 +112,7 @@ def test_row_band_runs_layerwise(gpu, oracle):
 
 def test_runs_with_weights_through_lds_layerwise(gpu, oracle):
     """Register-resident runs, whose weight matrices the work-group stages through LDS: 128-64 and 128-32 bottlenecks at
-    16x16 (conv2's matrix in three pieces, conv1's and conv3's in turn in one area), basic and post-activation blocks of
+    16x16 (conv2's matrix in one piece or in three, conv1's and conv3's in turn in one area), basic and post-activation blocks of
     32 channels at 16x16 and of 16 channels at 32x32 (one matrix at a time).
     Three blocks, so that the staging of the first block, of a following block and of the last one all run; an odd
     number of images; one call per micro-batch and one for all."""
@@ -124,8 +124,8 @@ def test_runs_with_weights_through_lds_layerwise(gpu, oracle):
         "3x postact32@16x16": (tuple(W.Block(W.POSTACT, 32, 32, 32, 1) for _ in range(3)), 16, 32, False),
         "3x postact16@32x32": (tuple(W.Block(W.POSTACT, 16, 16, 16, 1) for _ in range(3)), 32, 16, False),
     }
-    # 40 images per micro-batch: two chunks of polled members in the forward, three and five in the exchanges of a 128-64 block's backward;
-    # the largest size of the 128-32 runs
+    # 40 images per micro-batch: two chunks of polled members in the forward, three in the exchanges of a 128-64 block's backward; the
+    # largest size of the 128-32 runs
     spec = W.PartitionSpec(name="wide-3x(128-64-128)@16x16-b40", in_h=16, in_w=16, in_c=128, blocks=runs["wide-3x(128-64-128)@16x16"][0],
                            microbatch=40, num_microbatches=2, seed=37)
     layerwise(oracle, spec, "bf16", blockwise=False)
